@@ -435,7 +435,10 @@ static int ensure_tables()
     static uint32_t eh[kExpHiEntries], el[kExpLoEntries];
     for (int i = 0; i <= kSigEntries; ++i)
         sig[i] = (uint32_t)std::llround(std::ldexp(1.0 / (1.0 + std::exp(-(i - 1024) / 64.0)), 24));
-    for (int i = 0; i < kSigEntries; ++i) cell[i] = make_uint2(sig[i], (sig[i + 1] - sig[i]) << 6);
+    for (int i = 0; i < kSigEntries; ++i) {
+        const uint32_t rise = sig[i + 1] - sig[i];  // at most 2^16
+        cell[i] = make_uint2(rise << 11, sig[i] - rise * (uint32_t)i);
+    }
     for (int i = 0; i < kExpHiEntries; ++i)
         eh[i] = (uint32_t)std::llround(std::ldexp(std::exp(4.0 - i / 64.0), 26));
     for (int i = 0; i < kExpLoEntries; ++i)
@@ -630,8 +633,6 @@ static bool chunks_aligned(const Geo &g, const void *img, const pilc_params *p)
            ((uintptr_t)p->log_scale & 15) == 0;
 }
 
-// Workgroup size of the thread-per-lane kernels (at most kRingMaxThreads: the decoder's word ring
-// in LDS is sized for that).
 // On top of chunks_aligned: every row of every lane is a whole number of 16-pixel chunk pairs
 // that start at multiples of 16 pixels, and the pixels allow 16-byte loads.
 static bool chunks_pair_up(const Geo &g, const void *img)
@@ -649,7 +650,8 @@ static bool lanes_line_up(const Geo &g, const pilc_params *p)
            ((uintptr_t)p->mu & 127) == 0 && ((uintptr_t)p->log_scale & 127) == 0;
 }
 
-static int lane_block_threads(const Geo &g) { return g.lanes >= (1u << 16) ? kRingMaxThreads : 64; }
+// Workgroup size of the thread-per-lane kernels.
+static int lane_block_threads(const Geo &g) { return g.lanes >= (1u << 16) ? kLaneMaxThreads : 64; }
 
 }  // namespace pilc
 
@@ -979,25 +981,14 @@ int pilc_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t coded_by
         else PILC_DECODE_ROWS(true, false);
 #undef PILC_DECODE_ROWS
     } else {
+        const bool vec = chunks_aligned(g, img_out_dev, params);
+        const bool pair = vec && chunks_pair_up(g, img_out_dev);
+        auto kern = pair ? k_decode_lanes<true, true> : (vec ? k_decode_lanes<true, false> : k_decode_lanes<false, false>);
         const int bt = lane_block_threads(g);
         const uint32_t nb = (uint32_t)ceil_div64(g.lanes, bt);
-        if (chunks_aligned(g, img_out_dev, params) && chunks_pair_up(g, img_out_dev) && lanes_line_up(g, params))
-            k_decode_lanes<true, true, true><<<nb, bt, 0, stream>>>(g, coded_dev, params->mu, params->log_scale,
-                                                                    params->chan_coef, img_out_dev,
-                                                                    &status->code, &status->payload_bytes);
-        else if (chunks_aligned(g, img_out_dev, params) && chunks_pair_up(g, img_out_dev))
-            k_decode_lanes<true, true><<<nb, bt, 0, stream>>>(g, coded_dev, params->mu, params->log_scale,
-                                                              params->chan_coef, img_out_dev,
-                                                              &status->code, &status->payload_bytes);
-        else if (chunks_aligned(g, img_out_dev, params))
-            k_decode_lanes<true, false><<<nb, bt, 0, stream>>>(g, coded_dev, params->mu, params->log_scale,
-                                                               params->chan_coef, img_out_dev,
-                                                               &status->code, &status->payload_bytes);
-        else
-            k_decode_lanes<false, false><<<nb, bt, 0, stream>>>(g, coded_dev, params->mu,
-                                                                params->log_scale, params->chan_coef,
-                                                                img_out_dev, &status->code,
-                                                                &status->payload_bytes);
+        kern<<<nb, bt, (size_t)bt * kRingRow * sizeof(uint16_t), stream>>>(g, coded_dev, params->mu, params->log_scale,
+                                                            params->chan_coef, img_out_dev, &status->code,
+                                                            &status->payload_bytes);
     }
     timer.mark(few_lanes ? "k_decode_rows" : "k_decode_lanes");
     HIP_TRY(hipGetLastError());

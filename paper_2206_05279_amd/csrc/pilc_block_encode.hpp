@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_block(
     const uint32_t lane0 = blockIdx.x * kEncLanes;
     const uint32_t nl = min((uint32_t)kEncLanes, g.lanes - lane0);
     const uint32_t m_bits = g.prec_bits;
-    const uint32_t spread = (1u << m_bits) - 256u, top = 1u << m_bits;
+    const uint32_t scale = mass_scale(m_bits), top = 1u << m_bits;
 
     const bool producer = tid >= 64u;
     const uint32_t q = tid - 64u;
@@ -123,9 +123,10 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_block(
                            in.m[2] + rsh14_mul(in.a[1], e_r) + rsh14_mul(in.a[2], e_g)};
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const uint32_t inv_s = inv_scale(in.ls[c], tab);
-            const uint32_t lo = in.x[c] == 0 ? 0u : cum_inner(in.x[c], me[c], inv_s, spread, tab);
-            const uint32_t hi = in.x[c] == 255 ? top : cum_inner(in.x[c] + 1, me[c], inv_s, spread, tab);
+            const EdgeLaw law = edge_law(me[c], inv_scale(in.ls[c], tab));
+            const double y = edge_y(in.x[c], law);
+            const uint32_t lo = in.x[c] == 0 ? 0u : cum_inner(in.x[c], y, scale, tab);
+            const uint32_t hi = in.x[c] == 255 ? top : cum_inner(in.x[c] + 1, y + law.a, scale, tab);
             // the chain walks a batch last symbol first: pixel pj from the end, B before G before R
             rec[buf][3u * pj + (2 - c)][my] =
                 in.valid ? encode_record(lo, hi - lo, m_bits) : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);

@@ -16,9 +16,9 @@ constexpr int kExpHiEntries = 640;
 constexpr int kExpLoEntries = 64;
 
 // Constant tables in device globals, filled by the host once per device.
-//   g_sig_cell[i] = { T[i], (T[i+1]-T[i]) * 64 },  T[i] = round(2^24 * sigmoid((i-1024)/64))
-//     (the slope is below 2^16, so slope * 64 * r for a 10-bit r stays below 2^32 and its upper
-//     half is floor(slope * r / 2^10): the interpolation is one multiply and one add of a half)
+//   g_sig_cell[i] = { D[i] * 2^11, (T[i] - D[i] * i) mod 2^32 },  D[i] = T[i+1] - T[i],
+//     T[i] = round(2^24 * sigmoid((i-1024)/64)): the line through a cell's two ends as the 64-bit
+//     addend of one multiply-add (interpolate below)
 //   g_exp_hi[i]   = round(2^26 * exp(4 - i/64)),  g_exp_lo[j] = round(2^31 * exp(-j/4096))
 extern __device__ uint2 g_sig_cell[kSigEntries];
 extern __device__ uint32_t g_exp_hi[kExpHiEntries];
@@ -42,6 +42,7 @@ __device__ __forceinline__ void load_tables(LdsTables &t)
 // Sixteen bytes as the compiler's own vector type (arrays of it stay in registers where arrays of
 // the HIP struct type of the same size go to private memory).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));  // a register pair
 
 // Orders this wavefront's LDS accesses: LDS instructions of one wavefront execute in order, so
 // all that is needed is that the compiler keeps them in order too.
@@ -56,12 +57,6 @@ __device__ __forceinline__ void wave_lds_sync()
 // the 32-bit product, the compiler first sign-extends operands it cannot prove to be 24 bits wide,
 // which costs more instructions than the multiply.)  Operands must lie within +-2^23; only plain
 // vector ALU instructions consume the results.
-__device__ __forceinline__ int mul_i24(int a, int b)
-{
-    int r;
-    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
 __device__ __forceinline__ int mad_i24(int a, int b, int c)
 {
     int r;
@@ -158,69 +153,104 @@ __device__ __forceinline__ int rsh14(int v) { return (v + 8192) >> 14; }
 
 // rsh14(a * e) for a Q2.14 coefficient a (16 bits) and an innovation e = 256 x - mu (18 bits): the
 // product is below 2^31 in magnitude, so the 24-bit multiply-add gives it exactly at full rate.
-__device__ __forceinline__ int rsh14_mul(int a, int e) { return (__mul24(a, e) + 8192) >> 14; }
+__device__ __forceinline__ int rsh14_mul(int a, int e) { return mad_i24(a, e, 8192) >> 14; }
 
 // Q6.25 value of exp(-log_scale); log_scale Q4.12 clamped to [-4, 6).
 __device__ __forceinline__ uint32_t inv_scale(int ls, const LdsTables &t)
 {
     int u = min(max(ls, -16384), 24575) + 16384;
-    return __umulhi(t.exp_hi[u >> 6], t.exp_lo[u & 63]);
+    uint32_t inv_s = __umulhi(t.exp_hi[u >> 6], t.exp_lo[u & 63]);
+    asm("" : "+v"(inv_s));  // (else its conversion to double is made from the 64-bit product)
+    return inv_s;
 }
 
-// F(k) in 24 bits at the edge k - 1/2:  d = 256*k - 128 - mu'  (Q8.8), inv_s Q6.25 < 2^31.
-// z = clamp(floor(d * inv_s / 2^17), -2^20, 2^20 - 1) and w = z + 2^20 is bits 17..48 of the
-// 64-bit value d * inv_s + 2^37; z saturates exactly when the high word of that sum leaves 0..63.
-// Clamping the high word to -1..64 first keeps the saturated cases on their side of 0..2^21 - 1
-// after the shift (all ones above bit 14, or bit 21 set), so one more clamp finishes the job.
+// F(k) in 24 bits at the edge k - 1/2:  d = 256*k - 128 - mu'  (Q8.8), inv_s Q6.25 < 2^31,
+// w = clamp(floor(d * inv_s / 2^17) + 2^20, 0, 2^21 - 1), and F = T[i] + floor(D[i] * r / 2^10) for
+// i = w >> 10, r = w & 1023.
+// What bounds the kernels that evaluate this is vector instruction issue, and on this chip a
+// double-precision multiply-add and the conversions to and from double issue like any other
+// instruction (4.3 cycles a wavefront with four on a SIMD, measured; min, max, alignbit, mul24 the
+// same; plain add, and, or, shift right 2.6), so the position is formed in double: the product and
+// the sum have at most 51 significant bits, hence every step is exact, and the conversion to
+// uint32 brings the floor and both clamps.  For that the position is scaled by 2^11 (the top of
+// its range is the top of the uint32 range) and lowered by one:
+//     u = sat(floor((d * inv_s / 2^17 + 2^20 - 1) * 2^11)),   u >> 11 = w - 1 within the clamps.
+// The cell is then taken from w - 1 = 1024 i + r', with 1 + r' instead of r along its line: where r
+// is 0 that is the far end of the cell before, which has the same value.  At the ends of the range w
+// counts as 1 for 0 and 2^21 for 2^21 - 1; the first and the last cell are flat, so F is the same.
+constexpr double kEdgeBias = 1048575.0 * 2048.0;  // (2^20 - 1) * 2^11
+
+__device__ __forceinline__ uint32_t edge_pos(double y)
+{
+    uint32_t u;  // (the language leaves conversions of values out of range open; the instruction saturates)
+    asm("v_cvt_u32_f64 %0, %1" : "=v"(u) : "v"(y));
+    return u;
+}
+
+// F at position u: with the cell's slope s = D * 2^11 and R = u | 2^11 - 1 = i * 2^21 + (r' + 1) * 2^11 - 1,
+// s * (R + 1) = D * (i * 2^32 + (r' + 1) * 2^22), so the upper word of s * R + {s, T - D i} is
+// T + floor(D * (r' + 1) / 2^10): one OR and one 64-bit multiply-add, no field of u is cut out.
+__device__ __forceinline__ uint32_t interpolate(uint32_t u, const uint2 cell)
+{
+    const unsigned long long line = ((unsigned long long)cell.y << 32) | cell.x;
+    return (uint32_t)((line + (unsigned long long)cell.x * (u | 2047u)) >> 32);
+}
+
+__device__ __forceinline__ uint32_t edge_at(double y, const LdsTables &t)
+{
+    const uint32_t u = edge_pos(y);
+    return interpolate(u, t.sig[u >> 21]);
+}
+
+// The position as a function of k, for laws that are evaluated more than once: y(k) = k a + b.
+struct EdgeLaw {
+    double a, b;
+};
+__device__ __forceinline__ EdgeLaw edge_law(int mu_eff, uint32_t inv_s)
+{
+    const double inv = (double)inv_s;
+    EdgeLaw l;
+    l.a = inv * 4.0;
+    l.b = __builtin_fma((double)(-128 - mu_eff), inv * 0x1p-6, kEdgeBias);
+    return l;
+}
+__device__ __forceinline__ double edge_y(int k, const EdgeLaw &l) { return __builtin_fma((double)k, l.a, l.b); }
+
 __device__ __forceinline__ uint32_t edge_cdf(int d, uint32_t inv_s, const LdsTables &t)
 {
-    long long p = (long long)d * (long long)(int)inv_s + (1ll << 37);  // Q.33
-    asm("" : "+v"(p));  // keep the clamps below on 32-bit words
-    const int hi = min(max((int)(p >> 32), -1), 64);
-    const int v = (int)__builtin_amdgcn_alignbit((uint32_t)hi, (uint32_t)p, 17);
-    const uint32_t w = (uint32_t)min(max(v, 0), (1 << 21) - 1);
-    const uint2 cell = t.sig[w >> 10];
-    return cell.x + ((uint32_t)__umul24(cell.y, w & 1023u) >> 16);
+    return edge_at(__builtin_fma((double)d, (double)inv_s * 0x1p-6, kEdgeBias), t);
 }
 
-// floor(f * (2^M - 256) / 2^24) for a 24-bit f:  2^M - 256 = 256 * (spread >> 8) and the product
-// f * (spread >> 8) stays below 2^32 for M <= 16.
-__device__ __forceinline__ uint32_t scale_mass(uint32_t f, uint32_t spread)
+// 2^M - 256 as the multiplier of mass_of: 2^M - 256 = 256 * (2^(M-8) - 1).
+__device__ __forceinline__ uint32_t mass_scale(uint32_t prec_bits) { return ((1u << (prec_bits - 8u)) - 1u) << 16; }
+
+// floor(f * (2^M - 256) / 2^24) for a 24-bit f
+__device__ __forceinline__ uint32_t mass_of(uint32_t f, uint32_t scale) { return __umulhi(f, scale); }
+
+// k + mass_of(f, scale) as the upper word of one multiply-add, for a k that is kept as the upper word
+// of a register pair whose lower word is zero.  (Written as a sum, the compiler takes k out of it again
+// and adds it in an instruction of its own.)
+__device__ __forceinline__ uint32_t cum_from_pair(u32x2 zero_k, uint32_t f, uint32_t scale)
 {
-    return (uint32_t)__umul24(f, spread >> 8) >> 16;  // the builtin's result type is int
+    u32x2 sum;
+    unsigned long long carry;
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(sum), "=s"(carry) : "v"(f), "s"(scale), "v"(zero_k));
+    return sum.y;
 }
 
 // C(k), 1 <= k <= 255:  k + floor(F(k) * (2^M - 256) / 2^24).
-__device__ __forceinline__ uint32_t cum_inner(int k, int mu_eff, uint32_t inv_s, uint32_t spread,
-                                              const LdsTables &t)
+__device__ __forceinline__ uint32_t cum_inner(int k, double y, uint32_t scale, const LdsTables &t)
 {
-    return (uint32_t)k + scale_mass(edge_cdf(256 * k + (-128 - mu_eff), inv_s, t), spread);
-}
-
-// -128 - mu' in a register of its own: the edge offset of C(k) is then one shift-and-add per k,
-// instead of being formed again from a packed parameter at every evaluation.
-__device__ __forceinline__ int edge_offset(int mu_eff)
-{
-    int c0 = -128 - mu_eff;
-    asm("" : "+v"(c0));
-    return c0;
-}
-
-// C(k), 1 <= k <= 255, from c0 = edge_offset(mu').
-__device__ __forceinline__ uint32_t cum_inner_at(int k, int c0, uint32_t inv_s, uint32_t spread,
-                                                 const LdsTables &t)
-{
-    return (uint32_t)k + scale_mass(edge_cdf(256 * k + c0, inv_s, t), spread);
+    return (uint32_t)k + mass_of(edge_at(y, t), scale);
 }
 
 // C(k) for any k in 0..256.
 __device__ __forceinline__ uint32_t cum_at(int k, int mu_eff, uint32_t inv_s, uint32_t prec_bits,
                                            const LdsTables &t)
 {
-    uint32_t spread = (1u << prec_bits) - 256u;
     if (k <= 0) return 0u;
     if (k >= 256) return 1u << prec_bits;
-    return cum_inner(k, mu_eff, inv_s, spread, t);
+    return cum_inner(k, edge_y(k, edge_law(mu_eff, inv_s)), mass_scale(prec_bits), t);
 }
 
 }  // namespace pilc

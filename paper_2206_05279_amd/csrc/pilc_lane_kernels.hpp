@@ -131,8 +131,8 @@ __device__ __forceinline__ void load_pair(ChunkPair &r, uint32_t p, const uint8_
 // comes back to it.  Here a thread asks for whole lines, eight 16-byte pieces at once, when a pair
 // first needs one, and carries the pieces the pair does not use in registers to the pairs that
 // do: every line is fetched once.  The pixels go the same way in halves of a group (96 bytes).
-// `v` is the pair's number within its group (0..3); forward feeds pairs in the order 0,1,2,3,
-// backward in the order 3,2,1,0.
+// `v` is the pair's number within its group (0..3); the encoder walks its lane backwards, so the
+// pairs come in the order 3, 2, 1, 0.
 struct LineCarry {
     uint4 m[6], l[6], x[3];
 };
@@ -147,93 +147,58 @@ __device__ __forceinline__ void load_piece(uint32_t *w, int i, const uint4 *__re
 {
     put_piece(w, i, *src);
 }
-template <bool kBackward>
 __device__ __forceinline__ void feed_array(uint32_t *w, uint4 *carry, uint32_t v, const uint4 *__restrict__ grp)
 {
-    // forward:  v=0 line A: use A0-5, keep A6,7 | v=1 line B: kept + B0-3, keep B4-7 |
-    //           v=2 line C: kept + C0,1, keep C2-7 | v=3: kept
-    // backward: v=3 line C: use C2-7, keep C0,1 | v=2 line B: B4-7 + kept, keep B0-3 |
-    //           v=1 line A: A6,7 + kept, keep A0-5 | v=0: kept
-    if (!kBackward) {
-        switch (v) {
-        case 0:
+    // v=3 line C: use C2-7, keep C0,1 | v=2 line B: B4-7 + kept, keep B0-3 |
+    // v=1 line A: A6,7 + kept, keep A0-5 | v=0: kept
+    switch (v) {
+    case 3:
 #pragma unroll
-            for (int i = 0; i < 6; ++i) load_piece(w, i, grp + i);
-            carry[0] = grp[6]; carry[1] = grp[7];
-            break;
-        case 1:
-            put_piece(w, 0, carry[0]); put_piece(w, 1, carry[1]);
+        for (int i = 0; i < 6; ++i) load_piece(w, i, grp + 18 + i);
+        carry[0] = grp[16]; carry[1] = grp[17];
+        break;
+    case 2:
 #pragma unroll
-            for (int i = 0; i < 4; ++i) load_piece(w, 2 + i, grp + 8 + i);
+        for (int i = 0; i < 4; ++i) load_piece(w, i, grp + 12 + i);
+        put_piece(w, 4, carry[0]); put_piece(w, 5, carry[1]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) carry[i] = grp[12 + i];
-            break;
-        case 2:
+        for (int i = 0; i < 4; ++i) carry[i] = grp[8 + i];
+        break;
+    case 1:
+        load_piece(w, 0, grp + 6); load_piece(w, 1, grp + 7);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) put_piece(w, i, carry[i]);
-            load_piece(w, 4, grp + 16); load_piece(w, 5, grp + 17);
+        for (int i = 0; i < 4; ++i) put_piece(w, 2 + i, carry[i]);
 #pragma unroll
-            for (int i = 0; i < 6; ++i) carry[i] = grp[18 + i];
-            break;
-        default:
+        for (int i = 0; i < 6; ++i) carry[i] = grp[i];
+        break;
+    default:
 #pragma unroll
-            for (int i = 0; i < 6; ++i) put_piece(w, i, carry[i]);
-            break;
-        }
-    } else {
-        switch (v) {
-        case 3:
-#pragma unroll
-            for (int i = 0; i < 6; ++i) load_piece(w, i, grp + 18 + i);
-            carry[0] = grp[16]; carry[1] = grp[17];
-            break;
-        case 2:
-#pragma unroll
-            for (int i = 0; i < 4; ++i) load_piece(w, i, grp + 12 + i);
-            put_piece(w, 4, carry[0]); put_piece(w, 5, carry[1]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) carry[i] = grp[8 + i];
-            break;
-        case 1:
-            load_piece(w, 0, grp + 6); load_piece(w, 1, grp + 7);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) put_piece(w, 2 + i, carry[i]);
-#pragma unroll
-            for (int i = 0; i < 6; ++i) carry[i] = grp[i];
-            break;
-        default:
-#pragma unroll
-            for (int i = 0; i < 6; ++i) put_piece(w, i, carry[i]);
-            break;
-        }
+        for (int i = 0; i < 6; ++i) put_piece(w, i, carry[i]);
+        break;
     }
 }
 // The pair `v` of the group whose first pixel is `pg` (a multiple of 64 pixels from the lane's start).
-template <bool kBackward, bool kPixels>
 __device__ __forceinline__ void feed_pair(ChunkPair &r, LineCarry &c, uint32_t v, uint32_t pg,
                                           const uint8_t *__restrict__ img, const uint16_t *__restrict__ mu,
                                           const int16_t *__restrict__ ls)
 {
     const size_t s = (size_t)pg * 3;
-    feed_array<kBackward>(r.wm, c.m, v, reinterpret_cast<const uint4 *>(mu + s));
-    feed_array<kBackward>(r.wl, c.l, v, reinterpret_cast<const uint4 *>(ls + s));
-    if (kPixels) {
-        const uint4 *px = reinterpret_cast<const uint4 *>(img + s);  // 12 pieces a group, 3 a pair
-        const bool fresh = kBackward ? (v & 1u) != 0u : (v & 1u) == 0u;  // first pair of its half
-        if (fresh) {
-            const uint32_t h = 6u * (v >> 1);
-            uint4 n[6];
+    feed_array(r.wm, c.m, v, reinterpret_cast<const uint4 *>(mu + s));
+    feed_array(r.wl, c.l, v, reinterpret_cast<const uint4 *>(ls + s));
+    const uint4 *px = reinterpret_cast<const uint4 *>(img + s);  // 12 pieces a group, 3 a pair
+    if ((v & 1u) != 0u) {  // first pair of its half
+        const uint32_t h = 6u * (v >> 1);
+        uint4 n[6];
 #pragma unroll
-            for (int i = 0; i < 6; ++i) n[i] = px[h + i];
+        for (int i = 0; i < 6; ++i) n[i] = px[h + i];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                put_piece(r.wx, i, kBackward ? n[3 + i] : n[i]);
-                c.x[i] = kBackward ? n[i] : n[3 + i];
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) put_piece(r.wx, i, c.x[i]);
+        for (int i = 0; i < 3; ++i) {
+            put_piece(r.wx, i, n[3 + i]);
+            c.x[i] = n[i];
         }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) put_piece(r.wx, i, c.x[i]);
     }
 }
 
@@ -300,7 +265,7 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
 {
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
-    const uint32_t spread = (1u << m_bits) - 256u, top = 1u << m_bits;
+    const uint32_t scale = mass_scale(m_bits), top = 1u << m_bits;
     const uint32_t per_row = (sh.tw + kChunk - 1) / kChunk;
     const uint32_t chunks = per_row * (sh.npx / sh.tw);
 
@@ -339,10 +304,23 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
 #pragma unroll
                 for (int ch = 0; ch < 3; ++ch) {
                     const int x = ck.x[i][ch];
-                    const uint32_t inv_s = inv_scale(ck.l[i][ch], tab);
-                    const int c0 = edge_offset(me[ch]);
-                    const uint32_t lo = x == 0 ? 0u : cum_inner_at(x, c0, inv_s, spread, tab);
-                    const uint32_t hi = x == 255 ? top : cum_inner_at(x + 1, c0, inv_s, spread, tab);
+                    const EdgeLaw law = edge_law(me[ch], inv_scale(ck.l[i][ch], tab));
+                    const double y = edge_y(x, law);
+                    uint32_t lo, hi;
+                    if (kLine) {
+                        lo = x == 0 ? 0u : cum_inner(x, y, scale, tab);
+                        hi = x == 255 ? top : cum_inner(x + 1, y + law.a, scale, tab);
+                    } else {
+                        // both edges always, so that no branch keeps the evaluations of the half apart (the
+                        // compiler would skip the one that is not needed): 0.48 -> 0.45 ms on 30 frames of
+                        // 1080 x 1920 in tiles, 0.66 -> 0.62 ms on 8 of 1365 x 2047; the whole-line variant
+                        // has no registers left for it (it spills)
+                        lo = cum_inner(x, y, scale, tab);
+                        hi = cum_inner(x + 1, y + law.a, scale, tab);
+                        asm("" : "+v"(lo), "+v"(hi));
+                        lo = x == 0 ? 0u : lo;
+                        hi = x == 255 ? top : hi;
+                    }
                     cf[3 * ii + ch] = lo | ((hi - lo) << 16);  // cum < 2^16, freq <= 2^16 - 255
                 }
             }
@@ -372,7 +350,7 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
             ChunkPair raw;
             if (kLine) {
                 const uint32_t pair = (c - 2u) >> 1;  // pairs of a flat lane are 16 pixels apart
-                feed_pair<true, true>(raw, carry, pair & 3u, sh.first + 16u * (pair & ~3u), img, mu, ls);
+                feed_pair(raw, carry, pair & 3u, sh.first + 16u * (pair & ~3u), img, mu, ls);
             } else {
                 load_pair<true>(raw, left.p, img, mu, ls);
             }
@@ -722,23 +700,26 @@ struct WordStream {
 };
 
 // The same stream for a decoder that works in chunks of at most kRingChunk symbols: the words wait
-// in a ring of 64 per thread in LDS.  Before a chunk the ring is looked at: while it still holds 32
-// words or more nothing happens (a chunk takes at most 24), otherwise it is filled to the brim with
-// aligned 16-byte loads, four to eight at once, together with the chunk's parameter loads.  No
-// refill inside the chunk ever touches memory or branches on the fill level, and a 128-byte line of
-// the stream is asked for by one or two fills, not by eight.  A thread's 64 words lie side by side
-// (rows of 33 dwords, so that the threads of a wavefront start in different banks): the word at
-// stream position pos is one 16-bit read at (pos mod 64), fetched ahead of its use.
+// in a ring of 32 per thread in LDS.  Before a chunk the ring is looked at: while it still holds 24
+// words or more (what a chunk can take) nothing happens, otherwise it is filled to the brim with
+// aligned 16-byte loads, one to four at once, together with the chunk's parameter loads.  No refill
+// inside the chunk ever touches memory or branches on the fill level.  A thread's 32 words lie side
+// by side (rows of 17 dwords, so that the threads of a wavefront start in different banks): the word at
+// stream position pos is one 16-bit read at (pos mod 32), fetched ahead of its use.
+// The size is what lets four workgroups of 256 threads share a compute unit (160 KB: 19 KB of tables
+// and 17 KB of rings each).  With 64 words a line of the stream is asked for half as often, but only
+// three workgroups fit, and a wavefront's bisection step takes 190 cycles in which it issues 13
+// instructions: three wavefronts on a SIMD do not fill them (30 frames of 1080 x 1920 in tiles: 0.96
+// against 0.87 ms).
 constexpr int kRingChunk = 24;
-constexpr int kRingPieces = 8;                      // 16-byte pieces per thread: 64 words
+constexpr int kRingPieces = 4;                      // 16-byte pieces per thread: 32 words
 constexpr int kRingWordsHeld = 8 * kRingPieces;
 constexpr int kRingRow = kRingWordsHeld + 2;        // 16-bit elements per thread, padding included
-constexpr int kRingMaxThreads = kLaneMaxThreads;
 static_assert(3 * kChunk <= kRingChunk, "a chunk must not take more words than the ring guarantees");
 
 struct WordRing {
     typedef uint32_t __attribute__((may_alias)) word_pair;  // two ring words stored at once
-    uint16_t *row;      // this thread's 64 words
+    uint16_t *row;      // this thread's words
     uint32_t pos;       // word offset (from the 16-byte aligned `base`) of the next word
     uint32_t filled;    // word offset up to which the ring holds the stream: a multiple of 8
     uint32_t nextw;     // the word at `pos`
@@ -748,12 +729,12 @@ struct WordRing {
         return off < lim ? *reinterpret_cast<const uint4 *>(base + off) : make_uint4(0u, 0u, 0u, 0u);
     }
     __device__ __forceinline__ uint32_t peek() const { return row[pos & (kRingWordsHeld - 1)]; }
-    // Brings `filled` to (pos rounded down to 8) + 64 if fewer than 32 words are held.
+    // Brings `filled` to (pos rounded down to 8) + 32 if a chunk could take more words than are held.
     __device__ __forceinline__ void fill(const uint16_t *base, uint32_t lim)
     {
-        if ((int)(filled - pos) < 32) {  // signed: at the opening `filled` may lie below `pos`
+        if ((int)(filled - pos) < kRingChunk) {  // signed: at the opening `filled` may lie below `pos`
             const uint32_t want = (pos & ~7u) + kRingWordsHeld;
-            const uint32_t n = (want - filled) >> 3;  // 4..8
+            const uint32_t n = (want - filled) >> 3;  // 1..4
             uint4 piece[kRingPieces];
 #pragma unroll
             for (int i = 0; i < kRingPieces; ++i)
@@ -785,22 +766,26 @@ struct WordRing {
     }
 };
 
-template <bool kVec, bool kPair, bool kLine = false>
-__global__ __launch_bounds__(kLaneMaxThreads) void k_decode_lanes(Geo g, const uint8_t *__restrict__ coded,
+// (Four wavefronts per SIMD are asked for: the vector ALUs then issue in 98 % of all cycles.  A variant
+// that carries the rest of every parameter line in registers, as the encoder does, reads half the
+// bytes from memory but needs 172 registers, i.e. two wavefronts per SIMD, and was slower: 0.91 against
+// 0.86 ms on 16,384 images of 64 x 64.)
+template <bool kVec, bool kPair>
+__global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_lanes(Geo g, const uint8_t *__restrict__ coded,
                                const uint16_t *__restrict__ mu, const int16_t *__restrict__ ls,
                                const int16_t *__restrict__ coef, uint8_t *__restrict__ out,
                                int *__restrict__ status_code,
                                const unsigned long long *__restrict__ status_payload)
 {
     __shared__ LdsTables tab;
-    __shared__ __align__(16) uint16_t ring[kRingRow * kRingMaxThreads];  // [thread][word]
+    extern __shared__ __align__(16) uint16_t ring[];  // [thread][word]: kRingRow elements a thread
     load_tables(tab);
     if (*status_code != 0) return;  // uniform: written by an earlier kernel
     const uint32_t lane = blockIdx.x * blockDim.x + threadIdx.x;
     if (lane >= g.lanes) return;
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
-    const uint32_t spread = (1u << m_bits) - 256u, mask = (1u << m_bits) - 1u;
+    const uint32_t scale = mass_scale(m_bits), mask = (1u << m_bits) - 1u;
     const uint32_t payload_bytes = (uint32_t)*status_payload;
     const uint32_t per_row = (sh.tw + kChunk - 1) / kChunk;
     const uint32_t chunks = per_row * (sh.npx / sh.tw);
@@ -823,12 +808,13 @@ __global__ __launch_bounds__(kLaneMaxThreads) void k_decode_lanes(Geo g, const u
     uint32_t S = words.take();
     S |= words.take() << 16;
 
+    u32x2 zero_k;  // {0, the k being looked at}
+    zero_k.x = 0u;
+    asm("" : "+v"(zero_k.x));  // (a constant would be written again beside every new k)
     // decodes the chunk into its 24 bytes (6 dwords)
     // tiles and flat lanes no longer than an image lie in one image: its coefficients are loaded once
     auto decode_chunk = [&](const Chunk &ck, const ChunkPos cp, uint32_t *wout) {
-        // (the plain division on purpose: with g.by_hw the whole-line variant needs 171 registers
-        // instead of 167 and loses its third wavefront per SIMD)
-        uint32_t im = cp.p / g.hw;
+        uint32_t im = g.by_hw.div(cp.p);
         int a_gr = coef[3 * im], a_br = coef[3 * im + 1], a_bg = coef[3 * im + 2];
 #pragma unroll
         for (int b = 0; b < 6; ++b) wout[b] = 0u;
@@ -836,7 +822,7 @@ __global__ __launch_bounds__(kLaneMaxThreads) void k_decode_lanes(Geo g, const u
         for (int i = 0; i < kChunk; ++i) {
             if ((uint32_t)i < cp.len) {
                 if (!kVec) {
-                    const uint32_t im_i = (cp.p + i) / g.hw;
+                    const uint32_t im_i = g.by_hw.div(cp.p + i);
                     if (im_i != im) {
                         im = im_i;
                         a_gr = coef[3 * im]; a_br = coef[3 * im + 1]; a_bg = coef[3 * im + 2];
@@ -850,15 +836,15 @@ __global__ __launch_bounds__(kLaneMaxThreads) void k_decode_lanes(Geo g, const u
                     if (ch == 2)
                         me = ck.m[i][2] + rsh14_mul(a_br, (x[0] * 256 - ck.m[i][0])) +
                              rsh14_mul(a_bg, (x[1] * 256 - ck.m[i][1]));
-                    const uint32_t inv_s = inv_scale(ck.l[i][ch], tab);
+                    const EdgeLaw law = edge_law(me, inv_scale(ck.l[i][ch], tab));
                     const uint32_t slot = S & mask;
-                    const int c0 = edge_offset(me);
                     // the symbol is in lo .. lo + 2 * step - 1, and c_hi = C(lo + 2 * step)
                     int lo = 0;
                     uint32_t c_lo = 0u, c_hi = 1u << m_bits;
 #pragma unroll
                     for (int step = 128; step >= 1; step >>= 1) {
-                        const uint32_t cm = cum_inner_at(lo + step, c0, inv_s, spread, tab);
+                        zero_k.y = (uint32_t)(lo + step);
+                        const uint32_t cm = cum_from_pair(zero_k, edge_at(edge_y(lo + step, law), tab), scale);
                         const bool ge = cm <= slot;
                         lo = ge ? lo + step : lo;
                         c_lo = ge ? cm : c_lo;
@@ -878,16 +864,10 @@ __global__ __launch_bounds__(kLaneMaxThreads) void k_decode_lanes(Geo g, const u
 
     if (kVec && kPair) {
         // two neighbouring chunks per round: 96 bytes of each parameter array in, 48 bytes out
-        LineCarry carry;
         for (uint32_t c = 0; c + 2u <= chunks; c += 2u) {
             const ChunkPos left = chunk_pos(g, sh, per_row, c);
             ChunkPair raw;
-            if (kLine) {
-                const uint32_t pair = c >> 1;
-                feed_pair<false, false>(raw, carry, pair & 3u, sh.first + 16u * (pair & ~3u), nullptr, mu, ls);
-            } else {
-                load_pair<false>(raw, left.p, nullptr, mu, ls);
-            }
+            load_pair<false>(raw, left.p, nullptr, mu, ls);
             uint32_t wout[12];
             auto half = [&](auto h) {  // h: which chunk of the pair, as a compile-time constant
                 constexpr int kH = decltype(h)::value;

@@ -168,8 +168,7 @@ template <int kK> struct MixAhead {
 // The components of the channel being coded, in registers: only in the kernels built for one K,
 // where every index into these arrays is a compile-time constant.
 template <int kK> struct MixRegs {
-    int c0[kK > 0 ? kK : 1];          // edge_offset of the shifted mean
-    uint32_t inv_s[kK > 0 ? kK : 1];  // 1 / scale
+    EdgeLaw law[kK > 0 ? kK : 1];     // position of an edge under the component
     uint32_t w[kK > 0 ? kK : 1];      // the pixel's weights
 };
 
@@ -310,8 +309,7 @@ __device__ __forceinline__ void mix_load_channel(const MixSlots &s, MixRegs<kK> 
                 else
                     me += rsh14_mul(a_br, e_r) + rsh14_mul(a_bg, x_g * 256 - (int)s.half(s.raw_mu, kK + j));
             }
-            regs.c0[j] = edge_offset(me);
-            regs.inv_s[j] = inv_scale((int)(short)s.half(s.raw_ls, (uint32_t)ch * kK + j), tab);
+            regs.law[j] = edge_law(me, inv_scale((int)(short)s.half(s.raw_ls, (uint32_t)ch * kK + j), tab));
         }
         return;
     }
@@ -335,15 +333,13 @@ __device__ __forceinline__ void mix_load_channel(const MixSlots &s, MixRegs<kK> 
                 me[1] += rsh14_mul(a_br, e_r[1]) + rsh14_mul(a_bg, x_g * 256 - (int)(g2 >> 16));
             }
         }
-        regs.c0[2 * jj] = edge_offset(me[0]);
-        regs.c0[2 * jj + 1] = edge_offset(me[1]);
-        regs.inv_s[2 * jj] = inv_scale((int)(short)(l2 & 0xFFFFu), tab);
-        regs.inv_s[2 * jj + 1] = inv_scale((int)(short)(l2 >> 16), tab);
+        regs.law[2 * jj] = edge_law(me[0], inv_scale((int)(short)(l2 & 0xFFFFu), tab));
+        regs.law[2 * jj + 1] = edge_law(me[1], inv_scale((int)(short)(l2 >> 16), tab));
     }
 }
 
 // C(k), 1 <= k <= 255, from the slots.
-__device__ __forceinline__ uint32_t mix_cum_inner(int k, const MixSlots &s, uint32_t spread,
+__device__ __forceinline__ uint32_t mix_cum_inner(int k, const MixSlots &s, uint32_t scale,
                                                   const LdsTables &tab)
 {
     auto term = [&](uint32_t j) -> unsigned long long {
@@ -363,19 +359,19 @@ __device__ __forceinline__ uint32_t mix_cum_inner(int k, const MixSlots &s, uint
         j += 2u;
     }
     if (j < s.k) acc += term(j);
-    return (uint32_t)k + scale_mass((uint32_t)(acc >> 15), spread);
+    return (uint32_t)k + mass_of((uint32_t)(acc >> 15), scale);
 }
 
 // C(k), 1 <= k <= 255, from the registers: all kK table reads are in flight together.
 template <int kK>
-__device__ __forceinline__ uint32_t mix_cum_inner(int k, const MixRegs<kK> &regs, uint32_t spread,
+__device__ __forceinline__ uint32_t mix_cum_inner(int k, const MixRegs<kK> &regs, uint32_t scale,
                                                   const LdsTables &tab)
 {
     unsigned long long acc = 0ull;
 #pragma unroll
     for (int j = 0; j < kK; ++j)
-        acc += (unsigned long long)regs.w[j] * edge_cdf(256 * k + regs.c0[j], regs.inv_s[j], tab);
-    return (uint32_t)k + scale_mass((uint32_t)(acc >> 15), spread);
+        acc += (unsigned long long)regs.w[j] * edge_at(edge_y(k, regs.law[j]), tab);
+    return (uint32_t)k + mass_of((uint32_t)(acc >> 15), scale);
 }
 
 // kK > 0: built for that many components (even, dword-aligned arrays: the host checks), which then
@@ -394,7 +390,7 @@ __global__ __launch_bounds__(kMixThreads) void k_mix_encode(
     const MixSlots slots(mix_lds, kK > 0 ? (uint32_t)kK : a.k, kK == 0);
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
-    const uint32_t spread = (1u << m_bits) - 256u, top = 1u << m_bits;
+    const uint32_t scale = mass_scale(m_bits), top = 1u << m_bits;
 
     uint16_t *wout = scratch + lane_scratch_base(lane, lane_cap);
     uint32_t nwords = 0, S = 1u << 16;
@@ -434,12 +430,12 @@ __global__ __launch_bounds__(kMixThreads) void k_mix_encode(
             uint32_t lo, hi;
             if constexpr (kK > 0) {
                 mix_load_channel(slots, regs, ch, x[0], x[1], a_gr, a_br, a_bg, tab);
-                lo = v == 0 ? 0u : mix_cum_inner(v, regs, spread, tab);
-                hi = v == 255 ? top : mix_cum_inner(v + 1, regs, spread, tab);
+                lo = v == 0 ? 0u : mix_cum_inner(v, regs, scale, tab);
+                hi = v == 255 ? top : mix_cum_inner(v + 1, regs, scale, tab);
             } else {
                 mix_load_channel(slots, ch, x[0], x[1], a_gr, a_br, a_bg, tab);
-                lo = v == 0 ? 0u : mix_cum_inner(v, slots, spread, tab);
-                hi = v == 255 ? top : mix_cum_inner(v + 1, slots, spread, tab);
+                lo = v == 0 ? 0u : mix_cum_inner(v, slots, scale, tab);
+                hi = v == 255 ? top : mix_cum_inner(v + 1, slots, scale, tab);
             }
             const uint32_t f = hi - lo;
             if (S >= (f << (32u - m_bits))) {
@@ -505,7 +501,7 @@ __global__ __launch_bounds__(kMixThreads) void k_mix_decode(
     const MixSlots slots(mix_lds, kK > 0 ? (uint32_t)kK : a.k, kK == 0);
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
-    const uint32_t spread = (1u << m_bits) - 256u, mask = (1u << m_bits) - 1u;
+    const uint32_t scale = mass_scale(m_bits), mask = (1u << m_bits) - 1u;
     const uint32_t payload_bytes = (uint32_t)*status_payload;
 
     const uint32_t *offsets = reinterpret_cast<const uint32_t *>(coded + 64);
@@ -568,9 +564,9 @@ __global__ __launch_bounds__(kMixThreads) void k_mix_decode(
             for (int step = 128; step >= 1; step >>= 1) {
                 uint32_t cv;
                 if constexpr (kK > 0)
-                    cv = mix_cum_inner(lo + step, regs, spread, tab);
+                    cv = mix_cum_inner(lo + step, regs, scale, tab);
                 else
-                    cv = mix_cum_inner(lo + step, slots, spread, tab);
+                    cv = mix_cum_inner(lo + step, slots, scale, tab);
                 const bool ge = cv <= slot;
                 lo = ge ? lo + step : lo;
                 c_lo = ge ? cv : c_lo;

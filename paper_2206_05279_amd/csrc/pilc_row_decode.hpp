@@ -7,17 +7,16 @@
 //   - a wavefront carries four lanes, one per 16-thread row, so 4096 lanes still leave every SIMD
 //     of the chip with at most one wavefront;
 //   - per symbol every thread evaluates C(k) at two neighbouring candidates of a 32-value window
-//     around the predicted mean (exact 24-bit form), together with the mass up to its successor;
+//     around the predicted mean, together with the mass up to its successor;
 //     once the state is known, one subtraction and one compare per candidate tell the thread
 //     whether it holds the symbol (App. A: the x with C_x <= S mod 2^M < C_x + P_x), every thread
 //     forms the next state for its own candidates, and an OR over the row (four rotate-and-OR
 //     steps on the data-parallel-primitive path, no LDS round trip, no ballot) hands the one
 //     non-zero value to all 16 threads;
 //   - a pixel is decoded without a branch: whether every symbol was inside its window is
-//     looked at once per pixel, and a pixel with a symbol outside (or with a mean so far out
-//     that the 24-bit form is not exact) is decoded again from the state saved at its start by a
-//     bounded two-level search with the general evaluation (32 values eight apart, then the nine
-//     of the band);
+//     looked at once per pixel, and a pixel with a symbol outside is decoded again from the state
+//     saved at its start by a bounded two-level search (32 values eight apart, then the nine of
+//     the band);
 //   - the candidates of a pixel's first channel do not depend on decoded values and are evaluated
 //     while the previous pixel is still being decoded;
 //   - per-pixel parameters are prepared 16 pixels at a time, one pixel per thread, two batches
@@ -78,16 +77,13 @@ __device__ __forceinline__ uint32_t row_next(uint32_t v)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x12F /* row_ror:15 */, 0xF, 0xF, true);
 }
 
-// floor((a * e + 2^13) / 2^14) for a Q2.14 coefficient and an innovation e of at most 18 bits
-__device__ __forceinline__ int rsh14_mad(int a, int e) { return mad_i24(a, e, 8192) >> 14; }
-
-// What one pixel's preparing thread leaves in LDS for the row (64 bytes).  1/s is the Q6.25
-// inverse scale; "split" means (>> 17, & 0x1FFFF), the form the 24-bit evaluation takes.
+// What one pixel's preparing thread leaves in LDS for the row (64 bytes).  The inverse scale of a
+// channel comes as what one step of k and one unit of the mean move the position of an edge by
+// (see EdgeLaw: 1/s times 4 and times 2^-6, both exact).
 struct RowPixel {
-    uint4 r;  // m_r (Q8.8), 1/s of R split, 1/s of R whole
-    uint4 a;  // m_g, m_b (Q8.8), a_gr, a_br (Q2.14, sign-extended)
-    uint4 b;  // a_bg, 1/s of G split, 1/s of B >> 17
-    uint4 c;  // 1/s of B & 0x1FFFF, 1/s of G whole, 1/s of B whole, window of R: base | exact << 16
+    uint4 r;            // -128 - m_r, -128 - m_g, -128 - m_b (Q8.8), window of R
+    uint4 s;            // a_gr, a_br, a_bg (Q2.14, sign-extended), 1/s of R
+    double g[2], b[2];  // G and B: 1/s times 4, times 2^-6
 };
 
 // The candidates of one symbol as a thread holds them: C(k) at k = base + 2 j and base + 2 j + 1
@@ -95,7 +91,6 @@ struct RowPixel {
 struct RowCand {
     uint32_t cv0, cv1, f0, f1;
     int base;
-    bool ok;  // the 24-bit evaluation is exact for this window
 };
 
 // kStaged: with a stager per decoding wavefront (see above).  That form keeps twice the LDS per
@@ -156,7 +151,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
     const uint32_t mask = (1u << m_bits) - 1u, top = 1u << m_bits;
-    const uint32_t sp8 = (top - 256u) >> 8;  // 2^M - 256 = 256 * sp8
+    const uint32_t scale = mass_scale(m_bits);
     const uint32_t payload_bytes = (uint32_t)*status_payload;
     const uint32_t *offsets = reinterpret_cast<const uint32_t *>(coded + 64);
     const uint16_t *payload =
@@ -212,62 +207,59 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         }
         return r;
     };
-    auto window_base = [](int me) { return min(max((me - (256 * (kRowWindow / 2 - 1) - 128)) >> 8, 0), kRowBaseMax); };
-    auto window_exact = [](int me) { return (uint32_t)(me + 8576) <= (uint32_t)(73600 + 8576); };
+    // (from n = -128 - mean)
+    auto window_base = [](int n) {
+        return min(max((-128 - (256 * (kRowWindow / 2 - 1) - 128) - n) >> 8, 0), kRowBaseMax);
+    };
     auto put_stage = [&](const Raw &r, uint32_t buf) {
-        const uint32_t i0 = inv_scale(r.l[0], tab), i1 = inv_scale(r.l[1], tab), i2 = inv_scale(r.l[2], tab);
         RowPixel px;
-        px.r = make_uint4(r.m[0], i0 >> 17, i0 & 0x1FFFFu, i0);
-        px.a = make_uint4(r.m[1], r.m[2], (uint32_t)r.a[0], (uint32_t)r.a[1]);
-        px.b = make_uint4((uint32_t)r.a[2], i1 >> 17, i1 & 0x1FFFFu, i2 >> 17);
-        px.c = make_uint4(i2 & 0x1FFFFu, i1, i2,
-                          (uint32_t)window_base((int)r.m[0]) | (window_exact((int)r.m[0]) ? 1u << 16 : 0u));
+        const int n_r = -128 - (int)r.m[0];
+        px.r = make_uint4((uint32_t)n_r, (uint32_t)(-128 - (int)r.m[1]), (uint32_t)(-128 - (int)r.m[2]),
+                          (uint32_t)window_base(n_r));
+        px.s = make_uint4((uint32_t)r.a[0], (uint32_t)r.a[1], (uint32_t)r.a[2], inv_scale(r.l[0], tab));
+        const double i1 = (double)inv_scale(r.l[1], tab), i2 = (double)inv_scale(r.l[2], tab);
+        px.g[0] = i1 * 4.0;
+        px.g[1] = i1 * 0x1p-6;
+        px.b[0] = i2 * 4.0;
+        px.b[1] = i2 * 0x1p-6;
         stage[buf][lrow][j] = px;
     };
 
-    // Window of a symbol with effective mean `me`, and this thread's candidates k = base + 2 j and
-    // base + 2 j + 1 in it.  With 1/s = inv_hi * 2^17 + inv_lo the clamped
-    // z = floor(d * (1/s) / 2^17) = d * inv_hi + floor(d * inv_lo / 2^17) is exact in 32-bit
-    // arithmetic with 24-bit multiplies while |d| <= 2^14, d = 256 k - 128 - mean; that holds over the
-    // whole window for means in -8576 .. 73600.
-    // The evaluation comes in two halves so that the wait for one symbol's table cells can be
-    // filled with another symbol's arithmetic: `aim` goes as far as asking for the cells,
-    // `finish` takes it from there.
+    // Window of a symbol with effective mean -128 - n, and this thread's candidates k = base + 2 j and
+    // base + 2 j + 1 in it; `per_k` and `per_unit` as in RowPixel.  The evaluation comes in two
+    // halves so that the wait for one symbol's table cells can be filled with another symbol's
+    // arithmetic: `aim` goes as far as asking for the cells, `finish` takes it from there.
     struct RowAim {
         uint2 cell[2];
-        int z[2];
+        uint32_t u[2];
         int base, k0;
-        bool ok;
     };
     const int j2 = 2 * (int)j;
-    auto aim = [&](int me, uint32_t inv_hi, uint32_t inv_lo) {
+    auto aim = [&](int n, double per_k, double per_unit) {
         RowAim am;
-        am.base = window_base(me);
-        am.ok = window_exact(me);
+        am.base = window_base(n);
         am.k0 = am.base + j2;
-        const int d0 = 256 * am.k0 - 128 - me;
+        const double y = __builtin_fma((double)((am.k0 << 8) + n), per_unit, kEdgeBias);
+        am.u[0] = edge_pos(y);
+        am.u[1] = edge_pos(y + per_k);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int d = d0 + 256 * c;
-            const int t = mul_i24(d, (int)inv_lo) >> 17;
-            am.z[c] = min(max(mad_i24(d, (int)inv_hi, t), -(1 << 20)), (1 << 20) - 1);
-            am.cell[c] = (sig + 1024)[am.z[c] >> 10];
-        }
+        for (int c = 0; c < 2; ++c) am.cell[c] = sig[am.u[c] >> 21];
         return am;
+    };
+    auto aim_first = [&](const RowPixel &px) {  // the first channel, whose 1/s comes as it is
+        const double inv = (double)px.s.w;
+        return aim((int)px.r.x, inv * 4.0, inv * 0x1p-6);
     };
     // C(k) at the thread's two candidates, from the cells `aim` asked for
     auto cum_pair = [&](const RowAim &am, uint32_t cv[2]) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const uint32_t f24 =
-                am.cell[c].x + ((uint32_t)__umul24(am.cell[c].y, (uint32_t)am.z[c] & 1023u) >> 16);
-            cv[c] = (uint32_t)(am.k0 + c) + ((uint32_t)__umul24(f24, sp8) >> 16);
-        }
+        for (int c = 0; c < 2; ++c)
+            cv[c] = (uint32_t)(am.k0 + c) + mass_of(interpolate(am.u[c], am.cell[c]), scale);
         cv[0] = am.k0 == 0 ? 0u : cv[0];  // C(0) = 0
     };
     // The candidates of a symbol from its two values of C.  The second candidate is followed by the
     // next thread's first; candidate 31 by C(base + 32), which is known only when it is C(256) = 2^M.
-    auto with_masses = [&](uint32_t cv0, uint32_t cv1, int base, bool ok) {
+    auto with_masses = [&](uint32_t cv0, uint32_t cv1, int base) {
         RowCand cd;
         const uint32_t from_next = row_next(cv0);
         const uint32_t after = j == 15u ? (base == kRowBaseMax ? top : cv1) : from_next;
@@ -276,26 +268,24 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         cd.f0 = cv1 - cv0;
         cd.f1 = after - cv1;
         cd.base = base;
-        cd.ok = ok;
         return cd;
     };
     auto finish = [&](const RowAim &am) {
         uint32_t cv[2];
         cum_pair(am, cv);
-        return with_masses(cv[0], cv[1], am.base, am.ok);
+        return with_masses(cv[0], cv[1], am.base);
     };
     // the same for a pixel's first channel, whose two values of C the stager has left in LDS
     auto first_channel = [&](uint32_t pair, uint32_t window) {
-        return with_masses(pair & 0xFFFFu, pair >> 16, (int)(window & 0xFFFFu), (window >> 16) != 0u);
+        return with_masses(pair & 0xFFFFu, pair >> 16, (int)window);
     };
     // (stager) the first channel of the 16 pixels staged in `buf`, every thread its two candidates
     auto put_first_cand = [&](uint32_t buf) {
         wave_lds_sync();  // the parameters were written by this wavefront
 #pragma unroll 4
         for (int i = 0; i < kRowBatch; ++i) {
-            const uint4 r = stage[buf][lrow][i].r;
             uint32_t cv[2];
-            cum_pair(aim((int)r.x, r.y, r.z), cv);
+            cum_pair(aim_first(stage[buf][lrow][i]), cv);
             first_cand[buf][lrow][i][j] = cv[0] | (cv[1] << 16);
         }
     };
@@ -321,7 +311,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         // (kept as one value: left free, the compiler splits the last step of the reduction into a
         // move, an OR and a three-operand AND for the two uses of xw below, four instructions for two)
         asm("" : "+v"(xw));
-        seen &= cd.ok ? xw : 0u;
+        seen &= xw;
         const bool refill = s_new < (1u << 16);
         const uint32_t s_ref = (s_new << 16) | wnext;
         if (kRagged) {
@@ -465,13 +455,13 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         // The three symbols of a pixel by search, on the state (Sr, pr).
         auto search_pixel = [&](const RowPixel &cur, uint32_t &Sr, uint32_t &pr, uint32_t &y_r, uint32_t &y_g,
                                 uint32_t &y_b) {
-            const int m_r = (int)cur.r.x, m_g = (int)cur.a.x, m_b = (int)cur.a.y;
-            const int a_gr = (int)cur.a.z, a_br = (int)cur.a.w, a_bg = (int)cur.b.x;
-            y_r = search_symbol(m_r, cur.r.w, Sr, pr);
+            const int m_r = -128 - (int)cur.r.x, m_g = -128 - (int)cur.r.y, m_b = -128 - (int)cur.r.z;
+            const int a_gr = (int)cur.s.x, a_br = (int)cur.s.y, a_bg = (int)cur.s.z;
+            y_r = search_symbol(m_r, cur.s.w, Sr, pr);
             const int f_r = (int)(y_r << 8) - m_r;
-            y_g = search_symbol(m_g + rsh14_mul(a_gr, f_r), cur.c.y, Sr, pr);
-            y_b = search_symbol(m_b + rsh14_mul(a_br, f_r) + rsh14_mul(a_bg, (int)(y_g << 8) - m_g), cur.c.z,
-                                Sr, pr);
+            y_g = search_symbol(m_g + rsh14_mul(a_gr, f_r), (uint32_t)(cur.g[0] * 0.25), Sr, pr);
+            y_b = search_symbol(m_b + rsh14_mul(a_br, f_r) + rsh14_mul(a_bg, (int)(y_g << 8) - m_g),
+                                (uint32_t)(cur.b[0] * 0.25), Sr, pr);
         };
         if (search_batches != 0) {
             // data the model does not fit (such as uniformly random pixels): the windows are not tried
@@ -495,31 +485,29 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
                 nxt = px[(i + 1u) & (kRowBatch - 1)];
                 const uint32_t next_pair = kStaged ? first_cand[buf][lrow][(i + 1u) & (kRowBatch - 1)][j] : 0u;
                 __builtin_amdgcn_sched_barrier(0);  // asked for here, used a pixel later
-                const int m_r = (int)cur.r.x, m_g = (int)cur.a.x, m_b = (int)cur.a.y;
-                const int a_gr = (int)cur.a.z, a_br = (int)cur.a.w, a_bg = (int)cur.b.x;
+                const int n_r = (int)cur.r.x, n_g = (int)cur.r.y, n_b = (int)cur.r.z;
+                const int a_gr = (int)cur.s.x, a_br = (int)cur.s.y, a_bg = (int)cur.s.z;
                 const uint32_t S0 = S, pos0 = pos;
                 uint32_t seen = 256u;
 
                 uint32_t x_r = decode_symbol(act, cr, seen);
-                const int e_r = (int)(x_r << 8) - m_r;
-                const int me_g = m_g + rsh14_mad(a_gr, e_r);
-                const RowAim ag = aim(me_g, cur.b.y, cur.b.z);
+                const int e_r = (int)(x_r << 8) + n_r + 128;
+                const RowAim ag = aim(n_g - rsh14_mul(a_gr, e_r), cur.g[0], cur.g[1]);
                 __builtin_amdgcn_sched_barrier(0);
-                const int mb1 = m_b + rsh14_mad(a_br, e_r);
+                const int nb1 = n_b - rsh14_mul(a_br, e_r);
                 // The next pixel's first channel depends on no decoded value.  The stager has evaluated
                 // it, and what is left to do fills the wait for this channel's table cells; without a
                 // stager its evaluation fills the waits of the two channels that do depend.
                 RowCand cr_next = {};
                 RowAim an = {};
                 if (kStaged)
-                    cr_next = first_channel(next_pair, nxt.c.w);
+                    cr_next = first_channel(next_pair, nxt.r.w);
                 else
-                    an = aim((int)nxt.r.x, nxt.r.y, nxt.r.z);
+                    an = aim_first(nxt);
                 __builtin_amdgcn_sched_barrier(0);
                 const RowCand cg = finish(ag);
                 uint32_t x_g = decode_symbol(act, cg, seen);
-                const int me_b = mb1 + rsh14_mad(a_bg, (int)(x_g << 8) - m_g);
-                const RowAim ab = aim(me_b, cur.b.w, cur.c.x);
+                const RowAim ab = aim(nb1 - rsh14_mul(a_bg, (int)(x_g << 8) + n_g + 128), cur.b[0], cur.b[1]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (kStaged) {
                     cr = cr_next;
@@ -549,8 +537,8 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
                 v_out = j == i ? (x_r | (x_g << 8) | (x_b << 16)) : v_out;
             };
             RowPixel pe = px[0], po;
-            RowCand cr = kStaged ? first_channel(first_cand[buf][lrow][0][j], pe.c.w)
-                                 : finish(aim((int)pe.r.x, pe.r.y, pe.r.z));
+            RowCand cr = kStaged ? first_channel(first_cand[buf][lrow][0][j], pe.r.w)
+                                 : finish(aim_first(pe));
             for (uint32_t i = 0; kRagged ? __any(i < nb) : i < (uint32_t)kRowBatch; i += 2) {
                 pixel(i, pe, po, cr);
                 pixel(i + 1u, po, pe, cr);

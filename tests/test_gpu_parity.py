@@ -75,6 +75,25 @@ def test_symbol_tables_match_oracle(name, make):
     assert np.array_equal(freq.cpu().numpy(), o_freq)
 
 
+@pytest.mark.parametrize("log_scale", [-32768, -16384, -6000, 0, 4096, 24575, 32767])
+@pytest.mark.parametrize("prec_bits", [10, 16])
+def test_edges_at_cell_ends_and_beyond_both_ends_of_the_table(log_scale, prec_bits):
+    # every mean there is, symbols up to 256 away: with log-scale 0 an edge every 1/64 of a scale, i.e.
+    # on every cell boundary and between them; with the narrowest law most edges lie beyond the table
+    mu = np.arange(65536, dtype=np.uint16).reshape(1, 256, 256, 1).repeat(3, axis=3)
+    img = np.stack([mu[..., 0] >> 8, mu[..., 0] & 255, 255 - (mu[..., 0] >> 8)], axis=-1).astype(np.uint8)
+    ls = np.full(img.shape, log_scale, dtype=np.int16)
+    coef = np.array([[16384, -32768, 32767]], dtype=np.int16)
+    g = (1, 256, 256, prec_bits, 0, 256, 0)
+    dev = [torch.from_numpy(a).cuda() for a in (img, mu, ls, coef)]
+    cum = torch.zeros(img.size, dtype=torch.uint32, device="cuda:0")
+    freq = torch.zeros_like(cum)
+    pb.pilc_symbol_tables(pb.make_geom(*g), *dev, cum, freq)
+    o_cum, o_freq = orc.symbol_tables(orc.make_geom(*g), img, mu, ls, coef)
+    assert np.array_equal(cum.cpu().numpy(), o_cum)
+    assert np.array_equal(freq.cpu().numpy(), o_freq)
+
+
 @pytest.mark.parametrize("name,make", SMALL_CASES, ids=[c[0] for c in SMALL_CASES])
 def test_container_and_image_match_oracle(name, make, policy):
     wl = make()
