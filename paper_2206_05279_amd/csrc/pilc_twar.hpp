@@ -4,7 +4,7 @@
 //   G(u,v)                from G(u,v-1),   R(u,v-1), R(u,v)     (left G, left R, this pixel's R)
 //   B(u,v)                from B(u,v-1),   G(u,v-1), G(u,v)     (left B, left G, this pixel's G)
 // with three weights and a bias each, zero padding above and to the left, and the residual
-// r = (x - x^) mod 256.  Forward, every pixel is independent (k_twar_forward).  Inverse, a pixel
+// r = (x - x^) mod 256.  Forward, every pixel is independent (k_twar_forward4, k_twar_forward_any).  Inverse, a pixel
 // needs its left, upper and upper-left neighbours: the paper's schedule runs the red channel along
 // anti-diagonals and then green and blue column by column; here a wavefront takes 64 rows, one
 // per thread, and walks the anti-diagonals once, recovering R, G and B of a pixel in the same
@@ -50,39 +50,6 @@ __device__ __forceinline__ int add_byte_of(uint32_t a, int b)
     else
         asm("v_add_u32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD" : "=v"(r) : "v"(a), "v"(b));
     return r;
-}
-
-// One thread per pixel.  A workgroup takes 256 / w whole rows (or one row, in steps of 256
-// pixels, when w > 256); neighbouring threads read neighbouring bytes and the row above comes from
-// the caches.
-__global__ __launch_bounds__(256) void k_twar_forward(TwarK p, uint32_t rows, uint32_t h, uint32_t w,
-                                                      uint32_t rows_per_block,
-                                                      const uint8_t *__restrict__ img,
-                                                      uint8_t *__restrict__ res)
-{
-    const uint32_t local = threadIdx.x / w, v0 = threadIdx.x % w;
-    const uint32_t row = blockIdx.x * rows_per_block + local;
-    if (local >= rows_per_block || row >= rows) return;
-    const uint32_t u = row % h;
-    const size_t row_off = (size_t)row * w * 3u;
-    for (uint32_t v = v0; v < w; v += 256u) {  // one turn unless w > 256
-        const uint8_t *x = img + row_off + 3u * v;
-        const int r0 = x[0], g0 = x[1], b0 = x[2];
-        int rl = 0, gl = 0, bl = 0, ru = 0, rul = 0;
-        if (v > 0) {
-            rl = x[-3];
-            gl = x[-2];
-            bl = x[-1];
-        }
-        if (u > 0) {
-            ru = x[-3ll * (long long)w];
-            if (v > 0) rul = x[-3ll * (long long)w - 3];
-        }
-        uint8_t *o = res + row_off + 3u * v;
-        o[0] = (uint8_t)(r0 - twar_predict(p, 0, rul, ru, rl));
-        o[1] = (uint8_t)(g0 - twar_predict(p, 1, gl, rl, r0));
-        o[2] = (uint8_t)(b0 - twar_predict(p, 2, bl, gl, g0));
-    }
 }
 
 // Byte b (-4 <= b < 12) of the 16 bytes {prev, c0, c1, c2}, b = 0 being the first byte of c0.
@@ -143,6 +110,73 @@ __global__ __launch_bounds__(256) void k_twar_forward4(TwarK p, uint32_t groups,
     o[2] = out[2];
 }
 
+// The same four pixels a thread for rows of any width at any address: the groups are counted through the
+// rows without regard to where one ends, and every pixel knows its own place.  Bound by memory
+// (a byte at a time, a pixel a thread, 16 images of 1365 x 2047 took 168 us and 40,000 of 31 x 33 166; now
+// 66 and 60 us, 4.0 and 4.1 TB/s read and written).  `first_row`: the flat row the launch starts with,
+// `pixels`: how many it has.
+__global__ __launch_bounds__(256) void k_twar_forward_any(TwarK p, uint32_t first_row, uint32_t pixels, FastDiv by_h,
+                                                          FastDiv by_w, const uint8_t *__restrict__ img,
+                                                          uint8_t *__restrict__ res)
+{
+    const uint32_t q = 4u * (blockIdx.x * blockDim.x + threadIdx.x);
+    if (q >= pixels) return;
+    const uint32_t w = by_w.d, h = by_h.d;
+    const uint32_t in = by_w.div(q), row = first_row + in;
+    uint32_t v = q - in * w, u = row - by_h.div(row) * h;
+    const size_t off = ((size_t)first_row * w + q) * 3u;
+    const uint8_t *x = img + off;
+    uint32_t c[4], a[4];  // the four pixels with the four bytes before them, and the same of the row above
+    const uint32_t here = min(4u, pixels - q);
+    if (here == 4u && off >= (size_t)3u * w + 4u) {
+        __builtin_memcpy(c, x - 4, 16);
+        __builtin_memcpy(a, x - 3 * (size_t)w - 4, 16);
+    } else {  // the first row of all and the last pixels of all: bytes that are not there are never used
+        uint8_t cb[16] = {}, ab[16] = {};
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            if (off + k >= 4u && (uint32_t)k < 4u + 3u * here) cb[k] = x[k - 4];
+            if (off + k >= (size_t)3u * w + 4u && (uint32_t)k < 4u + 3u * here) ab[k] = x[k - 4 - 3ll * w];
+        }
+        __builtin_memcpy(c, cb, 16);
+        __builtin_memcpy(a, ab, 16);
+    }
+    uint32_t out[3] = {0u, 0u, 0u};
+#define PILC_TWAR_PIXEL(J)                                                                         \
+    {                                                                                              \
+        const bool left = v != 0u, up = u != 0u;                                                   \
+        const int r0 = byte_at<3 * J>(c[0], c[1], c[2], c[3]), g0 = byte_at<3 * J + 1>(c[0], c[1], c[2], c[3]); \
+        const int b0 = byte_at<3 * J + 2>(c[0], c[1], c[2], c[3]);                                 \
+        const int rl = left ? byte_at<3 * J - 3>(c[0], c[1], c[2], c[3]) : 0;                      \
+        const int gl = left ? byte_at<3 * J - 2>(c[0], c[1], c[2], c[3]) : 0;                      \
+        const int bl = left ? byte_at<3 * J - 1>(c[0], c[1], c[2], c[3]) : 0;                      \
+        const int ru = up ? byte_at<3 * J>(a[0], a[1], a[2], a[3]) : 0;                            \
+        const int rul = up && left ? byte_at<3 * J - 3>(a[0], a[1], a[2], a[3]) : 0;               \
+        const uint32_t e0 = (uint32_t)(r0 - twar_predict(p, 0, rul, ru, rl)) & 255u;               \
+        const uint32_t e1 = (uint32_t)(g0 - twar_predict(p, 1, gl, rl, r0)) & 255u;                \
+        const uint32_t e2 = (uint32_t)(b0 - twar_predict(p, 2, bl, gl, g0)) & 255u;                \
+        out[(3 * J) >> 2] |= e0 << (8 * ((3 * J) & 3));                                            \
+        out[(3 * J + 1) >> 2] |= e1 << (8 * ((3 * J + 1) & 3));                                    \
+        out[(3 * J + 2) >> 2] |= e2 << (8 * ((3 * J + 2) & 3));                                    \
+        const bool wraps = v + 1u == w;                                                            \
+        v = wraps ? 0u : v + 1u;                                                                   \
+        u = wraps ? (u + 1u == h ? 0u : u + 1u) : u;                                               \
+    }
+    PILC_TWAR_PIXEL(0)
+    PILC_TWAR_PIXEL(1)
+    PILC_TWAR_PIXEL(2)
+    PILC_TWAR_PIXEL(3)
+#undef PILC_TWAR_PIXEL
+    uint8_t *o = res + off;
+    if (here == 4u) {
+        __builtin_memcpy(o, out, 12);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+            if ((uint32_t)k < 3u * here) o[k] = (uint8_t)(out[k >> 2] >> (8 * (k & 3)));
+    }
+}
+
 // A flat copy by one wavefront: `total` >= 1 elements, element lane + 64 i, four of them a turn, so
 // that four loads are under way together (taken one at a time, every load waits for the one
 // before).  Loads past the end read the last element again instead of being skipped (a register
@@ -163,15 +197,14 @@ __device__ __forceinline__ void flat_copy(const T *__restrict__ src, T *__restri
 
 // A wavefront per group of up to 64 rows: whole images when h <= 64 (64 / h of them side by side),
 // else the bands of 64 rows of one image one after the other, the last row's red values of a band
-// kept in LDS for the first row of the next.  kTile: the group's residuals are copied to LDS
+// kept in LDS for the first row of the next.  The group's residuals are copied to LDS
 // first and the pixels copied back at the end, so that global memory only sees whole, coalesced
-// rows; without it every thread reads and writes its row in place in global memory.  The tile is
-// the group exactly as it lies in memory (its rows are contiguous there), copied as a flat run of
+// rows.  The tile is the group exactly as it lies in memory (its rows are contiguous there), copied as a flat run of
 // elements of type T (16 bytes, 4 bytes or single bytes: what the sizes and addresses allow); the
 // skew between rows keeps the threads' accesses on different banks without any padding.
 constexpr int kTwarWaves = 4;
 
-template <bool kTile, typename T>
+template <typename T>
 __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint32_t n, uint32_t h,
                                                                   uint32_t w, uint32_t last_bytes,
                                                                   const uint8_t *__restrict__ res,
@@ -186,7 +219,7 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
     const uint32_t bands = h <= 64u ? 1u : (h + 63u) / 64u;
     // LDS of this wavefront: [last_bytes >= w, a multiple of 16: red values of the row above a band][tile]
     const uint32_t row_stride = 3u * w;
-    uint8_t *lastrow = twar_lds + (size_t)wave * (last_bytes + (kTile ? 64u * row_stride : 0u));
+    uint8_t *lastrow = twar_lds + (size_t)wave * (last_bytes + 64u * row_stride);
     uint8_t *tile = lastrow + last_bytes;
     const size_t row_bytes = (size_t)w * 3u;
 
@@ -203,9 +236,8 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
             u = band * 64u + lane;
             have = u < h;
         }
-        const size_t row_off = ((size_t)image * h + u) * row_bytes;
         const uint32_t rows_here = h <= 64u ? min(per, n - g * per) * h : min(64u, h - band * 64u);
-        if (kTile) {  // the group's rows are contiguous in memory: copy them row by row
+        {  // the group's rows are contiguous in memory: copy them row by row
             const size_t first = h <= 64u ? (size_t)g * per * h * row_bytes : ((size_t)g * h + band * 64u) * row_bytes;
             wave_lds_sync();
             flat_copy(reinterpret_cast<const T *>(res + first), reinterpret_cast<T *>(tile),
@@ -233,18 +265,8 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
             const bool on = have && v >= 0 && v < (int)w;
             if (from_lds && on) up = lastrow[v];
             if (on) {
-                int r0, r1, r2;
-                if (kTile) {
-                    const uint8_t *s = tile + lane * row_stride + 3u * v;
-                    r0 = s[0];
-                    r1 = s[1];
-                    r2 = s[2];
-                } else {
-                    const uint8_t *s = res + row_off + 3u * v;
-                    r0 = s[0];
-                    r1 = s[1];
-                    r2 = s[2];
-                }
+                const uint8_t *s = tile + lane * row_stride + 3u * v;
+                const int r0 = s[0], r1 = s[1], r2 = s[2];
                 // Three multiply-adds each.  What only needs the pixel to the left comes first, so
                 // that each new value can take the place of the one it replaces; the operand that
                 // arrives last (the value just decoded) goes into the last multiply-add.
@@ -255,17 +277,10 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
                 const int xr = add_low_byte(r0, clamp8(__mul24(p.w[0][2], rl) + tr));
                 const int xg = add_low_byte(r1, clamp8(__mul24(p.w[1][2], xr) + tg));
                 const int xb = add_low_byte(r2, clamp8(__mul24(p.w[2][2], xg) + tb));
-                if (kTile) {
-                    uint8_t *o = tile + lane * row_stride + 3u * v;
-                    o[0] = (uint8_t)xr;
-                    o[1] = (uint8_t)xg;
-                    o[2] = (uint8_t)xb;
-                } else {
-                    uint8_t *o = img + row_off + 3u * v;
-                    o[0] = (uint8_t)xr;
-                    o[1] = (uint8_t)xg;
-                    o[2] = (uint8_t)xb;
-                }
+                uint8_t *o = tile + lane * row_stride + 3u * v;
+                o[0] = (uint8_t)xr;
+                o[1] = (uint8_t)xg;
+                o[2] = (uint8_t)xb;
                 // the last row of a band leaves its red values for the next band; it runs 63
                 // positions behind the first row's reads of the same buffer
                 if (bands > 1u && lane == 63u) lastrow[v] = (uint8_t)xr;
@@ -275,7 +290,7 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
                 bl = xb;
             }
         }
-        if (kTile) {
+        {
             const size_t first = h <= 64u ? (size_t)g * per * h * row_bytes : ((size_t)g * h + band * 64u) * row_bytes;
             wave_lds_sync();
             flat_copy(reinterpret_cast<const T *>(tile), reinterpret_cast<T *>(img + first),
@@ -285,399 +300,533 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
     }
 }
 
-// Images taller than 64 rows whose rows are whole 16-pixel chunks in 16-byte aligned arrays: a
-// thread per row, every wavefront 64 rows, all wavefronts of a workgroup under way at once.
-// Thread t of the workgroup runs t + 16 (t / 64) positions behind thread 0, so inside a wavefront
-// a row still gets the two values it needs from the row above by a cross-lane shift, and the first
-// row of a wavefront finds them in LDS, where the last row of the wavefront above left them 17
-// steps earlier; a workgroup barrier every 16 steps separates the two.  A row passes through a
-// three-chunk ring in LDS (a chunk is 16 pixels, 48 bytes): the chunk the row is in, the next one,
-// and the one it left, which is written back and then filled again; what is to fill it was asked
-// for a turn earlier and waits in registers.  The chunks of a wavefront's 64 rows are moved as 192
-// pieces of 16 bytes, three neighbouring threads taking the 48 contiguous bytes of one row.  The
-// work goes in blocks of 16 steps: barrier, chunk turn, then 16 steps without a branch on anything
-// but the loop count (a step used to spend more time in its dozen branches than in its arithmetic).
+// Everything that does not fit the tile kernel (images taller than 64 rows, or rows wider than a
+// tile's): the walk along the anti-diagonals with a wavefront per colour channel.
 //
-// kBands false: a workgroup per image, every wavefront turns the chunks of its own rows before its
-// 16 steps; images with more rows than a workgroup has threads go in rounds, the last row's red
-// values of a round kept in LDS for the first row of the next.
-// kBands true (few images): an image is cut into bands of rows, a workgroup per band, so that one
-// image keeps several compute units busy.  Here the workgroup has a second set of wavefronts, the
-// movers: mover k turns the chunks of wavefront k's rows while wavefront k decodes (with one
-// or two decoding wavefronts on a SIMD a turn's trip to memory and back, a third of a block's
-// time, is not hidden by anything else).  The first row of a band needs the red values of the last
-// row of the band above, which belongs to another workgroup: the mover of that row publishes, after
-// every chunk it has written back to the image, how many chunks of the row are final (a counter per
-// band in global memory; the row's bytes and the count are stored at device scope, the count once
-// no store of the wavefront is outstanding), and three threads of the first mover of the band below
-// fetch the chunk of that row two chunks ahead of their first row from the image as soon as the
-// counter allows (acquire at device scope).  Bands number themselves with a ticket taken at
-// their start (image-major), so the band above is always a workgroup that is already running, and
-// it never waits for the band below.  The wait is bounded by the constant-rate clock; a band that
-// gives up sets an abort word, every band that sees it while waiting leaves too, and the host
-// returns PILC_E_TIMEOUT.
-constexpr int kTallLag = 16;         // steps between barriers = extra lag per wavefront
-constexpr int kTallChunk = 48;       // bytes of a chunk of 16 pixels
-constexpr int kTallRing = 3 * kTallChunk;
-constexpr int kTallStride = kTallRing + 4;  // LDS bytes per thread: 37 dwords, odd
-constexpr int kTallMaxThreads = 768;
-constexpr int kTallLead = 32;        // steps a wavefront runs before its first pixel (two chunk turns)
-// a band's progress counter has a 128-byte line to itself (32 words): the band below polls it while
-// the band's own mover writes it
-constexpr uint32_t kBandStride = 32;
+// What bounds this is the chain of the red channel: an image takes at least w + h dependent steps,
+// however many threads work on it.  Only red needs the row above; green and blue of a row need that
+// row alone.  So the channels of 64 rows (a thread per row) are decoded by three wavefronts, green
+// a block of 16 columns behind red and blue a block behind green, and moving the data is the
+// business of two more, one that fetches residuals four blocks ahead and one that stores pixels.
+// A red step is then eight vector instructions, and a block of 16 takes 1210 cycles, barrier included.
+// (One wavefront that did all three channels took 280 cycles a step: 30 frames of 1080 x 1920 487 us,
+// now 265; and rows that were not whole 16-byte pieces went 64 at a time through one wavefront, 16
+// images of 1365 x 2047 in 37.8 ms, now 227 us.)
+//
+// Thread r of a wavefront runs r columns behind thread 0, so its block of 16 columns number b is
+// the window [16 b - r, 16 b - r + 16) of its row.  Data is moved in these windows, as 48 bytes at
+// whatever address they start, so rows need no alignment, every block is the same for all threads,
+// and a step needs no address arithmetic: the 16 steps are unrolled over registers.  A window
+// reaches past the ends of its row at the row's first and last blocks; what is read there is not
+// used, what is decoded there is not stored.
+//
+// A workgroup takes 64 rows, a band, and steps in time with one barrier per block.  An image's bands run
+// at the same time in workgroups of their own, each some eleven blocks behind the one above: the last row of
+// a band is passed on through global memory as 64-bit words of four red values and a mark, each
+// stored and loaded whole at device scope, so that a word that has its mark has its values and
+// neither side waits for anything but the word itself.  A sixth wavefront asks for the next eight
+// blocks of such words over and over and puts what has arrived into LDS.  Bands number themselves
+// with a ticket (image by image, top to bottom), so the band above is always a workgroup that is
+// already running and never waits for the band below.  The wait is bounded by the constant-rate clock;
+// a band that gives up sets an abort word and goes on with what it has, bands below it that find the
+// word set do the same, every loop has a fixed count, and the host returns PILC_E_TIMEOUT.
+// (Two or three times 64 rows in a workgroup, which pass their last rows on through LDS, save
+// that trip through memory, 3.3 us a band, but the wavefronts that then share a SIMD cost more: one
+// frame of 2160 x 3840 takes 0.30 ms with 64 rows, 0.35 with 128, 0.45 with 192.)
+constexpr int kDiagAhead = 4;   // blocks between asking for a window and putting it into LDS
+constexpr int kDiagSlots = 6;   // intervals a window stays in LDS: put, taken apart, red, green, blue, stored
+constexpr int kDiagCarry = 32;  // blocks of the row above a band kept in LDS
+constexpr int kDiagPolls = 4;   // requests for words of the row above under way at once
 
-struct TallBands {
-    uint32_t bands, band_rows;
-    uint32_t *progress;   // [images * bands]: chunks of the band's last row that are final
-    uint32_t *ticket;
+struct Diag {
+    uint32_t h, w;
+    uint32_t strip_rows;        // consecutive rows decoded together: an image, or as many whole ones as fit a band
+    unsigned long long rows;    // n h
+    uint32_t blocks;            // of 16 columns, ceil((w + 63) / 16): the last thread has to get through its row
+    unsigned long long strip0;  // this launch: strips from strip0 on, bands band0 .. band0 + bands - 1
+    uint32_t band0, bands;
+    unsigned long long *words;  // [strip, band][block][4]: {four red values of a band's last row, mark}; null: one band
+    uint32_t *ticket;           // null: one band
     uint32_t *abort_word;
     unsigned long long wait_ticks;
-    uint32_t withhold;    // tests of the give-up path: nothing is published
+    uint32_t withhold;          // tests of the give-up path: nothing is passed on
 };
 
-template <bool kBands>
-__global__ __launch_bounds__(kTallMaxThreads) void k_twar_inverse_tall(TwarK p, uint32_t h, uint32_t w,
-                                                                       uint32_t rounds, TallBands tb,
-                                                                       const uint8_t *__restrict__ res,
-                                                                       uint8_t *__restrict__ img)
+// The 24-bit signed multiply as the compiler's own operation.  (Around inline assembly it puts wait
+// states that a chain of dependent steps has no use for.)
+extern "C" __device__ int mul_i24(int a, int b) __asm("llvm.amdgcn.mul.i24.i32");
+
+// A weight, and the start of a sum.  The sums are kept times four, so that the prediction is the upper
+// half of the clamped sum; beyond 2^26 a bias saturates the prediction whatever the three products are.
+__device__ __forceinline__ int diag_weight(int w) { return 4 * w; }
+__device__ __forceinline__ int diag_bias(int bias) { return 4 * (min(max(bias, -(1 << 26)), 1 << 26) + 8192); }
+// (the prediction with sum `acc` plus the residual) mod 256
+__device__ __forceinline__ int diag_value(int acc, int residual)
 {
-    extern __shared__ uint8_t twar_lds[];
+    return (int)(((uint32_t)min(max(acc, 0), 0xFFFFFF) >> 16) + (uint32_t)residual) & 255;
+}
+
+__device__ __forceinline__ int byte_value(uint32_t w, int i) { return (int)((w >> (8 * i)) & 255u); }
+
+// Sixteen steps of a channel once every thread has entered its row, the values packed four to a register
+// as they are made: the instructions that form a value put it into its byte, and those that use it
+// pick the byte (sub-dword operands), so nothing is shifted, masked or gathered.  The steps are
+// written out because an instruction that reads a register whose byte the instruction before it
+// wrote, or reads a neighbour's register less than three instructions after it was written, would get
+// old values: the order below keeps both apart.
+//
+// Red, eight instructions a step.  `up` holds, by bytes, what the thread above packed, a step behind; thread
+// 0 has no thread above and its lane of `up` is not written by the shift: it keeps the four
+// values of `above` that are moved there before every fourth step.
+#define PILC_RED_STEP(X, L, E, K, KP, KPP, DST, SWITCH)                                              \
+    "v_mul_i32_i24_sdwa %[t], %[up], %[w_upleft] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #KPP " src1_sel:DWORD\n" \
+    "v_add_u32_e32 %[t], %[bias], %[t]\n" SWITCH                                                     \
+    "v_mov_b32_dpp %[up], %[" L "] wave_shr:1 row_mask:0xf bank_mask:0xf\n"                          \
+    "v_mul_i32_i24_sdwa %[m], %[" L "], %[w_left] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #KP " src1_sel:DWORD\n" \
+    "v_mul_i32_i24_sdwa %[n], %[up], %[w_up] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #KP " src1_sel:DWORD\n" \
+    "v_add3_u32 %[t], %[t], %[m], %[n]\n"                                                            \
+    "v_med3_i32 %[t], %[t], 0, %[most]\n"                                                            \
+    "v_add_u32_sdwa %[" X "], %[t], %[" E "] dst_sel:BYTE_" #K " dst_unused:" DST " src0_sel:WORD_1 src1_sel:BYTE_" #K "\n"
+#define PILC_RED_FOUR(X, L, E, A)                                                                    \
+    PILC_RED_STEP(X, L, E, 0, 3, 2, "UNUSED_PAD", "")                                                \
+    PILC_RED_STEP(X, X, E, 1, 0, 3, "UNUSED_PRESERVE", "v_mov_b32_e32 %[up], %[" A "]\n")           \
+    PILC_RED_STEP(X, X, E, 2, 1, 0, "UNUSED_PRESERVE", "")                                           \
+    PILC_RED_STEP(X, X, E, 3, 2, 1, "UNUSED_PRESERVE", "")
+// `left`: the four values before these; `above`: those above thread 0 from the second step on (the one above the
+// first step is the last of the block before and still stands in `up`)
+__device__ __forceinline__ void red_steps(int w_upleft, int w_up, int w_left, int bias, const uint32_t (&e)[4],
+                                          const uint32_t (&above)[4], uint32_t left, uint32_t &up, uint32_t (&x)[4])
+{
+    int t, m, n;
+    uint32_t u = up;
+    asm(PILC_RED_FOUR("x0", "left", "e0", "a0") PILC_RED_FOUR("x1", "x0", "e1", "a1")
+        PILC_RED_FOUR("x2", "x1", "e2", "a2") PILC_RED_FOUR("x3", "x2", "e3", "a3")
+        : [x0] "=&v"(x[0]), [x1] "=&v"(x[1]), [x2] "=&v"(x[2]), [x3] "=&v"(x[3]), [up] "+&v"(u), [t] "=&v"(t),
+          [m] "=&v"(m), [n] "=&v"(n)
+        : [e0] "v"(e[0]), [e1] "v"(e[1]), [e2] "v"(e[2]), [e3] "v"(e[3]), [a0] "v"(above[0]), [a1] "v"(above[1]),
+          [a2] "v"(above[2]), [a3] "v"(above[3]), [left] "v"(left), [w_upleft] "v"(w_upleft), [w_up] "v"(w_up),
+          [w_left] "v"(w_left), [bias] "v"(bias), [most] "v"(0xFFFFFF));
+    up = u;
+}
+#undef PILC_RED_FOUR
+#undef PILC_RED_STEP
+
+// Green and blue, seven instructions a step, from the channel decoded before (`before`, with its four values
+// before these in `before_left`).
+#define PILC_ROW_STEP(X, L, E, B, BL, K, KP, DST)                                                    \
+    "v_mul_i32_i24_sdwa %[t], %[" B "], %[w_before] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #K " src1_sel:DWORD\n" \
+    "v_mul_i32_i24_sdwa %[m], %[" BL "], %[w_left_before] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #KP " src1_sel:DWORD\n" \
+    "v_add3_u32 %[t], %[t], %[m], %[bias]\n"                                                         \
+    "v_mul_i32_i24_sdwa %[m], %[" L "], %[w_left] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #KP " src1_sel:DWORD\n" \
+    "v_add_u32_e32 %[t], %[t], %[m]\n"                                                               \
+    "v_med3_i32 %[t], %[t], 0, %[most]\n"                                                            \
+    "v_add_u32_sdwa %[" X "], %[t], %[" E "] dst_sel:BYTE_" #K " dst_unused:" DST " src0_sel:WORD_1 src1_sel:BYTE_" #K "\n"
+#define PILC_ROW_FOUR(X, L, E, B, BL)                                                                \
+    PILC_ROW_STEP(X, L, E, B, BL, 0, 3, "UNUSED_PAD")                                                \
+    PILC_ROW_STEP(X, X, E, B, B, 1, 0, "UNUSED_PRESERVE")                                            \
+    PILC_ROW_STEP(X, X, E, B, B, 2, 1, "UNUSED_PRESERVE")                                            \
+    PILC_ROW_STEP(X, X, E, B, B, 3, 2, "UNUSED_PRESERVE")
+__device__ __forceinline__ void row_steps(int w_left, int w_left_before, int w_before, int bias, const uint32_t (&e)[4],
+                                          const uint32_t (&before)[4], uint32_t before_left, uint32_t left,
+                                          uint32_t (&x)[4])
+{
+    int t, m;
+    asm(PILC_ROW_FOUR("x0", "left", "e0", "b0", "bl") PILC_ROW_FOUR("x1", "x0", "e1", "b1", "b0")
+        PILC_ROW_FOUR("x2", "x1", "e2", "b2", "b1") PILC_ROW_FOUR("x3", "x2", "e3", "b3", "b2")
+        : [x0] "=&v"(x[0]), [x1] "=&v"(x[1]), [x2] "=&v"(x[2]), [x3] "=&v"(x[3]), [t] "=&v"(t), [m] "=&v"(m)
+        : [e0] "v"(e[0]), [e1] "v"(e[1]), [e2] "v"(e[2]), [e3] "v"(e[3]), [b0] "v"(before[0]), [b1] "v"(before[1]),
+          [b2] "v"(before[2]), [b3] "v"(before[3]), [bl] "v"(before_left), [left] "v"(left), [w_left] "v"(w_left),
+          [w_left_before] "v"(w_left_before), [w_before] "v"(w_before), [bias] "v"(bias), [most] "v"(0xFFFFFF));
+}
+#undef PILC_ROW_FOUR
+#undef PILC_ROW_STEP
+
+// The 16 values of channel kCh from a window's 48 interleaved bytes.
+template <int kCh>
+__device__ __forceinline__ void window_channel(const u32x4 (&d)[3], uint32_t (&out)[4])
+{
+    const uint32_t w[12] = {d[0].x, d[0].y, d[0].z, d[0].w, d[1].x, d[1].y, d[1].z, d[1].w, d[2].x, d[2].y, d[2].z, d[2].w};
+    // of four pixels' twelve bytes: numbers kCh, kCh + 3, kCh + 6, kCh + 9
+    constexpr uint32_t kFirst = kCh == 0 ? 0x00060300u : kCh == 1 ? 0x00070401u : 0x00000502u;
+    constexpr uint32_t kThen = kCh == 0 ? 0x05020100u : kCh == 1 ? 0x06020100u : 0x07040100u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        out[g] = __builtin_amdgcn_perm(w[3 * g + 2], __builtin_amdgcn_perm(w[3 * g + 1], w[3 * g], kFirst), kThen);
+}
+
+// The 48 bytes of a window from its three channels.
+__device__ __forceinline__ void window_pixels(const uint32_t (&r)[4], const uint32_t (&g)[4], const uint32_t (&b)[4],
+                                              u32x4 (&d)[3])
+{
+    uint32_t w[12];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        w[3 * k] = __builtin_amdgcn_perm(b[k], __builtin_amdgcn_perm(g[k], r[k], 0x01000400u), 0x03040100u);
+        w[3 * k + 1] = __builtin_amdgcn_perm(b[k], __builtin_amdgcn_perm(g[k], r[k], 0x06020005u), 0x03020500u);
+        w[3 * k + 2] = __builtin_amdgcn_perm(b[k], __builtin_amdgcn_perm(g[k], r[k], 0x00070300u), 0x07020106u);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        d[i].x = w[4 * i];
+        d[i].y = w[4 * i + 1];
+        d[i].z = w[4 * i + 2];
+        d[i].w = w[4 * i + 3];
+    }
+}
+
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));  // sixteen bytes at any address
+
+// A barrier at the head of a loop whose turns write to LDS.  (The wait for those writes is written out: at
+// the head of a loop, the compiler leaves it away.)
+__device__ __forceinline__ void interval_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, const uint8_t *__restrict__ res,
+                                                              uint8_t *__restrict__ img)
+{
+    __shared__ u32x4 raw[kDiagSlots][3][64];  // [slot][third of the window][row]: residuals, then pixels
+    __shared__ u32x4 red[4][64];              // [block mod 4][row]
+    __shared__ u32x4 green[2][64];            // [block mod 2][row]
+    __shared__ uint32_t carry[kDiagCarry][4]; // [block mod kDiagCarry][word]: red of the row above
     __shared__ uint32_t s_id;
-    __shared__ int s_abort;
-    // (bands) the second half of the workgroup are the movers: wavefront waves + k moves the chunks of
-    // wavefront k's rows between memory and the ring while wavefront k decodes
-    const uint32_t nt = kBands ? blockDim.x >> 1 : blockDim.x, waves = nt >> 6;
-    const bool mover = kBands && threadIdx.x >= nt;
-    const uint32_t wave = (threadIdx.x >> 6) - (mover ? waves : 0u), lane = threadIdx.x & 63u;
-    const uint32_t thread = wave * 64u + lane;  // the row of the workgroup this thread decodes (a mover: none)
-    uint32_t image = blockIdx.x, band = 0u, id = 0u;
-    if (kBands) {
-        if (threadIdx.x == 0u) {
-            s_id = atomicAdd(tb.ticket, 1u);
-            s_abort = 0;
-        }
+    uint32_t id = blockIdx.x;
+    if (a.ticket != nullptr) {
+        if (threadIdx.x == 0u) s_id = atomicAdd(a.ticket, 1u);
         __syncthreads();
         id = s_id;
-        image = id / tb.bands;
-        band = id % tb.bands;
     }
-    uint8_t *my = twar_lds + (size_t)thread * kTallStride;
-    uint8_t *hand = twar_lds + (size_t)nt * kTallStride;  // [wavefront][64]: red of its last row, by column mod 64
-    // red of the row above the workgroup's first row: the whole row of the round before, or (bands) a
-    // ring of 32 values filled from the image
-    uint8_t *carry = hand + waves * 64u;
-    const size_t row_bytes = (size_t)w * 3u;
-    const int chunks = (int)(w >> 4);
-    const int lag = (int)(wave * (64u + kTallLag));
-    // a mover asks for a chunk three turns before its row enters it, a decoding wavefront two
-    constexpr int kLead = kBands ? kTallLead + kTallLag : kTallLead;
-    // local steps -kLead .. w + 63 + 16: the last lane's last chunk is written back by then
-    const uint32_t total = kLead + w + 80u + (waves - 1u) * (64u + kTallLag);
-    const uint32_t rows_here = kBands ? tb.band_rows : nt;
-    // where the first thread of this wavefront finds the red values above its row
-    const uint8_t *above_ptr = wave != 0u ? hand + (wave - 1u) * 64u : carry;
-    const uint32_t above_mask = wave != 0u ? 63u : (kBands ? 31u : 0xFFFFFFFFu);
-    const bool first_lane = lane == 0u;
-    // the rounding biases and the weights of the multiply-adds written out below in vector
-    // registers of their own (as scalar operands they would be copied into one at every use)
-    int bias_r = p.bias[0] + 8192, bias_g = p.bias[1] + 8192, bias_b = p.bias[2] + 8192;
-    int w_r0 = p.w[0][0], w_r1 = p.w[0][1], w_g0 = p.w[1][0], w_g1 = p.w[1][1], w_b0 = p.w[2][0], w_b1 = p.w[2][1];
-    asm volatile("" : "+v"(bias_r), "+v"(bias_g), "+v"(bias_b));
-    asm volatile("" : "+v"(w_r0), "+v"(w_r1), "+v"(w_g0), "+v"(w_g1), "+v"(w_b0), "+v"(w_b1));
+    const uint32_t in_strip = id / a.bands, band = a.band0 + (id - in_strip * a.bands);
+    const unsigned long long strip = a.strip0 + in_strip;
+    const uint32_t role = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t band_row0 = band * 64u;       // row of the strip
+    const int blocks = (int)a.blocks;
+    // intervals between barriers, a multiple of 4: a window is fetched kDiagAhead intervals before it is put
+    // into LDS, red takes it apart in the next and decodes it in the one after, then green, blue, and the store
+    const int lead = kDiagAhead + 2;
+    const int times = (lead + blocks + 3 + 3) & ~3;
 
-    for (uint32_t round = 0; round < rounds; ++round) {
-        const uint32_t u = kBands ? band * tb.band_rows + thread : round * nt + thread;
-        const bool have = !mover && thread < rows_here && u < h;
-        const bool last_row = have && (u + 1u == h || thread + 1u == rows_here);
-        const bool keeps_row = !kBands && last_row;  // leaves its red values for the next round
-        const bool has_above = wave != 0u || (kBands ? band != 0u : round != 0u);
-        // (bands) the three threads that fetch the row above the band, 16 bytes of a chunk each
-        const bool fetches = mover && band != 0u && wave == 0u && lane < 3u;
-        const uint4 *above_src = reinterpret_cast<const uint4 *>(
-            img + ((size_t)image * h + (kBands && band != 0u ? band * tb.band_rows - 1u : 0u)) * row_bytes);
-        const uint32_t *above_progress = tb.progress + (size_t)(id - (band != 0u ? 1u : 0u)) * kBandStride;
-        uint4 above_ahead = make_uint4(0u, 0u, 0u, 0u);
-        uint32_t above_done = 0u;  // chunks of the row above known to be final
-
-        // The 64 rows of a wavefront move one chunk on per turn, as 192 pieces of 16 bytes: piece k of
-        // the turn is piece k mod 3 of row k / 3, so three neighbouring threads move the 48 contiguous
-        // bytes of one row's chunk.  These are this thread's three pieces.
-        uint32_t piece_row[3];
-        bool piece_have[3];
-        const uint4 *piece_src[3];
-        uint4 *piece_dst[3];
-        uint8_t *piece_lds[3];
+    if (role == 0u) {  // ---- red
+        const uint32_t u = band_row0 + lane;
+        const bool top = u % a.h == 0u;  // the row above is padding: its two weights are zero here
+        const int w_upleft = top ? 0 : diag_weight(p.w[0][0]), w_up = top ? 0 : diag_weight(p.w[0][1]);
+        const int w_left = diag_weight(p.w[0][2]);
+        const int bias = diag_bias(p.bias[0]);
+        const bool passes_on = a.words != nullptr && a.withhold == 0u && band + 1u < a.band0 + a.bands;
+        unsigned long long *out = a.words + (size_t)id * (4u * a.blocks);
+        uint32_t left = 0, up = 0;  // the last four values, and the four above them as red_steps keeps them
+        uint32_t slot = 0, e[4] = {};
+        for (int time = 0; time < times; ++time) {
+            interval_barrier();
+            const int b = time - lead;
+            if (b < -1 || b >= blocks) continue;
+            if (b >= 0) {
+                uint32_t above[4], x[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                // thread 0 is at columns 16 b .. + 15; column v of the row above is value v + 63 of its blocks
+                for (int k = 0; k < 4; ++k) above[k] = carry[(b + 4) % kDiagCarry][k];
+                if (b >= 4) {
+                    red_steps(w_upleft, w_up, w_left, bias, e, above, left, up, x);
+                } else {
+                    // some thread has not reached its row's first column yet and keeps zeros
+                    if (b == 0 && lane == 0u) up = carry[3][3] & 0xFF000000u;  // column 0; left of it is padding
+                    const int left_to_go = (int)lane - 16 * b;
+                    int last_up = byte_value(up, 2), rl = byte_value(left, 3);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const uint32_t word = i == 0 ? up : above[(i - 1) >> 2];
+                        // thread 0 has no neighbour to take from and keeps what stands there: the value above it
+                        const int now_up = __builtin_amdgcn_update_dpp(byte_value(word, (i + 3) & 3), rl,
+                                                                       0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+                        const int acc = mul_i24(w_up, now_up) + (mul_i24(w_left, rl) + (mul_i24(w_upleft, last_up) + bias));
+                        int v = diag_value(acc, byte_value(e[i >> 2], i & 3));
+                        v = i >= left_to_go ? v : 0;
+                        x[i >> 2] |= (uint32_t)v << (8 * (i & 3));
+                        rl = v;
+                        last_up = now_up;
+                    }
+                    up = (uint32_t)__builtin_amdgcn_update_dpp((int)above[3], (int)x[3], 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+                }
+                left = x[3];
+                u32x4 o;
+                o.x = x[0];
+                o.y = x[1];
+                o.z = x[2];
+                o.w = x[3];
+                red[b & 3][lane] = o;
+                if (passes_on && lane == 63u) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        __hip_atomic_store(out + 4 * b + k, (1ull << 32) | x[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+            // the next block's residuals, which no barrier has to be waited for
+            u32x4 d[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) d[i] = raw[slot][i][lane];
+            slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
+            window_channel<0>(d, e);
+        }
+    } else if (role == 1u || role == 2u) {  // ---- green and blue
+        auto channel = [&](auto blue) {
+            constexpr int kCh = decltype(blue)::value ? 2 : 1;
+            // green from the left green, the left red and the red here; blue likewise from blue and green
+            const int w_left = diag_weight(p.w[kCh][0]), w_left_before = diag_weight(p.w[kCh][1]);
+            const int w_before = diag_weight(p.w[kCh][2]);
+            const int bias = diag_bias(p.bias[kCh]);
+            uint32_t left = 0, before_left = 0;  // the last four values of this channel and of the one decoded before it
+            uint32_t slot = 0;
+            for (int time = 0; time < times; ++time) {
+                interval_barrier();
+                const int b = time - lead - kCh;
+                if (b < 0 || b >= blocks) continue;
+                u32x4 d[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) d[i] = raw[slot][i][lane];
+                const u32x4 r = red[b & 3][lane];
+                const uint32_t rd[4] = {r.x, r.y, r.z, r.w};
+                uint32_t gr[4] = {0u, 0u, 0u, 0u};
+                if (kCh == 2) {
+                    const u32x4 g = green[b & 1][lane];
+                    gr[0] = g.x;
+                    gr[1] = g.y;
+                    gr[2] = g.z;
+                    gr[3] = g.w;
+                }
+                const uint32_t(&before)[4] = kCh == 2 ? gr : rd;
+                uint32_t e[4], x[4] = {0u, 0u, 0u, 0u};
+                window_channel<kCh>(d, e);
+                if (b >= 4) {
+                    row_steps(w_left, w_left_before, w_before, bias, e, before, before_left, left, x);
+                } else {
+                    const int left_to_go = (int)lane - 16 * b;
+                    int v = byte_value(left, 3), last = byte_value(before_left, 3);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int here = byte_value(before[i >> 2], i & 3);
+                        const int acc = mul_i24(w_left, v) + (mul_i24(w_before, here) + (mul_i24(w_left_before, last) + bias));
+                        v = diag_value(acc, byte_value(e[i >> 2], i & 3));
+                        v = i >= left_to_go ? v : 0;
+                        x[i >> 2] |= (uint32_t)v << (8 * (i & 3));
+                        last = here;
+                    }
+                }
+                left = x[3];
+                before_left = before[3];
+                if (kCh == 1) {
+                    u32x4 o;
+                    o.x = x[0];
+                    o.y = x[1];
+                    o.z = x[2];
+                    o.w = x[3];
+                    green[b & 1][lane] = o;
+                } else {  // all three channels are here: the window's pixels take the place of its residuals
+                    window_pixels(rd, gr, x, d);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) raw[slot][i][lane] = d[i];
+                }
+                slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
+            }
+        };
+        if (role == 1u)
+            channel(std::false_type{});
+        else
+            channel(std::true_type{});
+    } else if (role == 3u) {  // ---- residuals from memory to LDS
+        // the windows of 64 rows move as 192 pieces of 16 bytes, three neighbouring threads taking the
+        // 48 bytes of a row.  An address outside the array is moved inside; that brings the wrong
+        // bytes only where none is used, or at the end of the array's last row, where they are put right.
+        const long long last = (long long)(a.rows * a.w * 3ull) - 16;
+        long long at[3];
+        uint32_t put[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;  // r = k / 3 for k < 192
-            const uint32_t t = wave * 64u + r;
-            const uint32_t ur = kBands ? band * tb.band_rows + t : round * nt + t;
-            piece_row[i] = r;
-            piece_have[i] = t < rows_here && ur < h;
-            const size_t off = ((size_t)image * h + (piece_have[i] ? ur : 0u)) * row_bytes + 16u * part;
-            piece_src[i] = reinterpret_cast<const uint4 *>(res + off);
-            piece_dst[i] = reinterpret_cast<uint4 *>(img + off);
-            piece_lds[i] = twar_lds + (size_t)t * kTallStride + 16u * part;
+            const unsigned long long row = strip * a.strip_rows + band_row0 + r;
+            at[i] = (long long)(row * a.w * 3ull) + 16ll * part - 3ll * r;  // block 0
+            put[i] = part * 64u + r;
         }
-        // (bands) the thread of the band's last row, which the band below waits for
-        const uint32_t pub_thread = kBands ? min(rows_here, h - band * tb.band_rows) - 1u : 0u;
-        const uint32_t pub_wave = kBands && band + 1u < tb.bands ? pub_thread >> 6 : 0xFFFFFFFFu;
-        const uint32_t pub_lane = pub_thread & 63u;
-        bool piece_published[3];
+        u32x4 ahead[kDiagAhead][3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) piece_published[i] = wave == pub_wave && piece_row[i] == pub_lane;
-        uint4 ahead[3] = {};  // this thread's three pieces of the chunks asked for in the last turn
-
-        // One chunk turn of the rows of this wavefront, whose thread 0 stands at column d0: row r is in
-        // chunk c = (d0 - r) >> 4.  Chunk c - 1 was left for good and is written back; chunk c + kFill,
-        // asked for a turn ago, goes into the ring; chunk c + kFill + 1 is asked for.  The ring has
-        // three slots (chunk mod 3): a decoding wavefront that turns its own rows fills the slot its
-        // rows enter during the coming 16 steps (kFill 1); a mover works beside the wavefront that is
-        // in chunks c and c + 1, so it fills the slot it has just read out (kFill 2), a turn before
-        // that wavefront needs it.  What is written back is read out of the ring first; the ring is
-        // filled before the stores are issued: loads and stores share one counter of outstanding
-        // accesses, and a wait for last turn's loads placed after this turn's stores would wait for
-        // the stores too.
-        auto turn = [&](int d0, int kFill) {
-            uint4 back[3];
-            bool backs[3];
+        for (int j = 0; j < kDiagAhead; ++j)
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int c_prev = ((d0 - (int)piece_row[i]) >> 4) - 1;
-                backs[i] = piece_have[i] && c_prev >= 0 && c_prev < chunks;
-                const uint32_t *q = reinterpret_cast<const uint32_t *>(
-                    piece_lds[i] + ((uint32_t)(c_prev + 48) % 3u) * kTallChunk);
-                back[i] = make_uint4(q[0], q[1], q[2], q[3]);
-            }
+            for (int i = 0; i < 3; ++i) ahead[j][i] = u32x4{};
+        // Without a condition on anything, so that the number of loads under way is known when one is
+        // waited for: what is put before the first block or after the last is not looked at (a
+        // slot is written again no sooner than the interval after its pixels have been stored).
+        uint32_t slot = kDiagSlots - kDiagAhead;  // of block -kDiagAhead
+        static_assert(kDiagSlots >= kDiagAhead, "");
+        for (int time0 = 0; time0 < times; time0 += kDiagAhead) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int c_fill = ((d0 - (int)piece_row[i]) >> 4) + kFill;
-                if (piece_have[i] && c_fill >= 0 && c_fill < chunks) {
-                    uint32_t *q = reinterpret_cast<uint32_t *>(piece_lds[i] + ((uint32_t)(c_fill + 48) % 3u) * kTallChunk);
-                    q[0] = ahead[i].x;
-                    q[1] = ahead[i].y;
-                    q[2] = ahead[i].z;
-                    q[3] = ahead[i].w;
+            for (int j = 0; j < kDiagAhead; ++j) {
+                interval_barrier();
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    (&raw[slot][0][0])[put[i]] = ahead[j][i];
+                    const long long over = at[i] - 48 * kDiagAhead - last;
+                    if (over > 0 && over < 16) {  // the array's end is inside the piece: one piece of the whole grid
+                        uint8_t *q = reinterpret_cast<uint8_t *>(&raw[slot][0][0] + put[i]);
+#pragma unroll 1
+                        for (int k = 0; k < 16 - (int)over; ++k) q[k] = q[k + (int)over];
+                    }
+                }
+                slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const long long from = min(max(at[i], 0ll), last);
+                    ahead[j][i] = *reinterpret_cast<const u32x4_any *>(res + from);
+                    at[i] += 48;
                 }
             }
+        }
+    } else if (role == 4u) {  // ---- pixels from LDS to memory
+        const int row_bytes = (int)(3u * a.w);
+        uint8_t *to[3];
+        int in_row[3];  // where the piece lies in its row
+        uint32_t get[3];
+        bool have[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;
+            const uint32_t u = band_row0 + r;
+            const unsigned long long row = strip * a.strip_rows + u;
+            have[i] = u < a.strip_rows && row < a.rows;
+            in_row[i] = 16 * (int)part - 3 * (int)r;
+            to[i] = img + (long long)((have[i] ? row : 0ull) * a.w * 3ull) + in_row[i];
+            get[i] = part * 64u + r;
+        }
+        uint32_t slot = 0;
+        for (int time = 0; time < times; ++time) {
+            interval_barrier();
+            const int b = time - lead - 3;
+            if (b < 0 || b >= blocks) continue;
+            u32x4 v[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) v[i] = (&raw[slot][0][0])[get[i]];
+            slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                if (!backs[i]) continue;
-                uint4 *to = piece_dst[i] + 3 * (((d0 - (int)piece_row[i]) >> 4) - 1);
-                if (kBands && piece_published[i]) {
-                    // the band's last row, which another workgroup reads: stores at device scope go
-                    // through to memory, so that no write-back of the whole L2 is needed to publish them
-                    uint32_t *t32 = reinterpret_cast<uint32_t *>(to);
-                    __hip_atomic_store(t32 + 0, back[i].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(t32 + 1, back[i].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(t32 + 2, back[i].z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(t32 + 3, back[i].w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                } else {
-                    *to = back[i];
-                }
-            }
-            if (kBands && wave == pub_wave && !tb.withhold) {
-                // chunks 0 .. c - 1 of the band's last row are final.  Its pieces were stored by threads
-                // of this wavefront, at device scope; once the wavefront has no store outstanding they
-                // are in memory, and the count may follow (a release fence would do the same and also
-                // write the whole L2 back: 2.5 us each, a third of a block of 16 steps).
-                const int c = (d0 - (int)pub_lane) >> 4;
-                if (c >= 1 && c <= chunks) {
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    if (lane == pub_lane)
-                        __hip_atomic_store(tb.progress + (size_t)id * kBandStride, (uint32_t)c, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
+                const int first = in_row[i] + 48 * b;
+                uint8_t *q = to[i] + 48ll * b;
+                if (!have[i]) continue;
+                if (first >= 0 && first + 16 <= row_bytes) {
+                    *reinterpret_cast<u32x4_any *>(q) = v[i];
+                } else if (first > -16 && first < row_bytes) {  // an end of the row
+                    const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int c_ask = ((d0 - (int)piece_row[i]) >> 4) + kFill + 1;
-                // (a piece with nothing to ask for reads the row's first chunk: no branch round a load)
-                const bool asks = piece_have[i] && c_ask >= 0 && c_ask < chunks;
-                ahead[i] = piece_src[i][asks ? 3 * c_ask : 0];
+                    for (int k = 0; k < 16; ++k)
+                        if (first + k >= 0 && first + k < row_bytes) q[k] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
+                }
+            }
+        }
+    } else {  // ---- the red values of the row above the band
+        // Block q, word k of the band above holds columns 16 q + 4 k - 63 .. + 3 of its last row.  Red's block
+        // b needs blocks b + 3 and b + 4.  Threads 0 .. 31 ask for eight blocks at a time.
+        const bool some = band != 0u, first_of_launch = band == a.band0;
+        // (the first band of a launch: the band above is done, its last row is in the image)
+        const uint8_t *above_row =
+            img + (size_t)((strip * a.strip_rows + (some ? band_row0 - 1u : 0u)) * a.w) * 3u;
+        const unsigned long long *words = a.words + (size_t)(id - (some && !first_of_launch ? 1u : 0u)) * (4u * a.blocks);
+        int got = 0;  // blocks in LDS so far
+        bool gave_up = false;
+        auto follow = [&](auto in_image) {
+            auto ask = [&](int base) -> unsigned long long {
+                const int q = min(base + (int)((lane & 31u) >> 2), blocks - 1), k = (int)(lane & 3u);
+                if (!decltype(in_image)::value)
+                    return __hip_atomic_load(words + 4 * q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                uint32_t v = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int col = 16 * q + 4 * k + i - 63;
+                    const uint32_t x = above_row[3 * min(max(col, 0), (int)a.w - 1)];
+                    v |= x << (8 * i);  // (what is outside the row is not used)
+                }
+                return (1ull << 32) | v;
+            };
+            // `now`: the block red is at; a block goes into LDS once the one it replaces has been used
+            auto take = [&](unsigned long long v, int base, int now) {
+                const uint32_t missing = ~(uint32_t)__ballot((uint32_t)(v >> 32) != 0u);
+                const int whole = missing == 0u ? 8 : (__ffs((int)missing) - 1) >> 2;
+                const int upto = min(min(base + whole, blocks), now + kDiagCarry);
+                const int q = base + (int)(lane >> 2);
+                if (lane < 32u && q >= got && q < upto) carry[q % kDiagCarry][lane & 3u] = (uint32_t)v;
+                got = max(got, upto);
+            };
+            unsigned long long asked[kDiagPolls] = {};
+            int asked_at[kDiagPolls] = {};
+            for (int time0 = 0; time0 < times; time0 += kDiagPolls) {
+#pragma unroll
+                for (int j = 0; j < kDiagPolls; ++j) {
+                    interval_barrier();
+                    if (decltype(in_image)::value && j != 0) continue;  // eight blocks every four intervals will do
+                    const int now = time0 + j - lead;
+                    take(asked[j], asked_at[j], now);
+                    // what red reads after the next barrier (or by the time this is looked at again)
+                    const int need = min(now + (decltype(in_image)::value ? 6 + kDiagPolls - 1 : 6), blocks);
+                    if (got < need && !gave_up) {
+                        const unsigned long long since = wall_clock64();
+                        for (;;) {
+                            const int base = got;
+                            take(ask(base), base, now);
+                            if (got >= need) break;
+                            if (__hip_atomic_load(a.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
+                                gave_up = true;
+                                break;
+                            }
+                            if (wall_clock64() - since > a.wait_ticks) {
+                                gave_up = true;
+                                __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                break;
+                            }
+                            __builtin_amdgcn_s_sleep(8);
+                        }
+                    }
+                    asked_at[j] = got;
+                    asked[j] = ask(got);
+                }
             }
         };
-
-        int rl = 0, gl = 0, bl = 0;
-        int prev_up = 0;  // the red value above the pixel decoded last: above-left of the next one
-        uint32_t ptr = 0;             // ring offset of the pixel about to be decoded
-        for (uint32_t D0 = 0; D0 < total; D0 += kTallLag) {
-            __syncthreads();
-            if (kBands && s_abort) return;  // the same for every thread: written before the barrier
-            const int d0 = (int)D0 - lag - kLead;  // this wavefront's step; lane 0 is at column d0
-            if (d0 < -kLead || d0 >= (int)(w + 80u)) continue;  // (the same for the whole wavefront)
-            if (fetches) {
-                // thread 0 of the band enters chunk T now: the red values of chunk T + 1 of the row
-                // above, fetched a turn ago, go to the ring (the half that thread is not reading), and
-                // chunk T + 2 is fetched as soon as it is final
-                const int T = d0 >> 4;
-                if (T + 1 >= 0 && T + 1 < chunks) {
-                    // this thread holds bytes 16 lane .. 16 lane + 15 of the chunk; red is every third
-                    const uint32_t wd[4] = {above_ahead.x, above_ahead.y, above_ahead.z, above_ahead.w};
-                    const uint32_t skip = (3u - (16u * lane) % 3u) % 3u;  // offset of the first red byte
-#pragma unroll
-                    for (uint32_t k = 0; k < 6u; ++k) {
-                        const uint32_t o = skip + 3u * k;  // byte within these 16
-                        if (o < 16u) {
-                            const uint32_t px = (16u * lane + o) / 3u;  // pixel within the chunk
-                            carry[(16u * (uint32_t)(T + 1) + px) & 31u] = (uint8_t)(wd[o >> 2] >> (8u * (o & 3u)));
-                        }
-                    }
-                }
-                if (T + 2 >= 0 && T + 2 < chunks) {
-                    const unsigned long long t0 = wall_clock64();
-                    while (above_done < (uint32_t)(T + 3)) {  // what is known to be final does not need asking
-                        above_done = __hip_atomic_load(above_progress, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-                        if (above_done >= (uint32_t)(T + 3)) break;
-                        if (__hip_atomic_load(tb.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
-                            s_abort = 1;
-                            break;
-                        }
-                        if (wall_clock64() - t0 > tb.wait_ticks) {
-                            s_abort = 1;
-                            __hip_atomic_store(tb.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(32);
-                    }
-                    if (!s_abort) above_ahead = above_src[3 * (T + 2) + (int)lane];
-                }
-            }
-            if (mover) {
-                turn(d0, 2);
-                continue;
-            }
-            if (!kBands) {
-                turn(d0, 1);
-                wave_lds_sync();
-            }
-            // ---- 16 steps ----
-            // The 16 steps.  Within a pixel green waits for red and blue for green, three chains of
-            // dependent instructions one after the other, and a wavefront alone on its SIMD has
-            // nothing else to issue meanwhile; red of the next pixel, however, only needs red.  So
-            // the channels run skewed: turn i decodes red of pixel i, green of pixel i - 1 and blue
-            // of pixel i - 2, which do not depend on each other, and two more turns drain the block
-            // (at its end every pixel is whole, as the chunk turns and the barrier expect).
-            // A pixel's three residual bytes are asked for a step ahead, as the two aligned dwords
-            // that hold them (the second may be the spare bytes behind the ring), and taken apart
-            // when used: a byte read is widened where it is read, and that use would put the wait for
-            // it right behind the read; the wait stands before the next reads are issued, because
-            // LDS answers in order.  The next pixel's ring offset is never this pixel's; what the
-            // last step asks for is not used.
-            // The values above the 16 pixels that the wavefront's first thread decodes in this block
-            // (columns d0 .. d0 + 15: 16 neighbouring bytes, all written before the last barrier, the
-            // last of them 17 steps ago) are read once, by every thread alike.
-            int v = d0 - (int)lane;
-            bool on = have && (uint32_t)v < w;
-            auto ring_dwords = [&](uint32_t at) { return reinterpret_cast<const uint32_t *>(my + (at & ~3u)); };
-            uint32_t above16[4] = {0u, 0u, 0u, 0u};
-            if (has_above) {
-                const uint32_t at = (d0 >= 0 && (uint32_t)d0 < w ? (uint32_t)d0 : 0u) & above_mask;
-                const uint32_t *a = reinterpret_cast<const uint32_t *>(above_ptr + at);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) above16[k] = a[k];
-            }
-            uint32_t e_lo = ring_dwords(ptr)[0], e_hi = ring_dwords(ptr)[1];
-            uint8_t *const spare = my + kTallRing;  // the four bytes after the ring: where writes of idle steps go
-            auto clamp8 = [](int acc) { return min(max(acc >> 14, 0), 255); };
-            // what a pixel's later channels need from its earlier ones, one and two turns later
-            struct InFlight {
-                uint32_t e;     // its residual bytes
-                uint8_t *q;     // where it goes in the ring (the spare bytes for an idle step)
-                bool on;
-                int left_r, xr; // red to its left, its own red
-                int left_g, xg; // green to its left, its own green
-            };
-            InFlight one = {}, two = {};  // the pixels of one and two turns ago
-#pragma unroll
-            for (int i = 0; i < kTallLag + 2; ++i) {
-                InFlight now = {};
-                int xr = 0;
-                if (i < kTallLag) {
-                    // the wait for what the last step asked for stands here, before this step asks
-                    asm volatile("" : "+v"(e_lo), "+v"(e_hi));
-                    now.on = on;
-                    now.e = __builtin_amdgcn_alignbyte(e_hi, e_lo, ptr & 3u);  // bytes ptr .. ptr + 3 of the ring
-                    now.q = on ? my + ptr : spare;
-                    const uint32_t nptr = ptr + 3u == (uint32_t)kTallRing ? 0u : ptr + 3u;
-                    ptr = on ? nptr : ptr;
-                    e_lo = ring_dwords(ptr)[0];
-                    e_hi = ring_dwords(ptr)[1];
-                }
-                // ---- red of this turn's pixel, green of the one before, blue of the one before that:
-                // three multiply-adds each; what only needs the pixel to the left comes first, the
-                // operand that arrives last (the value just decoded) goes into the last of them
-                int acc_r = 0, acc_g = 0, acc_b = 0;
-                if (i < kTallLag) {
-                    const int above = (int)((above16[i >> 2] >> (8 * (i & 3))) & 0xFFu);
-                    int up = __builtin_amdgcn_update_dpp(0, rl, 0x138 /* wave_shr:1 */, 0xF, 0xF, true);
-                    // the first thread of a wavefront: the row above belongs to another wavefront, to
-                    // the round or band before, or is padding
-                    up = first_lane ? above : up;
-                    const int upleft = prev_up;
-                    prev_up = on ? up : prev_up;
-                    acc_r = mad_i24(p.w[0][2], rl, mad_i24(w_r1, up, mad_i24(w_r0, upleft, bias_r)));
-                }
-                if (i >= 1 && i <= kTallLag)
-                    acc_g = mad_i24(p.w[1][2], one.xr, mad_i24(w_g1, one.left_r, mad_i24(w_g0, gl, bias_g)));
-                if (i >= 2)
-                    acc_b = mad_i24(p.w[2][2], two.xg, mad_i24(w_b1, two.left_g, mad_i24(w_b0, bl, bias_b)));
-                if (i < kTallLag) {
-                    xr = add_byte_of<0>(now.e, clamp8(acc_r));
-                    now.left_r = rl;
-                    now.xr = xr;
-                    const uint32_t col = on ? (uint32_t)v : 0u;
-                    uint8_t *const to_next_wave = on && lane == 63u ? hand + wave * 64u + (col & 63u) : spare + 3;
-                    *to_next_wave = (uint8_t)xr;
-                    if (on && keeps_row) carry[col] = (uint8_t)xr;
-                    rl = on ? xr : rl;
-                }
-                if (i >= 1 && i <= kTallLag) {
-                    const int xg = add_byte_of<1>(one.e, clamp8(acc_g));
-                    one.left_g = gl;
-                    one.xg = xg;
-                    gl = one.on ? xg : gl;
-                }
-                if (i >= 2) {
-                    const int xb = add_byte_of<2>(two.e, clamp8(acc_b));
-                    bl = two.on ? xb : bl;
-                    two.q[0] = (uint8_t)two.xr;
-                    two.q[1] = (uint8_t)two.xg;
-                    two.q[2] = (uint8_t)xb;
-                }
-                two = one;
-                one = now;
-                if (i < kTallLag) {
-                    ++v;
-                    on = have && (uint32_t)v < w;
-                }
-            }
+        if (!some) {
+            for (int time = 0; time < times; ++time) interval_barrier();
+        } else if (first_of_launch) {
+            follow(std::true_type{});
+        } else {
+            follow(std::false_type{});
         }
-        __syncthreads();
     }
 }
 
-// Progress counters of the band kernel: a few sets in device globals (the entry points take no
-// workspace), handed out under a lock so that concurrent calls do not share one; a call that finds
-// none free uses the workgroup-per-image kernel instead.  Layout of a set: the progress counters of
-// up to 4096 bands, kBandStride words apart (2 MB for the four sets), then the ticket and the abort
-// word.
+// The words that bands pass on, with the ticket and the abort word: a few sets in device globals (the
+// entry points take no workspace), handed out under a lock so that concurrent calls do not share
+// one; a call that finds none free goes a band at a time, a launch each, every band reading the row
+// above it from the image.
+constexpr uint64_t kDiagManyStrips = 256;   // a workgroup for every compute unit
+constexpr uint32_t kTileManyImages = 1024;  // a wavefront for every SIMD
 constexpr int kBandSlots = 4;
-constexpr uint32_t kBandFlags = 4096 * kBandStride;
-static __device__ uint32_t g_band_flags[kBandSlots][kBandFlags + 2];
+constexpr uint32_t kBandWords = 1u << 19;  // 4 MB a set: 132 bands of 16384 columns, 1057 of 1920
+struct BandSet {
+    unsigned long long words[kBandWords];
+    uint32_t ticket, abort_word;
+};
+static __device__ BandSet g_band_sets[kBandSlots];
 static std::mutex g_band_mutex;
 static bool g_band_in_use[kBandSlots];
-static std::map<int, uint32_t *> g_band_base;  // per device: address of g_band_flags there
+static std::map<int, BandSet *> g_band_base;  // per device: address of g_band_sets there
 
-__global__ void k_band_clear(uint32_t *flags, uint32_t n)
+__global__ __launch_bounds__(256) void k_band_clear(BandSet *set, uint32_t words, bool first)
 {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) flags[i] = 0u;
-    if (i < 2u) flags[kBandFlags + i] = 0u;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x) set->words[i] = 0ull;
+    if (blockIdx.x == 0u && threadIdx.x == 0u) {
+        set->ticket = 0u;
+        if (first) set->abort_word = 0u;
+    }
 }
 
-// A free set of counters on the current device (null if none), and its release.
-static uint32_t *band_flags_acquire(int *slot_out)
+// A free set on the current device (null if none), and its release.
+static BandSet *band_set_acquire(int *slot_out)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
@@ -685,18 +834,18 @@ static uint32_t *band_flags_acquire(int *slot_out)
     auto it = g_band_base.find(dev);
     if (it == g_band_base.end()) {
         void *ptr = nullptr;
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_band_flags)) != hipSuccess) return nullptr;
-        it = g_band_base.emplace(dev, static_cast<uint32_t *>(ptr)).first;
+        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_band_sets)) != hipSuccess) return nullptr;
+        it = g_band_base.emplace(dev, static_cast<BandSet *>(ptr)).first;
     }
     for (int i = 0; i < kBandSlots; ++i)
         if (!g_band_in_use[i]) {
             g_band_in_use[i] = true;
             *slot_out = i;
-            return it->second + (size_t)i * (kBandFlags + 2);
+            return it->second + i;
         }
     return nullptr;
 }
-static void band_flags_release(int slot)
+static void band_set_release(int slot)
 {
     std::lock_guard<std::mutex> lock(g_band_mutex);
     g_band_in_use[slot] = false;
@@ -730,21 +879,92 @@ int pilc_twar_forward(uint32_t n, uint32_t h, uint32_t w, const uint8_t *img_dev
     hipStream_t stream = (hipStream_t)hip_stream;
     const uint64_t rows = (uint64_t)n * h;
     if (rows >= (1ull << 31)) return PILC_E_TOO_LARGE;
-    const uint32_t rpb = w >= 256 ? 1u : 256u / w;
-    const uint32_t blocks = (uint32_t)((rows + rpb - 1) / rpb);
     Timer timer(stream);
     const uint64_t groups = rows * (w / 4);
     if (w % 4 == 0 && ((((uintptr_t)img_dev) | ((uintptr_t)res_dev)) & 3) == 0 && groups < (1ull << 32))
         k_twar_forward4<<<(uint32_t)((groups + 255) / 256), 256, 0, stream>>>(
             k, (uint32_t)groups, FastDiv::make(h), FastDiv::make(w / 4), reinterpret_cast<const uint32_t *>(img_dev),
             reinterpret_cast<uint32_t *>(res_dev));
-    else
-        k_twar_forward<<<blocks, 256, 0, stream>>>(k, (uint32_t)rows, h, w, rpb, img_dev, res_dev);
+    else {
+        // whole rows of less than 2^31 pixels a launch
+        const uint32_t most = std::max(1u, (1u << 31) / w - 1u);
+        for (uint64_t row = 0; row < rows; row += most) {
+            const uint32_t pixels = (uint32_t)std::min<uint64_t>(most, rows - row) * w;
+            k_twar_forward_any<<<(uint32_t)ceil_div64(pixels, 1024), 256, 0, stream>>>(
+                k, (uint32_t)row, pixels, FastDiv::make(h), FastDiv::make(w), img_dev, res_dev);
+        }
+    }
     timer.mark("k_twar_forward");
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(stream));
     timer.finish();
     return PILC_OK;
+}
+
+// pilc_twar_inverse by k_twar_inverse_diag.
+static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev, const TwarK &k,
+                             uint8_t *img_dev, hipStream_t stream, Timer &timer)
+{
+    Diag a = {};
+    a.h = h;
+    a.w = w;
+    a.rows = (unsigned long long)n * h;
+    a.strip_rows = h <= 64u ? 64u / h * h : h;
+    a.blocks = (w + 63u + 15u) / 16u;
+    const uint64_t strips = (a.rows + a.strip_rows - 1u) / a.strip_rows;
+    const uint32_t bands = (a.strip_rows + 63u) / 64u;
+    // With enough strips to fill the chip by themselves, bands go one at a time, a launch each: a band that
+    // waits for the one above takes the place of one that would not have to (together against one at a
+    // time: 64 images of 200 x 301 43 against 77 us, 128 of 512 x 512 167 against 217; 256 of either 107
+    // against 84 and 365 against 259; 2048 of 256 x 256 1081 against 470).
+    int slot = -1;
+    BandSet *set = bands > 1u && strips < kDiagManyStrips ? band_set_acquire(&slot) : nullptr;
+    // bands of a strip and strips in a launch: what the words passed on have room for
+    const uint32_t band_words = 4u * a.blocks;
+    const uint32_t together = set ? (uint32_t)std::min<uint64_t>(bands, kBandWords / band_words) : 1u;
+    const uint64_t most_strips = together > 1u ? std::max<uint64_t>(1u, kBandWords / ((uint64_t)together * band_words)) : 1u << 20;
+    const uint32_t threads = bands > 1u ? 64u * 6u : 64u * 5u;
+    int dev = 0, khz = 0;
+    const unsigned long long wait = g_one_pass_wait.load(std::memory_order_relaxed);
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0)
+        khz = 100000;
+    a.wait_ticks = wait ? wait : 2000ull * (unsigned long long)khz;
+    a.withhold = (uint32_t)g_one_pass_withhold.load(std::memory_order_relaxed);
+    if (set) {
+        a.ticket = &set->ticket;
+        a.abort_word = &set->abort_word;
+    }
+    int rc = PILC_OK;
+    bool first = true;
+    for (uint64_t s = 0; rc == PILC_OK && s < strips; s += most_strips) {
+        const uint32_t here = (uint32_t)std::min<uint64_t>(most_strips, strips - s);
+        for (uint32_t b = 0; b < bands; b += together) {
+            a.strip0 = s;
+            a.band0 = b;
+            a.bands = std::min(together, bands - b);
+            a.words = a.bands > 1u ? set->words : nullptr;
+            if (set) {
+                const uint32_t words = a.bands > 1u ? here * a.bands * band_words : 0u;
+                k_band_clear<<<std::max(1u, std::min(1024u, words / 256u)), 256, 0, stream>>>(set, words, first);
+                first = false;
+            }
+            k_twar_inverse_diag<<<here * a.bands, threads, 0, stream>>>(k, a, res_dev, img_dev);
+        }
+    }
+    timer.mark("k_twar_inverse");
+    uint32_t aborted = 0u;
+    if (rc == PILC_OK) {
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess && set)
+            e = hipMemcpyAsync(&aborted, &set->abort_word, sizeof(aborted), hipMemcpyDeviceToHost, stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) rc = hip_fail(e, "k_twar_inverse_diag");
+    }
+    if (set) band_set_release(slot);
+    if (rc != PILC_OK) return rc;
+    timer.finish();
+    return aborted ? PILC_E_TIMEOUT : PILC_OK;
 }
 
 int pilc_twar_inverse(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev,
@@ -755,11 +975,18 @@ int pilc_twar_inverse(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev
     if (rc != PILC_OK) return rc;
     if (!img_dev || !res_dev || img_dev == res_dev) return PILC_E_ARG;
     hipStream_t stream = (hipStream_t)hip_stream;
+    Timer timer(stream);
+    const uint32_t last_bytes = (w + 15u) & ~15u;
+    const size_t tile_lds = (size_t)kTwarWaves * (last_bytes + 64u * (size_t)w * 3u);
+    // Narrow images in LDS tiles: up to 64 rows whole, taller ones 64 rows after 64 if there are enough
+    // images for that (tile against diagonals: 512 images of 300 x 64 109 against 89 us, 3000 of 128 x 33
+    // 88 against 135, 8192 of 96 x 64 153 against 362); rows of less than 16 pixels are too short for
+    // the diagonal kernel, and always fit a tile.
+    if (tile_lds > 64 * 1024 || (h > 64u && w >= 16u && n < kTileManyImages))
+        return twar_inverse_diag(n, h, w, res_dev, k, img_dev, stream, timer);
     const uint32_t per = h <= 64 ? 64 / h : 1;
     const uint32_t groups = (n + per - 1) / per;
     const uint32_t blocks = (groups + kTwarWaves - 1) / kTwarWaves;
-    const uint32_t last_bytes = (w + 15u) & ~15u;
-    const size_t tile_lds = (size_t)kTwarWaves * (last_bytes + 64u * (size_t)w * 3u);
     // the element of the tile copies: every group (whole images, or a band of 64 rows) must start
     // and end on a multiple of it
     const uint32_t row_bytes = w * 3u;
@@ -767,66 +994,12 @@ int pilc_twar_inverse(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev
     const bool whole_images = h <= 64;
     const uint32_t unit_bytes = whole_images ? h * row_bytes : row_bytes;
     const int elem = unit_bytes % 16u == 0u && (both & 15) == 0 ? 16 : unit_bytes % 4u == 0u && (both & 3) == 0 ? 4 : 1;
-    Timer timer(stream);
-    const bool tall = h > 64 && w % 16 == 0 && w <= 16384 && ((((uintptr_t)img_dev) | ((uintptr_t)res_dev)) & 15) == 0;
-    // few tall images: bands of up to 256 rows in workgroups of their own, four decoding wavefronts
-    // (one per SIMD) and their four movers (on 30 frames of 1080 x 1920: five bands of 216 rows
-    // 0.49 ms, six of 180 0.50, three of 360 0.57; one workgroup per frame 2.2)
-    uint32_t bands = tall && n < 256u ? (h + 255u) / 256u : 1u;
-    int slot = -1;
-    uint32_t *flags = nullptr;
-    if (bands > 1u && (uint64_t)n * bands * kBandStride <= kBandFlags) flags = band_flags_acquire(&slot);
-    if (tall && flags) {
-        const uint32_t band_rows = (h + bands - 1) / bands;
-        bands = (h + band_rows - 1) / band_rows;
-        const uint32_t nt = (band_rows + 63u) & ~63u;
-        const size_t lds = (size_t)nt * kTallStride + (nt / 64) * 64 + 32;
-        int dev = 0, khz = 0;
-        const unsigned long long wait = g_one_pass_wait.load(std::memory_order_relaxed);
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0)
-            khz = 100000;
-        rc = allow_large_lds(reinterpret_cast<const void *>(k_twar_inverse_tall<true>));
-        uint32_t aborted = 0u;
-        if (rc == PILC_OK) {
-            k_band_clear<<<(n * bands * kBandStride + 255u) / 256u, 256, 0, stream>>>(flags, n * bands * kBandStride);
-            const TallBands tb = {bands, band_rows, flags, flags + kBandFlags, flags + kBandFlags + 1,
-                                  wait ? wait : 2000ull * (unsigned long long)khz,
-                                  (uint32_t)g_one_pass_withhold.load(std::memory_order_relaxed)};
-            // a decoding and a moving wavefront per 64 rows
-            k_twar_inverse_tall<true><<<n * bands, 2u * nt, lds, stream>>>(k, h, w, 1u, tb, res_dev, img_dev);
-            timer.mark("k_twar_inverse");
-            hipError_t e = hipGetLastError();
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(&aborted, flags + kBandFlags + 1, sizeof(aborted), hipMemcpyDeviceToHost, stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(stream);
-            if (e != hipSuccess) rc = hip_fail(e, "k_twar_inverse_bands");
-        }
-        band_flags_release(slot);
-        if (rc != PILC_OK) return rc;
-        timer.finish();
-        return aborted ? PILC_E_TIMEOUT : PILC_OK;
-    }
-    if (tall) {
-        // as few rounds as the workgroup size allows, of equal size (three rounds of 512, 512 and 56
-        // rows of a 1080-row frame took 2.8 ms where two rounds of 540 take 2.2)
-        const uint32_t rounds = (h + kTallMaxThreads - 1) / kTallMaxThreads;
-        const uint32_t per = (h + rounds - 1) / rounds;
-        const uint32_t nt = (per + 63u) & ~63u;
-        const size_t lds = (size_t)nt * kTallStride + (nt / 64) * 64 + w;
-        if ((rc = allow_large_lds(reinterpret_cast<const void *>(k_twar_inverse_tall<false>))) != PILC_OK) return rc;
-        k_twar_inverse_tall<false><<<n, nt, lds, stream>>>(k, h, w, rounds, TallBands{}, res_dev, img_dev);
-    } else if (tile_lds <= 64 * 1024) {
-        if (elem == 16)
-            k_twar_inverse<true, u32x4><<<blocks, 64 * kTwarWaves, tile_lds, stream>>>(k, n, h, w, last_bytes, res_dev, img_dev);
-        else if (elem == 4)
-            k_twar_inverse<true, uint32_t><<<blocks, 64 * kTwarWaves, tile_lds, stream>>>(k, n, h, w, last_bytes, res_dev, img_dev);
-        else
-            k_twar_inverse<true, uint8_t><<<blocks, 64 * kTwarWaves, tile_lds, stream>>>(k, n, h, w, last_bytes, res_dev, img_dev);
-    } else {
-        k_twar_inverse<false, uint8_t><<<blocks, 64 * kTwarWaves, (size_t)kTwarWaves * last_bytes, stream>>>(
-            k, n, h, w, last_bytes, res_dev, img_dev);
-    }
+    if (elem == 16)
+        k_twar_inverse<u32x4><<<blocks, 64 * kTwarWaves, tile_lds, stream>>>(k, n, h, w, last_bytes, res_dev, img_dev);
+    else if (elem == 4)
+        k_twar_inverse<uint32_t><<<blocks, 64 * kTwarWaves, tile_lds, stream>>>(k, n, h, w, last_bytes, res_dev, img_dev);
+    else
+        k_twar_inverse<uint8_t><<<blocks, 64 * kTwarWaves, tile_lds, stream>>>(k, n, h, w, last_bytes, res_dev, img_dev);
     timer.mark("k_twar_inverse");
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(stream));

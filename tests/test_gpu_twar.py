@@ -102,6 +102,78 @@ def test_bands_give_up_a_wait_that_is_never_answered():
     assert np.array_equal(d_back.cpu().numpy(), img)
 
 
+# Rows of any width at any address, decoded along the anti-diagonals: one group of 64 rows and one row
+# more, the most and one more than a band, several bands, images that share a group of rows, widths
+# around the 16 columns of a block and the narrowest there are, photographs.
+@pytest.mark.parametrize("offset", [0, 1, 7], ids=lambda o: "at%d" % o)
+@pytest.mark.parametrize("shape", [(1, 65, 16), (2, 65, 17), (1, 128, 31), (3, 129, 33), (2, 300, 47), (1, 700, 85),
+                                   (5, 20, 333), (3, 64, 97), (65, 1, 129), (2, 33, 1000), (2, 1365, 2047)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_any_width_at_any_address(shape, offset):
+    print("shape", shape, "offset", offset, flush=True)
+    rng = np.random.default_rng(sum(shape) + offset)
+    noise = rng.integers(0, 256, shape + (3,), dtype=np.uint8)
+    _, wq, bq = list(models(rng))[offset % 3]
+    ref = to.inverse(to.make_params(wq, bq), noise)
+    size = noise.size
+
+    def at_offset(fill):
+        whole = torch.full((size + 64,), fill, dtype=torch.uint8, device="cuda:0")
+        return whole, whole[16 + offset:16 + offset + size].view(noise.shape)
+    p = pb.make_twar_params(wq, bq)
+    _, d_noise = at_offset(0x33)
+    d_noise.copy_(torch.from_numpy(noise))
+    whole, d_back = at_offset(0xA5)
+    pb.pilc_twar_inverse(p, d_noise, d_back)
+    assert np.array_equal(d_back.cpu().numpy(), ref)
+    whole, d_res = at_offset(0x5A)
+    pb.pilc_twar_forward(p, d_back, d_res)
+    assert np.array_equal(d_res.cpu().numpy(), noise)
+    # nothing beside the array has been written
+    assert bool((whole[:16 + offset] == 0x5A).all()) and bool((whole[16 + offset + size:] == 0x5A).all())
+
+
+@pytest.mark.parametrize("shape", [(6000, 129, 100), (1, 4100, 65535)], ids=lambda s: "x".join(map(str, s)))
+def test_more_bands_than_one_launch_takes(shape):
+    """More bands than there is room for the rows they pass on: several launches, over images or, for
+    an image with more bands than that by itself, over its bands."""
+    print("shape", shape, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    img = torch.randint(0, 256, shape + (3,), dtype=torch.uint8, device="cuda:0", generator=g)
+    p = pb.make_twar_params([[-ONE, ONE, ONE], [ONE // 2, -ONE // 2, ONE], [ONE // 2, -ONE // 2, ONE]], [0, 0, 0])
+    res, back = torch.empty_like(img), torch.full_like(img, 0xA5)
+    pb.pilc_twar_forward(p, img, res)
+    pb.pilc_twar_inverse(p, res, back)
+    assert torch.equal(back, img)
+
+
+def test_more_calls_at_once_than_sets_of_words():
+    """Eight threads with a stream each: the calls that find no set of words free go a band at a time."""
+    import threading
+    g = torch.Generator(device="cuda:0").manual_seed(4)
+    img = torch.randint(0, 256, (2, 900, 1001, 3), dtype=torch.uint8, device="cuda:0", generator=g)
+    p = pb.make_twar_params([[-ONE, ONE, ONE], [ONE // 2, -ONE // 2, ONE], [ONE // 2, -ONE // 2, ONE]], [0, 0, 0])
+    res = torch.empty_like(img)
+    pb.pilc_twar_forward(p, img, res)
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            back = torch.full_like(img, i)
+            for _ in range(6):
+                pb.pilc_twar_inverse(p, res, back, stream=stream)
+                if not torch.equal(back, img):
+                    wrong.append(i)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
 def test_bad_arguments():
     img = torch.zeros((2, 4, 4, 3), dtype=torch.uint8, device="cuda:0")
     out = torch.zeros_like(img)
