@@ -1,11 +1,10 @@
 // The table-driven coder of Sec. 3.2 (Alg. 3 "ANS-AI: Encode x", Alg. 4 "ANS-AI: Decode one
 // symbol") for gfx950: one thread per piece (Sec. 4.3), the tables of a workgroup in LDS.
 //
-// What bounds these kernels is memory, not arithmetic (a symbol costs about twenty integer
-// instructions, and two to three bytes of HBM traffic), so the layout work is all about moving
-// whole cache lines:
-//   - the symbol and index rows of a wavefront's 64 pieces are staged through LDS in chunks that
-//     are aligned in the arrays, with 16-byte loads in which consecutive threads cover one
+// A symbol costs some twenty to thirty instructions and two to three bytes of HBM traffic, and the layout work is
+// about moving whole cache lines:
+//   - the symbol and index rows of a wavefront's 64 pieces are staged through LDS in chunks (in the
+//     encoder chunks that are aligned in the arrays), with 16-byte loads in which consecutive threads cover one
 //     row's chunk, so every line is fetched once and fully used;
 //   - the encoder's words go to a scratch area laid out [wavefront][word][thread], so the 64
 //     threads of a wavefront, which emit at nearly the same rate, fill the same lines together;
@@ -125,7 +124,7 @@ __global__ __launch_bounds__(256) void k_ansai_build(uint32_t M, uint32_t X,
 // ---------------------------------------------------------------------------------------------
 // A row is the `count` bytes of one piece in a [pieces, count] array.  Rows are cut at multiples
 // of 128 bytes of the array ("lines"); line-stage number `ls` of a row is its ls-th line from the
-// front (decode) or from the back (encode).  A wavefront fetches a line-stage of all its rows with
+// front or from the back.  A wavefront fetches a line-stage of all its rows with
 // 16-byte loads in which eight consecutive threads cover one row's line: thread `lane` holds, for
 // i = 0..7, bytes [16c, 16c+16) of the line of row 8i + lane/8, with c = lane%8.  Every line is
 // thus requested once, whole.  The threads then pass the line through LDS in two halves of 64
@@ -481,28 +480,33 @@ __global__ void k_ansai_check_header(AShape sh, const uint8_t *__restrict__ code
     status->payload_bytes = payload;
 }
 
-// A thread's view of its piece's stream.  The words still to be taken sit in the payload below
-// `widx`; the next ones are kept ahead of use in a small per-thread ring in LDS, which is topped
-// up with aligned 16-byte loads issued a group of symbols before their data is needed, so no
-// step of the decoding chain ever waits for global memory.
-// LDS is what limits how many pieces a compute unit decodes at once (the tables take most of
-// it), so both per-thread areas are kept small: a ring of three quads and a row of 32 bytes.
-constexpr uint32_t kRingWords = 12;   // per thread: three aligned quads
-constexpr uint32_t kRingStride = 13;  // odd: threads reading their own rings hit distinct banks
-constexpr int kGroupSyms = 8;         // symbols between top-ups; they take at most 4 words (M <= 15)
-constexpr uint32_t kPart = 32;        // bytes of a row passed through LDS at a time: a quarter line
-constexpr uint32_t kDecRow = 10;      // LDS dwords per row: 32 bytes and a pad that keeps rows 8-byte aligned
+// What bounds the decoder is the instructions of a symbol and the two table reads in its chain (the symbol, and
+// the entry that gives the next state), so the stream is read by position: two symbols pop at most 30 bits,
+// and one 32-bit piece of the stream, cut out of two words wherever it starts, serves both.  There
+// is no bit buffer to shift, count and fill up: the position is all there is to keep.  The words wait
+// in a ring of 16 per thread in LDS that is topped up with aligned 16-byte loads asked for one or two groups
+// of symbols before they are needed.  Indices and symbols pass through LDS 32 to a row, and rows are
+// cut from their own start, whatever its alignment, so that all threads have the same positions of
+// their rows at the same time.
+// (A 63-bit window refilled a word at a time, with rows cut at 128-byte lines of the arrays, took 36.6 vector
+// instructions a symbol; now 20.  10^6 pieces of 1000 symbols under eight laws 1.68 -> 1.55 ms, which is
+// the chain of table reads with ten wavefronts on a compute unit (1.13 ms without the stores) and the
+// lines of the streams that are fetched again for every quad; 10^6 of 256 under one law 435 -> 290 us,
+// 1000 of 700 under four 146 -> 71 us.  Not faster: quads two at a time, fewer fetches but a shorter
+// lead (1.72 ms), symbols stored 32 bytes at a time (1.67 ms), non-temporal stores (2.28 ms), rows cut at
+// lines (1.68 ms).)
+// LDS is what limits how many pieces a compute unit decodes at once (the tables take most of it):
+// 6400 bytes a wavefront, ten wavefronts beside the 96 KB of eight laws at 12 bits.
+constexpr uint32_t kRingWords = 16;                    // per thread: four aligned quads
+constexpr int kGroupSyms = 8;                          // symbols between top-ups; they take at most 120 bits
+constexpr uint32_t kPart = 32;                         // bytes of a row passed through LDS at a time
+constexpr uint32_t kDecWaveDwords = 64u * (kPart / 4u + kRingWords + 1u);  // LDS of a wavefront
 
 struct DecLane {
-    uint32_t s;              // state minus 2^M
-    unsigned long long win;  // the next n bits of the stream from bit 62 downwards; bit 63 is 0
-    int n;                   // <= 63; negative once a corrupt stream has run dry
-    uint32_t widx;           // dword index (from the container's start) one past the next word
-    uint32_t lp;             // the ring holds the words [lp, widx); a multiple of 4
-    uint32_t first;          // dword index of the piece's first word; widx - first words are left
-    uint32_t rs;             // ring slot of word widx-1; slots fall with the word index, 0 wraps to 11
-    uint32_t ws;             // ring slot of word lp: 0, 4 or 8
-    uint32_t cand;           // word widx-1, read ahead from the ring
+    uint32_t s;      // state minus 2^M
+    uint32_t pos;    // bits below this one are still to be taken; counted from the container's start, mod 2^32
+    uint32_t lp;     // the ring holds the words from lp on; dword index, a multiple of 4
+    uint32_t first;  // dword index of the piece's first word
 };
 
 // An aligned quad that holds at least one word of the container: it lies inside the container's
@@ -512,144 +516,230 @@ __device__ __forceinline__ uint4 ansai_quad_load(const uint32_t *__restrict__ cw
     return *reinterpret_cast<const uint4 *>(cw + q);
 }
 
+// The ring is [row][thread]: word w in row (w mod 16) + 1, and in row 0 as well if that is row 16, so that
+// the word before any word is in the row before it.
 __device__ __forceinline__ void ansai_ring_put(uint32_t *ring, uint32_t slot, const uint4 &v)
 {
-    ring[slot] = v.x;
-    ring[slot + 1u] = v.y;
-    ring[slot + 2u] = v.z;
-    ring[slot + 3u] = v.w;
+    uint32_t *q = ring + 64u * (slot + 1u);
+    q[0] = v.x;
+    q[64] = v.y;
+    q[128] = v.z;
+    q[192] = v.w;
+    if (slot == kRingWords - 4u) ring[0] = v.w;
 }
 
-// Takes the next word into the window when fewer than 32 bits are left in it.  Written without
-// a branch: in a wavefront of 64 streams some thread needs a word at almost every call.
-__device__ __forceinline__ void ansai_refill(DecLane &L)
+// The 31 bits of the stream below the position, the highest in bit 30.
+__device__ __forceinline__ uint32_t ansai_next_bits(const DecLane &L, const uint32_t *ring)
 {
-    const bool need = L.n < 32 && L.widx > L.first;
-    const uint32_t c = need ? L.cand : 0u;
-    L.win |= (unsigned long long)c << ((31 - L.n) & 63);  // need implies 0 <= n <= 31
-    const uint32_t t = need ? 1u : 0u;
-    L.n += (int)(t << 5);
-    L.widx -= t;
-    const uint32_t below = L.rs == 0u ? kRingWords - 1u : L.rs - 1u;
-    L.rs = need ? below : L.rs;
+    const uint32_t *q = ring + 64u * ((L.pos >> 5) & (kRingWords - 1u));
+    return __builtin_amdgcn_alignbit(q[64], q[0], L.pos) >> 1;
 }
 
-__device__ __forceinline__ void ansai_peek(DecLane &L, const uint32_t *ring)
+// The table entry of a state: c = 15 - B[d,S] and n = N[d,S] - 2^M.  In global memory an entry holds n above its
+// low four bits and c in them; in LDS it is turned so that c is on top.
+struct DecEntry {
+    uint32_t c, n, x;
+};
+template <bool kWide, bool kTabLds>
+__device__ __forceinline__ DecEntry ansai_entry(uint32_t index, const uint8_t *theta, const void *nb_raw)
 {
-    L.cand = ring[L.rs];
+    const uint32_t e = kWide ? static_cast<const uint32_t *>(nb_raw)[index]
+                             : (uint32_t) static_cast<const uint16_t *>(nb_raw)[index];
+    DecEntry r;
+    r.x = theta[index];
+    if (!kTabLds) {
+        r.c = e & 15u;
+        r.n = e >> 4;
+    } else if (kWide) {
+        r.c = e >> 28;
+        r.n = e & 0x0FFFFFFFu;
+    } else {
+        r.c = e >> 12;
+        r.n = e & 0x0FFFu;
+    }
+    return r;
 }
 
-// One step of Alg. 4.  `dm` = d << M.  The table entry holds N[d,S] - 2^M above its low four
-// bits and 15 - B[d,S] in them, so that 31 - B, the shift that leaves the B popped bits (kept in
-// the order they were pushed) at the bottom of the window's upper word, is the low five bits of
-// (entry | 16).  A stream that has run dry yields zeros here; the count n then ends below zero and
-// the piece fails its final check.  With `active` false the step is the identity (no symbol of
-// this thread's row at this position).
-template <bool kWide, bool kMasked>
-__device__ __forceinline__ uint32_t ansai_pop(DecLane &L, uint32_t dm, bool active, const uint8_t *theta,
-                                              const void *nb_raw)
+// Two steps of Alg. 4 (S <- N[d,S] + popped bits; N - 2^M has zeros where the B popped bits go).  `dm` = d << M.
+template <bool kWide, bool kTabLds>
+__device__ __forceinline__ void ansai_pop_two(DecLane &L, uint32_t bits, uint32_t dm0, uint32_t dm1, uint32_t &x0,
+                                              uint32_t &x1, const uint8_t *theta, const void *nb)
 {
-    const uint32_t ti = dm + L.s;
-    uint32_t e = kWide ? static_cast<const uint32_t *>(nb_raw)[ti]
-                       : (uint32_t) static_cast<const uint16_t *>(nb_raw)[ti];
-    const uint32_t x = theta[ti];
-    if (kMasked) e = active ? e : (L.s << 4 | 15u);  // pops nothing, keeps the state
-    const uint32_t v = (uint32_t)(L.win >> 32) >> ((e | 16u) & 31u);
-    L.s = (e >> 4) + v;  // S <- N[d,S] + popped bits
-    const uint32_t b = ~e & 15u;
-    L.win = (L.win << b) & 0x7FFFFFFFFFFFFFFFull;
-    L.n -= (int)b;
-    return x;
+    const DecEntry a = ansai_entry<kWide, kTabLds>(dm0 + L.s, theta, nb);
+    L.s = a.n | (bits >> (a.c | 16u));  // by 31 - B
+    const DecEntry b = ansai_entry<kWide, kTabLds>(dm1 + L.s, theta, nb);
+    const uint32_t at = a.c + b.c + 1u;  // 31 - B - B'
+    L.s = b.n | __builtin_amdgcn_ubfe(bits, at, 15u - b.c);
+    L.pos += at - 31u;
+    x0 = a.x;
+    x1 = b.x;
 }
 
-// The part of [lo, hi) that falls into quarter `ph` of the line, relative to that quarter.
-__device__ __forceinline__ void part_range(const RowLine &r, uint32_t ph, uint32_t *lo, uint32_t *hi)
+template <bool kWide, bool kTabLds>
+__device__ __forceinline__ uint32_t ansai_pop_one(DecLane &L, const uint32_t *ring, uint32_t dm, const uint8_t *theta,
+                                                  const void *nb)
 {
-    const uint32_t base = ph * kPart;
-    *lo = min(max(r.lo, base), base + kPart) - base;
-    *hi = min(max(r.hi, base), base + kPart) - base;
+    const uint32_t bits = ansai_next_bits(L, ring);
+    const DecEntry a = ansai_entry<kWide, kTabLds>(dm + L.s, theta, nb);
+    L.s = a.n | (bits >> (a.c | 16u));
+    L.pos += a.c - 15u;
+    return a.x;
 }
 
-// Puts quarter `ph` of the fetched index lines into LDS, 32 bytes per row.
+// The bytes of a 16-byte aligned array from `off` to its end, fewer than 16, and zeros: from the array's last 16
+// bytes, or from its first 16-byte block if it is no longer than that.
+__device__ __forceinline__ uint4 array_tail(const uint8_t *__restrict__ arr, uint32_t total_bytes, uint32_t off)
+{
+    const uint32_t from = total_bytes >= 16u ? total_bytes - 16u : 0u;
+    unsigned __int128 x;
+    __builtin_memcpy(&x, arr + from, 16);
+    x >>= 8u * (off - from);
+    x &= ((unsigned __int128)1 << (8u * (total_bytes - off))) - 1u;
+    return make_uint4((uint32_t)x, (uint32_t)(x >> 32), (uint32_t)(x >> 64), (uint32_t)(x >> 96));
+}
+
+// Bytes [pos, pos + 128) of the rows of pieces p0 .. p0 + np - 1, thread `lane` holding, for i = 0 .. 7, sixteen
+// of row 8 i + lane / 8, those from pos + 16 (lane % 8) on: eight neighbouring threads cover 128 bytes of
+// a row.  Vectors that start in a row may end in the next one; zeros beyond a row's end.
+__device__ __forceinline__ void rows_load(const uint8_t *__restrict__ arr, uint32_t total_bytes, uint32_t p0, uint32_t np,
+                                          uint32_t count, uint32_t pos, uint4 (&v)[8])
+{
+    const uint32_t lane = threadIdx.x & 63u, at = pos + 16u * (lane & 7u);
+    uint32_t off = (p0 + (lane >> 3)) * count + at;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        v[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (8u * i + (lane >> 3) < np && at < count) {
+            if (off + 16u <= total_bytes) {
+                __builtin_memcpy(&v[i], arr + off, 16);
+            } else {  // at most one vector of the whole grid
+                asm volatile("" ::: "memory");  // keep this a branch
+                v[i] = array_tail(arr, total_bytes, off);
+            }
+        }
+        off += 8u * count;
+    }
+}
+
+// Quarter `ph` of the fetched 128 bytes into LDS as [dword][row].
 __device__ __forceinline__ void dec_put(uint32_t *rows, const uint4 (&dv)[8], uint32_t ph)
 {
     const uint32_t lane = threadIdx.x & 63u, c = lane & 7u;
     if ((c >> 1) != ph) return;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        uint2 *dst = reinterpret_cast<uint2 *>(rows + (i * 8 + (lane >> 3)) * kDecRow + (c & 1u) * 4u);
-        dst[0] = make_uint2(dv[i].x, dv[i].y);
-        dst[1] = make_uint2(dv[i].z, dv[i].w);
+        uint32_t *dst = rows + 64u * 4u * (c & 1u) + i * 8 + (lane >> 3);
+        dst[0] = dv[i].x;
+        dst[64] = dv[i].y;
+        dst[128] = dv[i].z;
+        dst[192] = dv[i].w;
     }
 }
 
-// Writes the decoded symbols of quarter `ph` of line-stage `ls` from LDS to the output rows:
-// only bytes that belong to a row.  Two threads cover a row's 32 bytes.
-__device__ __forceinline__ void dec_store(uint8_t *__restrict__ out, const uint32_t *rows, uint32_t p0,
-                                          uint32_t np, uint32_t count, uint32_t ls, uint32_t ph)
+// The decoded symbols of 32 positions from LDS, two threads a row: thread `lane` has sixteen bytes of rows lane / 2
+// and 32 + lane / 2.
+__device__ __forceinline__ void dec_get(const uint32_t *rows, u32x4 (&ov)[2])
 {
     const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t *src = rows + 64u * 4u * (lane & 1u) + (lane >> 1);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const uint32_t r = i * 32 + (lane >> 1), c = lane & 1u;
-        const RowLine rl = row_line(p0 + r, count, ls, false, r < np);
-        uint32_t lo, hi;
-        part_range(rl, ph, &lo, &hi);
-        const uint32_t vb = c * 16u;
-        if (hi > lo && vb < hi && vb + 16u > lo) {
-            const uint32_t *src = rows + r * kDecRow + c * 4u;
-            const uint32_t off = rl.line * kLine + ph * kPart + vb;
-            if (lo <= vb && vb + 16u <= hi) {
-                *reinterpret_cast<uint4 *>(out + off) = make_uint4(src[0], src[1], src[2], src[3]);
-            } else {
-                for (uint32_t k = 0; k < 16u; ++k)
-                    if (vb + k >= lo && vb + k < hi) out[off + k] = (uint8_t)(src[k >> 2] >> (8u * (k & 3u)));
-            }
+        ov[i].x = src[32 * i];
+        ov[i].y = src[32 * i + 64];
+        ov[i].z = src[32 * i + 128];
+        ov[i].w = src[32 * i + 192];
+    }
+}
+
+// The same to bytes [pos, pos + 32) of the rows.
+__device__ __forceinline__ void dec_store(uint8_t *__restrict__ out, const u32x4 (&ov)[2], uint32_t p0, uint32_t np,
+                                          uint32_t count, uint32_t pos)
+{
+    const uint32_t lane = threadIdx.x & 63u, at = pos + 16u * (lane & 1u);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t r = i * 32 + (lane >> 1);
+        if (r >= np || at >= count) continue;
+        uint8_t *q = out + (size_t)((p0 + r) * count + at);
+        if (at + 16u <= count) {
+            __builtin_memcpy(q, &ov[i], 16);
+        } else {
+            const uint32_t w[4] = {ov[i].x, ov[i].y, ov[i].z, ov[i].w};
+#pragma unroll
+            for (uint32_t k = 0; k < 15u; ++k)
+                if (at + k < count) q[k] = (uint8_t)(w[k >> 2] >> (8u * (k & 3u)));
         }
     }
 }
 
-// The 32 symbols of one quarter line of this thread's row, in groups of eight.  Before a group
-// the quad below the ring is requested when there is room for it (it lies below the quads fetched
-// at the start, hence inside the container) and after the group it is stored, so its latency
-// hides behind eight symbols of every wavefront on the SIMD.  A group takes at most four words
-// and starts with at least four in the ring: with room for a quad (at most 8 words held) the quad
-// arrives by the end of the group, without room at least 9 - 4 are left.
-// kMasked: positions outside [lo, hi) are skipped by identity steps.
-template <bool kWide, bool kMasked>
-__device__ __forceinline__ void dec_part(DecLane &L, uint32_t *my, uint32_t *ring,
-                                         const uint32_t *__restrict__ cw, uint32_t M, uint32_t lo,
-                                         uint32_t hi, const uint8_t *theta, const void *nb)
+// What a thread asks for before a group of symbols if there is room for it: the aligned quad below the ring (below
+// the quads fetched at the start, hence inside the container).  It is put into the ring at the end of the
+// next group, or of its own if that is the last of 32 symbols.  There is room while fewer than 384 bits lie
+// between the ring's end and the position; a group then starts with at least 385 - 120 - 120 bits
+// that have arrived, and takes words no further than 122 down.  (A load in any case, of the header's
+// first quad if none is wanted: with loads that may or may not be under way, the wait for one is a
+// wait for all.)
+struct DecAhead {
+    uint4 quad;
+    uint32_t slot;  // kRingWords: none
+};
+__device__ __forceinline__ DecAhead ansai_ask(DecLane &L, const uint32_t *__restrict__ cw)
 {
-#pragma unroll 1
-    for (int g = 0; g < (int)kPart / kGroupSyms; ++g) {
-        const uint32_t qb = L.lp - 4u;
-        const bool want = L.widx - L.lp <= kRingWords - 4u && L.lp > L.first;
-        uint4 q;
-        if (want) q = ansai_quad_load(cw, qb);
-        ansai_peek(L, ring);
-#pragma unroll 1
-        for (int hh = 0; hh < kGroupSyms / 4; ++hh) {
-            const int dw = g * (kGroupSyms / 4) + hh;
-            const uint32_t d4 = my[dw];
-            uint32_t x4 = 0u;
+    const bool want = L.pos - 32u * L.lp < 384u && L.lp > L.first;
+    L.lp -= want ? 4u : 0u;
+    DecAhead a;
+    a.quad = ansai_quad_load(cw, want ? L.lp : 0u);
+    a.slot = want ? L.lp & (kRingWords - 1u) : kRingWords;
+    return a;
+}
+__device__ __forceinline__ void ansai_put_ahead(uint32_t *ring, const DecAhead &a)
+{
+    if (a.slot != kRingWords) ansai_ring_put(ring, a.slot, a.quad);
+}
+
+// The next `n` symbols (1 .. 32, the same for every thread) of this thread's row, in groups of eight.
+template <bool kWide, bool kTabLds>
+__device__ __forceinline__ void dec_part(DecLane &L, uint32_t *my, uint32_t *ring, const uint32_t *__restrict__ cw,
+                                         uint32_t M, uint32_t n, const uint8_t *theta, const void *nb)
+{
+    auto group = [&](uint32_t g) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if ((k & 1) == 0) {
-                    ansai_refill(L);
-                    ansai_peek(L, ring);
-                }
-                const uint32_t dm = ((d4 >> (8 * k)) & 255u) << M;
-                const bool active = !kMasked || (uint32_t)(dw * 4 + k) - lo < hi - lo;
-                x4 |= ansai_pop<kWide, kMasked>(L, dm, active, theta, nb) << (8 * k);
-            }
-            my[dw] = x4;
+        for (uint32_t h = 0; h < (uint32_t)kGroupSyms / 4u; ++h) {
+            uint32_t *cell = my + 64u * (g / 4u + h);
+            const uint32_t d4 = *cell;
+            uint32_t x[4];
+            ansai_pop_two<kWide, kTabLds>(L, ansai_next_bits(L, ring), (d4 & 255u) << M, ((d4 >> 8) & 255u) << M, x[0], x[1], theta, nb);
+            ansai_pop_two<kWide, kTabLds>(L, ansai_next_bits(L, ring), ((d4 >> 16) & 255u) << M, (d4 >> 24) << M, x[2], x[3], theta, nb);
+            *cell = x[0] | (x[1] << 8) | (x[2] << 16) | (x[3] << 24);
         }
-        if (want) {
-            L.ws = L.ws == 0u ? kRingWords - 4u : L.ws - 4u;
-            ansai_ring_put(ring, L.ws, q);
-            L.lp = qb;
-        }
+    };
+    if (n == kPart) {
+        DecAhead a = ansai_ask(L, cw);
+        group(0u);
+        DecAhead b = ansai_ask(L, cw);
+        group(8u);
+        ansai_put_ahead(ring, a);
+        a = ansai_ask(L, cw);
+        group(16u);
+        ansai_put_ahead(ring, b);
+        b = ansai_ask(L, cw);
+        group(24u);
+        ansai_put_ahead(ring, a);
+        ansai_put_ahead(ring, b);
+        return;
+    }
+    uint32_t g = 0;
+#pragma unroll 1
+    for (; g + kGroupSyms <= n; g += kGroupSyms) {
+        const DecAhead a = ansai_ask(L, cw);
+        group(g);
+        ansai_put_ahead(ring, a);
+    }
+    // the row's last symbols, fewer than a group
+#pragma unroll 1
+    for (; g < n; ++g) {
+        uint8_t *cell = reinterpret_cast<uint8_t *>(my + 64u * (g / 4u)) + (g & 3u);
+        *cell = (uint8_t)ansai_pop_one<kWide, kTabLds>(L, ring, (uint32_t)*cell << M, theta, nb);
     }
 }
 
@@ -670,7 +760,11 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
         const uint32_t th_dw = (entries + 3u) >> 2, nb_dw = kWide ? entries : (entries + 1u) >> 1;
         const uint32_t *tg = reinterpret_cast<const uint32_t *>(theta_g);
         const uint32_t *ng = reinterpret_cast<const uint32_t *>(nb_g);
-        for (uint32_t i = threadIdx.x; i < nb_dw; i += blockDim.x) lds[i] = ng[i];
+        for (uint32_t i = threadIdx.x; i < nb_dw; i += blockDim.x) {  // (entries turned: see DecEntry)
+            const uint32_t e = ng[i];
+            lds[i] = kWide ? __builtin_amdgcn_alignbit(e, e, 4)
+                           : ((e >> 4) & 0x0FFF0FFFu) | ((e << 12) & 0xF000F000u);
+        }
         for (uint32_t i = threadIdx.x; i < th_dw; i += blockDim.x) lds[nb_dw + i] = tg[i];
         nb = lds;
         theta = reinterpret_cast<const uint8_t *>(lds + nb_dw);
@@ -683,9 +777,9 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
     const uint32_t p0 = gw * 64u;
     if (p0 >= sh.pieces) return;
     const uint32_t np = min(64u, sh.pieces - p0);
-    uint32_t *rows = stage_base + wave * 64u * (kDecRow + kRingStride);
-    uint32_t *ring = rows + 64u * kDecRow + lane * kRingStride;
-    uint32_t *my = rows + lane * kDecRow;
+    uint32_t *rows = stage_base + wave * kDecWaveDwords;
+    uint32_t *my = rows + lane;
+    uint32_t *ring = rows + 64u * (kPart / 4u) + lane;
     const uint32_t total = sh.pieces * sh.count;
     const uint32_t top = 1u << sh.M, M = sh.M;
     const uint32_t *cw = reinterpret_cast<const uint32_t *>(coded);
@@ -697,14 +791,9 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
     uint32_t corrupt = 0u, bad = 0u;
     DecLane L;
     L.s = 0u;
-    L.win = 0ull;
-    L.n = 0;
-    L.widx = pay_dw + 4u;
-    L.lp = L.widx & ~3u;
-    L.first = L.widx;
-    L.rs = 0u;
-    L.ws = 0u;
-    L.cand = 0u;
+    L.first = pay_dw;
+    L.pos = 32u * L.first;
+    L.lp = L.first;
     if (mine) {
         const uint32_t begin = cw[off_dw + p0 + lane], end = cw[off_dw + p0 + lane + 1u];
         bool ok = end >= begin && end - begin >= 8u && end <= payload_bytes && ((begin | end) & 3u) == 0u;
@@ -717,22 +806,13 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
             if (ok) {
                 L.s = state - top;
                 L.first = rec + 2u;
-                L.widx = L.first + nw;
-                if (nw > 0u) {  // the last word holds the top 1..32 bits
-                    const uint32_t r = bits - 32u * (nw - 1u);
-                    L.widx -= 1u;
-                    L.win = (unsigned long long)(cw[L.widx] & (0xFFFFFFFFu >> (32u - r))) << (63u - r);
-                    L.n = (int)r;
-                }
-                // fill the ring with the 12 words that end at the aligned quad holding word widx-1
-                L.lp = (L.widx + 3u) & ~3u;
-                if (L.widx > L.first) {
-                    L.rs = 8u + ((L.widx - 1u) & 3u);
+                L.pos = 32u * L.first + bits;
+                L.lp = L.first;
+                if (nw > 0u) {  // the 16 words that end with the aligned quad holding the last one
+                    L.lp = ((L.first + nw - 1u) & ~3u) - 12u;  // (below the first piece's words lie header and offsets)
 #pragma unroll
-                    for (int i = 2; i >= 0; --i) {
-                        L.lp -= 4u;
-                        ansai_ring_put(ring, 4u * i, ansai_quad_load(cw, L.lp));
-                    }
+                    for (uint32_t i = 0; i < 4u; ++i)
+                        ansai_ring_put(ring, (L.lp + 4u * i) & (kRingWords - 1u), ansai_quad_load(cw, L.lp + 4u * i));
                 }
             }
         }
@@ -743,32 +823,32 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
     }
 
     uint4 dv[8];
-    const uint32_t lines = line_stage_count(sh.count);
-    line_load(dist, total, p0, np, sh.count, 0u, false, dv);
-    for (uint32_t ls = 0; ls < lines; ++ls) {
-        // the row geometry is recomputed per line-stage instead of being kept in registers for
-        // all the rows a thread helps to move: that keeps the kernel free of register spills
-        asm volatile("" : "+s"(sh.count));
-        const RowLine rl = row_line(p0 + lane, sh.count, ls, false, mine);
+    rows_load(dist, total, p0, np, sh.count, 0u, dv);
+    for (uint32_t pos0 = 0; pos0 < sh.count; pos0 += 4u * kPart) {
         bad |= lines_check(dv, lim_d);
 #pragma unroll 1
-        for (uint32_t h = 0; h < kLine / kPart; ++h) {
-            wave_lds_sync();
-            dec_put(rows, dv, h);
-            wave_lds_sync();
-            if (h == kLine / kPart - 1u && ls + 1u < lines)
-                line_load(dist, total, p0, np, sh.count, ls + 1u, false, dv);
-            uint32_t lo, hi;
-            part_range(rl, h, &lo, &hi);
-            if (__all(lo == 0u && hi == kPart))
-                dec_part<kWide, false>(L, my, ring, cw, M, lo, hi, theta, nb);
-            else
-                dec_part<kWide, true>(L, my, ring, cw, M, lo, hi, theta, nb);
-            wave_lds_sync();
-            dec_store(out, rows, p0, np, sh.count, ls, h);
+        for (uint32_t half = 0; half < 2u; ++half) {
+            // two times 32 symbols, which leave together: memory takes writes 64 bytes at a time
+            u32x4 ov[2][2] = {};
+#pragma unroll
+            for (uint32_t h = 0; h < 2u; ++h) {
+                const uint32_t pos = pos0 + (2u * half + h) * kPart;
+                if (pos >= sh.count) break;
+                wave_lds_sync();
+                dec_put(rows, dv, 2u * half + h);
+                wave_lds_sync();
+                if (h == 1u && half == 1u && pos0 + 4u * kPart < sh.count)
+                    rows_load(dist, total, p0, np, sh.count, pos0 + 4u * kPart, dv);
+                dec_part<kWide, kTabLds>(L, my, ring, cw, M, min(kPart, sh.count - pos), theta, nb);
+                wave_lds_sync();
+                dec_get(rows, ov[h]);
+            }
+            const uint32_t pos = pos0 + 2u * half * kPart;
+            if (pos < sh.count) dec_store(out, ov[0], p0, np, sh.count, pos);
+            if (pos + kPart < sh.count) dec_store(out, ov[1], p0, np, sh.count, pos + kPart);
         }
     }
-    if (mine && (L.s != 0u || L.n != 0 || L.widx != L.first)) corrupt = 1u;
+    if (mine && (L.s != 0u || L.pos != 32u * L.first)) corrupt = 1u;
     // many threads may report: the larger code (a damaged container) wins, whatever the order
     if (corrupt)
         atomicMax(&status->code, ST_CORRUPT);
@@ -1042,7 +1122,7 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
     // wavefronts' staging rows; as many wavefronts (<= kAnsaiDecMaxWaves) as then fit.
     const size_t entries = (size_t)sh.D << sh.M;
     const size_t tab_lds = ((entries + 3) / 4 + (t.wide ? entries : (entries + 1) / 2)) * 4;
-    const size_t row_lds = (size_t)64 * (kDecRow + kRingStride) * 4;
+    const size_t row_lds = (size_t)kDecWaveDwords * 4;
     bool tab_in_lds = tab_lds + 4 * row_lds <= lds_max;
     uint32_t waves = 4;
     if (tab_in_lds) {

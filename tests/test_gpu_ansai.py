@@ -91,6 +91,25 @@ def test_decode_returns_the_symbols(case):
     assert np.array_equal(dp.decoded_numpy(), dp.sym_np)
 
 
+@pytest.mark.parametrize("m,d", [(12, 8), (15, 2), (13, 1)], ids=["M12", "M15", "M13"])
+@pytest.mark.parametrize("count", [1, 2, 7, 8, 9, 31, 32, 33, 40, 63, 64, 65, 95, 127, 128, 129, 136, 255, 300])
+def test_rows_of_every_length_decode(count, m, d):
+    """Row lengths around the eight symbols of a group, the 32 that pass through LDS together and the 128
+    that are fetched together, at every alignment of the rows; symbols drawn uniformly, so that the rare
+    ones with the longest codes come as often as the others; arrays of fewer than 16 bytes among them."""
+    mass = sp.logistic_masses(m, d)
+    for pieces in (1, 3, 67, 200):
+        print("M", m, "D", d, "count", count, "pieces", pieces, flush=True)
+        sym, dist = sp.draw_pieces(mass, m, pieces, count, seed=count + pieces, uniform_sym=True, threads=1)
+        dp = DevicePieces(m, mass, sym, dist)
+        rc, ref = ao.encode(m, mass, sym, dist)
+        assert rc == ao.OK
+        buf = torch.zeros(ref.size + 16, dtype=torch.uint8, device="cuda:0")
+        buf[: ref.size] = torch.from_numpy(ref).cuda()
+        dp.decode(coded=buf, nbytes=ref.size)
+        assert np.array_equal(dp.decoded_numpy(), sym)
+
+
 def test_every_workgroup_shape_of_the_decoder_gives_the_same_symbols():
     """One input through workgroups of 1 .. 12 wavefronts (as many as fit beside the tables), for
     tables in LDS with 16-bit and with 32-bit entries and for tables in global memory."""
