@@ -174,7 +174,7 @@ def measure_traffic(argv, count):
 
 
 def _matches(kernel, name):
-    # the timing name is the kernel's, or its stem (k_twar_inverse: k_twar_inverse<..>, .._tall)
+    # the timing name is the kernel's, or its stem (k_twar_inverse: k_twar_inverse<..>, .._diag)
     return ("::" + kernel) in name and not name.split("::" + kernel)[1][:1].isalpha()
 
 
