@@ -744,6 +744,11 @@ __device__ __forceinline__ void dec_part(DecLane &L, uint32_t *my, uint32_t *rin
 }
 
 constexpr int kAnsaiDecMaxWaves = 12;
+// Three wavefronts a compute unit with the tables in LDS are still faster than many with the tables in global memory
+// (200,000 pieces of 500 symbols under 91 laws at 9 bits 486 against 813 us, under 23 at 11 bits 482
+// against 815; 2000 pieces under 91 laws 96 against 134); tables for which only two would fit were not
+// timed in LDS and stay in global memory.
+constexpr int kAnsaiDecLeastWaves = 3;
 
 template <bool kWide, bool kTabLds>
 __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
@@ -1118,12 +1123,12 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
     const ATabLayout t = ansai_tab_layout(sh.M, sh.D, sh.X);
     const uint8_t *tb = static_cast<const uint8_t *>(tables_dev);
 
-    // Workgroup shape: the decode tables in LDS when they leave room for at least four
+    // Workgroup shape: the decode tables in LDS when they leave room for at least kAnsaiDecLeastWaves
     // wavefronts' staging rows; as many wavefronts (<= kAnsaiDecMaxWaves) as then fit.
     const size_t entries = (size_t)sh.D << sh.M;
     const size_t tab_lds = ((entries + 3) / 4 + (t.wide ? entries : (entries + 1) / 2)) * 4;
     const size_t row_lds = (size_t)kDecWaveDwords * 4;
-    bool tab_in_lds = tab_lds + 4 * row_lds <= lds_max;
+    bool tab_in_lds = tab_lds + kAnsaiDecLeastWaves * row_lds <= lds_max;
     uint32_t waves = 4;
     if (tab_in_lds) {
         // small tables: several workgroups per compute unit; large ones: one big workgroup

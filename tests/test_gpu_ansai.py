@@ -110,6 +110,28 @@ def test_rows_of_every_length_decode(count, m, d):
         assert np.array_equal(dp.decoded_numpy(), sym)
 
 
+@pytest.mark.parametrize("m,d", [(9, 90), (9, 91), (9, 94), (9, 95), (11, 23), (11, 24)])
+def test_tables_that_just_fit_beside_the_rows(m, d):
+    """Decode tables around the size up to which they are kept in LDS: the most laws that leave room for four
+    wavefronts' rows, the least and the most that leave room for three, and one law more, whose tables stay
+    in global memory; as many wavefronts as the library likes, one, and as many as fit."""
+    mass = sp.logistic_masses(m, d)
+    sym, dist = sp.draw_pieces(mass, m, 900, 77, seed=d, uniform_sym=True, threads=1)
+    dp = DevicePieces(m, mass, sym, dist)
+    rc, ref = ao.encode(m, mass, sym, dist)
+    assert rc == ao.OK
+    buf = torch.zeros(ref.size + 16, dtype=torch.uint8, device="cuda:0")
+    buf[: ref.size] = torch.from_numpy(ref).cuda()
+    try:
+        for waves in (0, 1, 12):
+            print("M", m, "D", d, "waves", waves, flush=True)
+            pb.pilc_set_ansai_decode_waves(waves)
+            dp.decode(coded=buf, nbytes=ref.size)
+            assert np.array_equal(dp.decoded_numpy(), sym)
+    finally:
+        pb.pilc_set_ansai_decode_waves(0)
+
+
 def test_every_workgroup_shape_of_the_decoder_gives_the_same_symbols():
     """One input through workgroups of 1 .. 12 wavefronts (as many as fit beside the tables), for
     tables in LDS with 16-bit and with 32-bit entries and for tables in global memory."""
