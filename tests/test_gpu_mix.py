@@ -35,6 +35,10 @@ CASES = [
     ("cfg1-k10-long-lanes", lambda: synth_mix.make_mix_workload(1, 16 * 2 + 5, 10)),
     ("cfg4-k10-M16", lambda: synth_mix.make_mix_workload(4, 6, 10, h=32, w=32, prec_bits=16, lanes_per_image=16)),
     ("many-lanes-k10", lambda: synth_mix.from_base(synth.make_random_case(19, 70, 16, 16, 14, 0, 8), 10, 19)),
+    # the component counts that no case above has: every count from 1 to 16 has kernels of its own
+    *[("wild-k%d-ragged-tiles" % k, lambda k=k: synth_mix.from_base(
+        synth.make_random_case(20 + k, 3, 21, 37, 11 + k % 5, 1, 8, 16, wild=True), k, 20 + k))
+      for k in (6, 8, 11, 12, 13, 14, 15)],
 ]
 
 
