@@ -21,7 +21,8 @@
  *     The library's only process-wide state: the constant tables (filled once per device under a
  *     lock), the knobs pilc_set_timing, pilc_set_kernel_policy, pilc_set_one_pass_wait and
  *     pilc_set_ansai_decode_waves (atomic integers, read once at the start of a call), the scratch array of pilc_encode_static, and four
- *     sets of words that calls of pilc_twar_inverse on tall images pass rows on through, one a call.
+ *     sets of words (4 MB each, on every GPU) that calls of pilc_twar_inverse on tall images pass rows on
+ *     through, one a call.
  *   - Tensors are dense, row-major, channel-interleaved: index ((i*h + y)*w + x)*3 + c.
  */
 #ifndef PILC_H
@@ -295,9 +296,10 @@ int pilc_twar_forward(uint32_t n, uint32_t h, uint32_t w, const uint8_t *img_dev
                       const pilc_twar_params *params_host, uint8_t *res_dev, void *hip_stream);
 
 /* The image back from the residual (Sec. 3.1: the anti-diagonal / column schedule of the paper's
- * decoding figure, here one walk along the anti-diagonals of 64 rows at a time).  Fewer than
- * 256 images of more than 64 rows are decoded in bands of 64 that follow each other through words
- * in the library's device globals; their wait for the band above is bounded
+ * decoding figure, here one walk along the anti-diagonals of 64 rows at a time).  Images of more than
+ * 64 rows that are too few to fill the GPU by themselves (fewer than 192, at most) are decoded in bands
+ * of 64 rows that follow each other through words in the library's device globals (16 MB on every GPU,
+ * there from the time the library is loaded); their wait for the band above is bounded
  * like the one-pass encoder's (pilc_set_one_pass_wait) and ends in PILC_E_TIMEOUT.
  * Errors: PILC_E_ARG, PILC_E_TOO_LARGE, PILC_E_HIP, PILC_E_TIMEOUT (img_dev contents undefined). */
 int pilc_twar_inverse(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev,

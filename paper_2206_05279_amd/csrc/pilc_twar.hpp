@@ -803,7 +803,6 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
 // entry points take no workspace), handed out under a lock so that concurrent calls do not share
 // one; a call that finds none free goes a band at a time, a launch each, every band reading the row
 // above it from the image.
-constexpr uint64_t kDiagManyStrips = 256;   // a workgroup for every compute unit
 constexpr uint32_t kTileManyImages = 1024;  // a wavefront for every SIMD
 constexpr int kBandSlots = 4;
 constexpr uint32_t kBandWords = 1u << 19;  // 4 MB a set: 132 bands of 16384 columns, 1057 of 1920
@@ -901,6 +900,25 @@ int pilc_twar_forward(uint32_t n, uint32_t h, uint32_t w, const uint8_t *img_dev
     return PILC_OK;
 }
 
+// Whether the bands of a batch are decoded one at a time, a launch each, and not together.  Together, a band waits
+// a good part of its time for the one above and takes a place that another strip could have; one at a
+// time, a launch has no more workgroups than there are strips.  So it depends on how well the strips
+// fill the chip by themselves, and how far beyond its places (four workgroups a compute unit, 1024) all bands
+// together would go; wider rows wait less.  Together against one at a time, us:
+//   strips x bands   64 columns    400 columns       strips x bands   64 columns    400 columns
+//     64 x 12         106  166      137  291           160 x 8        163  124      203  203
+//    112 x 10         152  150      189  247           160 x 12       264  178      327  300
+//    112 x 16         274  232      337  389           176 x 5         94   83      123  133
+//    128 x 8          129  123      165  202           200 x 3         60   53       86   87
+//    128 x 12         218  178      263  296           250 x 5        136   79      185  135
+// and two bands of up to 192 columns are too short to gain anything from running together (48 x 2, 128 columns:
+// 49 and 46; 160 x 2: 55 and 47).
+static bool bands_one_at_a_time(uint64_t strips, uint32_t bands, uint32_t w)
+{
+    if (strips >= 192u || (bands == 2u && w < 192u)) return true;
+    return strips * strips * bands >= (w < 192u ? 131000u : 200000u);
+}
+
 // pilc_twar_inverse by k_twar_inverse_diag.
 static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev, const TwarK &k,
                              uint8_t *img_dev, hipStream_t stream, Timer &timer)
@@ -913,12 +931,8 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
     a.blocks = (w + 63u + 15u) / 16u;
     const uint64_t strips = (a.rows + a.strip_rows - 1u) / a.strip_rows;
     const uint32_t bands = (a.strip_rows + 63u) / 64u;
-    // With enough strips to fill the chip by themselves, bands go one at a time, a launch each: a band that
-    // waits for the one above takes the place of one that would not have to (together against one at a
-    // time: 64 images of 200 x 301 43 against 77 us, 128 of 512 x 512 167 against 217; 256 of either 107
-    // against 84 and 365 against 259; 2048 of 256 x 256 1081 against 470).
     int slot = -1;
-    BandSet *set = bands > 1u && strips < kDiagManyStrips ? band_set_acquire(&slot) : nullptr;
+    BandSet *set = bands > 1u && !bands_one_at_a_time(strips, bands, w) ? band_set_acquire(&slot) : nullptr;
     // bands of a strip and strips in a launch: what the words passed on have room for
     const uint32_t band_words = 4u * a.blocks;
     const uint32_t together = set ? (uint32_t)std::min<uint64_t>(bands, kBandWords / band_words) : 1u;
@@ -967,6 +981,26 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
     return aborted ? PILC_E_TIMEOUT : PILC_OK;
 }
 
+// Whether images of more than 64 rows whose rows fit a tile go 64 rows after 64 through the tile kernel.  That takes
+// a wavefront an image, whose time does not change until every SIMD has one; the diagonal kernel takes a
+// workgroup an image and slows down with every further one on a compute unit.  Rows of less than 16 pixels are
+// too short for the diagonal kernel; tiles copied by single bytes are slower.  Tile against diagonal, us,
+// images of 500 rows:
+//   images    20 columns   28 columns   40 columns   60 columns   17 columns (single bytes)
+//     500     127  131     146  138     169  142     211  155     174  128
+//     700     128  152     146  160     170  166     211  181     174  147
+//     850     128  204     147  218     170  224     212  246     175  197
+//    1000     128  207     147  221     171  227     213  250     176  199
+// and the last band of an image costs the tile kernel less if it has few rows: 700 images of 65 rows 44 against 47 us
+// at 40 columns.
+static bool tall_in_tiles(uint32_t n, uint32_t h, uint32_t w, int elem)
+{
+    if (w < 16u || n >= kTileManyImages) return true;
+    const uint32_t each = (n + 255u) / 256u;  // workgroups of the diagonal kernel on a compute unit
+    const uint32_t most = elem == 1 ? (each >= 4u ? 28u : 0u) : each >= 4u ? 84u : each == 3u ? 36u : each == 2u ? 24u : 0u;
+    return most != 0u && w <= most + (h <= 96u ? 12u : 0u);
+}
+
 int pilc_twar_inverse(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev,
                       const pilc_twar_params *params_host, uint8_t *img_dev, void *hip_stream)
 {
@@ -978,15 +1012,6 @@ int pilc_twar_inverse(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev
     Timer timer(stream);
     const uint32_t last_bytes = (w + 15u) & ~15u;
     const size_t tile_lds = (size_t)kTwarWaves * (last_bytes + 64u * (size_t)w * 3u);
-    // Narrow images in LDS tiles: up to 64 rows whole, taller ones 64 rows after 64 if there are enough
-    // images for that (tile against diagonals: 512 images of 300 x 64 109 against 89 us, 3000 of 128 x 33
-    // 88 against 135, 8192 of 96 x 64 153 against 362); rows of less than 16 pixels are too short for
-    // the diagonal kernel, and always fit a tile.
-    if (tile_lds > 64 * 1024 || (h > 64u && w >= 16u && n < kTileManyImages))
-        return twar_inverse_diag(n, h, w, res_dev, k, img_dev, stream, timer);
-    const uint32_t per = h <= 64 ? 64 / h : 1;
-    const uint32_t groups = (n + per - 1) / per;
-    const uint32_t blocks = (groups + kTwarWaves - 1) / kTwarWaves;
     // the element of the tile copies: every group (whole images, or a band of 64 rows) must start
     // and end on a multiple of it
     const uint32_t row_bytes = w * 3u;
@@ -994,6 +1019,11 @@ int pilc_twar_inverse(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev
     const bool whole_images = h <= 64;
     const uint32_t unit_bytes = whole_images ? h * row_bytes : row_bytes;
     const int elem = unit_bytes % 16u == 0u && (both & 15) == 0 ? 16 : unit_bytes % 4u == 0u && (both & 3) == 0 ? 4 : 1;
+    if (tile_lds > 64 * 1024 || (!whole_images && !tall_in_tiles(n, h, w, elem)))
+        return twar_inverse_diag(n, h, w, res_dev, k, img_dev, stream, timer);
+    const uint32_t per = h <= 64 ? 64 / h : 1;
+    const uint32_t groups = (n + per - 1) / per;
+    const uint32_t blocks = (groups + kTwarWaves - 1) / kTwarWaves;
     if (elem == 16)
         k_twar_inverse<u32x4><<<blocks, 64 * kTwarWaves, tile_lds, stream>>>(k, n, h, w, last_bytes, res_dev, img_dev);
     else if (elem == 4)

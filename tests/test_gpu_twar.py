@@ -133,6 +133,30 @@ def test_any_width_at_any_address(shape, offset):
     assert bool((whole[:16 + offset] == 0x5A).all()) and bool((whole[16 + offset + size:] == 0x5A).all())
 
 
+# Images of more than 64 rows on either side of each line at which the route changes: tiles or diagonals (by how
+# many there are and how wide), bands together or one at a time (by how many strips, bands and columns).
+@pytest.mark.parametrize("offset", [0, 1], ids=lambda o: "at%d" % o)
+@pytest.mark.parametrize("shape", [(256, 65, 24), (257, 97, 24), (257, 97, 28), (300, 65, 36), (300, 65, 40), (512, 97, 36),
+                                   (513, 97, 36), (513, 97, 40), (768, 97, 84), (769, 97, 84), (769, 129, 27),
+                                   (769, 129, 29), (769, 96, 39), (769, 96, 41), (1023, 70, 83), (1024, 70, 83),
+                                   (1030, 65, 15), (191, 150, 64), (192, 150, 64), (40, 128, 191), (40, 128, 192),
+                                   (127, 512, 64), (128, 512, 64), (128, 512, 192), (128, 770, 192), (111, 1000, 192)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_both_sides_of_every_line(shape, offset):
+    print("shape", shape, "offset", offset, flush=True)
+    rng = np.random.default_rng(sum(shape) + offset)
+    noise = rng.integers(0, 256, shape + (3,), dtype=np.uint8)
+    _, wq, bq = list(models(rng))[1 + offset]
+    size = noise.size
+    d_noise, d_back = (torch.full((size + 64,), 0xA5, dtype=torch.uint8, device="cuda:0") for _ in range(2))
+    d_noise[16 + offset:16 + offset + size] = torch.from_numpy(noise.reshape(-1)).cuda()
+    pb.pilc_twar_inverse(pb.make_twar_params(wq, bq), d_noise[16 + offset:16 + offset + size].view(noise.shape),
+                         d_back[16 + offset:16 + offset + size].view(noise.shape))
+    back = d_back.cpu().numpy()
+    assert np.array_equal(back[16 + offset:16 + offset + size], to.inverse(to.make_params(wq, bq), noise).reshape(-1))
+    assert (back[:16 + offset] == 0xA5).all() and (back[16 + offset + size:] == 0xA5).all()
+
+
 @pytest.mark.parametrize("shape", [(6000, 129, 100), (1, 4100, 65535)], ids=lambda s: "x".join(map(str, s)))
 def test_more_bands_than_one_launch_takes(shape):
     """More bands than there is room for the rows they pass on: several launches, over images or, for
