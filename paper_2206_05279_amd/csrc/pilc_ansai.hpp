@@ -1140,7 +1140,19 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
         if (waves > 4u && hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
             const uint32_t each = (uint32_t)ceil_div64(ws.waves, (uint64_t)cus);
-            waves = each < 4u ? 4u : (each < waves ? each : waves);
+            if (each <= waves)
+                waves = std::max(4u, each);
+            else if (waves >= 8u && sh.count >= 256u) {
+                // Several rounds: workgroups of a size that fills them all, not full ones and a remainder, because a
+                // compute unit takes its next workgroup when the last wavefront of this one is done.  (Eight
+                // laws at 12 bits, ten wavefronts at most: 175,000 pieces of 4000 symbols, 2735
+                // wavefronts, 1368 us with ten, 1133 with six; 10^6 of 1000 1572 with ten, 1512 with nine.  With small
+                // workgroups to begin with, and with short rows, the tables that every workgroup loads cost
+                // more: 100,000 of 500 under ten laws 180 us with six, 194 with four; 10^6 of 128 259 with ten, 268
+                // with nine.)
+                const uint32_t rounds = (each + waves - 1u) / waves;
+                waves = (each + rounds - 1u) / rounds;
+            }
         }
     }
     const uint32_t asked = (uint32_t)g_ansai_decode_waves.load(std::memory_order_relaxed);
