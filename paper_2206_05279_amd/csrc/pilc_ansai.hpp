@@ -487,14 +487,14 @@ __global__ void k_ansai_check_header(AShape sh, const uint8_t *__restrict__ code
 // in a ring of 16 per thread in LDS that is topped up with aligned 16-byte loads asked for one or two groups
 // of symbols before they are needed.  Indices and symbols pass through LDS 32 to a row, and rows are
 // cut from their own start, whatever its alignment, so that all threads have the same positions of
-// their rows at the same time.
-// (A 63-bit window refilled a word at a time, with rows cut at 128-byte lines of the arrays, took 36.6 vector
-// instructions a symbol; now 20.  10^6 pieces of 1000 symbols under eight laws 1.68 -> 1.55 ms, which is
-// the chain of table reads with ten wavefronts on a compute unit (1.13 ms without the stores) and the
-// lines of the streams that are fetched again for every quad; 10^6 of 256 under one law 435 -> 290 us,
-// 1000 of 700 under four 146 -> 71 us.  Not faster: quads two at a time, fewer fetches but a shorter
-// lead (1.72 ms), symbols stored 32 bytes at a time (1.67 ms), non-temporal stores (2.28 ms), rows cut at
-// lines (1.68 ms).)
+// their rows at the same time; long rows of a large batch are cut at the array's 128-byte lines, with steps that
+// change nothing where a thread's row has not begun or has ended (the host chooses, with figures there).
+// (A 63-bit window refilled a word at a time, with all rows cut at lines, took 36.6 vector instructions a
+// symbol; now 20.  10^6 pieces of 1000 symbols under eight laws 1.68 -> 1.49 ms, which is the chain of
+// table reads with nine wavefronts on a compute unit and the lines of the streams that are fetched again
+// for every quad; 10^6 of 256 under one law 435 -> 290 us, 1000 of 700 under four 146 -> 71 us.  Not
+// faster: quads two at a time, fewer fetches but a shorter lead (1.72 ms), symbols stored 32 bytes at a time
+// (1.67 ms), non-temporal stores (2.28 ms); 1.55 ms as it was then.)
 // LDS is what limits how many pieces a compute unit decodes at once (the tables take most of it):
 // 6400 bytes a wavefront, ten wavefronts beside the 96 KB of eight laws at 12 bits.
 constexpr uint32_t kRingWords = 16;                    // per thread: four aligned quads
@@ -561,13 +561,23 @@ __device__ __forceinline__ DecEntry ansai_entry(uint32_t index, const uint8_t *t
 }
 
 // Two steps of Alg. 4 (S <- N[d,S] + popped bits; N - 2^M has zeros where the B popped bits go).  `dm` = d << M.
-template <bool kWide, bool kTabLds>
+// kMasked: a step that is not `on` (no symbol of this thread's row at its position) pops nothing and keeps the state.
+template <bool kWide, bool kTabLds, bool kMasked = false>
 __device__ __forceinline__ void ansai_pop_two(DecLane &L, uint32_t bits, uint32_t dm0, uint32_t dm1, uint32_t &x0,
-                                              uint32_t &x1, const uint8_t *theta, const void *nb)
+                                              uint32_t &x1, const uint8_t *theta, const void *nb, bool on0 = true,
+                                              bool on1 = true)
 {
-    const DecEntry a = ansai_entry<kWide, kTabLds>(dm0 + L.s, theta, nb);
+    DecEntry a = ansai_entry<kWide, kTabLds>(dm0 + L.s, theta, nb);
+    if (kMasked) {
+        a.c = on0 ? a.c : 15u;
+        a.n = on0 ? a.n : L.s;
+    }
     L.s = a.n | (bits >> (a.c | 16u));  // by 31 - B
-    const DecEntry b = ansai_entry<kWide, kTabLds>(dm1 + L.s, theta, nb);
+    DecEntry b = ansai_entry<kWide, kTabLds>(dm1 + L.s, theta, nb);
+    if (kMasked) {
+        b.c = on1 ? b.c : 15u;
+        b.n = on1 ? b.n : L.s;
+    }
     const uint32_t at = a.c + b.c + 1u;  // 31 - B - B'
     L.s = b.n | __builtin_amdgcn_ubfe(bits, at, 15u - b.c);
     L.pos += at - 31u;
@@ -598,9 +608,14 @@ __device__ __forceinline__ uint4 array_tail(const uint8_t *__restrict__ arr, uin
     return make_uint4((uint32_t)x, (uint32_t)(x >> 32), (uint32_t)(x >> 64), (uint32_t)(x >> 96));
 }
 
-// Bytes [pos, pos + 128) of the rows of pieces p0 .. p0 + np - 1, thread `lane` holding, for i = 0 .. 7, sixteen
+// Where row `row_off` of the array (its first byte) is cut: kLines, at the array's 128-byte lines, so that position 0
+// is the start of the line in which the row starts; otherwise at the row's own start.
+template <bool kLines> __device__ __forceinline__ uint32_t row_skew(uint32_t row_off) { return kLines ? row_off & 127u : 0u; }
+
+// Positions [pos, pos + 128) of the rows of pieces p0 .. p0 + np - 1, thread `lane` holding, for i = 0 .. 7, sixteen
 // of row 8 i + lane / 8, those from pos + 16 (lane % 8) on: eight neighbouring threads cover 128 bytes of
-// a row.  Vectors that start in a row may end in the next one; zeros beyond a row's end.
+// a row.  Vectors that hold a byte of the row may hold bytes of its neighbours as well; zeros elsewhere.
+template <bool kLines>
 __device__ __forceinline__ void rows_load(const uint8_t *__restrict__ arr, uint32_t total_bytes, uint32_t p0, uint32_t np,
                                           uint32_t count, uint32_t pos, uint4 (&v)[8])
 {
@@ -608,13 +623,14 @@ __device__ __forceinline__ void rows_load(const uint8_t *__restrict__ arr, uint3
     uint32_t off = (p0 + (lane >> 3)) * count + at;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
+        const uint32_t skew = row_skew<kLines>(off - at), from = off - skew;
         v[i] = make_uint4(0u, 0u, 0u, 0u);
-        if (8u * i + (lane >> 3) < np && at < count) {
-            if (off + 16u <= total_bytes) {
-                __builtin_memcpy(&v[i], arr + off, 16);
-            } else {  // at most one vector of the whole grid
+        if (8u * i + (lane >> 3) < np && at < count + skew && (!kLines || at + 16u > skew)) {
+            if (from + 16u <= total_bytes) {
+                __builtin_memcpy(&v[i], arr + from, 16);
+            } else {  // at the array's end: up to 15 vectors of the whole grid
                 asm volatile("" ::: "memory");  // keep this a branch
-                v[i] = array_tail(arr, total_bytes, off);
+                v[i] = array_tail(arr, total_bytes, from);
             }
         }
         off += 8u * count;
@@ -651,23 +667,24 @@ __device__ __forceinline__ void dec_get(const uint32_t *rows, u32x4 (&ov)[2])
     }
 }
 
-// The same to bytes [pos, pos + 32) of the rows.
+// The same to positions [pos, pos + 32) of the rows: only bytes that belong to them.
+template <bool kLines>
 __device__ __forceinline__ void dec_store(uint8_t *__restrict__ out, const u32x4 (&ov)[2], uint32_t p0, uint32_t np,
                                           uint32_t count, uint32_t pos)
 {
     const uint32_t lane = threadIdx.x & 63u, at = pos + 16u * (lane & 1u);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const uint32_t r = i * 32 + (lane >> 1);
-        if (r >= np || at >= count) continue;
-        uint8_t *q = out + (size_t)((p0 + r) * count + at);
-        if (at + 16u <= count) {
+        const uint32_t r = i * 32 + (lane >> 1), row_off = (p0 + r) * count, skew = row_skew<kLines>(row_off);
+        if (r >= np || at >= count + skew || (kLines && at + 16u <= skew)) continue;
+        uint8_t *q = out + (size_t)(row_off - skew + at);
+        if (at + 16u <= count + skew && (!kLines || at >= skew)) {
             __builtin_memcpy(q, &ov[i], 16);
         } else {
             const uint32_t w[4] = {ov[i].x, ov[i].y, ov[i].z, ov[i].w};
 #pragma unroll
-            for (uint32_t k = 0; k < 15u; ++k)
-                if (at + k < count) q[k] = (uint8_t)(w[k >> 2] >> (8u * (k & 3u)));
+            for (uint32_t k = 0; k < (kLines ? 16u : 15u); ++k)
+                if (at + k < count + skew && (!kLines || at + k >= skew)) q[k] = (uint8_t)(w[k >> 2] >> (8u * (k & 3u)));
         }
     }
 }
@@ -697,10 +714,12 @@ __device__ __forceinline__ void ansai_put_ahead(uint32_t *ring, const DecAhead &
     if (a.slot != kRingWords) ansai_ring_put(ring, a.slot, a.quad);
 }
 
-// The next `n` symbols (1 .. 32, the same for every thread) of this thread's row, in groups of eight.
-template <bool kWide, bool kTabLds>
+// The next `n` symbols (1 .. 32, the same for every thread) of this thread's row, in groups of eight; kMasked: 32
+// positions, of which those in [lo, hi) have a symbol.
+template <bool kWide, bool kTabLds, bool kMasked = false>
 __device__ __forceinline__ void dec_part(DecLane &L, uint32_t *my, uint32_t *ring, const uint32_t *__restrict__ cw,
-                                         uint32_t M, uint32_t n, const uint8_t *theta, const void *nb)
+                                         uint32_t M, uint32_t n, const uint8_t *theta, const void *nb, uint32_t lo = 0u,
+                                         uint32_t hi = kPart)
 {
     auto group = [&](uint32_t g) {
 #pragma unroll
@@ -708,8 +727,11 @@ __device__ __forceinline__ void dec_part(DecLane &L, uint32_t *my, uint32_t *rin
             uint32_t *cell = my + 64u * (g / 4u + h);
             const uint32_t d4 = *cell;
             uint32_t x[4];
-            ansai_pop_two<kWide, kTabLds>(L, ansai_next_bits(L, ring), (d4 & 255u) << M, ((d4 >> 8) & 255u) << M, x[0], x[1], theta, nb);
-            ansai_pop_two<kWide, kTabLds>(L, ansai_next_bits(L, ring), ((d4 >> 16) & 255u) << M, (d4 >> 24) << M, x[2], x[3], theta, nb);
+            const uint32_t j = g + 4u * h - lo, m = hi - lo;  // position k of the four: j + k < m
+            ansai_pop_two<kWide, kTabLds, kMasked>(L, ansai_next_bits(L, ring), (d4 & 255u) << M, ((d4 >> 8) & 255u) << M,
+                                                   x[0], x[1], theta, nb, j < m, j + 1u < m);
+            ansai_pop_two<kWide, kTabLds, kMasked>(L, ansai_next_bits(L, ring), ((d4 >> 16) & 255u) << M, (d4 >> 24) << M,
+                                                   x[2], x[3], theta, nb, j + 2u < m, j + 3u < m);
             *cell = x[0] | (x[1] << 8) | (x[2] << 16) | (x[3] << 24);
         }
     };
@@ -750,7 +772,7 @@ constexpr int kAnsaiDecMaxWaves = 12;
 // timed in LDS and stay in global memory.
 constexpr int kAnsaiDecLeastWaves = 3;
 
-template <bool kWide, bool kTabLds>
+template <bool kWide, bool kTabLds, bool kLines>
 __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
     AShape sh, const uint8_t *__restrict__ coded, const uint8_t *__restrict__ dist, const uint8_t *__restrict__ theta_g,
     const void *__restrict__ nb_g, uint8_t *__restrict__ out, uint32_t maxw, Status *status)
@@ -828,8 +850,11 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
     }
 
     uint4 dv[8];
-    rows_load(dist, total, p0, np, sh.count, 0u, dv);
-    for (uint32_t pos0 = 0; pos0 < sh.count; pos0 += 4u * kPart) {
+    rows_load<kLines>(dist, total, p0, np, sh.count, 0u, dv);
+    const uint32_t skew = row_skew<kLines>((p0 + lane) * sh.count), row_end = skew + sh.count;  // this thread's symbols
+    const uint32_t end = sh.count + (kLines ? 127u : 0u);  // positions that any row may have
+    for (uint32_t pos0 = 0; pos0 < end; pos0 += 4u * kPart) {
+        if (kLines) asm volatile("" : "+s"(sh.count));  // the rows' places are formed again, not kept in registers
         bad |= lines_check(dv, lim_d);
 #pragma unroll 1
         for (uint32_t half = 0; half < 2u; ++half) {
@@ -838,19 +863,27 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
 #pragma unroll
             for (uint32_t h = 0; h < 2u; ++h) {
                 const uint32_t pos = pos0 + (2u * half + h) * kPart;
-                if (pos >= sh.count) break;
+                if (pos >= end) break;
                 wave_lds_sync();
                 dec_put(rows, dv, 2u * half + h);
                 wave_lds_sync();
-                if (h == 1u && half == 1u && pos0 + 4u * kPart < sh.count)
-                    rows_load(dist, total, p0, np, sh.count, pos0 + 4u * kPart, dv);
-                dec_part<kWide, kTabLds>(L, my, ring, cw, M, min(kPart, sh.count - pos), theta, nb);
+                if (h == 1u && half == 1u && pos0 + 4u * kPart < end)
+                    rows_load<kLines>(dist, total, p0, np, sh.count, pos0 + 4u * kPart, dv);
+                if (!kLines) {
+                    dec_part<kWide, kTabLds>(L, my, ring, cw, M, min(kPart, sh.count - pos), theta, nb);
+                } else {
+                    const uint32_t lo = max(skew, pos) - pos, hi = min(max(row_end, pos) - pos, kPart);
+                    if (__all(lo == 0u && hi == kPart))
+                        dec_part<kWide, kTabLds>(L, my, ring, cw, M, kPart, theta, nb);
+                    else
+                        dec_part<kWide, kTabLds, true>(L, my, ring, cw, M, kPart, theta, nb, min(lo, hi), hi);
+                }
                 wave_lds_sync();
                 dec_get(rows, ov[h]);
             }
             const uint32_t pos = pos0 + 2u * half * kPart;
-            if (pos < sh.count) dec_store(out, ov[0], p0, np, sh.count, pos);
-            if (pos + kPart < sh.count) dec_store(out, ov[1], p0, np, sh.count, pos + kPart);
+            if (pos < end) dec_store<kLines>(out, ov[0], p0, np, sh.count, pos);
+            if (pos + kPart < end) dec_store<kLines>(out, ov[1], p0, np, sh.count, pos + kPart);
         }
     }
     if (mine && (L.s != 0u || L.pos != 32u * L.first)) corrupt = 1u;
@@ -1167,9 +1200,9 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
     // A build of this kernel that needed private memory (register spills) once decoded wrongly in
     // the wavefronts beyond the fourth of a workgroup, and the cause was never found.  The kernel as
     // written compiles without private memory; a build that does not is refused rather than run.
-#define PILC_ANSAI_DECODE(WIDE, LDS)                                                                  \
+#define PILC_ANSAI_DECODE(WIDE, LDS, LINES)                                                           \
     do {                                                                                              \
-        auto kern = k_ansai_decode<WIDE, LDS>;                                                        \
+        auto kern = k_ansai_decode<WIDE, LDS, LINES>;                                                 \
         hipFuncAttributes fa;                                                                         \
         HIP_TRY(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(kern)));                     \
         if (fa.localSizeBytes != 0) {                                                                 \
@@ -1184,17 +1217,32 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
         kern<<<blocks, 64 * waves, lds_bytes, stream>>>(sh, coded_dev, dist_dev, tb + t.theta_off,    \
                                                         tb + t.nb_off, sym_out_dev, ws.maxw, status); \
     } while (0)
+    // Rows cut at the array's lines or at their own start.  A row cut at its own start has no step without a symbol, but
+    // its lines are asked for twice, 128 symbols apart, and written in pieces; that costs nothing while the
+    // batch fits the 256 MB of cache in front of memory, and little in rows of whole half lines.  Own start
+    // against lines, us: 100,000 pieces of 1001 symbols 197 and 201, 80,000 of 2001 357 and 340, 160,000 of 4001
+    // 1132 and 848, 556,881 of 1257 1127 and 907, 10^6 of 700 1124 and 985, of 501 787 and 767, of 333 553
+    // and 574, 700,000 of 960 790 and 811 (four laws at 10 bits).
+    const bool lines = sh.count % 64u != 0u && sh.count >= 640u && (uint64_t)sh.pieces * sh.count >= (1ull << 27);
+#define PILC_ANSAI_DECODE_CUT(WIDE, LDS)          \
+    do {                                          \
+        if (lines)                                \
+            PILC_ANSAI_DECODE(WIDE, LDS, true);   \
+        else                                      \
+            PILC_ANSAI_DECODE(WIDE, LDS, false);  \
+    } while (0)
     if (t.wide) {
         if (tab_in_lds)
-            PILC_ANSAI_DECODE(true, true);
+            PILC_ANSAI_DECODE_CUT(true, true);
         else
-            PILC_ANSAI_DECODE(true, false);
+            PILC_ANSAI_DECODE_CUT(true, false);
     } else {
         if (tab_in_lds)
-            PILC_ANSAI_DECODE(false, true);
+            PILC_ANSAI_DECODE_CUT(false, true);
         else
-            PILC_ANSAI_DECODE(false, false);
+            PILC_ANSAI_DECODE_CUT(false, false);
     }
+#undef PILC_ANSAI_DECODE_CUT
 #undef PILC_ANSAI_DECODE
     timer.mark("k_ansai_decode");
     HIP_TRY(hipGetLastError());

@@ -132,6 +132,24 @@ def test_tables_that_just_fit_beside_the_rows(m, d):
         pb.pilc_set_ansai_decode_waves(0)
 
 
+@pytest.mark.parametrize("m,d,count,pieces", [(12, 8, 641, 209_500), (10, 3, 1001, 134_150), (13, 1, 4001, 33_601), (15, 2, 1000, 134_300),
+                                              (15, 1, 20_003, 6_713), (12, 8, 640, 209_800), (12, 8, 639, 210_100)])
+def test_long_rows_of_a_large_batch_decode(m, d, count, pieces):
+    """Rows of 640 symbols and more in a batch of 2^27 and more are cut at the array's lines: every alignment of the
+    rows, tables in LDS and in global memory, a last wavefront that is not full; and on the other side of the
+    line, rows of whole half lines and rows of 639.  Symbols drawn uniformly, by the library's encoder
+    (compared with the reference in the cases above)."""
+    print("M", m, "D", d, "count", count, "pieces", pieces, flush=True)
+    assert pieces * count >= 1 << 27
+    rng = np.random.default_rng(count)
+    sym = rng.integers(0, 256, (pieces, count), dtype=np.uint8)
+    dist = rng.integers(0, d, (pieces, count), dtype=np.uint8)
+    dp = DevicePieces(m, sp.logistic_masses(m, d), sym, dist)
+    dp.encode()
+    dp.decode()
+    assert torch.equal(dp.out, dp.sym)
+
+
 def test_every_workgroup_shape_of_the_decoder_gives_the_same_symbols():
     """One input through workgroups of 1 .. 12 wavefronts (as many as fit beside the tables), for
     tables in LDS with 16-bit and with 32-bit entries and for tables in global memory."""
