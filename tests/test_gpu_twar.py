@@ -1,7 +1,7 @@
 """GPU parity of the Three-Way AR residual transform (Sec. 3.1 eqs. (2)-(4)) against the CPU
 reference, through the C ABI: residuals and recovered images byte for byte, on shapes that
-cover several images per wavefront, bands of 64 rows, the LDS-tile and the in-place path, and
-the workgroup-per-image path for tall images."""
+cover several images per wavefront, bands of 64 rows, tiles in LDS, and the kernel that decodes
+along the diagonals with its bands together, one at a time and in several launches."""
 import numpy as np
 import pytest
 import torch
@@ -14,15 +14,11 @@ pytestmark = pytest.mark.gpu
 ONE = 1 << 14
 SHAPES = [(1, 1, 1), (3, 32, 32), (5, 7, 9), (2, 64, 64), (7, 16, 16), (2, 33, 5), (1, 100, 37),
           (1, 130, 300), (2, 3, 700), (513, 32, 32), (1, 200, 64),
-          # taller than a wavefront with rows of whole 16-pixel chunks: a workgroup per image with all
-          # bands under way at once; one band and a bit, a band boundary at the last row, three
-          # rounds of a workgroup, a full-size frame
+          # taller than a wavefront: one row more than a band, two whole bands, 25 bands, a full-size frame
           (3, 65, 16), (2, 128, 48), (1, 1600, 32), (2, 1080, 1920),
-          # few images taller than 256 rows: bands of an image in workgroups of their own that follow
-          # each other through counters in global memory (three bands of 234 rows; nine of 234; two
-          # of 193 and two of 129, whose last wavefront has a single row; two full bands of 256)
+          # bands that follow each other: 11, 33, 7 and 5 of them, the last with 60, 52, 1 and 1 rows; eight whole ones
           (2, 700, 64), (1, 2100, 160), (3, 385, 32), (3, 257, 32), (2, 512, 48),
-          # many images with more rows than a workgroup has threads: rounds within a workgroup
+          # many images, the bands of which go one at a time
           (256, 800, 16),
           # more groups of small images: eight images a group, rows of 27 dwords, an odd number of
           # groups, 17-row images (13 idle threads), many groups with a single-image group at the end
@@ -63,10 +59,10 @@ def test_forward_and_inverse_match_the_reference(shape):
 
 
 def test_thirty_frames_come_back_every_time():
-    """The workload bench.py times (30 frames of 1080 x 1920, five bands each, 150 workgroups that
-    follow each other through the image itself): the inverse of the forward transform is the
+    """The workload bench.py times (30 frames of 1080 x 1920, 17 bands each, 510 workgroups that
+    follow each other through words in global memory): the inverse of the forward transform is the
     image, on five calls in a row into a buffer poisoned before each, compared on the device.  A
-    band that read a row of the band above before it was there would pick up the poison."""
+    band that took a word of the band above before it was there would decode the rest of its rows wrongly."""
     g = torch.Generator().manual_seed(11)
     img = torch.randint(0, 256, (30, 1080, 1920, 3), dtype=torch.uint8, generator=g).cuda()
     p = pb.make_twar_params([[-ONE, ONE, ONE], [ONE // 2, -ONE // 2, ONE], [ONE // 2, -ONE // 2, ONE]], [0, 0, 0])
@@ -123,14 +119,15 @@ def test_any_width_at_any_address(shape, offset):
     p = pb.make_twar_params(wq, bq)
     _, d_noise = at_offset(0x33)
     d_noise.copy_(torch.from_numpy(noise))
-    whole, d_back = at_offset(0xA5)
+    whole_back, d_back = at_offset(0xA5)
     pb.pilc_twar_inverse(p, d_noise, d_back)
     assert np.array_equal(d_back.cpu().numpy(), ref)
-    whole, d_res = at_offset(0x5A)
+    whole_res, d_res = at_offset(0x5A)
     pb.pilc_twar_forward(p, d_back, d_res)
     assert np.array_equal(d_res.cpu().numpy(), noise)
-    # nothing beside the array has been written
-    assert bool((whole[:16 + offset] == 0x5A).all()) and bool((whole[16 + offset + size:] == 0x5A).all())
+    # nothing beside either array has been written
+    for whole, fill in ((whole_back, 0xA5), (whole_res, 0x5A)):
+        assert bool((whole[:16 + offset] == fill).all()) and bool((whole[16 + offset + size:] == fill).all()), fill
 
 
 # Images of more than 64 rows on either side of each line at which the route changes: tiles or diagonals (by how
@@ -157,10 +154,13 @@ def test_both_sides_of_every_line(shape, offset):
     assert (back[:16 + offset] == 0xA5).all() and (back[16 + offset + size:] == 0xA5).all()
 
 
-@pytest.mark.parametrize("shape", [(6000, 129, 100), (1, 4100, 65535)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(70, 1080, 1920), (23, 150, 50000), (1, 4100, 65535), (6000, 129, 100)],
+                         ids=lambda s: "x".join(map(str, s)))
 def test_more_bands_than_one_launch_takes(shape):
-    """More bands than there is room for the rows they pass on: several launches, over images or, for
-    an image with more bands than that by itself, over its bands."""
+    """More bands than there is room for the rows they pass on: several launches with all bands of an image, over
+    the images (62 and 8 frames, 13 and 10 wide images), whose rows pass through the same words; for an image
+    with more bands than that by itself, over its bands; and so many images that bands go one at a time, a
+    launch each."""
     print("shape", shape, flush=True)
     g = torch.Generator(device="cuda:0").manual_seed(3)
     img = torch.randint(0, 256, shape + (3,), dtype=torch.uint8, device="cuda:0", generator=g)
