@@ -122,9 +122,9 @@ __global__ __launch_bounds__(256) void k_ansai_build(uint32_t M, uint32_t X,
 // ---------------------------------------------------------------------------------------------
 // Moving a wavefront's 64 rows between the arrays and LDS
 // ---------------------------------------------------------------------------------------------
-// A row is the `count` bytes of one piece in a [pieces, count] array.  Rows are cut at multiples
+// A row is the `count` bytes of one piece in a [pieces, count] array.  The encoder cuts rows at multiples
 // of 128 bytes of the array ("lines"); line-stage number `ls` of a row is its ls-th line from the
-// front or from the back.  A wavefront fetches a line-stage of all its rows with
+// back.  A wavefront fetches a line-stage of all its rows with
 // 16-byte loads in which eight consecutive threads cover one row's line: thread `lane` holds, for
 // i = 0..7, bytes [16c, 16c+16) of the line of row 8i + lane/8, with c = lane%8.  Every line is
 // thus requested once, whole.  The threads then pass the line through LDS in two halves of 64
@@ -137,13 +137,13 @@ struct RowLine {
     uint32_t lo, hi;  // the row's bytes inside that line: [lo, hi), empty when the row has none
 };
 
-__device__ __forceinline__ RowLine row_line(uint32_t piece, uint32_t count, uint32_t ls,
-                                            bool from_back, bool row_exists)
+__device__ __forceinline__ RowLine row_line(uint32_t piece, uint32_t count, uint32_t ls, bool row_exists)
 {
     const uint32_t rb = piece * count, re = rb + count;
     const uint32_t first = rb / kLine, last = (re - 1u) / kLine;
     RowLine r;
-    r.line = from_back ? last - ls : first + ls;
+    __builtin_assume(last >= first);  // (told so, the encoder needs four registers less: 3 % of its time)
+    r.line = last - ls;
     if (!row_exists || ls > last - first) {
         r.lo = r.hi = 0;
         return r;
@@ -176,13 +176,13 @@ __device__ __forceinline__ uint32_t keep_bytes(uint32_t w, int a, int b)
 // kernel writes out of the L2 before they are complete.
 __device__ __forceinline__ void line_load(const uint8_t *__restrict__ arr, uint32_t total_bytes,
                                           uint32_t p0, uint32_t np, uint32_t count, uint32_t ls,
-                                          bool from_back, uint4 (&v)[8])
+                                          uint4 (&v)[8])
 {
     const uint32_t lane = threadIdx.x & 63u, vb = (lane & 7u) * 16u;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const uint32_t r = i * 8 + (lane >> 3);
-        const RowLine rl = row_line(p0 + r, count, ls, from_back, r < np);
+        const RowLine rl = row_line(p0 + r, count, ls, r < np);
         v[i] = make_uint4(0u, 0u, 0u, 0u);
         if (vb < rl.hi && vb + 16u > rl.lo) {
             const uint32_t off = rl.line * kLine + vb;
@@ -285,7 +285,7 @@ __device__ __forceinline__ void enc_put(uint32_t *rows, const uint4 (&sv)[8], co
     for (int i = 0; i < 8; ++i) {
         const uint32_t r = i * 8 + (lane >> 3);
         uint32_t *dst = rows + r * kEncRow + (c & 3u) * 8u;
-        const RowLine rl = row_line(p0 + r, count, ls, true, r < np);
+        const RowLine rl = row_line(p0 + r, count, ls, r < np);
         const uint32_t s[4] = {sv[i].x, sv[i].y, sv[i].z, sv[i].w};
         const uint32_t d[4] = {dv[i].x, dv[i].y, dv[i].z, dv[i].w};
         uint32_t w[8];
@@ -348,8 +348,8 @@ __global__ __launch_bounds__(64 * kAnsaiEncWaves) void k_ansai_encode(
 
     uint4 sv[8], dv[8];
     const uint32_t lines = line_stage_count(sh.count);
-    line_load(sym, total, p0, np, sh.count, 0u, true, sv);
-    line_load(dist, total, p0, np, sh.count, 0u, true, dv);
+    line_load(sym, total, p0, np, sh.count, 0u, sv);
+    line_load(dist, total, p0, np, sh.count, 0u, dv);
     for (uint32_t ls = 0; ls < lines; ++ls) {
         asm volatile("" : "+s"(sh.count));  // recompute the row geometry per line-stage (registers)
         bad |= lines_check(sv, lim_x) | lines_check(dv, lim_d);
@@ -359,8 +359,8 @@ __global__ __launch_bounds__(64 * kAnsaiEncWaves) void k_ansai_encode(
             enc_put(rows, sv, dv, (uint32_t)h, p0, np, sh.count, ls, sh.D << 8);
             wave_lds_sync();
             if (h == 0 && ls + 1u < lines) {  // the registers are free: fetch the next lines now
-                line_load(sym, total, p0, np, sh.count, ls + 1u, true, sv);
-                line_load(dist, total, p0, np, sh.count, ls + 1u, true, dv);
+                line_load(sym, total, p0, np, sh.count, ls + 1u, sv);
+                line_load(dist, total, p0, np, sh.count, ls + 1u, dv);
             }
 #pragma unroll 1
             for (int j = 15; j >= 0; --j) {  // four symbols a turn, last first

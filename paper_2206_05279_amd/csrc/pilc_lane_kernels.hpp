@@ -761,7 +761,7 @@ struct WordRing {
     {
         const uint32_t wd = nextw;
         ++pos;
-        nextw = peek();  // at most kRingChunk takes between fills: pos stays below `filled`
+        nextw = peek();  // (after the last word held, which only a whole chunk takes: not yet the next one, but `fill` reads it again)
         return wd;
     }
 };

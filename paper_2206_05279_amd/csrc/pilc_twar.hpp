@@ -38,20 +38,6 @@ __device__ __forceinline__ int add_low_byte(int a, int b)
     return r;
 }
 
-// (byte kByte of a + b) mod 256
-template <int kByte>
-__device__ __forceinline__ int add_byte_of(uint32_t a, int b)
-{
-    int r;
-    if (kByte == 0)
-        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD" : "=v"(r) : "v"(a), "v"(b));
-    else if (kByte == 1)
-        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD" : "=v"(r) : "v"(a), "v"(b));
-    else
-        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 // Byte b (-4 <= b < 12) of the 16 bytes {prev, c0, c1, c2}, b = 0 being the first byte of c0.
 template <int B>
 __device__ __forceinline__ int byte_at(uint32_t prev, uint32_t c0, uint32_t c1, uint32_t c2)
@@ -352,8 +338,8 @@ struct Diag {
     uint32_t withhold;          // tests of the give-up path: nothing is passed on
 };
 
-// The 24-bit signed multiply as the compiler's own operation.  (Around inline assembly it puts wait
-// states that a chain of dependent steps has no use for.)
+// The 24-bit signed multiply by the name the compiler's own operation has.  (__mul24 first extends both operands from 24
+// bits where the compiler cannot see that they are no wider: one frame of 2160 x 3840 318 against 314 us.)
 extern "C" __device__ int mul_i24(int a, int b) __asm("llvm.amdgcn.mul.i24.i32");
 
 // A weight, and the start of a sum.  The sums are kept times four, so that the prediction is the upper
@@ -667,7 +653,7 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
                 for (int i = 0; i < 3; ++i) {
                     (&raw[slot][0][0])[put[i]] = ahead[j][i];
                     const long long over = at[i] - 48 * kDiagAhead - last;
-                    if (over > 0 && over < 16) {  // the array's end is inside the piece: one piece of the whole grid
+                    if (over > 0 && over < 16) {  // the array's end is inside the piece: a few pieces near it
                         uint8_t *q = reinterpret_cast<uint8_t *>(&raw[slot][0][0] + put[i]);
 #pragma unroll 1
                         for (int k = 0; k < 16 - (int)over; ++k) q[k] = q[k + (int)over];
@@ -805,7 +791,7 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
 // above it from the image.
 constexpr uint32_t kTileManyImages = 1024;  // a wavefront for every SIMD
 constexpr int kBandSlots = 4;
-constexpr uint32_t kBandWords = 1u << 19;  // 4 MB a set: 132 bands of 16384 columns, 1057 of 1920
+constexpr uint32_t kBandWords = 1u << 19;  // 4 MB a set: 127 bands of 16384 columns, 1057 of 1920
 struct BandSet {
     unsigned long long words[kBandWords];
     uint32_t ticket, abort_word;
