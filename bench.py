@@ -12,8 +12,8 @@ JSON line: the headline workload (--config, default 1: the CIFAR-shaped batch) w
                 `plain_copy_GBs` is a device-to-device copy timed in the same run (read + written
                 bytes per second): the achievable figure beside the published peak;
   cpu_baseline  the CPU oracle timed on the host cores on a bounded prefix of the workload;
-and, under other_workloads, the same three things (rates, roofline with traffic, cpu_baseline) for
-every other single-GPU workload: the tiny, ImageNet64-shaped, 1080p and entropy-extreme batches
+and, under other_workloads, the same things in short (rates, kernels, shares, the oracle's rate; whole
+on stderr) for every other single-GPU workload: the tiny, ImageNet64-shaped, 1080p and entropy-extreme batches
 (the last at 12 and 16 bits of precision with 64 lanes per image on all 8192 images, and at 1 and
 1024 lanes per image on its first 512), the paper's own table-driven coder (Sec. 3.2 Algs. 3-4) on
 the recipe of its coder measurement (Sec. 4.3) and on the stream of vector indices (Sec. 3.1), the
@@ -729,6 +729,35 @@ def report(run, r, seg, torch, with_copy=False):
     return out
 
 
+def rounded(v, digits=5):
+    """The same record with its floating-point numbers to a few significant digits."""
+    if isinstance(v, float):
+        return float("%.*g" % (digits, v))
+    if isinstance(v, dict):
+        return {k: rounded(x, digits) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [rounded(x, digits) for x in v]
+    return v
+
+
+def in_short(rep):
+    """What the printed line says of a workload beside the headline one: with all of them whole it would be
+    some 20,000 characters long."""
+    roof, valu = rep["roofline"], rep["roofline"].get("valu")
+    out = {"value": rep["value"]}
+    out.update((k, v) for k, v in rep.items() if k.endswith("_MB_s") or k.startswith("bits_per"))
+    out["exact"] = rep["round_trip_exact"]
+    out["ms"] = {k: v for k, v in rep["kernel_ms"].items() if v >= 0.03 * sum(rep["kernel_ms"].values())}
+    out["hbm_frac"] = roof["frac"]
+    if roof.get("traffic"):
+        out["traffic_ratio"] = roof["traffic"] / roof["algorithmic_bytes"]
+    if valu:
+        out["issue_frac"] = valu["issue_frac"]
+    if "cpu_baseline" in rep:
+        out["oracle_MB_s"] = rep["cpu_baseline"]["value"]
+    return rounded(out, 4)
+
+
 def lane_sweep():
     """The stress workload over lanes per image: whole pilc_encode / pilc_decode calls, mean of
     three after a warm-up, round trip checked in every row."""
@@ -931,9 +960,10 @@ def main():
             others[run.name] = rep
         ok = ok and r["ok"]
         del run
-    if others:
-        result["other_workloads"] = others
-    print(json.dumps(result))
+    if others:  # whole on stderr, in short in the line itself
+        print(json.dumps({"other_workloads": others}), file=sys.stderr)
+        result["other_workloads"] = {name: in_short(rep) for name, rep in others.items()}
+    print(json.dumps(rounded(result, 7)))
     if not ok:
         sys.exit(4)
 

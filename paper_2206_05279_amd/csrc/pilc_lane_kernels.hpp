@@ -766,7 +766,7 @@ struct WordRing {
     }
 };
 
-// (Four wavefronts per SIMD are asked for: the vector ALUs then issue in 98 % of all cycles.  A variant
+// (Four wavefronts per SIMD are asked for: where the lanes fill the chip the vector ALUs then issue in 94-98 % of all cycles.  A variant
 // that carries the rest of every parameter line in registers, as the encoder does, reads half the
 // bytes from memory but needs 172 registers, i.e. two wavefronts per SIMD, and was slower: 0.91 against
 // 0.86 ms on 16,384 images of 64 x 64.)
