@@ -25,6 +25,7 @@
 namespace pilc {
 
 __device__ uint2 g_sig_cell[kSigEntries];
+__device__ float2 g_guide[kGuideEntries];
 __device__ uint32_t g_exp_hi[kExpHiEntries];
 __device__ uint32_t g_exp_lo[kExpLoEntries];
 
@@ -425,6 +426,32 @@ static int hip_fail(hipError_t e, const char *what)
 static std::mutex g_table_mutex;
 static bool g_table_ready[64] = {false};
 
+// psi(q) = ln w where w + ln w = q, by Newton's method for e^p + p = q (convex and increasing: from above it converges
+// without overshooting).
+static double guide_psi(double q)
+{
+    double p = q > 1.0 ? std::log(q) : q;
+    for (int i = 0; i < 50; ++i) {
+        const double e = std::exp(p);
+        p -= (e + p - q) / (e + 1.0);
+    }
+    return p;
+}
+
+// The lines of g_guide: chords of psi(x - kGuideShift) + kGuideShift, moved by half of what they miss the middle by.
+static void make_guide(float2 *guide)
+{
+    for (int i = 0; i < kGuideEntries; ++i) {
+        const int octave = i >> kGuideBits, part = i & ((1 << kGuideBits) - 1);
+        const double x0 = std::ldexp(1.0 + std::ldexp(part, -kGuideBits), octave);
+        const double x1 = x0 + std::ldexp(1.0, octave - kGuideBits);
+        const double p0 = guide_psi(x0 - kGuideShift), p1 = guide_psi(x1 - kGuideShift);
+        const double pm = guide_psi(0.5 * (x0 + x1) - kGuideShift);
+        const float slope = (float)((p1 - p0) / (x1 - x0));
+        guide[i] = make_float2(slope, (float)(p0 - slope * x0 + 0.5 * (pm - 0.5 * (p0 + p1)) + kGuideShift));
+    }
+}
+
 static int ensure_tables()
 {
     int dev = 0;
@@ -446,6 +473,9 @@ static int ensure_tables()
     for (int i = 0; i < kExpLoEntries; ++i)
         el[i] = (uint32_t)std::llround(std::ldexp(std::exp(-i / 4096.0), 31));
     HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(g_sig_cell), cell, sizeof(cell)));
+    static float2 guide[kGuideEntries];
+    make_guide(guide);
+    HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(g_guide), guide, sizeof(guide)));
     HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(g_exp_hi), eh, sizeof(eh)));
     HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(g_exp_lo), el, sizeof(el)));
     HIP_TRY(hipDeviceSynchronize());

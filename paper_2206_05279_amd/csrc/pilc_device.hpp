@@ -14,6 +14,9 @@ namespace pilc {
 constexpr int kSigEntries = 2048;  // interpolation cells of the sigmoid table
 constexpr int kExpHiEntries = 640;
 constexpr int kExpLoEntries = 64;
+constexpr int kGuideOctaves = 21, kGuideBits = 4;  // sixteen lines an octave of 1 .. 2^21
+constexpr int kGuideEntries = kGuideOctaves << kGuideBits;
+constexpr float kGuideShift = 9.0f;
 
 // Constant tables in device globals, filled by the host once per device.
 //   g_sig_cell[i] = { D[i] * 2^11, (T[i] - D[i] * i) mod 2^32 },  D[i] = T[i+1] - T[i],
@@ -21,6 +24,7 @@ constexpr int kExpLoEntries = 64;
 //     addend of one multiply-add (interpolate below)
 //   g_exp_hi[i]   = round(2^26 * exp(4 - i/64)),  g_exp_lo[j] = round(2^31 * exp(-j/4096))
 extern __device__ uint2 g_sig_cell[kSigEntries];
+extern __device__ float2 g_guide[kGuideEntries];  // see SymbolGuide
 extern __device__ uint32_t g_exp_hi[kExpHiEntries];
 extern __device__ uint32_t g_exp_lo[kExpLoEntries];
 
@@ -42,7 +46,6 @@ __device__ __forceinline__ void load_tables(LdsTables &t)
 // Sixteen bytes as the compiler's own vector type (arrays of it stay in registers where arrays of
 // the HIP struct type of the same size go to private memory).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));  // a register pair
 
 // Orders this wavefront's LDS accesses: LDS instructions of one wavefront execute in order, so
 // all that is needed is that the compiler keeps them in order too.
@@ -155,10 +158,13 @@ __device__ __forceinline__ int rsh14(int v) { return (v + 8192) >> 14; }
 // product is below 2^31 in magnitude, so the 24-bit multiply-add gives it exactly at full rate.
 __device__ __forceinline__ int rsh14_mul(int a, int e) { return mad_i24(a, e, 8192) >> 14; }
 
-// Q6.25 value of exp(-log_scale); log_scale Q4.12 clamped to [-4, 6).
+// log_scale Q4.12 clamped to [-4, 6), counted from -4.
+__device__ __forceinline__ int scale_index(int ls) { return min(max(ls, -16384), 24575) + 16384; }
+
+// Q6.25 value of exp(-log_scale).
 __device__ __forceinline__ uint32_t inv_scale(int ls, const LdsTables &t)
 {
-    int u = min(max(ls, -16384), 24575) + 16384;
+    const int u = scale_index(ls);
     uint32_t inv_s = __umulhi(t.exp_hi[u >> 6], t.exp_lo[u & 63]);
     asm("" : "+v"(inv_s));  // (else its conversion to double is made from the 64-bit product)
     return inv_s;
@@ -227,17 +233,6 @@ __device__ __forceinline__ uint32_t mass_scale(uint32_t prec_bits) { return ((1u
 // floor(f * (2^M - 256) / 2^24) for a 24-bit f
 __device__ __forceinline__ uint32_t mass_of(uint32_t f, uint32_t scale) { return __umulhi(f, scale); }
 
-// k + mass_of(f, scale) as the upper word of one multiply-add, for a k that is kept as the upper word
-// of a register pair whose lower word is zero.  (Written as a sum, the compiler takes k out of it again
-// and adds it in an instruction of its own.)
-__device__ __forceinline__ uint32_t cum_from_pair(u32x2 zero_k, uint32_t f, uint32_t scale)
-{
-    u32x2 sum;
-    unsigned long long carry;
-    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(sum), "=s"(carry) : "v"(f), "s"(scale), "v"(zero_k));
-    return sum.y;
-}
-
 // C(k), 1 <= k <= 255:  k + floor(F(k) * (2^M - 256) / 2^24).
 __device__ __forceinline__ uint32_t cum_inner(int k, double y, uint32_t scale, const LdsTables &t)
 {
@@ -251,6 +246,53 @@ __device__ __forceinline__ uint32_t cum_at(int k, int mu_eff, uint32_t inv_s, ui
     if (k <= 0) return 0u;
     if (k >= 256) return 1u << prec_bits;
     return cum_inner(k, edge_y(k, edge_law(mu_eff, inv_s)), mass_scale(prec_bits), t);
+}
+
+// --------------------------------------------------------------------------------------------
+// Where a symbol lies, from the lower part of the state (`slot`), by solving C(k) = k + N F(k) for k (N = 2^M - 256)
+// in single precision instead of searching.  With m = mean + 1/2, v = k - m and T = slot + 1 - m - N / 2 the equation is
+//     v + N (sigmoid(v / s) - 1/2) = T,
+// which is odd in v and T, so take T <= 0, v = -u and y = sigmoid(-u / s) = (A + u) / N with A = N / 2 - |T|.  From
+// ln y - ln(1 - y) = -u / s, the number w = N y / s satisfies
+//     w + ln w = q,   q = A / s + ln(N / s) + ln(1 - y),
+// so ln w is a function psi of q alone (the logarithm of the Wright omega function), and
+//     u = s (ln(N / s) + ln(1 - y) - psi(q)).
+// psi comes from a table of lines (g_guide: over x = q + kGuideShift, cut by the leading bits of x as a float; below
+// it psi is q), and ln(1 - y) changes so slowly that y may be taken from the tangent of the sigmoid
+// at its middle, 1 - y = min(1/2 + |T| / (N + 4 s), 1).  The result is within 0.1 of the true k for scales up to 20 and
+// within 0.6 for those up to 400 (2^M = 1024), so the two values around the nearest edge to it hold
+// the symbol; the caller evaluates the exact C at three edges and searches on where they do not.
+// --------------------------------------------------------------------------------------------
+struct GuideScale {  // per launch
+    float half, mid, full, log_n;
+    __device__ __forceinline__ explicit GuideScale(uint32_t prec_bits)
+    {
+        const float n = (float)((1u << prec_bits) - 256u);
+        full = n;
+        half = 0.5f * n;
+        mid = 0.5f * n - 0.5f + 1.0f / 64;  // (a little below slot + 1, so that rounding does not reach the next edge)
+        log_n = __logf(n) + 4.0f + kGuideShift;
+    }
+};
+
+// The edge nearest to where the symbol begins, 1 .. 255, under the law with mean `mu_eff`, inverse scale `inv_s` (Q6.25)
+// and scale index `su`.
+__device__ __forceinline__ uint32_t guide_edge(uint32_t slot, int mu_eff, uint32_t inv_s, int su, const GuideScale &gs,
+                                               const float2 *guide)
+{
+    const float mean = (float)mu_eff, inv = (float)inv_s * 0x1p-25f;
+    const float s = __builtin_amdgcn_rcpf(inv);
+    const float t = (float)slot - __builtin_fmaf(mean, 1.0f / 256, gs.mid);
+    const float not_y = __builtin_fminf(__builtin_fmaf(__builtin_fabsf(t), __builtin_amdgcn_rcpf(__builtin_fmaf(4.0f, s, gs.full)), 0.5f), 1.0f);
+    const float b = __builtin_fmaf(__builtin_amdgcn_logf(not_y), 0.693147181f, __builtin_fmaf((float)su, -1.0f / 4096, gs.log_n));
+    const float q = __builtin_fmaf(gs.half - __builtin_fabsf(t), inv, b);
+    const float x = __builtin_fmaxf(q, 1.0f);  // below 2^21: half <= 32640, inv <= 54.6, b < 25
+    const float2 line = guide[(__float_as_uint(x) >> (23 - kGuideBits)) - (127u << kGuideBits)];
+    const float psi = __builtin_fminf(__builtin_fmaf(x, line.x, line.y), q);
+    const float k = __builtin_fmaf(__builtin_copysignf(s, t), b - psi, __builtin_fmaf(mean, 1.0f / 256, 1.0f));
+    uint32_t edge;  // (saturates)
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(edge) : "v"(k));
+    return min(max(edge, 1u), 255u);
 }
 
 }  // namespace pilc

@@ -632,7 +632,13 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
 }
 
 // --------------------------------------------------------------------------------------------
-// Decode.  The symbol is found by an 8-step bisection on C(k) (App. A names a binary search).
+// Decode.  The symbol is guessed from the inverse of the law (guide_edge) and checked at three edges of the exact C;
+// App. A names a binary search, which is what a wavefront falls back to when the guess of one of its lanes
+// is not good enough (scales of 200 and more).  Bound by vector instructions where the lanes fill
+// the chip, by the length of a symbol's chain where they do not; the guess and three edges, whose
+// table reads are under way together, are 77 instructions and two waits for LDS instead of the 104 and
+// eight of eight steps of bisection: 30 frames of 1080 x 1920 in tiles of 16 x 16 809 -> 560 us, 16,384
+// images of 64 x 64 with a lane a row 805 -> 622, 256 lanes of 16,384 pixels 25.1 -> 14.3 ms.
 // --------------------------------------------------------------------------------------------
 
 // A lane's 16-bit words, fetched as aligned 32-byte pairs of 16-byte pieces, a piece ahead of
@@ -706,11 +712,10 @@ struct WordStream {
 // inside the chunk ever touches memory or branches on the fill level.  A thread's 32 words lie side
 // by side (rows of 17 dwords, so that the threads of a wavefront start in different banks): the word at
 // stream position pos is one 16-bit read at (pos mod 32), fetched ahead of its use.
-// The size is what lets four workgroups of 256 threads share a compute unit (160 KB: 19 KB of tables
+// The size is what lets four workgroups of 256 threads share a compute unit (160 KB: 22 KB of tables
 // and 17 KB of rings each).  With 64 words a line of the stream is asked for half as often, but only
-// three workgroups fit, and a wavefront's bisection step takes 190 cycles in which it issues 13
-// instructions: three wavefronts on a SIMD do not fill them (30 frames of 1080 x 1920 in tiles: 0.96
-// against 0.87 ms).
+// three workgroups fit, which do not fill the issue slots (30 frames of 1080 x 1920 in tiles, with a
+// search by bisection: 0.96 against 0.87 ms).
 constexpr int kRingChunk = 24;
 constexpr int kRingPieces = 4;                      // 16-byte pieces per thread: 32 words
 constexpr int kRingWordsHeld = 8 * kRingPieces;
@@ -766,7 +771,7 @@ struct WordRing {
     }
 };
 
-// (Four wavefronts per SIMD are asked for: where the lanes fill the chip the vector ALUs then issue in 94-98 % of all cycles.  A variant
+// (Four wavefronts per SIMD are asked for, which keep the vector ALUs busy where the lanes fill the chip.  A variant
 // that carries the rest of every parameter line in registers, as the encoder does, reads half the
 // bytes from memory but needs 172 registers, i.e. two wavefronts per SIMD, and was slower: 0.91 against
 // 0.86 ms on 16,384 images of 64 x 64.)
@@ -778,8 +783,11 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
                                const unsigned long long *__restrict__ status_payload)
 {
     __shared__ LdsTables tab;
+    __shared__ float2 guide[kGuideEntries];
     extern __shared__ __align__(16) uint16_t ring[];  // [thread][word]: kRingRow elements a thread
-    load_tables(tab);
+    for (int i = threadIdx.x; i < kGuideEntries; i += blockDim.x) guide[i] = g_guide[i];
+    load_tables(tab);  // ends with a barrier
+    const GuideScale gs(g.prec_bits);
     if (*status_code != 0) return;  // uniform: written by an earlier kernel
     const uint32_t lane = blockIdx.x * blockDim.x + threadIdx.x;
     if (lane >= g.lanes) return;
@@ -808,9 +816,6 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
     uint32_t S = words.take();
     S |= words.take() << 16;
 
-    u32x2 zero_k;  // {0, the k being looked at}
-    zero_k.x = 0u;
-    asm("" : "+v"(zero_k.x));  // (a constant would be written again beside every new k)
     // decodes the chunk into its 24 bytes (6 dwords)
     // tiles and flat lanes no longer than an image lie in one image: its coefficients are loaded once
     auto decode_chunk = [&](const Chunk &ck, const ChunkPos cp, uint32_t *wout) {
@@ -836,27 +841,41 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
                     if (ch == 2)
                         me = ck.m[i][2] + rsh14_mul(a_br, (x[0] * 256 - ck.m[i][0])) +
                              rsh14_mul(a_bg, (x[1] * 256 - ck.m[i][1]));
-                    const EdgeLaw law = edge_law(me, inv_scale(ck.l[i][ch], tab));
+                    const uint32_t inv_s = inv_scale(ck.l[i][ch], tab);
+                    const EdgeLaw law = edge_law(me, inv_s);
                     const uint32_t slot = S & mask;
-                    // the symbol is in lo .. lo + 2 * step - 1, and c_hi = C(lo + 2 * step)
-                    int lo = 0;
-                    uint32_t c_lo = 0u, c_hi = 1u << m_bits;
-#pragma unroll
-                    for (int step = 128; step >= 1; step >>= 1) {
-                        zero_k.y = (uint32_t)(lo + step);
-                        const uint32_t cm = cum_from_pair(zero_k, edge_at(edge_y(lo + step, law), tab), scale);
-                        const bool ge = cm <= slot;
-                        lo = ge ? lo + step : lo;
-                        c_lo = ge ? cm : c_lo;
-                        c_hi = ge ? c_hi : cm;
+                    // C at the edge where the symbol should begin or end and at its two neighbours
+                    const uint32_t mid = guide_edge(slot, me, inv_s, scale_index(ck.l[i][ch]), gs, guide);
+                    const double y = edge_y((int)mid, law);
+                    const uint32_t c_mid = cum_inner((int)mid, y, scale, tab);
+                    uint32_t c_below = cum_inner((int)mid - 1, y - law.a, scale, tab);
+                    uint32_t c_above = cum_inner((int)mid + 1, y + law.a, scale, tab);
+                    c_below = mid == 1u ? 0u : c_below;
+                    c_above = mid == 255u ? 1u << m_bits : c_above;
+                    const bool up = c_mid <= slot;
+                    uint32_t lo = up ? mid : mid - 1u;
+                    uint32_t c_lo = up ? c_mid : c_below, c_hi = up ? c_above : c_mid;
+                    if (__builtin_expect(__any(slot - c_lo >= c_hi - c_lo), 0)) {
+                        // for the whole wavefront: the symbol is in lo .. lo + 2 * step - 1, and c_hi = C(lo + 2 * step)
+                        lo = 0u;
+                        c_lo = 0u;
+                        c_hi = 1u << m_bits;
+#pragma unroll 1
+                        for (uint32_t step = 128; step >= 1u; step >>= 1) {
+                            const uint32_t cm = cum_inner((int)(lo + step), edge_y((int)(lo + step), law), scale, tab);
+                            const bool ge = cm <= slot;
+                            lo = ge ? lo + step : lo;
+                            c_lo = ge ? cm : c_lo;
+                            c_hi = ge ? c_hi : cm;
+                        }
                     }
-                    x[ch] = lo;
+                    x[ch] = (int)lo;
                     // App. A eq. (12)
                     // the mass is at most 2^16 and S >> M below 2^22: a 24-bit multiply is exact
                     S = (uint32_t)__umul24(c_hi - c_lo, S >> m_bits) + slot - c_lo;
                     if (S < (1u << 16)) S = (S << 16) | words.take();
                     const int b = 3 * i + ch;
-                    wout[b >> 2] |= (uint32_t)lo << (8 * (b & 3));
+                    wout[b >> 2] |= lo << (8 * (b & 3));
                 }
             }
         }
