@@ -1,7 +1,8 @@
 """The thread-per-lane kernels where they can go wrong: the decoder's guess of a symbol over the whole range of scales,
-means and precisions."""
+means and precisions, and chunks of pixels in arrays that are not aligned."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import pilc_oracle as orc
 from paper_2206_05279_amd import binding as pb
@@ -42,3 +43,21 @@ def test_guess_over_the_range_of_the_law(prec_bits, log_scale):
     wl.mu[...] = np.where(rng.random(wl.img.shape) < 0.7, near, far).astype(np.uint16)
     wl.log_scale[...] = log_scale
     _check(wl, DeviceWorkload(wl))
+
+
+# Rows of lanes shorter and longer than a chunk of eight pixels, arrays that start on any element: the last chunk of
+# the last row of the last image is the one that must not be read past.
+@pytest.mark.parametrize("w", [1, 7, 8, 9, 15, 17, 24])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_chunks_of_unaligned_rows(w, shift):
+    wl = synth.make_random_case(w, 3, 5, w, 12, 1, 2, 17)
+    device = DeviceWorkload(wl)
+
+    def moved(t):
+        room = torch.empty(t.numel() + shift, dtype=t.dtype, device=t.device)
+        room[shift:] = t.reshape(-1)
+        return room[shift:].reshape(t.shape)
+
+    device.img, device.mu, device.log_scale = moved(device.img), moved(device.mu), moved(device.log_scale)
+    device.out = moved(device.out)
+    _check(wl, device)
