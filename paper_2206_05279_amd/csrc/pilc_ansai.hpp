@@ -1,14 +1,13 @@
 // The table-driven coder of Sec. 3.2 (Alg. 3 "ANS-AI: Encode x", Alg. 4 "ANS-AI: Decode one
 // symbol") for gfx950: one thread per piece (Sec. 4.3), the tables of a workgroup in LDS.
 //
-// A symbol costs some twenty to thirty instructions and two to three bytes of HBM traffic, and the layout work is
+// A symbol costs some twenty instructions and two to three bytes of HBM traffic, and the layout work is
 // about moving whole cache lines:
 //   - the symbol and index rows of a wavefront's 64 pieces are staged through LDS in chunks (in the
 //     encoder chunks that are aligned in the arrays), with 16-byte loads in which consecutive threads cover one
 //     row's chunk, so every line is fetched once and fully used;
-//   - the encoder's words go to a scratch area laid out [wavefront][word][thread], so the 64
-//     threads of a wavefront, which emit at nearly the same rate, fill the same lines together;
-//   - k_ansai_pack turns that layout into the container's records through an LDS transpose.
+//   - the encoder's words go to a row per piece of a scratch area, 32 bytes at a time;
+//   - k_ansai_pack copies the rows into the container's records.
 //
 // Included at the end of pilc.hip (needs its Status, scan kernels, Timer and host helpers).
 #pragma once
@@ -130,6 +129,8 @@ __global__ __launch_bounds__(256) void k_ansai_build(uint32_t M, uint32_t X,
 // thus requested once, whole.  The threads then pass the line through LDS in two halves of 64
 // bytes, where thread r finds the bytes of row r; the registers of the second half simply wait.
 
+typedef uint32_t u32x4_dword __attribute__((ext_vector_type(4), aligned(4)));  // sixteen bytes at any dword
+
 constexpr uint32_t kLine = 128;
 
 struct RowLine {
@@ -160,6 +161,13 @@ __device__ __forceinline__ uint32_t line_stage_count(uint32_t count)
     return (count + 2u * kLine - 2u) / kLine;
 }
 
+// Whether line-stage `ls` is a whole line of every row of the wavefront: stage 0 takes at most a line of a row, and what
+// is left, count - 128 bytes or more, begins with whole lines.
+__device__ __forceinline__ bool whole_line_stage(uint32_t np, uint32_t count, uint32_t ls)
+{
+    return np == 64u && ls != 0u && ls < count / kLine;
+}
+
 // Bytes [a, b) of a dword, the others cleared (a, b may lie outside 0..4).
 __device__ __forceinline__ uint32_t keep_bytes(uint32_t w, int a, int b)
 {
@@ -168,31 +176,59 @@ __device__ __forceinline__ uint32_t keep_bytes(uint32_t w, int a, int b)
     return w & below_b & ~below_a;
 }
 
-// Fetches line-stage `ls` of the rows of pieces p0 .. p0+np-1: for every row the 16-byte vectors
+// A vector of the arrays `sym` and `dist` at byte `off`; the bytes past the arrays' end cleared.  The data is used once: the
+// loads are marked non-temporal so that they do not push the lines this kernel writes out of the L2 before
+// they are complete.
+__device__ __forceinline__ uint4 once_load(const uint8_t *__restrict__ from)
+{
+    const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(from));
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+__device__ __forceinline__ void cut_at_end(uint4 &v, int bytes)
+{
+    v = make_uint4(keep_bytes(v.x, 0, bytes), keep_bytes(v.y, 0, bytes - 4), keep_bytes(v.z, 0, bytes - 8),
+                   keep_bytes(v.w, 0, bytes - 12));
+}
+
+// Fetches line-stage `ls` of the rows of pieces p0 .. p0+np-1 of both arrays: for every row the 16-byte vectors
 // of its line that hold at least one of its bytes (they may also hold bytes of its neighbours);
 // zeros elsewhere.  A vector is aligned and holds a byte of the array, so it lies inside the
-// array's last page even where it reaches past the array's end; such bytes are cleared.  The
-// data is used once: the loads are marked non-temporal so that they do not push the lines this
-// kernel writes out of the L2 before they are complete.
-__device__ __forceinline__ void line_load(const uint8_t *__restrict__ arr, uint32_t total_bytes,
-                                          uint32_t p0, uint32_t np, uint32_t count, uint32_t ls,
-                                          uint4 (&v)[8])
+// array's last page even where it reaches past the array's end; such bytes are cleared.
+// `whole` (the same for the wavefront, see whole_line_stage): every row has a whole line, nothing is asked per row.
+__device__ __forceinline__ void line_load(const uint8_t *__restrict__ sym, const uint8_t *__restrict__ dist,
+                                          uint32_t total_bytes, uint32_t p0, uint32_t np, uint32_t count, uint32_t ls,
+                                          bool whole, uint4 (&sv)[8], uint4 (&dv)[8])
 {
-    const uint32_t lane = threadIdx.x & 63u, vb = (lane & 7u) * 16u;
+    uint32_t lane = threadIdx.x & 63u;
+    asm volatile("" : "+v"(lane));  // (the rows' places are formed again in every call, not kept in registers)
+    const uint32_t vb = (lane & 7u) * 16u;
+    if (whole) {
+        uint32_t last = (p0 + (lane >> 3) + 1u) * count - 1u;  // the last byte of the row
+        uint32_t off[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            off[i] = (last & ~(kLine - 1u)) - ls * kLine + vb;
+            last += 8u * count;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sv[i] = once_load(sym + off[i]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dv[i] = once_load(dist + off[i]);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const uint32_t r = i * 8 + (lane >> 3);
         const RowLine rl = row_line(p0 + r, count, ls, r < np);
-        v[i] = make_uint4(0u, 0u, 0u, 0u);
+        sv[i] = dv[i] = make_uint4(0u, 0u, 0u, 0u);
         if (vb < rl.hi && vb + 16u > rl.lo) {
             const uint32_t off = rl.line * kLine + vb;
-            const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(arr + off));
-            v[i] = make_uint4(t.x, t.y, t.z, t.w);
+            sv[i] = once_load(sym + off);
+            dv[i] = once_load(dist + off);
             if (off + 16u > total_bytes) {  // at most one vector of the whole grid
                 asm volatile("" ::: "memory");  // keep this a branch, not a chain of selects
-                const int b = (int)(total_bytes - off);
-                v[i] = make_uint4(keep_bytes(t.x, 0, b), keep_bytes(t.y, 0, b - 4), keep_bytes(t.z, 0, b - 8),
-                                  keep_bytes(t.w, 0, b - 12));
+                cut_at_end(sv[i], (int)(total_bytes - off));
+                cut_at_end(dv[i], (int)(total_bytes - off));
             }
         }
     }
@@ -221,11 +257,16 @@ __device__ __forceinline__ uint32_t bytes_at_or_above(uint32_t w, const ByteLimi
 }
 
 // Checks the 8 vectors against a limit; a vector with an offending byte is zeroed (so that no
-// table index leaves its table) and reported.
+// table index leaves its table) and reported.  The OR of all bytes is looked at first: it is at least as large as each
+// of them, so nothing more has to be asked while it is below the limit.
 __device__ __forceinline__ uint32_t lines_check(uint4 (&v)[8], const ByteLimit &b)
 {
     uint32_t bad = 0u;
     if (b.none) return 0u;
+    uint32_t all = 0u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) all |= (v[i].x | v[i].y) | (v[i].z | v[i].w);
+    if (!__any(bytes_at_or_above(all, b) != 0u)) return 0u;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const uint32_t f = bytes_at_or_above(v[i].x, b) | bytes_at_or_above(v[i].y, b) |
@@ -239,80 +280,173 @@ __device__ __forceinline__ uint32_t lines_check(uint4 (&v)[8], const ByteLimit &
 // ---------------------------------------------------------------------------------------------
 // Encode (Alg. 3), symbols of a piece taken last-first
 // ---------------------------------------------------------------------------------------------
-constexpr int kAnsaiEncWaves = 4;
-constexpr uint32_t kEncRow = 33;  // LDS dwords per row: 64 table indices of 16 bits, one dword pad
+constexpr int kAnsaiEncWaves = 4;      // wavefronts of a workgroup at most; three such workgroups fit a compute unit
+constexpr uint32_t kEncPart = 32;       // positions of a row in LDS at a time
+constexpr uint32_t kEncRow = 16;        // LDS dwords of a row: their symbols and their indices
+constexpr uint32_t kEncBlock = 8;       // words that leave together, to 32 bytes that start on a multiple of 32
+constexpr uint32_t kEncRing = 16;       // words of a piece that wait in LDS at most: 7, and eight more of sixteen symbols
+constexpr uint32_t kEncWaveDwords = 64u * (kEncRow + kEncRing + 2u);  // LDS of a wavefront
 
+// A piece under way.  The bits pushed and not yet written stand at the top of `top`, the last one highest, above bits
+// that have been written already; `room` (1 .. 32) is how many more make a word.
 struct EncLane {
-    uint32_t S;              // state in [2^M, 2^(M+1))
-    unsigned long long acc;  // bits pushed and not yet written, low bit first
-    uint32_t nacc;           // how many of them, < 32 between pairs of symbols
-    uint32_t woff;           // scratch index of the next word
+    uint32_t S;      // state in [2^M, 2^(M+1))
+    uint32_t top;
+    int room;
+    uint32_t nw;     // words made so far, counted from the multiple of kEncBlock words at or before the piece's first
 };
 
-// One step of Alg. 3 with the table entry e = {delta, phi} already fetched.
-__device__ __forceinline__ void ansai_push(EncLane &L, const uint2 e, uint32_t M)
+// Two steps of Alg. 3, the first with the table entry `a` = {delta, phi}, the second with `b`.  Each pushes at most 15
+// bits, so the two fill no more than one word; they are put together first and pushed as one.
+// A word that is complete goes to this thread's column of `ring` ([word mod kEncRing][thread]).
+__device__ __forceinline__ void ansai_push_two(EncLane &L, const uint2 a, const uint2 b, uint32_t M, uint32_t *ring)
 {
-    const uint32_t b = (e.x + L.S) >> M;  // number of bits to push, <= 15
-    const uint32_t low = L.S & ((1u << b) - 1u);
-    L.acc |= (unsigned long long)low << L.nacc;
-    L.nacc += b;
-    L.S = (L.S >> b) + e.y;
-}
-
-// Writes a word once 32 bits are there.  Called after every second symbol: two symbols add at
-// most 30 bits to fewer than 32, so the accumulator never overflows.
-__device__ __forceinline__ void ansai_emit(EncLane &L, uint32_t *__restrict__ scratch)
-{
-    if (L.nacc >= 32u) {
-        scratch[L.woff] = (uint32_t)L.acc;
-        L.woff += 64u;
-        L.acc >>= 32;
-        L.nacc -= 32u;
+    const uint32_t na = (a.x + L.S) >> M;
+    const uint32_t low = __builtin_amdgcn_ubfe(L.S, 0u, na);
+    L.S = (L.S >> na) + a.y;
+    const uint32_t nb = (b.x + L.S) >> M;
+    const uint32_t bits = low | (__builtin_amdgcn_ubfe(L.S, 0u, nb) << na);
+    L.S = (L.S >> nb) + b.y;
+    const uint32_t n = na + nb;
+    const uint32_t word = __builtin_amdgcn_alignbit(bits, L.top, (uint32_t)L.room);  // (room 32: not a word yet)
+    L.top = __builtin_amdgcn_alignbit(bits, L.top, n);
+    L.room -= (int)n;
+    if (L.room <= 0) {
+        ring[(L.nw % kEncRing) * 64u] = word;
+        ++L.nw;
+        L.room += 32;
     }
 }
 
-// Puts half `h` of the fetched lines into LDS as table indices d << 8 | x, 16 bits per symbol;
-// positions that are not part of a row get the index of the identity step, so that every thread
-// can run all 64 positions of the half without asking which are its own.
-__device__ __forceinline__ void enc_put(uint32_t *rows, const uint4 (&sv)[8], const uint4 (&dv)[8],
-                                        uint32_t h, uint32_t p0, uint32_t np, uint32_t count,
-                                        uint32_t ls, uint32_t ident)
+// The words of a wavefront's pieces on their way to the pieces' rows of the scratch: kEncBlock of them leave when they are
+// complete, which is looked at after every sixteen symbols (they make at most eight words).  Two neighbouring
+// threads store a block: the threads whose pieces have one write a list of them, and all threads go through
+// the list.  (What the kernel waits for otherwise is the number of separate places that are stored to: a word at
+// a time as they are made, or sixteen bytes of every piece by its own thread, cost 10^6 pieces of 1000
+// symbols 300 us, whether to whole lines or not.)
+struct EncOut {
+    uint32_t *base;    // of the wavefront's first piece
+    uint32_t *ring;    // of the wavefront: [word mod kEncRing][thread]
+    uint2 *list;       // {where a block goes, from which thread | which half of the ring << 8}
+    uint32_t at;       // where word `done` goes, from `base`
+    uint32_t done;     // words stored, counted as EncLane.nw
+
+    __device__ __forceinline__ void own(uint32_t upto)
+    {
+        for (; done < upto; ++done, ++at) base[at] = ring[(done % kEncRing) * 64u + (threadIdx.x & 63u)];
+    }
+    __device__ __forceinline__ void look(uint32_t nw)
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        if ((done % kEncBlock) != 0u && nw >= kEncBlock) own(kEncBlock);  // a piece's first words, which start anywhere
+        const bool full = (done % kEncBlock) == 0u && nw - done >= kEncBlock;
+        const unsigned long long mask = __ballot(full);
+        if (mask == 0ull) return;
+        const uint32_t number = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        if (full) {
+            list[number] = make_uint2(at, lane | ((done % kEncRing) / kEncBlock << 8));
+            at += kEncBlock;
+            done += kEncBlock;
+        }
+        wave_lds_sync();
+        const uint32_t blocks = (uint32_t)__popcll(mask), part = (lane & 1u) * 4u;
+        for (uint32_t b = 0; b < blocks; b += 32u) {
+            const uint32_t mine = b + (lane >> 1);
+            const uint2 e = list[min(mine, blocks - 1u)];
+            const uint32_t *from = ring + ((e.y >> 8) * kEncBlock + part) * 64u + (e.y & 63u);
+            const u32x4 v = {from[0], from[64], from[128], from[192]};
+            if (mine < blocks) *reinterpret_cast<u32x4_dword *>(base + (size_t)e.x + part) = v;
+        }
+        wave_lds_sync();
+    }
+};
+
+// Place of the table entry whose index is the lower / upper half of w: one shift that picks the half.
+template <bool kUpper> __device__ __forceinline__ uint32_t enc_place(uint32_t w)
 {
-    const uint32_t lane = threadIdx.x & 63u, c = lane & 7u;
-    if ((c >> 2) != h) return;
-    const uint32_t vb = c * 16u;
+    uint32_t at;
+    if (kUpper)
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(at) : "v"(3u), "v"(w));
+    else
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(at) : "v"(3u), "v"(w));
+    return at;
+}
+
+// Puts quarter `ph` of the fetched lines into LDS: of a row four times sixteen bytes, those of positions 0 and 16 of the
+// symbols and then of the indices.  Number k of them stands in place k ^ (row / 4 mod 4) of the row, so that threads
+// that read theirs together meet on no bank.
+__device__ __forceinline__ void enc_put(uint32_t *rows, const uint4 (&sv)[8], const uint4 (&dv)[8], uint32_t ph)
+{
+    uint32_t lane = threadIdx.x & 63u;
+    asm volatile("" : "+v"(lane));  // (as in line_load)
+    const uint32_t c = lane & 7u;
+    if ((c >> 1) != ph) return;
+    uint32_t *dst = rows + (lane >> 3) * kEncRow + ((c & 1u) ^ (lane >> 5)) * 4u;  // row 8 i + lane / 8: row / 4 = 2 i + lane / 32
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const uint32_t r = i * 8 + (lane >> 3);
-        uint32_t *dst = rows + r * kEncRow + (c & 3u) * 8u;
-        const RowLine rl = row_line(p0 + r, count, ls, r < np);
-        const uint32_t s[4] = {sv[i].x, sv[i].y, sv[i].z, sv[i].w};
-        const uint32_t d[4] = {dv[i].x, dv[i].y, dv[i].z, dv[i].w};
-        uint32_t w[8];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            // bytes {s0, d0, s1, d1} and {s2, d2, s3, d3}
-            w[2 * k] = __builtin_amdgcn_perm(d[k], s[k], 0x05010400u);
-            w[2 * k + 1] = __builtin_amdgcn_perm(d[k], s[k], 0x07030602u);
-        }
-        if (vb < rl.lo || vb + 16u > rl.hi) {  // not wholly inside the row
-            asm volatile("" ::: "memory");      // keep this a branch, not a chain of selects
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const uint32_t pos = vb + 2u * k;
-                const bool in0 = pos - rl.lo < rl.hi - rl.lo, in1 = pos + 1u - rl.lo < rl.hi - rl.lo;
-                w[k] = (in0 ? (w[k] & 0xFFFFu) : ident) | (in1 ? (w[k] & 0xFFFF0000u) : ident << 16);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) dst[k] = w[k];
+        // (number 0 or 1 in place dst or dst + 8 dwords: 2 i changes bit 1 of the place)
+        *reinterpret_cast<u32x4 *>(dst + 8u * kEncRow * i + ((i & 1) ? 8u : 0u)) = u32x4{sv[i].x, sv[i].y, sv[i].z, sv[i].w};
+        *reinterpret_cast<u32x4 *>(dst + 8u * kEncRow * i + ((i & 1) ? 0u : 8u)) = u32x4{dv[i].x, dv[i].y, dv[i].z, dv[i].w};
     }
 }
 
+// Which positions of a line belong to this thread's row: position + `skew` < `count` (unsigned).
+struct EncOwn {
+    uint32_t skew, count;
+};
+
+// The next 32 positions of this thread's row, which are in LDS, last first.  kMasked: positions that are not part of the row
+// take the identity step (`ident`, its place in the table), so that every thread can run all of them.  `first`: the
+// number of the first of them in the line.
+template <bool kMasked>
+__device__ __forceinline__ void enc_part(EncLane &L, EncOut &out, const uint2 *tab, uint32_t M, const u32x4 *row, uint32_t *ring,
+                                         uint32_t first, const EncOwn &own, uint32_t ident)
+{
+    // Four symbols a turn; their table entries are asked for a turn ahead.
+    const uint32_t turned = (threadIdx.x >> 2) & 3u;  // (see enc_put)
+    const u32x4 x = row[1u ^ turned], d = row[3u ^ turned];
+    uint2 n[4];
+    auto ask = [&](uint32_t x4, uint32_t d4, uint32_t at) {  // bytes {x0, d0, x1, d1} and {x2, d2, x3, d3} are indices
+        const uint32_t lower = __builtin_amdgcn_perm(d4, x4, 0x05010400u), upper = __builtin_amdgcn_perm(d4, x4, 0x07030602u);
+        uint32_t place[4] = {enc_place<false>(lower), enc_place<true>(lower), enc_place<false>(upper), enc_place<true>(upper)};
+#pragma unroll
+        for (uint32_t i = 0; i < 4u; ++i) {
+            if (kMasked) place[i] = first + at + i + own.skew < own.count ? place[i] : ident;
+            n[i] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(tab) + place[i]);
+        }
+    };
+    auto push = [&](const uint2 (&e)[4]) {
+        ansai_push_two(L, e[3], e[2], M, ring);
+        ansai_push_two(L, e[1], e[0], M, ring);
+    };
+    auto turn = [&](uint32_t x4, uint32_t d4, uint32_t at) {  // those of the next turn
+        const uint2 e[4] = {n[0], n[1], n[2], n[3]};
+        ask(x4, d4, at);
+        __builtin_amdgcn_sched_barrier(0);
+        push(e);
+    };
+    ask(x.w, d.w, 28u);
+    const u32x4 xl = row[turned], dl = row[2u ^ turned];
+    turn(x.z, d.z, 24u);
+    turn(x.y, d.y, 20u);
+    turn(x.x, d.x, 16u);
+    turn(xl.w, dl.w, 12u);
+    out.look(L.nw);
+    turn(xl.z, dl.z, 8u);
+    turn(xl.y, dl.y, 4u);
+    turn(xl.x, dl.x, 0u);
+    push(n);
+}
+
+// Bound by LDS (a table entry of 64 threads at once is a gather), by the vector instructions of a symbol, 17 of them, and
+// by the places its words are stored to, with three wavefronts on a SIMD.  10^6 pieces of 1000 symbols under eight laws:
+// 1318 -> 965 us, of 64 x 100,000 9.6 -> 6.9 ms.  (Before, a step of a symbol kept the bits not yet
+// written in 64 bits of its own, indices were put together by the threads that loaded them, and every position of
+// the first and last lines of a row was masked there: 32 instructions a symbol and 189 registers, two wavefronts.)
 template <bool kTabLds>
 __global__ __launch_bounds__(64 * kAnsaiEncWaves) void k_ansai_encode(
     AShape sh, const uint8_t *__restrict__ sym, const uint8_t *__restrict__ dist,
-    const uint2 *__restrict__ enc_tab, uint32_t *__restrict__ scratch, uint32_t maxw,
+    const uint2 *__restrict__ enc_tab, uint32_t *__restrict__ scratch, uint32_t stride,
     uint32_t *__restrict__ piece_bits, uint32_t *__restrict__ piece_state, int *status)
 {
     extern __shared__ uint32_t lds[];
@@ -323,82 +457,91 @@ __global__ __launch_bounds__(64 * kAnsaiEncWaves) void k_ansai_encode(
         uint2 *t = reinterpret_cast<uint2 *>(lds);
         for (uint32_t i = threadIdx.x; i < sh.D * 256u + 1u; i += blockDim.x) t[i] = enc_tab[i];
         tab = t;
-        stage_base = lds + 2u * (sh.D * 256u + 1u);
+        stage_base = lds + 2u * (sh.D * 256u + 2u);  // (a multiple of sixteen bytes)
         __syncthreads();
     }
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-    const uint32_t gw = blockIdx.x * kAnsaiEncWaves + wave;
+    const uint32_t gw = blockIdx.x * (blockDim.x >> 6) + wave;
     const uint32_t p0 = gw * 64u;
     if (p0 >= sh.pieces) return;
     const uint32_t np = min(64u, sh.pieces - p0);
-    uint32_t *rows = stage_base + wave * 64u * kEncRow;
+    uint32_t *rows = stage_base + wave * kEncWaveDwords;
+
     const uint32_t total = sh.pieces * sh.count;
-    const uint32_t *my = rows + lane * kEncRow;
+    uint32_t *ring = rows + 64u * kEncRow + lane;
+    const u32x4 *my = reinterpret_cast<const u32x4 *>(rows + lane * kEncRow);
     const bool mine = lane < np;
     const ByteLimit lim_x = byte_limit(sh.X), lim_d = byte_limit(sh.D);
     const uint32_t M = sh.M;
 
     EncLane L;
     L.S = 1u << M;
-    L.acc = 0ull;
-    L.nacc = 0u;
-    L.woff = gw * maxw * 64u + lane;
-    const uint32_t woff0 = L.woff;
+    L.top = 0u;
+    L.room = 32;
+    uint32_t *const base = scratch + (size_t)p0 * stride;
+    const uint32_t first = (uint32_t)(reinterpret_cast<uintptr_t>(base + lane * stride) >> 2) % kEncBlock;
+    L.nw = first;
+    EncOut out = {base, rows + 64u * kEncRow, reinterpret_cast<uint2 *>(rows + 64u * (kEncRow + kEncRing)), lane * stride, first};
     uint32_t bad = 0u;
 
     uint4 sv[8], dv[8];
     const uint32_t lines = line_stage_count(sh.count);
-    line_load(sym, total, p0, np, sh.count, 0u, sv);
-    line_load(dist, total, p0, np, sh.count, 0u, dv);
+    line_load(sym, dist, total, p0, np, sh.count, 0u, false, sv, dv);
+    bad |= lines_check(sv, lim_x) | lines_check(dv, lim_d);
     for (uint32_t ls = 0; ls < lines; ++ls) {
         asm volatile("" : "+s"(sh.count));  // recompute the row geometry per line-stage (registers)
-        bad |= lines_check(sv, lim_x) | lines_check(dv, lim_d);
+        const bool whole = whole_line_stage(np, sh.count, ls);
+        EncOwn own = {0u, 0u};
+        if (!whole) {
+            const RowLine rl = row_line(p0 + lane, sh.count, ls, mine);
+            own.skew = 0u - rl.lo;
+            own.count = rl.hi - rl.lo;
+        }
 #pragma unroll 1
-        for (int h = 1; h >= 0; --h) {
+        for (int ph = 3; ph >= 0; --ph) {
             wave_lds_sync();
-            enc_put(rows, sv, dv, (uint32_t)h, p0, np, sh.count, ls, sh.D << 8);
+            enc_put(rows, sv, dv, (uint32_t)ph);
             wave_lds_sync();
-            if (h == 0 && ls + 1u < lines) {  // the registers are free: fetch the next lines now
-                line_load(sym, total, p0, np, sh.count, ls + 1u, sv);
-                line_load(dist, total, p0, np, sh.count, ls + 1u, dv);
+            if (ph == 0 && ls + 1u < lines)  // the registers are free: fetch the next lines now
+                line_load(sym, dist, total, p0, np, sh.count, ls + 1u, whole_line_stage(np, sh.count, ls + 1u), sv, dv);
+            if (whole)
+                enc_part<false>(L, out, tab, M, my, ring, 0u, own, 0u);
+            else
+                enc_part<true>(L, out, tab, M, my, ring, kEncPart * (uint32_t)ph, own, sh.D << 11);
+            if (ph == 0) {
+                // the next lines, asked for 32 symbols ago, are waited for before words are stored: a wait for them
+                // afterwards would wait for the stores as well
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+                bad |= lines_check(sv, lim_x) | lines_check(dv, lim_d);
             }
-#pragma unroll 1
-            for (int j = 15; j >= 0; --j) {  // four symbols a turn, last first
-                const uint32_t w0 = my[2 * j], w1 = my[2 * j + 1];
-                const uint2 e3 = tab[w1 >> 16], e2 = tab[w1 & 0xFFFFu];
-                const uint2 e1 = tab[w0 >> 16], e0 = tab[w0 & 0xFFFFu];
-                ansai_push(L, e3, M);
-                ansai_push(L, e2, M);
-                ansai_emit(L, scratch);
-                ansai_push(L, e1, M);
-                ansai_push(L, e0, M);
-                ansai_emit(L, scratch);
-            }
+            out.look(L.nw);
         }
     }
     if (mine) {
-        if (L.nacc) scratch[L.woff] = (uint32_t)L.acc;
-        piece_bits[p0 + lane] = ((L.woff - woff0) >> 6) * 32u + L.nacc;
+        piece_bits[p0 + lane] = (L.nw - first) * 32u + 32u - (uint32_t)L.room;
         piece_state[p0 + lane] = L.S;
+        out.own(L.nw);
+        if (L.room < 32) base[out.at] = L.top >> L.room;
     }
     if (bad) atomicMax(status, ST_ARG);  // the same value from every thread that found one
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pack: scratch [wavefront][word][thread] -> records {state, bit count, words} at the offsets
+// Pack: scratch [piece][word] -> records {state, bit count, words} at the offsets
 // ---------------------------------------------------------------------------------------------
 constexpr int kAnsaiPackWaves = 4;
-constexpr int kAnsaiPackRows = 64;
+constexpr int kAnsaiPackTogether = 16;  // pieces whose loads are under way together
 
+// Bound by memory.  A wavefront copies 64 pieces, sixteen at a time, sixteen bytes a thread; the last sixteen of a
+// piece overlap those before them, so that nothing is read or written beyond its words.  The stores are
+// non-temporal: what they would push out of the caches is still to be read.
 __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
-    AShape sh, const uint32_t *__restrict__ scratch, uint32_t maxw,
+    AShape sh, const uint32_t *__restrict__ scratch, uint32_t stride,
     const uint32_t *__restrict__ piece_bits, const uint32_t *__restrict__ piece_state,
     const uint32_t *__restrict__ offsets, uint32_t *__restrict__ payload,
     const Status *__restrict__ status)
 {
     if (status->code != ST_OK) return;
-    static_assert(kAnsaiPackRows == 64, "a pass writes 64 words of one piece, one per thread");
-    __shared__ uint32_t tile[kAnsaiPackWaves][64 * (kAnsaiPackRows + 1)];
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     const uint32_t gw = blockIdx.x * kAnsaiPackWaves + wave;
     const uint32_t p0 = gw * 64u;
@@ -412,40 +555,36 @@ __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
         payload[at + 1u] = bits;
         dst = at + 2u;
     }
-    uint32_t most = nw;
-    for (int d = 32; d >= 1; d >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, 64));
-    const uint32_t *src = scratch + (size_t)gw * maxw * 64u + lane;
-    uint32_t *mine = tile[wave] + lane * (kAnsaiPackRows + 1);
-    // A turn moves kAnsaiPackRows words of every piece.  All rows of a turn are asked for before the
-    // first is stored (guarded one by one, every load would wait for the one before; rows past the
-    // last one repeat it and are never read), and the next turn's rows are asked for before this
-    // turn's words are written out, so that they arrive meanwhile.
-    uint32_t v[kAnsaiPackRows];
-    auto fetch = [&](uint32_t j0) {
+#pragma unroll 1
+    for (uint32_t i0 = 0; i0 < np; i0 += kAnsaiPackTogether) {
+        // (pieces past the last one have no words)
+        uint32_t n[kAnsaiPackTogether], to[kAnsaiPackTogether], most = 0u, least = 4u;
 #pragma unroll
-        for (int jj = 0; jj < kAnsaiPackRows; ++jj) v[jj] = src[(size_t)min(j0 + jj, most - 1u) * 64u];
-    };
-    if (most != 0u) fetch(0u);
-    for (uint32_t j0 = 0; j0 < most; j0 += kAnsaiPackRows) {
-        wave_lds_sync();
+        for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i) {
+            n[i] = (uint32_t)__builtin_amdgcn_readlane((int)nw, (int)(i0 + i));
+            to[i] = (uint32_t)__builtin_amdgcn_readlane((int)dst, (int)(i0 + i));
+            most = max(most, n[i]);
+            least = min(least, n[i]);
+        }
+        const uint32_t *src = scratch + (size_t)(p0 + i0) * stride;
+        if (least < 4u) {  // some piece is too short for sixteen bytes, or there is none: four threads a piece, a word each
+            static_assert(kAnsaiPackTogether == 16, "");
+            const uint32_t i = lane >> 2;
+            const uint32_t ni = (uint32_t)__shfl((int)nw, (int)(i0 + i), 64), ti = (uint32_t)__shfl((int)dst, (int)(i0 + i), 64);
+            for (uint32_t j = lane & 3u; j < ni; j += 4u) payload[ti + j] = src[(size_t)i * stride + j];
+            continue;
+        }
+#pragma unroll 1
+        for (uint32_t j0 = 0; j0 < most; j0 += 256u) {
+            const uint32_t j = j0 + 4u * lane;
+            u32x4 v[kAnsaiPackTogether];
 #pragma unroll
-        for (int jj = 0; jj < kAnsaiPackRows; ++jj) mine[jj] = v[jj];
-        wave_lds_sync();
-        if (j0 + kAnsaiPackRows < most) fetch(j0 + kAnsaiPackRows);
-        // pass i writes words j0 .. j0 + 63 of piece i, a word per thread; the piece's length and
-        // place come from its thread's registers, and eight tile reads are under way at a time
-        const uint32_t j = j0 + lane;
+            for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i)  // (a thread with nothing to move reads the piece's end)
+                v[i] = *reinterpret_cast<const u32x4_dword *>(src + (size_t)i * stride + min(j, n[i] - 4u));
 #pragma unroll
-        for (int i0 = 0; i0 < 64; i0 += 8) {
-            uint32_t word[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) word[k] = tile[wave][(i0 + k) * (kAnsaiPackRows + 1) + lane];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const uint32_t nw_i = (uint32_t)__builtin_amdgcn_readlane((int)nw, i0 + k);
-                const uint32_t dst_i = (uint32_t)__builtin_amdgcn_readlane((int)dst, i0 + k);
-                if (j < nw_i) payload[dst_i + j] = word[k];
-            }
+            for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i)
+                if (j < n[i])
+                    __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4_dword *>(payload + to[i] + min(j, n[i] - 4u)));
         }
     }
 }
@@ -1096,15 +1235,18 @@ int pilc_ansai_encode(const pilc_ansai_shape *shape, const uint8_t *sym_dev, con
 
     Timer timer(stream);
     k_ansai_begin<<<1, 1, 0, stream>>>(sh, reinterpret_cast<const ATabHeader *>(tb), status);
-    const uint32_t blocks = (uint32_t)ceil_div64(ws.waves, kAnsaiEncWaves);
-    const size_t stage_lds = (size_t)kAnsaiEncWaves * 64 * kEncRow * 4;
-    const size_t tab_lds = 8 * ((size_t)sh.D * 256 + 1);
-    if (tab_lds <= 24576 + 8)
-        k_ansai_encode<true><<<blocks, 64 * kAnsaiEncWaves, stage_lds + tab_lds, stream>>>(
-            sh, sym_dev, dist_dev, enc_tab, scratch, ws.maxw, piece_bits, piece_state, &status->code);
-    else
-        k_ansai_encode<false><<<blocks, 64 * kAnsaiEncWaves, stage_lds, stream>>>(
-            sh, sym_dev, dist_dev, enc_tab, scratch, ws.maxw, piece_bits, piece_state, &status->code);
+    const size_t tab_lds = 8 * ((size_t)sh.D * 256 + 2);
+    const bool tab_in_lds = tab_lds <= 24576 + 16;
+    int dev = 0, cus = 0;  // (a batch of few wavefronts is spread over all compute units)
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    const uint32_t waves = (uint32_t)std::min<uint64_t>(kAnsaiEncWaves, ceil_div64(ws.waves, (uint64_t)cus));
+    const uint32_t blocks = (uint32_t)ceil_div64(ws.waves, waves);
+    auto kern = tab_in_lds ? k_ansai_encode<true> : k_ansai_encode<false>;
+    if ((rc = allow_large_lds(reinterpret_cast<const void *>(kern))) != PILC_OK) return rc;
+    kern<<<blocks, 64 * waves, (size_t)waves * kEncWaveDwords * 4 + (tab_in_lds ? tab_lds : 0), stream>>>(
+        sh, sym_dev, dist_dev, enc_tab, scratch, ws.maxw, piece_bits, piece_state, &status->code);
     timer.mark("k_ansai_encode");
     const ItemBytes piece_bytes = {8u, 4u, 31u, 5u};  // state, bit count, 32-bit words
     const HeaderWords head = {{kAnsaiMagic, 1u, sh.pieces, sh.count, sh.M, sh.D, sh.X, 0u, 0u, 0u, 0u, 0u}};

@@ -342,3 +342,27 @@ def test_centering_matches_the_reference():
         assert np.array_equal(out.cpu().numpy(), r), n
     pad = torch.zeros(64, dtype=torch.uint8, device="cuda:0")
     assert pb.pilc_ansai_center(pad[1:33], pad[:32], pad[32:], check=False) == pb.PILC_E_ARG
+
+
+# Pieces of one wavefront whose words differ in number as much as they can (a law of one very likely symbol against one of
+# equally likely ones), rows that end beside the edges of a line, of its quarters and of a block of words.
+@pytest.mark.parametrize("pieces", [1, 63, 65, 130])
+@pytest.mark.parametrize("count", [1, 4, 15, 16, 17, 31, 32, 33, 127, 128, 129, 255, 257, 640])
+def test_pieces_of_very_different_lengths(pieces, count):
+    m, x = 15, 200
+    mass = np.ones((2, x), dtype=np.uint32)
+    mass[0, 7] = (1 << m) - (x - 1)
+    mass[1] = (1 << m) // x
+    mass[1, 0] += (1 << m) - mass[1].sum()
+    rng = np.random.default_rng(1000 * pieces + count)
+    dist = np.broadcast_to((np.arange(pieces) % 3 == 0)[:, None], (pieces, count)).astype(np.uint8).copy()
+    sym = np.where(dist == 0, 7, rng.integers(0, x, (pieces, count))).astype(np.uint8)
+    sym[1::2] = np.where(rng.random(sym[1::2].shape) < 0.1, rng.integers(0, x, sym[1::2].shape), sym[1::2])
+    rc, want = ao.encode(m, mass, sym, dist)
+    assert rc == ao.OK
+    dp = DevicePieces(m, mass, sym, dist)
+    _, nbytes = dp.encode()
+    got = dp.coded_numpy()
+    assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+    assert dp.decode() == pb.PILC_OK
+    assert np.array_equal(dp.decoded_numpy(), sym)
