@@ -20,9 +20,10 @@
  *     different streams may run concurrently, from any threads, if they use different workspaces.
  *     The library's only process-wide state: the constant tables (filled once per device under a
  *     lock), the knobs pilc_set_timing, pilc_set_kernel_policy, pilc_set_one_pass_wait and
- *     pilc_set_ansai_decode_waves (atomic integers, read once at the start of a call), the scratch array of pilc_encode_static, and four
+ *     pilc_set_ansai_decode_waves (atomic integers, read once at the start of a call), the scratch array of pilc_encode_static, four
  *     sets of words (4 MB each, on every GPU) that calls of pilc_twar_inverse on tall images pass rows on
- *     through, one a call.
+ *     through, one a call, and a few KB of pinned host memory in which pilc_encode and pilc_decode report
+ *     their outcome (64 places, one a call; allocated by the first such call and kept).
  *   - Tensors are dense, row-major, channel-interleaved: index ((i*h + y)*w + x)*3 + c.
  */
 #ifndef PILC_H

@@ -1250,11 +1250,8 @@ int pilc_ansai_encode(const pilc_ansai_shape *shape, const uint8_t *sym_dev, con
     timer.mark("k_ansai_encode");
     const ItemBytes piece_bytes = {8u, 4u, 31u, 5u};  // state, bit count, 32-bit words
     const HeaderWords head = {{kAnsaiMagic, 1u, sh.pieces, sh.count, sh.M, sh.D, sh.X, 0u, 0u, 0u, 0u, 0u}};
-    k_scan_partials<<<ws.scan_blocks, kScanThreads, 0, stream>>>(sh.pieces, piece_bytes, piece_bits, sums);
-    k_scan_spine<<<1, kScanThreads, 0, stream>>>(head, sh.pieces, ws.scan_blocks, sums, coded_dev,
-                                                 (unsigned long long)coded_capacity, status);
-    k_scan_apply<<<ws.scan_blocks, kScanThreads, 0, stream>>>(sh.pieces, piece_bytes, piece_bits, sums,
-                                                              offsets);
+    (void)launch_scan(head, sh.pieces, ws.scan_blocks, piece_bytes, piece_bits, sums, coded_dev, coded_capacity, status, nullptr,
+                      offsets, true, stream);
     timer.mark("scan");
     k_ansai_pack<<<(uint32_t)ceil_div64(ws.waves, kAnsaiPackWaves), 64 * kAnsaiPackWaves, 0, stream>>>(
         sh, scratch, ws.maxw, piece_bits, piece_state, offsets, payload, status);

@@ -83,9 +83,10 @@ __device__ __forceinline__ uint32_t cum_of_integers(int k, int mu_eff, uint32_t 
 __global__ __launch_bounds__(kEncThreads) void k_encode_block(
     Geo g, const uint8_t *__restrict__ img, const uint16_t *__restrict__ mu,
     const int16_t *__restrict__ ls, const int16_t *__restrict__ coef, uint16_t *__restrict__ scratch,
-    uint32_t *__restrict__ lane_words, uint32_t *__restrict__ lane_state)
+    uint32_t *__restrict__ lane_words, uint32_t *__restrict__ lane_state, Status *__restrict__ status)
 {
     __shared__ LdsTables tab;
+    if (blockIdx.x == 0u && threadIdx.x == 0u) init_status(status);  // (for the kernels that follow)
     __shared__ uint4 rec[2][kEncSyms][kEncLanes];
     __shared__ uint32_t s_max_px;
     if (threadIdx.x == 0) s_max_px = 0;

@@ -593,6 +593,7 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
     __shared__ LdsTables tab;
     load_tables(tab);  // ends with a barrier
     if (!kOnePass) {
+        if (blockIdx.x == 0u && threadIdx.x == 0u) init_status(op.status);  // (for the kernels that follow)
         const uint32_t lane = blockIdx.x * blockDim.x + threadIdx.x;
         if (lane >= g.lanes) return;
         uint32_t S;
@@ -790,24 +791,29 @@ struct WordRing {
 // 0.86 ms on 16,384 images of 64 x 64.)
 template <bool kVec, bool kPair>
 __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_lanes(Geo g, const uint8_t *__restrict__ coded,
-                               const uint16_t *__restrict__ mu, const int16_t *__restrict__ ls,
-                               const int16_t *__restrict__ coef, uint8_t *__restrict__ out,
-                               int *__restrict__ status_code,
-                               const unsigned long long *__restrict__ status_payload)
+                               unsigned long long coded_bytes, const uint16_t *__restrict__ mu,
+                               const int16_t *__restrict__ ls, const int16_t *__restrict__ coef,
+                               uint8_t *__restrict__ out, Report *__restrict__ report)
 {
+    __shared__ int s_state;
+    __shared__ unsigned long long s_payload;
+    if (threadIdx.x == 0u) s_state = check_header(g, kMagicPilc, 0u, coded, coded_bytes, &s_payload);
     __shared__ LdsTables tab;
     __shared__ float2 guide[kGuideEntries];
     extern __shared__ __align__(16) uint16_t ring[];  // [thread][word]: kRingRow elements a thread
     for (int i = threadIdx.x; i < kGuideEntries; i += blockDim.x) guide[i] = g_guide[i];
     load_tables(tab);  // ends with a barrier
     const GuideScale gs(g.prec_bits);
-    if (*status_code != 0) return;  // uniform: written by an earlier kernel
+    if (s_state != ST_OK) {
+        if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, s_state);
+        return;
+    }
     const uint32_t lane = blockIdx.x * blockDim.x + threadIdx.x;
     if (lane >= g.lanes) return;
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
     const uint32_t scale = mass_scale(m_bits), mask = (1u << m_bits) - 1u;
-    const uint32_t payload_bytes = (uint32_t)*status_payload;
+    const uint32_t payload_bytes = (uint32_t)s_payload;
     const uint32_t per_row = (sh.tw + kChunk - 1) / kChunk;
     const uint32_t chunks = per_row * (sh.npx / sh.tw);
 
@@ -816,7 +822,7 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
         reinterpret_cast<const uint16_t *>(coded + 64 + 4ull * ((size_t)g.lanes + 1));
     const uint32_t begin = offsets[lane], end = offsets[lane + 1];
     if (end < begin || end > payload_bytes || end - begin < 4u || ((begin | end) & 1u)) {
-        atomicMax(status_code, 6);
+        raise_code(report, ST_CORRUPT);
         return;
     }
     // word offsets from the last 16-byte boundary at or below the payload (the payload is < 4 GiB)
@@ -941,7 +947,7 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
             }
         }
     }
-    if (S != (1u << 16) || words.pos - first != (end - begin) >> 1) atomicMax(status_code, 6);
+    if (S != (1u << 16) || words.pos - first != (end - begin) >> 1) raise_code(report, ST_CORRUPT);
 }
 
 }  // namespace pilc

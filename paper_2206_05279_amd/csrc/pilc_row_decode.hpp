@@ -99,10 +99,9 @@ struct RowCand {
 // wavefront stages its own batches, and two workgroups share a compute unit.
 template <bool kRagged, bool kStaged>
 __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_rows(
-    Geo g, const uint8_t *__restrict__ coded, const uint16_t *__restrict__ mu,
+    Geo g, const uint8_t *__restrict__ coded, unsigned long long coded_bytes, const uint16_t *__restrict__ mu,
     const int16_t *__restrict__ ls, const int16_t *__restrict__ coef, uint8_t *__restrict__ out,
-    int *__restrict__ status_code, const unsigned long long *__restrict__ status_payload,
-    unsigned long long wait_ticks, uint32_t withhold)
+    Report *__restrict__ report, unsigned long long wait_ticks, uint32_t withhold)
 {
     // wait_ticks: the bound of a wait between a decoding wavefront and its stager, in ticks of the
     // constant-rate clock; withhold: the stagers never say that a batch is ready (tests of the
@@ -128,16 +127,17 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         s_posted[threadIdx.x] = 0u;
         s_staged[threadIdx.x] = 0u;
     }
-    // Whether the call has failed already is looked at once for the whole workgroup: were every
-    // wavefront to look for itself, another workgroup's error could come between the looks, and a
-    // wavefront would wait for a partner that has left.
-    __shared__ int s_failed;
+    __shared__ int s_state;
+    __shared__ unsigned long long s_payload;
     if (threadIdx.x == 0u) {
         s_abort = 0u;
-        s_failed = *status_code;
+        s_state = check_header(g, kMagicPilc, 0u, coded, coded_bytes, &s_payload);
     }
     load_tables(tab);  // ends with a barrier
-    if (s_failed != 0) return;
+    if (s_state != ST_OK) {
+        if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, s_state);
+        return;
+    }
 
     const bool stager = kStaged && threadIdx.x >= 64u * kRowWaves;
     const uint32_t tix = threadIdx.x - (stager ? 64u * kRowWaves : 0u);  // index among the threads of its kind
@@ -152,7 +152,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     const uint32_t m_bits = g.prec_bits;
     const uint32_t mask = (1u << m_bits) - 1u, top = 1u << m_bits;
     const uint32_t scale = mass_scale(m_bits);
-    const uint32_t payload_bytes = (uint32_t)*status_payload;
+    const uint32_t payload_bytes = (uint32_t)s_payload;
     const uint32_t *offsets = reinterpret_cast<const uint32_t *>(coded + 64);
     const uint16_t *payload =
         reinterpret_cast<const uint16_t *>(coded + 64 + 4ull * ((size_t)g.lanes + 1));
@@ -164,7 +164,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     {
         const uint32_t begin = offsets[lane], end = offsets[lane + 1];
         if (end < begin || end > payload_bytes || end - begin < 4u || ((begin | end) & 1u)) {
-            if (j == 0 && has_lane) atomicMax(status_code, 6);
+            if (j == 0 && has_lane) raise_code(report, ST_CORRUPT);
         } else {
             npx = sh.npx;
             stop = end >> 1;
@@ -363,7 +363,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
             if (__hip_atomic_load(&s_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u) return false;
             if (wall_clock64() - since > wait_ticks) {
                 __hip_atomic_store(&s_abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (tid == 0u) atomicMax(status_code, 8);
+                if (tid == 0u) raise_code(report, ST_TIMEOUT);
                 return false;
             }
             __builtin_amdgcn_s_sleep(8);
@@ -557,7 +557,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
             out[s + 2] = (uint8_t)(v_out >> 16);
         }
     }
-    if (has_lane && npx != 0u && (S != (1u << 16) || pos != stop) && j == 0) atomicMax(status_code, 6);
+    if (has_lane && npx != 0u && (S != (1u << 16) || pos != stop) && j == 0) raise_code(report, ST_CORRUPT);
 }
 
 }  // namespace pilc
