@@ -500,16 +500,17 @@ static std::atomic<int> g_one_pass_withhold{0};
 // The few-lane kernels pay off while there are too few lanes to fill the chip with one thread
 // each (256 CUs x 4 SIMDs x 64 threads = 65,536 threads for a single wave per SIMD).  Measured
 // on CIFAR-shaped data cut into lanes of different lengths, the block encoder is ahead of the
-// thread-per-lane encoder up to about 28K lanes (1.85 against 2.15 ms at 25,000 lanes, 1.74
-// against 1.13 ms at 50,000) and the row decoder up to about 13K (7.8 against 15.5 ms at 6250
-// lanes, 7.5 against 7.8 ms at 12,500, 6.4 against 4.2 ms at 25,000; on uniformly random pixels
-// 5.3 against 7.7 ms at 8192 lanes, 4.7 against 3.9 ms at 16,384).
+// thread-per-lane encoder up to some 43,000 lanes (1.25 against 2.02 ms at 25,000 lanes of 2048 pixels, 1.57
+// against 1.91 at 37,800 of 1920, 1.14 against 1.08 at 50,000 of 1024; 94 against 105 us at 32,000 of 64, 119 against 112 at
+// 44,800) and the row decoder up to about 6600 (8.3 against 14.7 ms at 3125
+// lanes, 6.86 against 7.41 at 6250, 8.12 against 5.56 at 8334, 6.44 against 3.74 at 12,500).  Where the model does not
+// fit, the thread-per-lane decoder is ahead earlier (uniformly random pixels, 6250 lanes: 11.2 against 7.4 ms).
 static bool use_few_lane_kernels(const Geo &g, bool decode)
 {
     const int policy = g_kernel_policy.load(std::memory_order_relaxed);
     if (policy == 1 || policy == 3) return false;
     if (policy == 2) return true;
-    return g.lanes <= (decode ? 12288u : 28672u);
+    return g.lanes <= (decode ? 6656u : 40960u);
 }
 
 thread_local char t_hip_error[256] = "";
@@ -1042,7 +1043,15 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
     op.status = status;  // (set to zero by the lane kernel unless it works in one pass)
     CallReport report(reinterpret_cast<Report *>(base + ws.report_off), stream, timed);
     if (few_lanes) {
-        k_encode_block<<<(uint32_t)ceil_div64(g.lanes, kEncLanes), kEncThreads, 0, stream>>>(
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+            cus = 256;
+        const uint32_t blocks = (uint32_t)ceil_div64(g.lanes, kEncLanes);
+        const bool wide = max_lane_symbols(g) >= (1u << 27) - 1u, few = !wide && blocks > (uint32_t)cus;
+        auto kern = wide ? k_encode_block<kEncMostProducers, true>
+                    : few ? k_encode_block<kEncFewProducers, false> : k_encode_block<kEncMostProducers, false>;
+        kern<<<blocks, enc_threads(few ? kEncFewProducers : kEncMostProducers), 0, stream>>>(
             g, img_dev, params->mu, params->log_scale, params->chan_coef, scratch, lane_words, lane_state, status);
     } else {
         const int bt = lane_block_threads(g);

@@ -3,9 +3,8 @@
 // The rANS push (App. A eq. (11) of arXiv 2206.05279) is a serial chain per lane, but only
 // the state update itself is serial: the symbol's (cum, freq) and an exact reciprocal of freq
 // do not depend on the state.  A workgroup owns 16 lanes.  Wave 0 keeps the 16 states, one per
-// thread, and does nothing but the chain; the other seven waves run ahead by one batch of 28
-// pixels per lane (one pixel per thread) and leave, per symbol, one ready-made 16-byte record in
-// LDS (see
+// thread, and does nothing but the chain; the other waves run ahead by one batch of pixels (one
+// per thread, 24 or 12 per lane) and leave, per symbol, one ready-made 16-byte record in LDS (see
 // encode_record).  One barrier per batch hands a buffer over; the two roles never wait for each
 // other inside a batch.  The chain is branch-free: a word is stored on every step, below the
 // lane's words so far, and counted only when the state renormalises.
@@ -15,11 +14,13 @@
 
 namespace pilc {
 
-constexpr int kEncLanes = 16;             // lanes per workgroup (threads 0..15 of wave 0 chain)
-constexpr int kEncProducerWaves = 7;      // waves 1..7 prepare records
-constexpr int kEncThreads = 64 * (1 + kEncProducerWaves);
-constexpr int kEncPix = 64 * kEncProducerWaves / kEncLanes;  // pixels per lane and batch (28)
-constexpr int kEncSyms = 3 * kEncPix;
+constexpr int kEncLanes = 16;  // lanes per workgroup (threads 0..15 of wave 0 chain)
+// Wavefronts that prepare records (`kProducers`): six, or three where there are more workgroups than compute units, so that
+// workgroups that share one do not crowd its four SIMDs.  Six against three, us: 4000 lanes of 4096 pixels 466 and 523, 6000 of
+// 1024 256 and 206, 25,600 of 64 117 and 84, 28,000 of 256 265 and 193.  (Seven: 1 to 2 % slower than six.)
+constexpr int kEncMostProducers = 6, kEncFewProducers = 3;
+constexpr int enc_threads(int producers) { return 64 * (1 + producers); }
+constexpr int enc_pixels(int producers) { return 64 * producers / kEncLanes; }  // per lane and batch
 
 // floor(2^32 * a / f) for a < f < 2^17, by two 16-bit digits of long division
 __device__ __forceinline__ uint32_t frac32(uint32_t a, uint32_t f)
@@ -29,16 +30,6 @@ __device__ __forceinline__ uint32_t frac32(uint32_t a, uint32_t f)
     uint32_t r1 = n1 - q1 * f;
     uint32_t q0 = (r1 << 16) / f;
     return (q1 << 16) | q0;
-}
-
-// v >> (top byte of w): one instruction that takes its shift count from byte 3 of a register
-__device__ __forceinline__ uint32_t shift_right_by_top_byte(uint32_t v, uint32_t w)
-{
-    uint32_t r;
-    asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD"
-        : "=v"(r)
-        : "v"(w), "v"(v));
-    return r;
 }
 
 // Record of one symbol for the chain: { T, m, add, k | sh << 24 } such that one step is
@@ -58,6 +49,38 @@ __device__ __forceinline__ uint4 encode_record(uint32_t cum, uint32_t f, uint32_
     const uint32_t l = 32u - (uint32_t)__clz(f - 1u);
     const uint32_t magic = frac32((1u << l) - f, f) + 1u;
     return make_uint4((f << (32u - m_bits)) - 1u, magic, cum, k | ((l - 1u) << 24));
+}
+
+// The chain of one lane.
+struct EncChain {
+    uint32_t S;     // the state
+    uint32_t at;    // where the word below the words so far goes, in bytes ...
+    uint32_t back;  // ... once this has been taken off: 2 if the last step's word counts, else 0
+};
+
+// One step by a record.  The state's low word belongs at c.at after it.  The step is written out for its order: an
+// instruction that reads a condition has to stand three after the one that makes it, and left to itself the
+// compiler waits that out, and once more after each single instruction that is written out by itself: 12 of the 86
+// cycles of a step, and the kernel is as fast as its chain (3125 lanes of 16,384 pixels 1854 -> 1750 us, with six producers instead of seven 1726).
+__device__ __forceinline__ void encode_step(EncChain &c, const uint4 &r)
+{
+    uint32_t next, high, t;
+    asm("v_cmp_gt_u32_e32 vcc, %[s], %[T]\n"
+        "v_lshrrev_b32_e32 %[h], 16, %[s]\n"
+        "v_sub_u32_e32 %[at], %[at], %[back]\n"
+        "v_cndmask_b32_e32 %[n], %[s], %[h], vcc\n"
+        "v_mul_hi_u32 %[t], %[n], %[m]\n"
+        "v_cndmask_b32_e32 %[back], 0, %[two], vcc\n"
+        "v_sub_u32_e32 %[h], %[n], %[t]\n"
+        "v_lshrrev_b32_e32 %[h], 1, %[h]\n"
+        "v_add_u32_e32 %[t], %[h], %[t]\n"
+        "v_lshrrev_b32_sdwa %[t], %[w], %[t] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n"
+        "v_mul_u32_u24_e32 %[t], %[t], %[w]\n"
+        "v_add3_u32 %[n], %[t], %[add], %[n]"
+        : [n] "=&v"(next), [h] "=&v"(high), [t] "=&v"(t), [at] "+&v"(c.at), [back] "+&v"(c.back)
+        : [s] "v"(c.S), [T] "v"(r.x), [m] "v"(r.y), [add] "v"(r.z), [w] "v"(r.w), [two] "v"(2u)
+        : "vcc");
+    c.S = next;
 }
 
 // C(k), 1 <= k <= 255, with the position of the edge formed in integers.  (What bounds this kernel is the wavefront of
@@ -80,11 +103,14 @@ __device__ __forceinline__ uint32_t cum_of_integers(int k, int mu_eff, uint32_t 
     return (uint32_t)k + ((uint32_t)__umul24(f, scale >> 16) >> 16);
 }
 
-__global__ __launch_bounds__(kEncThreads) void k_encode_block(
+// kWide: lanes of 2^27 symbols and more, whose words lie further from the workgroup's first than 32 bits of bytes reach.
+template <int kProducers, bool kWide>
+__global__ __launch_bounds__(enc_threads(kProducers)) void k_encode_block(
     Geo g, const uint8_t *__restrict__ img, const uint16_t *__restrict__ mu,
     const int16_t *__restrict__ ls, const int16_t *__restrict__ coef, uint16_t *__restrict__ scratch,
     uint32_t *__restrict__ lane_words, uint32_t *__restrict__ lane_state, Status *__restrict__ status)
 {
+    constexpr uint32_t kEncPix = enc_pixels(kProducers), kEncSyms = 3u * kEncPix;
     __shared__ LdsTables tab;
     if (blockIdx.x == 0u && threadIdx.x == 0u) init_status(status);  // (for the kernels that follow)
     __shared__ uint4 rec[2][kEncSyms][kEncLanes];
@@ -109,10 +135,13 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_block(
     const uint32_t batches = (s_max_px + kEncPix - 1u) / kEncPix;
 
     // chain state (threads 0..nl-1 of wave 0)
-    uint32_t S = 1u << 16;
     // index into scratch, one past the lane's slot (block_slot_end: one spare word below every slot)
     const uint32_t slot_end = block_slot_end(sh, lane0 + (has_lane ? my : 0u));
-    uint32_t wat = slot_end - 1u;  // where the next word goes: just below the lane's words so far
+    // the words' places are counted from the first lane's slot (kWide: each lane's from its own, downwards)
+    const uint32_t first = kWide ? slot_end - 1u : block_slot_end(lane_shape(g, lane0), lane0) - 3u * lane_shape(g, lane0).npx - 1u;
+    uint16_t *const words = scratch + first;
+    EncChain chain = {1u << 16, kWide ? 0u : 2u * (slot_end - 1u - first), 0u};
+    uint32_t count = 0u;  // (kWide) words so far
 
     // producers: the nine input values of the pixel of batch b, loaded one batch ahead
     struct PixelIn {
@@ -157,23 +186,22 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_block(
         // all records of the batch first: the loads do not depend on the state
         uint4 r[kEncSyms];
 #pragma unroll
-        for (int k = 0; k < kEncSyms; ++k) r[k] = rec[buf][k][my];
+        for (uint32_t k = 0; k < kEncSyms; ++k) r[k] = rec[buf][k][my];
 #pragma unroll
-        for (int k = 0; k < kEncSyms; ++k) {
+        for (uint32_t k = 0; k < kEncSyms; ++k) {
             // The word is stored on every step, just below the words already there, and counted
             // only when the state renormalises: an uncounted word is overwritten by the next one
             // or stays below the lane's first word.  After i symbols at most i words are counted
             // and the slot has room for one per symbol, so the store stays in the slot, or, for the
             // empty steps after a lane's last symbol, in the spare word below it.
-            const bool emit = S > r[k].x;
-            scratch[wat] = (uint16_t)(S & 0xFFFFu);
-            wat -= emit ? 1u : 0u;
-            S = emit ? S >> 16 : S;
-            const uint32_t t = __umulhi(r[k].y, S);
-            // the shift count is the top byte of the record's last word (picked by the shift itself),
-            // the multiplier its low 24 bits (all the 24-bit multiply looks at)
-            const uint32_t quo = shift_right_by_top_byte(t + ((S - t) >> 1), r[k].w);
-            S = S + r[k].z + __umul24(quo, r[k].w);
+            const uint16_t low = (uint16_t)chain.S;
+            encode_step(chain, r[k]);
+            if (kWide) {
+                words[-(ptrdiff_t)count] = low;
+                count += chain.back >> 1;
+            } else {
+                *reinterpret_cast<uint16_t *>(reinterpret_cast<uint8_t *>(words) + chain.at) = low;
+            }
         }
     };
 
@@ -195,8 +223,8 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_block(
         __syncthreads();
     }
     if (!producer && has_lane) {
-        lane_words[lane0 + my] = slot_end - 1u - wat;
-        lane_state[lane0 + my] = S;
+        lane_words[lane0 + my] = kWide ? count : slot_end - 1u - first - ((chain.at - chain.back) >> 1);
+        lane_state[lane0 + my] = chain.S;
     }
 }
 
