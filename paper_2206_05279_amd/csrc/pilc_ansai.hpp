@@ -534,7 +534,8 @@ constexpr int kAnsaiPackTogether = 16;  // pieces whose loads are under way toge
 
 // Bound by memory.  A wavefront copies 64 pieces, sixteen at a time, sixteen bytes a thread; the last sixteen of a
 // piece overlap those before them, so that nothing is read or written beyond its words.  The stores are
-// non-temporal: what they would push out of the caches is still to be read.
+// non-temporal: what they would push out of the caches is still to be read.  The last group of a batch, which has fewer
+// pieces, goes the same way.
 __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
     AShape sh, const uint32_t *__restrict__ scratch, uint32_t stride,
     const uint32_t *__restrict__ piece_bits, const uint32_t *__restrict__ piece_state,
@@ -557,17 +558,18 @@ __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
     }
 #pragma unroll 1
     for (uint32_t i0 = 0; i0 < np; i0 += kAnsaiPackTogether) {
-        // (pieces past the last one have no words)
+        // (in the place of pieces past the last one it is read again, and not stored)
+        const uint32_t last = min(np - 1u - i0, (uint32_t)kAnsaiPackTogether - 1u);
         uint32_t n[kAnsaiPackTogether], to[kAnsaiPackTogether], most = 0u, least = 4u;
 #pragma unroll
         for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i) {
-            n[i] = (uint32_t)__builtin_amdgcn_readlane((int)nw, (int)(i0 + i));
-            to[i] = (uint32_t)__builtin_amdgcn_readlane((int)dst, (int)(i0 + i));
+            n[i] = (uint32_t)__builtin_amdgcn_readlane((int)nw, (int)(i0 + min(i, last)));
+            to[i] = (uint32_t)__builtin_amdgcn_readlane((int)dst, (int)(i0 + min(i, last)));
             most = max(most, n[i]);
             least = min(least, n[i]);
         }
         const uint32_t *src = scratch + (size_t)(p0 + i0) * stride;
-        if (least < 4u) {  // some piece is too short for sixteen bytes, or there is none: four threads a piece, a word each
+        if (least < 4u) {  // some piece is too short for sixteen bytes: four threads a piece, a word each
             static_assert(kAnsaiPackTogether == 16, "");
             const uint32_t i = lane >> 2;
             const uint32_t ni = (uint32_t)__shfl((int)nw, (int)(i0 + i), 64), ti = (uint32_t)__shfl((int)dst, (int)(i0 + i), 64);
@@ -580,10 +582,10 @@ __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
             u32x4 v[kAnsaiPackTogether];
 #pragma unroll
             for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i)  // (a thread with nothing to move reads the piece's end)
-                v[i] = *reinterpret_cast<const u32x4_dword *>(src + (size_t)i * stride + min(j, n[i] - 4u));
+                v[i] = *reinterpret_cast<const u32x4_dword *>(src + (size_t)min(i, last) * stride + min(j, n[i] - 4u));
 #pragma unroll
             for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i)
-                if (j < n[i])
+                if (i <= last && j < n[i])
                     __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4_dword *>(payload + to[i] + min(j, n[i] - 4u)));
         }
     }

@@ -366,3 +366,20 @@ def test_pieces_of_very_different_lengths(pieces, count):
     assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
     assert dp.decode() == pb.PILC_OK
     assert np.array_equal(dp.decoded_numpy(), sym)
+
+
+# A last group of sixteen that is not full, of pieces with few and with many words, beside full ones and alone.
+@pytest.mark.parametrize("pieces", [1, 2, 15, 17, 31, 33, 79, 81])
+@pytest.mark.parametrize("count", [9, 40, 600, 1300])
+def test_last_pieces_of_a_batch(pieces, count):
+    m, x = 12, 256
+    mass = np.full((1, x), (1 << m) // x, dtype=np.uint32)
+    rng = np.random.default_rng(pieces * 10000 + count)
+    sym = rng.integers(0, x, (pieces, count)).astype(np.uint8)
+    dist = np.zeros((pieces, count), dtype=np.uint8)
+    rc, want = ao.encode(m, mass, sym, dist)
+    assert rc == ao.OK
+    dp = DevicePieces(m, mass, sym, dist)
+    _, nbytes = dp.encode()
+    got = dp.coded_numpy()
+    assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
