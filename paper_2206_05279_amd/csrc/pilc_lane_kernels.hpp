@@ -646,9 +646,9 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
 }
 
 // --------------------------------------------------------------------------------------------
-// Decode.  The symbol is guessed from the inverse of the law (guide_edge) and checked at three edges of the exact C;
-// App. A names a binary search, which is what a wavefront falls back to when the guess of one of its lanes
-// is not good enough (scales of 200 and more).  Bound by vector instructions where the lanes fill
+// Decode.  The symbol (App. A names a binary search for it) is guessed from the inverse of the law (guide_edge) and checked
+// at three edges of the exact C; from a guess that is not good enough the lanes concerned walk on edge by edge
+// (walk_to_symbol), which wide laws at a low precision take.  Bound by vector instructions where the lanes fill
 // the chip, by the length of a symbol's chain where they do not; the guess and three edges, whose
 // table reads are under way together, are 77 instructions and two waits for LDS instead of the 104 and
 // eight of eight steps of bisection: 30 frames of 1080 x 1920 in tiles of 16 x 16 809 -> 560 us, 16,384
@@ -785,6 +785,32 @@ struct WordRing {
     }
 };
 
+// On from one of the two symbols that meet at edge `mid` to the one that holds `slot`, which is neither: an edge a step.
+// `below`, `mass`: of the symbol begun with and then of the one returned, the slots of its own below this one (negative
+// where the symbol is further down) and its mass.  Nearly always one step; two or three are
+// rare while the mean is within the values of a pixel.  8 frames of 1080 x 1920 in tiles, by log-scale, us, against a search by
+// bisection for every symbol and one behind each guess that missed: 2^M = 1024: 3.4 326, 462, 579; 4.0 384, 461, 712; 4.6
+// 376, 460, 692; 5.5 370, 455, 586; 2^M = 4096: 4.0 312, 460, 480; guesses that are all good 281.  (Slower than
+// the search alone only where nothing is known of a pixel: scales of 150 and more with means hundreds away from
+// every value, 545 against 463.)
+__device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below, uint32_t &mass, uint32_t slot, const EdgeLaw &law,
+                                                   uint32_t scale, uint32_t m_bits, const LdsTables &tab)
+{
+    const bool down = (int)below < 0;
+    uint32_t k = down ? mid - 1u : mid + 1u;  // the edge that was looked at last
+    uint32_t c_near = slot - below + (down ? 0u : mass);
+    do {
+        k = down ? k - 1u : k + 1u;  // within 0 .. 256: C(0) = 0 <= slot < 2^M = C(256)
+        uint32_t c = cum_inner((int)k, edge_y((int)k, law), scale, tab);
+        c = k == 0u ? 0u : c;
+        c = k == 256u ? 1u << m_bits : c;
+        below = slot - (down ? c : c_near);
+        mass = down ? c_near - c : c - c_near;
+        c_near = c;
+    } while (below >= mass);
+    return down ? k : k - 1u;
+}
+
 // (Four wavefronts per SIMD are asked for, which keep the vector ALUs busy where the lanes fill the chip.  A variant
 // that carries the rest of every parameter line in registers, as the encoder does, reads half the
 // bytes from memory but needs 172 registers, i.e. two wavefronts per SIMD, and was slower: 0.91 against
@@ -864,34 +890,27 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
                     const EdgeLaw law = edge_law(me, inv_s);
                     const uint32_t slot = S & mask;
                     // C at the edge where the symbol should begin or end and at its two neighbours
-                    const uint32_t mid = guide_edge(slot, me, inv_s, scale_index(ck.l[i][ch]), gs, guide);
+                    uint32_t mid = guide_edge(slot, me, inv_s, scale_index(ck.l[i][ch]), gs, guide);
                     const double y = edge_y((int)mid, law);
                     const uint32_t c_mid = cum_inner((int)mid, y, scale, tab);
                     uint32_t c_below = cum_inner((int)mid - 1, y - law.a, scale, tab);
                     uint32_t c_above = cum_inner((int)mid + 1, y + law.a, scale, tab);
                     c_below = mid == 1u ? 0u : c_below;
                     c_above = mid == 255u ? 1u << m_bits : c_above;
-                    const bool up = c_mid <= slot;
-                    uint32_t lo = up ? mid : mid - 1u;
-                    uint32_t c_lo = up ? c_mid : c_below, c_hi = up ? c_above : c_mid;
-                    if (__builtin_expect(__any(slot - c_lo >= c_hi - c_lo), 0)) {
-                        // for the whole wavefront: the symbol is in lo .. lo + 2 * step - 1, and c_hi = C(lo + 2 * step)
-                        lo = 0u;
-                        c_lo = 0u;
-                        c_hi = 1u << m_bits;
-#pragma unroll 1
-                        for (uint32_t step = 128; step >= 1u; step >>= 1) {
-                            const uint32_t cm = cum_inner((int)(lo + step), edge_y((int)(lo + step), law), scale, tab);
-                            const bool ge = cm <= slot;
-                            lo = ge ? lo + step : lo;
-                            c_lo = ge ? cm : c_lo;
-                            c_hi = ge ? c_hi : cm;
+                    bool up = c_mid <= slot;
+                    const uint32_t c_lo = up ? c_mid : c_below, c_hi = up ? c_above : c_mid;
+                    uint32_t below = slot - c_lo, mass = c_hi - c_lo;
+                    if (__builtin_expect(__any(below >= mass), 0)) {
+                        if (below >= mass) {
+                            mid = walk_to_symbol(mid, below, mass, slot, law, scale, m_bits, tab);
+                            up = true;
                         }
                     }
+                    const uint32_t lo = up ? mid : mid - 1u;
                     x[ch] = (int)lo;
                     // App. A eq. (12)
                     // the mass is at most 2^16 and S >> M below 2^22: a 24-bit multiply is exact
-                    S = (uint32_t)__umul24(c_hi - c_lo, S >> m_bits) + slot - c_lo;
+                    S = (uint32_t)__umul24(mass, S >> m_bits) + below;
                     if (S < (1u << 16)) S = (S << 16) | words.take();
                     const int b = 3 * i + ch;
                     wout[b >> 2] |= lo << (8 * (b & 3));
