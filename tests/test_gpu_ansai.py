@@ -383,3 +383,33 @@ def test_last_pieces_of_a_batch(pieces, count):
     _, nbytes = dp.encode()
     got = dp.coded_numpy()
     assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+
+
+# One piece in sixteen with a word or two beside pieces of a thousand words: the others of its group are not held up.
+def test_short_pieces_beside_long_ones():
+    m, pieces, count = 15, 8192, 4000
+    mass = np.ones((2, 256), dtype=np.uint32)
+    mass[0] = (1 << m) // 256
+    mass[1, 7] = (1 << m) - 255
+    rng = np.random.default_rng(11)
+    took = []
+    for short in (False, True):
+        sym = rng.integers(0, 256, (pieces, count), dtype=np.uint8)
+        dist = np.zeros((pieces, count), dtype=np.uint8)
+        if short:
+            dist[5::16] = 1
+            sym[5::16] = 7
+        dp = DevicePieces(m, mass, sym, dist)
+        times = []
+        pb.pilc_set_timing(True)
+        try:
+            for _ in range(5):
+                dp.encode()
+                times.append(dict(pb.pilc_last_timing())["k_ansai_pack"])
+        finally:
+            pb.pilc_set_timing(False)
+        assert dp.decode() == pb.PILC_OK
+        assert np.array_equal(dp.decoded_numpy(), sym)
+        took.append(min(times))
+    print("pack: %.0f us, with short pieces %.0f us" % (1e3 * took[0], 1e3 * took[1]))
+    assert took[1] < 2.0 * took[0]
