@@ -497,20 +497,33 @@ static std::atomic<int> g_ansai_decode_waves{0};  // 0: chosen per call
 static std::atomic<unsigned long long> g_one_pass_wait{0};
 static std::atomic<int> g_one_pass_withhold{0};
 
+static uint32_t compute_units()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    return (uint32_t)cus;
+}
+
 // The few-lane kernels pay off while there are too few lanes to fill the chip with one thread
 // each (256 CUs x 4 SIMDs x 64 threads = 65,536 threads for a single wave per SIMD).  Measured
 // on CIFAR-shaped data cut into lanes of different lengths, the block encoder is ahead of the
 // thread-per-lane encoder up to some 43,000 lanes (1.25 against 2.02 ms at 25,000 lanes of 2048 pixels, 1.57
 // against 1.91 at 37,800 of 1920, 1.14 against 1.08 at 50,000 of 1024; 94 against 105 us at 32,000 of 64, 119 against 112 at
-// 44,800) and the row decoder up to about 6600 (8.3 against 14.7 ms at 3125
-// lanes, 6.86 against 7.41 at 6250, 8.12 against 5.56 at 8334, 6.44 against 3.74 at 12,500).  Where the model does not
-// fit, the thread-per-lane decoder is ahead earlier (uniformly random pixels, 6250 lanes: 11.2 against 7.4 ms).
+// 44,800).  The row decoder is ahead while one round of its workgroups (two on a compute unit, kRowLanes lanes each)
+// takes all lanes, and behind from the second round on, whatever the lanes' shape.  Rows against thread per lane, us: flat lanes
+// of 64, 256 and 1024 pixels: 6804 lanes 76 and 79, 238 and 249, 854 and 917; 8192 lanes 76 and 79, 241 and 252, 874 and
+// 925; 8334 lanes 102 and 79, 335 and 254, 1243 and 915; tiles of 16 x 16 and 32 x 32 at their clipped edges: 8192 lanes 248 and 277, 915
+// and 1031; 8384 lanes 358 and 277, 1345 and 1029.  Where the model does not fit, the thread-per-lane
+// decoder is ahead earlier (uniformly random pixels, 6250 lanes: 11.2 against 7.4 ms; an error of the means of 4 under
+// scales around 1, 7360 lanes of 128: 192 against 132 us), but that is not known here.
 static bool use_few_lane_kernels(const Geo &g, bool decode)
 {
     const int policy = g_kernel_policy.load(std::memory_order_relaxed);
     if (policy == 1 || policy == 3) return false;
     if (policy == 2) return true;
-    return g.lanes <= (decode ? 6656u : 40960u);
+    return g.lanes <= (decode ? 2u * compute_units() * (uint32_t)kRowLanes : 40960u);
 }
 
 thread_local char t_hip_error[256] = "";
@@ -1043,12 +1056,9 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
     op.status = status;  // (set to zero by the lane kernel unless it works in one pass)
     CallReport report(reinterpret_cast<Report *>(base + ws.report_off), stream, timed);
     if (few_lanes) {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
+        const uint32_t cus = compute_units();
         const uint32_t blocks = (uint32_t)ceil_div64(g.lanes, kEncLanes);
-        const bool wide = max_lane_symbols(g) >= (1u << 27) - 1u, few = !wide && blocks > (uint32_t)cus;
+        const bool wide = max_lane_symbols(g) >= (1u << 27) - 1u, few = !wide && blocks > cus;
         auto kern = wide ? k_encode_block<kEncMostProducers, true>
                     : few ? k_encode_block<kEncFewProducers, false> : k_encode_block<kEncMostProducers, false>;
         kern<<<blocks, enc_threads(few ? kEncFewProducers : kEncMostProducers), 0, stream>>>(
@@ -1219,12 +1229,11 @@ int pilc_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t coded_by
                                               (g.lane_a * g.lane_b) % kRowBatch == 0);
         const uint32_t nblk = (uint32_t)ceil_div64(g.lanes, kRowLanes);
         // a stager beside every decoding wavefront while one workgroup per compute unit holds all lanes
-        int dev = 0, cus = 0, khz = 0;
+        int dev = 0, khz = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-        if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0) khz = 100000;
-        const bool staged = nblk <= (uint32_t)cus;
+            hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0)
+            khz = 100000;
+        const bool staged = nblk <= compute_units();
         // the bound of the waits between a decoding wavefront and its stager, and the test switch
         const unsigned long long asked = g_one_pass_wait.load(std::memory_order_relaxed);
         const unsigned long long wait_ticks = asked ? asked : 2000ull * (unsigned long long)khz;

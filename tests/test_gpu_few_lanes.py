@@ -1,8 +1,11 @@
-"""The few-lane encoder on a lane whose words do not fit 32 bits of bytes from the first one (2^27 symbols and more)."""
+"""The few-lane kernels: a lane whose words do not fit 32 bits of bytes from the first one (2^27 symbols and more), and
+the numbers of lanes up to which they are taken."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import pilc_oracle as orc
+from paper_2206_05279_amd import binding as pb
 from paper_2206_05279_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -25,3 +28,23 @@ def test_one_lane_of_more_than_2_to_the_27_symbols():
     _, nbytes = d.encode()
     got = d.coded_numpy()
     assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+
+
+def _kernels(call):
+    pb.pilc_set_timing(True)
+    try:
+        call()
+        return [name for name, _ in pb.pilc_last_timing()]
+    finally:
+        pb.pilc_set_timing(False)
+
+
+# Rows as long as one round of workgroups (two of 16 lanes on a compute unit) takes all lanes.
+@pytest.mark.parametrize("over", [0, 1])
+def test_decoder_takes_rows_for_one_round_of_workgroups(over):
+    lanes = 32 * torch.cuda.get_device_properties(0).multi_processor_count + over
+    wl = synth.make_random_case(9, lanes, 4, 4, 12, 0, 16)
+    d = DeviceWorkload(wl)
+    d.encode()
+    assert ("k_decode_rows" in _kernels(d.decode)) == (over == 0)
+    assert np.array_equal(d.decoded_numpy(), wl.img)
