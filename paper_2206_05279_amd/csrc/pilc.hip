@@ -506,26 +506,6 @@ static uint32_t compute_units()
     return (uint32_t)cus;
 }
 
-// The few-lane kernels pay off while there are too few lanes to fill the chip with one thread
-// each (256 CUs x 4 SIMDs x 64 threads = 65,536 threads for a single wave per SIMD).  Measured
-// on CIFAR-shaped data cut into lanes of different lengths, the block encoder is ahead of the
-// thread-per-lane encoder up to some 43,000 lanes (1.25 against 2.02 ms at 25,000 lanes of 2048 pixels, 1.57
-// against 1.91 at 37,800 of 1920, 1.14 against 1.08 at 50,000 of 1024; 94 against 105 us at 32,000 of 64, 119 against 112 at
-// 44,800).  The row decoder is ahead while one round of its workgroups (two on a compute unit, kRowLanes lanes each)
-// takes all lanes, and behind from the second round on, whatever the lanes' shape.  Rows against thread per lane, us: flat lanes
-// of 64, 256 and 1024 pixels: 6804 lanes 76 and 79, 238 and 249, 854 and 917; 8192 lanes 76 and 79, 241 and 252, 874 and
-// 925; 8334 lanes 102 and 79, 335 and 254, 1243 and 915; tiles of 16 x 16 and 32 x 32 at their clipped edges: 8192 lanes 248 and 277, 915
-// and 1031; 8384 lanes 358 and 277, 1345 and 1029.  Where the model does not fit, the thread-per-lane
-// decoder is ahead earlier (uniformly random pixels, 6250 lanes: 11.2 against 7.4 ms; an error of the means of 4 under
-// scales around 1, 7360 lanes of 128: 192 against 132 us), but that is not known here.
-static bool use_few_lane_kernels(const Geo &g, bool decode)
-{
-    const int policy = g_kernel_policy.load(std::memory_order_relaxed);
-    if (policy == 1 || policy == 3) return false;
-    if (policy == 2) return true;
-    return g.lanes <= (decode ? 2u * compute_units() * (uint32_t)kRowLanes : 40960u);
-}
-
 thread_local char t_hip_error[256] = "";
 thread_local float t_timing_ms[16];
 thread_local const char *t_timing_name[16];
@@ -890,6 +870,44 @@ static bool lanes_line_up(const Geo &g, const pilc_params *p)
            ((uintptr_t)p->mu & 127) == 0 && ((uintptr_t)p->log_scale & 127) == 0;
 }
 
+// The few-lane kernels pay off while there are too few lanes to fill the chip with one thread
+// each (256 CUs x 4 SIMDs x 64 threads = 65,536 threads for a single wave per SIMD).
+// Encoder: by then the block encoder's time goes with the number of pixels and the other's with a lane's chunks, so where they meet
+// depends on what a chunk costs there.  Block against thread per lane, us:
+//   lanes of whole lines (1.25 against 2.02 ms at 25,000 lanes of 2048 pixels, 1.57 and 1.91 at 37,800 of 1920, 1.14 and
+//   1.08 at 50,000 of 1024; 40,960 of 64 106 and 104, of 128 161 and 165, of 256 254 and 284) and rows that do not align
+//   (tiles of 16 x 16 at 40,960 lanes 241 and 250, of 10 x 10 0.89, flat lanes of 72 1.05) near 40,960, in tiles of at
+//   most 64 pixels earlier (8 x 8: 34,816 96 and 94, 40,960 104 and 95);
+//   other aligned rows, whose lines neighbouring lanes share, near 32,768 (tiles of 16 x 16: 30,720 200 and 206,
+//   32,768 208 and 212, 34,816 217 and 207, 40,960 241 and 208; of 8 x 16 30,720 127 and 124, 40,960 153 and 126; of 32 x
+//   32 at 40,960 850 and 735; flat lanes of 96 at 32,768 0.99, 40,960 1.14; latest tiles of 8 x 24, near 38,000);
+//   lanes of some 40 pixels and fewer below 28,672 (of 32: 26,000 62 and 57, 40,960 76 and 64).
+static bool use_few_lane_encoder(const Geo &g, bool aligned, bool lines)
+{
+    const int policy = g_kernel_policy.load(std::memory_order_relaxed);
+    if (policy == 1 || policy == 3) return false;
+    if (policy == 2) return true;
+    const uint32_t pixels = max_lane_symbols(g) / 3u;
+    if (pixels <= 40u) return g.lanes <= 28672u;
+    if (aligned && !lines) return g.lanes <= 32768u;
+    return g.lanes <= (aligned || pixels > 64u ? 40960u : 36864u);
+}
+
+// Decoder: the rows are ahead while one round of their workgroups (two on a compute unit, kRowLanes lanes each) takes
+// all lanes, and behind from the second round on, whatever the lanes' shape.  Rows against thread per lane, us: flat lanes of
+// 64, 256 and 1024 pixels: 6804 lanes 76 and 79, 238 and 249, 854 and 917; 8192 lanes 76 and 79, 241 and 252, 874 and 925;
+// 8334 lanes 102 and 79, 335 and 254, 1243 and 915; tiles of 16 x 16 and 32 x 32 at their clipped edges: 8192 lanes
+// 248 and 277, 915 and 1031; 8384 lanes 358 and 277, 1345 and 1029.  Where the model does not fit, the thread-per-lane
+// decoder is ahead earlier (uniformly random pixels, 6250 lanes: 11.2 against 7.4 ms; an error of the means of 4 under
+// scales around 1, 7360 lanes of 128: 192 against 132 us), but that is not known here.
+static bool use_few_lane_decoder(const Geo &g)
+{
+    const int policy = g_kernel_policy.load(std::memory_order_relaxed);
+    if (policy == 1 || policy == 3) return false;
+    if (policy == 2) return true;
+    return g.lanes <= 2u * compute_units() * (uint32_t)kRowLanes;
+}
+
 // Launches the scan of the items' bytes; true if it has also formed the offset table.
 static bool launch_scan(const HeaderWords &head, uint32_t items, uint32_t blocks, const ItemBytes &bytes, const uint32_t *counts,
                         unsigned long long *sums, uint8_t *coded, size_t capacity, Status *status, Report *report,
@@ -1025,7 +1043,10 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
     uint16_t *payload = reinterpret_cast<uint16_t *>(coded_dev + table_end);
 
     Timer timer(stream, timed);
-    const bool few_lanes = use_few_lane_kernels(g, false);
+    const bool vec = chunks_aligned(g, img_dev, params);
+    const bool pair = vec && chunks_pair_up(g, img_dev);
+    const bool line = pair && lanes_line_up(g, params);
+    const bool few_lanes = use_few_lane_encoder(g, vec, line);
     const uint32_t lane_cap = few_lanes ? 0u : max_lane_symbols(g);  // selects the scratch layout
     const HeaderWords head = {{kMagicPilc, PILC_VERSION, g.n, g.h, g.w, 3u, g.prec_bits,
                                g.lane_mode, g.lane_a, g.lane_b, g.lanes, 0u}};
@@ -1076,9 +1097,6 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
             const uint32_t resident = (uint32_t)cus * (uint32_t)(1024 / bt);
             if (nb > resident) nb = resident;
         }
-        const bool vec = chunks_aligned(g, img_dev, params);
-        const bool pair = vec && chunks_pair_up(g, img_dev);
-        const bool line = pair && lanes_line_up(g, params);
 #define PILC_LAUNCH_ENCODE(ONE, VEC, PAIR, LINE)                                                      \
     k_encode_lanes<ONE, VEC, PAIR, LINE><<<nb, bt, 0, stream>>>(g, img_dev, params->mu, params->log_scale, \
                                                                params->chan_coef, scratch, lane_cap,  \
@@ -1221,7 +1239,7 @@ int pilc_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t coded_by
     CallReport report(reinterpret_cast<Report *>(static_cast<uint8_t *>(workspace_dev) + ws.report_off), stream, true);
 
     Timer timer(stream);
-    const bool few_lanes = use_few_lane_kernels(g, true);
+    const bool few_lanes = use_few_lane_decoder(g);
     if (few_lanes) {
         // all lanes alike and made of whole batches of 16 pixels: no per-row activity masks
         const bool even = g.lane_mode == 0 ? (g.lane_a % kRowBatch == 0 && g.total_px % g.lane_a == 0)

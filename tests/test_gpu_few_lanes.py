@@ -48,3 +48,20 @@ def test_decoder_takes_rows_for_one_round_of_workgroups(over):
     d.encode()
     assert ("k_decode_rows" in _kernels(d.decode)) == (over == 0)
     assert np.array_equal(d.decoded_numpy(), wl.img)
+
+
+# The encoder's line by what a chunk of the lanes costs thread per lane: aligned tiles, tiles whose rows are not, flat
+# lanes of whole lines, tiny lanes.  The container is the oracle's on both sides of it.
+@pytest.mark.parametrize("h,w,mode,a,b,line", [
+    (256, 256, 1, 16, 16, 32768), (256, 250, 1, 16, 16, 40960), (64, 61, 1, 8, 8, 36864),
+    (32, 32, 0, 64, 0, 40960), (16, 16, 0, 32, 0, 28672)])
+def test_encoder_takes_blocks_up_to_its_line(h, w, mode, a, b, line):
+    per_image = -(-h // a) * -(-w // b) if mode else h * w // a
+    for n in (line // per_image, line // per_image + 1):
+        wl = synth.make_random_case(n, n, h, w, 12, mode, a, b) if mode else synth.make_random_case(n, n, h, w, 12, mode, a)
+        rc, want = orc.encode(orc.make_geom(*wl.geom), wl.img, wl.mu, wl.log_scale, wl.chan_coef)
+        assert rc == orc.OK
+        d = DeviceWorkload(wl)
+        assert ("k_encode_block" in _kernels(d.encode)) == (n * per_image <= line)
+        got = d.coded_numpy()
+        assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
