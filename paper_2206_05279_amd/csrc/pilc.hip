@@ -17,6 +17,7 @@
 #include <atomic>
 #include <map>
 #include <mutex>
+#include <optional>
 #include <utility>
 
 #include "../../include/pilc.h"
@@ -1075,7 +1076,8 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
         k_init_one_pass<<<(nb + 255u) / 256u, 256, 0, stream>>>(status, op.desc, nb);
     }
     op.status = status;  // (set to zero by the lane kernel unless it works in one pass)
-    CallReport report(reinterpret_cast<Report *>(base + ws.report_off), stream, timed);
+    std::optional<CallReport> report;  // (in one pass the outcome is in `status`)
+    if (!one_pass) report.emplace(reinterpret_cast<Report *>(base + ws.report_off), stream, timed);
     if (few_lanes) {
         const uint32_t cus = compute_units();
         const uint32_t blocks = (uint32_t)ceil_div64(g.lanes, kEncLanes);
@@ -1117,7 +1119,7 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
     timer.mark(few_lanes ? "k_encode_block" : "k_encode_lanes");
     if (!one_pass) {
         const bool formed = launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev, coded_capacity,
-                                        status, report.dev(), offsets, false, stream);
+                                        status, report->dev(), offsets, false, stream);
         timer.mark("scan");
         // a run of lanes per workgroup: about 16K symbols' worth, at most 256 lanes; of a small batch less, so that
         // there are kPackBlocks workgroups, but not less than kPackLeast symbols (64 images of 32 x 32 in
@@ -1146,7 +1148,7 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
         return PILC_OK;
     }
     Report seen;
-    HIP_TRY(report.wait(&seen));
+    HIP_TRY(report->wait(&seen));
     timer.finish();
     if (raised_code(seen) != ST_OK) return status_to_error(raised_code(seen));
     *coded_bytes_host = table_end + seen.payload_bytes;
