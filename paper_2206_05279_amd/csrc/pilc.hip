@@ -718,6 +718,7 @@ public:
             memset(host_, 0, sizeof(Report));
             dev_ = static_cast<Report *>(seen);
         } else {
+            if (host_) (void)hipGetLastError();  // (else the look at the launches would find it and fail the call)
             give_back();
             k_clear_report<<<1, 64, 0, stream_>>>(dev_);
         }
