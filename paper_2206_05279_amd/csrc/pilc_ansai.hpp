@@ -531,13 +531,16 @@ __global__ __launch_bounds__(64 * kAnsaiEncWaves) void k_ansai_encode(
 // ---------------------------------------------------------------------------------------------
 constexpr int kAnsaiPackWaves = 4;
 constexpr int kAnsaiPackTogether = 16;  // pieces whose loads are under way together
+constexpr uint32_t kAnsaiPackFewWords = 32;  // a group of pieces of at most so many goes a word a thread
 
 // Bound by memory.  A wavefront copies 64 pieces, sixteen at a time, sixteen bytes a thread; the last sixteen of a
 // piece overlap those before them, so that nothing is read or written beyond its words.  The stores are
 // non-temporal: what they would push out of the caches is still to be read.  Pieces of fewer than four words go a word a
 // thread, and a group that has some keeps the sixteen bytes for its others.  Whole calls with one such piece in sixteen, us,
 // against a group that went a word a thread altogether: 65,536 pieces of 4000 symbols 779 -> 469 (without short ones 474),
-// 10^5 of 1000 275 -> 211 (213).
+// 10^5 of 1000 275 -> 211 (213).  A group of pieces of at most 32 words goes a word a thread altogether, four threads a
+// piece: sixteen bytes a thread leave most threads without any.  The packer alone, us, words against sixteen bytes: 400,000 pieces of 4
+// words 13 and 36, of 8 17 and 39, 262,144 of 16 18 and 30, 167,772 of 25 20 and 22, 131,072 of 32 17.8 and 18.2, 104,857 of 40 20.9 and 17.7.
 __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
     AShape sh, const uint32_t *__restrict__ scratch, uint32_t stride,
     const uint32_t *__restrict__ piece_bits, const uint32_t *__restrict__ piece_state,
@@ -570,12 +573,13 @@ __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
             least = min(least, n[i]);
         }
         const uint32_t *src = scratch + (size_t)(p0 + i0) * stride;
-        if (least < 4u) {
+        if (least < 4u || most <= kAnsaiPackFewWords) {
             static_assert(kAnsaiPackTogether == 16, "four threads a piece");
             const uint32_t i = lane >> 2, j = lane & 3u;
             const uint32_t ni = (uint32_t)__shfl((int)nw, (int)(i0 + i), 64), ti = (uint32_t)__shfl((int)dst, (int)(i0 + i), 64);
-            if (ni < 4u && j < ni) payload[ti + j] = src[(size_t)i * stride + j];
-            if (most < 4u) continue;
+            const uint32_t by_words = most <= kAnsaiPackFewWords ? ni : (ni < 4u ? ni : 0u);
+            for (uint32_t k = j; k < by_words; k += 4u) payload[ti + k] = src[(size_t)i * stride + k];
+            if (most <= kAnsaiPackFewWords) continue;
         }
 #pragma unroll 1
         for (uint32_t j0 = 0; j0 < most; j0 += 256u) {

@@ -385,6 +385,22 @@ def test_last_pieces_of_a_batch(pieces, count):
     assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
 
 
+def _pack_time(m, mass, sym, dist):
+    """Fastest of some launches of the packer, in microseconds; what was packed decodes."""
+    dp = DevicePieces(m, mass, sym, dist)
+    times = []
+    pb.pilc_set_timing(True)
+    try:
+        for _ in range(5):
+            dp.encode()
+            times.append(1e3 * dict(pb.pilc_last_timing())["k_ansai_pack"])
+    finally:
+        pb.pilc_set_timing(False)
+    assert dp.decode() == pb.PILC_OK
+    assert np.array_equal(dp.decoded_numpy(), sym)
+    return min(times)
+
+
 # One piece in sixteen with a word or two beside pieces of a thousand words: the others of its group are not held up.
 def test_short_pieces_beside_long_ones():
     m, pieces, count = 15, 8192, 4000
@@ -399,17 +415,18 @@ def test_short_pieces_beside_long_ones():
         if short:
             dist[5::16] = 1
             sym[5::16] = 7
-        dp = DevicePieces(m, mass, sym, dist)
-        times = []
-        pb.pilc_set_timing(True)
-        try:
-            for _ in range(5):
-                dp.encode()
-                times.append(dict(pb.pilc_last_timing())["k_ansai_pack"])
-        finally:
-            pb.pilc_set_timing(False)
-        assert dp.decode() == pb.PILC_OK
-        assert np.array_equal(dp.decoded_numpy(), sym)
-        took.append(min(times))
-    print("pack: %.0f us, with short pieces %.0f us" % (1e3 * took[0], 1e3 * took[1]))
+        took.append(_pack_time(m, mass, sym, dist))
+    print("pack: %.0f us, with short pieces %.0f us" % tuple(took))
     assert took[1] < 2.0 * took[0]
+
+
+# Pieces of four words, which are long enough for sixteen bytes a thread, take about what pieces of three words take.
+def test_pieces_of_few_words():
+    rng = np.random.default_rng(12)
+    mass = np.full((1, 256), 16, dtype=np.uint32)
+    took = []
+    for count in (12, 16):
+        sym = rng.integers(0, 256, (400000, count), dtype=np.uint8)
+        took.append(_pack_time(12, mass, sym, np.zeros_like(sym)))
+    print("pack: %.0f us for three words, %.0f us for four" % tuple(took))
+    assert took[1] < 1.7 * took[0]
