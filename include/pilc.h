@@ -11,7 +11,7 @@
  *   - All `*_dev` pointers and the pointers inside pilc_params are DEVICE memory owned by
  *     the caller; pilc_geom, pilc_params and `*_host` pointers are HOST memory.
  *   - The library never allocates or frees device memory on behalf of a call: images,
- *     parameters, workspace and output are caller-owned.  (Three small constant tables
+ *     parameters, workspace and output are caller-owned.  (Four small constant tables
  *     live in the library's own device globals and are filled on first use per device.)
  *   - Work is enqueued on `hip_stream` (a hipStream_t passed as void*, NULL = default
  *     stream).  Every call synchronises that stream before it returns, so the status and

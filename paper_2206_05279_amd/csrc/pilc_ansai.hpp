@@ -280,7 +280,8 @@ __device__ __forceinline__ uint32_t lines_check(uint4 (&v)[8], const ByteLimit &
 // ---------------------------------------------------------------------------------------------
 // Encode (Alg. 3), symbols of a piece taken last-first
 // ---------------------------------------------------------------------------------------------
-constexpr int kAnsaiEncWaves = 4;      // wavefronts of a workgroup at most; three such workgroups fit a compute unit
+constexpr int kAnsaiEncWaves = 4;      // wavefronts of a workgroup at most; with the tables of up to nine laws three such workgroups fit a compute unit
+                                       // (53,264 bytes of LDS each), with those of ten to twelve two
 constexpr uint32_t kEncPart = 32;       // positions of a row in LDS at a time
 constexpr uint32_t kEncRow = 16;        // LDS dwords of a row: their symbols and their indices
 constexpr uint32_t kEncBlock = 8;       // words that leave together, to 32 bytes that start on a multiple of 32
@@ -439,7 +440,7 @@ __device__ __forceinline__ void enc_part(EncLane &L, EncOut &out, const uint2 *t
 }
 
 // Bound by LDS (a table entry of 64 threads at once is a gather), by the vector instructions of a symbol, 17 of them, and
-// by the places its words are stored to, with three wavefronts on a SIMD.  10^6 pieces of 1000 symbols under eight laws:
+// by the places its words are stored to, with three wavefronts on a SIMD (up to nine laws; see kAnsaiEncWaves).  10^6 pieces of 1000 symbols under eight laws:
 // 1318 -> 965 us, of 64 x 100,000 9.6 -> 6.9 ms.  (Before, a step of a symbol kept the bits not yet
 // written in 64 bits of its own, indices were put together by the threads that loaded them, and every position of
 // the first and last lines of a row was masked there: 32 instructions a symbol and 189 registers, two wavefronts.)
