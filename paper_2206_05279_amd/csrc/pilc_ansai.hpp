@@ -582,22 +582,27 @@ __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
             for (uint32_t k = j; k < by_words; k += 4u) payload[ti + k] = src[(size_t)i * stride + k];
             if (most <= kAnsaiPackFewWords) continue;
         }
+        // `some`: in the place of a piece that does not go this way the longest is read, and not stored
+        auto copy = [&](auto some) __attribute__((always_inline)) {
 #pragma unroll 1
-        for (uint32_t j0 = 0; j0 < most; j0 += 256u) {
-            const uint32_t j = j0 + 4u * lane;
-            u32x4 v[kAnsaiPackTogether];
+            for (uint32_t j0 = 0; j0 < most; j0 += 256u) {
+                const uint32_t j = j0 + 4u * lane;
+                u32x4 v[kAnsaiPackTogether];
 #pragma unroll
-            for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i) {
-                // a thread with nothing to move reads the piece's end; in the place of a piece that does not go this way the
-                // longest is read, and not stored
-                const bool goes = n[i] >= 4u;
-                v[i] = *reinterpret_cast<const u32x4_dword *>(src + (size_t)(goes ? i : longest) * stride + min(j, (goes ? n[i] : most) - 4u));
+                for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i) {  // (a thread with nothing to move reads the piece's end)
+                    const bool goes = !some || n[i] >= 4u;
+                    v[i] = *reinterpret_cast<const u32x4_dword *>(src + (size_t)(goes ? i : longest) * stride + min(j, (goes ? n[i] : most) - 4u));
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i)
+                    if ((!some || n[i] >= 4u) && j < n[i])
+                        __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4_dword *>(payload + to[i] + min(j, n[i] - 4u)));
             }
-#pragma unroll
-            for (uint32_t i = 0; i < (uint32_t)kAnsaiPackTogether; ++i)
-                if (n[i] >= 4u && j < n[i])
-                    __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4_dword *>(payload + to[i] + min(j, n[i] - 4u)));
-        }
+        };
+        if (least >= 4u)
+            copy(std::false_type());
+        else
+            copy(std::true_type());
     }
 }
 
