@@ -1082,11 +1082,14 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
     if (few_lanes) {
         const uint32_t cus = compute_units();
         const uint32_t blocks = (uint32_t)ceil_div64(g.lanes, kEncLanes);
-        const bool wide = max_lane_symbols(g) >= (1u << 27) - 1u, few = !wide && blocks > cus;
-        auto kern = wide ? k_encode_block<kEncMostProducers, true>
-                    : few ? k_encode_block<kEncFewProducers, false> : k_encode_block<kEncMostProducers, false>;
-        kern<<<blocks, enc_threads(few ? kEncFewProducers : kEncMostProducers), 0, stream>>>(
-            g, img_dev, params->mu, params->log_scale, params->chan_coef, scratch, lane_words, lane_state, status);
+        auto launch = [&](auto producers) {
+            constexpr int kProducers = decltype(producers)::value;
+            k_encode_block<kProducers><<<blocks, enc_threads(kProducers), 0, stream>>>(
+                g, img_dev, params->mu, params->log_scale, params->chan_coef, scratch, lane_words, lane_state, status);
+        };
+        if (blocks <= cus) launch(std::integral_constant<int, kEncAloneProducers>{});
+        else if (blocks <= 2u * cus) launch(std::integral_constant<int, kEncPairProducers>{});
+        else launch(std::integral_constant<int, kEncManyProducers>{});
     } else {
         const int bt = lane_block_threads(g);
         uint32_t nb = (uint32_t)ceil_div64(g.lanes, bt);

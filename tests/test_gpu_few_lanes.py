@@ -65,3 +65,23 @@ def test_encoder_takes_blocks_up_to_its_line(h, w, mode, a, b, line):
         assert ("k_encode_block" in _kernels(d.encode)) == (n * per_image <= line)
         got = d.coded_numpy()
         assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+
+
+# Batches of 20, 12 and 8 pixels (one workgroup on a compute unit, two, more): lanes of one pixel, of one less and more than
+# a batch, of several; masses from 1 to 2^M - 255, states at both ends of what a mass renormalises.
+@pytest.mark.parametrize("prec_bits", [10, 16])
+@pytest.mark.parametrize("wild", [False, True])
+@pytest.mark.parametrize("groups,pixels", [(0, (1, 19, 20, 21, 61)), (1, (1, 11, 12, 13, 37)), (2, (1, 7, 8, 9, 25))])
+def test_block_encoder_at_the_edges_of_its_batches(groups, pixels, wild, prec_bits):
+    lanes = 16 * groups * torch.cuda.get_device_properties(0).multi_processor_count + 35
+    for px in pixels:
+        wl = synth.make_random_case(prec_bits + px, lanes, 1, px, prec_bits, 0, px, wild=wild)
+        if not wild:
+            wl.log_scale[: lanes // 2] = -16384  # the narrowest law, at the pixel or off it
+            wl.mu[: lanes // 4] = wl.img[: lanes // 4].astype(np.uint16) * 256
+        rc, want = orc.encode(orc.make_geom(*wl.geom), wl.img, wl.mu, wl.log_scale, wl.chan_coef)
+        assert rc == orc.OK
+        d = DeviceWorkload(wl)
+        assert "k_encode_block" in _kernels(d.encode)
+        got = d.coded_numpy()
+        assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
