@@ -887,6 +887,7 @@ static bool lanes_line_up(const Geo &g, const pilc_params *p)
 static bool use_few_lane_encoder(const Geo &g, bool aligned, bool lines)
 {
     const int policy = g_kernel_policy.load(std::memory_order_relaxed);
+    if (max_lane_symbols(g) > kLaneMostSymbols) return true;  // (the other's words would be out of its reach)
     if (policy == 1 || policy == 3) return false;
     if (policy == 2) return true;
     const uint32_t pixels = max_lane_symbols(g) / 3u;

@@ -222,6 +222,21 @@ __device__ __forceinline__ EdgeLaw edge_law(int mu_eff, uint32_t inv_s)
 }
 __device__ __forceinline__ double edge_y(int k, const EdgeLaw &l) { return __builtin_fma((double)k, l.a, l.b); }
 
+// The positions of the two edges of a value: y(x) from d = 256 x - 128 - mu' and y(x + 1).  One conversion and two
+// multiply-adds; times 2^-6 is an addition to the exponent (inv_s is never 0), which issues in half a multiplication's time.
+struct EdgePair {
+    double lo, hi;
+};
+__device__ __forceinline__ EdgePair edge_pair(int d, uint32_t inv_s)
+{
+    const double inv = (double)inv_s;
+    const double unit = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, inv) - (6ull << 52));
+    EdgePair p;
+    p.lo = __builtin_fma((double)d, unit, kEdgeBias);
+    p.hi = __builtin_fma(4.0, inv, p.lo);
+    return p;
+}
+
 __device__ __forceinline__ uint32_t edge_cdf(int d, uint32_t inv_s, const LdsTables &t)
 {
     return edge_at(__builtin_fma((double)d, (double)inv_s * 0x1p-6, kEdgeBias), t);

@@ -215,25 +215,18 @@ __device__ __forceinline__ void feed_pair(ChunkPair &r, LineCarry &c, uint32_t v
     }
 }
 
-// floor(n / f) and the remainder for f <= 2^16 and n / f < 2^(32-M) (true after the
-// renormalisation of the encoder), given rf = 1/f to float accuracy.  Conversion, reciprocal and
-// product are each within 2^-24, 2^-23 and 2^-24 of exact, so scaling the estimate by 1 - 2^-21
-// keeps it at or below n / f and within 3.25 * 2^-22 of it: the truncated estimate is the
-// quotient or, for quotients below 2^20 (M >= 12), one less; for M = 10 and 11 up to four less
-// (`more_fixups`, the same for every thread of the launch).
-__device__ __forceinline__ uint32_t div_small(uint32_t n, uint32_t f, float rf, bool more_fixups,
-                                              uint32_t &rem)
+// A little more than 1 / f, for floor(S / f) of a state S < 2^32 as the low word of a double: S r + 2^52 - 1/2 rounded to
+// the nearest whole number is 2^52 + floor(S r) (S r is never whole, and S >= f), and that is the quotient while r lies in
+// 1/f .. (1 + 2^-33) / f.  One step of Newton's towards (1 + 2^-35) / f takes the single-precision reciprocal's error of 2^-22
+// to 2^-44.
+__device__ __forceinline__ double over_reciprocal(uint32_t f)
 {
-    uint32_t q = (uint32_t)(((float)n * rf) * 0.999999523162841796875f);
-    uint32_t r = n - (uint32_t)__umul24(q, f);  // q < 2^22 and f < 2^24; q * f <= n
-    if (more_fixups) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            if (r >= f) { r -= f; q += 1u; }
-    }
-    if (r >= f) { r -= f; q += 1u; }
-    rem = r;
-    return q;
+    const double r0 = (double)__builtin_amdgcn_rcpf((float)f);
+    return __builtin_fma(r0, __builtin_fma(-(double)f, r0, 1.0 + 0x1p-35), r0);
+}
+__device__ __forceinline__ uint32_t quotient(uint32_t n, double r)
+{
+    return (uint32_t)__builtin_bit_cast(unsigned long long, __builtin_fma((double)n, r, 0x1p52 - 0.5));
 }
 
 // Chunk c of a lane: rows of sh.tw pixels, g.w apart, each cut into pieces of 8 pixels.
@@ -258,6 +251,7 @@ __device__ __forceinline__ ChunkPos chunk_pos(const Geo &g, const LaneShape &sh,
 // touched.  `lane_cap` is the room every lane has (words); the packer reads a lane's words back
 // from the highest number down.
 // --------------------------------------------------------------------------------------------
+constexpr uint32_t kLaneMostSymbols = (1u << 25) - 1u;  // of a lane: 64 lanes' words are placed by 32 bits of bytes
 __device__ __forceinline__ size_t lane_scratch_base(uint32_t lane, uint32_t lane_cap)
 {
     return (size_t)(lane & ~63u) * lane_cap + (lane & 63u);
@@ -282,25 +276,31 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
     const uint32_t per_row = (sh.tw + kChunk - 1) / kChunk;
     const uint32_t chunks = per_row * (sh.npx / sh.tw);
 
-    uint16_t *wout = scratch + lane_scratch_base(lane, lane_cap);  // the lane's next word
-    uint32_t nwords = 0;
+    // the wavefront's columns, and the place of the lane's next word in them in bytes (below 2^32: kLaneMostSymbols)
+    char *columns = reinterpret_cast<char *>(scratch + (size_t)__builtin_amdgcn_readfirstlane(lane & ~63u) * lane_cap);
+    const uint32_t first_word = 2u * (lane & 63u);
+    uint32_t next_word = first_word;
     uint32_t S = 1u << 16;
 
-    const bool more_fixups = m_bits < 12u;
-
-    auto encode_chunk = [&](const Chunk &ck, const ChunkPos cp) {
+    // whole: a compile-time constant, no thread's chunk is a shorter one
+    auto encode_chunk = [&](const Chunk &ck, const ChunkPos cp, auto whole) {
         // a chunk never straddles two images when kVec; otherwise take the image per pixel
         uint32_t im = g.by_hw.div(cp.p);
         int a_gr = coef[3 * im], a_br = coef[3 * im + 1], a_bg = coef[3 * im + 2];
-        // The chunk in two halves of four pixels, the later half first.  Phase 1 of a half:
-        // (cum | freq << 16) of its 12 symbols; nothing there depends on the state, so the
-        // evaluations overlap freely.  Phase 2: the serial chain (App. A eq. (11)), last symbol
-        // first.  (Halves, and 1/freq formed in phase 2, keep the registers of the whole-line
-        // variant at three wavefronts per SIMD.)
-        constexpr int kHalf = kChunk / 2;
+        // The chunk in parts of four pixels (two in the whole-line variant, which has no registers for more), the last
+        // part first.  Phase 1 of a part: cum and freq of its symbols; nothing there depends on the state, so the
+        // evaluations overlap freely.  Phase 2: the serial chain (App. A eq. (11)), last symbol first.  What bounds the
+        // kernel is vector instructions (56 a symbol, 65 before), the waits for the tables and the stores of words.
+        // The quotient is exact at the first go (quotient above), where a single-precision estimate took a
+        // remainder and a correction; an edge takes one conversion less (edge_pair).  Whole calls, us, before and
+        // now: 16,384 images of 64 x 64 with a lane a row 640 and 587, 1024 of 256 x 256 700 and 606, 30 frames of 1080 x 1920 in
+        // tiles of 16 x 16 535 and 503, 8 images of 1365 x 2047 in the same 358 and 315.  A store in every step, of a word that
+        // is written over if it does not count, leaves no branch in a part but costs more than the branches: 689,
+        // 749, 580 and 328.
+        constexpr int kHalf = kLine ? kChunk / 4 : kChunk / 2;
 #pragma unroll
-        for (int hb = 1; hb >= 0; --hb) {
-            uint32_t cf[3 * kHalf];
+        for (int hb = kChunk / kHalf - 1; hb >= 0; --hb) {
+            uint32_t cum[3 * kHalf], freq[3 * kHalf];
 #pragma unroll
             for (int ii = 0; ii < kHalf; ++ii) {
                 const int i = kHalf * hb + ii;
@@ -311,46 +311,41 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
                         a_gr = coef[3 * im]; a_br = coef[3 * im + 1]; a_bg = coef[3 * im + 2];
                     }
                 }
+                // 256 x - mean of the three channels, from the last two what the channels before them say
                 const int e_r = ck.x[i][0] * 256 - ck.m[i][0], e_g = ck.x[i][1] * 256 - ck.m[i][1];
-                const int me[3] = {ck.m[i][0], ck.m[i][1] + rsh14_mul(a_gr, e_r),
-                                   ck.m[i][2] + rsh14_mul(a_br, e_r) + rsh14_mul(a_bg, e_g)};
+                const int e[3] = {e_r, e_g - rsh14_mul(a_gr, e_r),
+                                  ck.x[i][2] * 256 - ck.m[i][2] - rsh14_mul(a_br, e_r) - rsh14_mul(a_bg, e_g)};
 #pragma unroll
                 for (int ch = 0; ch < 3; ++ch) {
                     const int x = ck.x[i][ch];
-                    const EdgeLaw law = edge_law(me[ch], inv_scale(ck.l[i][ch], tab));
-                    const double y = edge_y(x, law);
-                    uint32_t lo, hi;
-                    if (kLine) {
-                        lo = x == 0 ? 0u : cum_inner(x, y, scale, tab);
-                        hi = x == 255 ? top : cum_inner(x + 1, y + law.a, scale, tab);
-                    } else {
-                        // both edges always, so that no branch keeps the evaluations of the half apart (the
-                        // compiler would skip the one that is not needed): 0.48 -> 0.45 ms on 30 frames of
-                        // 1080 x 1920 in tiles, 0.66 -> 0.62 ms on 8 of 1365 x 2047; the whole-line variant
-                        // has no registers left for it (it spills)
-                        lo = cum_inner(x, y, scale, tab);
-                        hi = cum_inner(x + 1, y + law.a, scale, tab);
-                        asm("" : "+v"(lo), "+v"(hi));
-                        lo = x == 0 ? 0u : lo;
-                        hi = x == 255 ? top : hi;
-                    }
-                    cf[3 * ii + ch] = lo | ((hi - lo) << 16);  // cum < 2^16, freq <= 2^16 - 255
+                    const EdgePair y = edge_pair(e[ch] - 128, inv_scale(ck.l[i][ch], tab));
+                    // both edges always, so that no branch keeps the evaluations of the half apart (the
+                    // compiler would skip the one that is not needed): 0.48 -> 0.45 ms on 30 frames of
+                    // 1080 x 1920 in tiles
+                    uint32_t lo = cum_inner(x, y.lo, scale, tab);
+                    uint32_t hi = cum_inner(x + 1, y.hi, scale, tab);
+                    asm("" : "+v"(lo), "+v"(hi));
+                    lo = x == 0 ? 0u : lo;
+                    hi = x == 255 ? top : hi;
+                    cum[3 * ii + ch] = lo;
+                    freq[3 * ii + ch] = hi - lo;
                 }
             }
 #pragma unroll
             for (int kk = 3 * kHalf - 1; kk >= 0; --kk) {
-                if ((uint32_t)(3 * kHalf * hb + kk) < 3u * cp.len) {
-                    const uint32_t f = cf[kk] >> 16, lo = cf[kk] & 0xFFFFu;
-                    if (S >= (f << (32u - m_bits))) {
-                        *wout = (uint16_t)(S & 0xFFFFu);
-                        wout += 64;
-                        ++nwords;
-                        S >>= 16;
-                    }
-                    uint32_t rem;
-                    const uint32_t q = div_small(S, f, __builtin_amdgcn_rcpf((float)f), more_fixups, rem);
-                    S = (q << m_bits) + rem + lo;
-                }
+                const uint32_t f = freq[kk];
+                const bool coded = decltype(whole)::value || (uint32_t)(3 * kHalf * hb + kk) < 3u * cp.len;
+                // S >= f << (32-M) gives its low word off
+                const uint32_t high = S >> 16;
+                const bool gives = high >= f << (16u - m_bits);
+                if (coded && gives) *reinterpret_cast<uint16_t *>(columns + next_word) = (uint16_t)S;
+                next_word += (coded && gives) ? 128u : 0u;
+                const uint32_t s = gives ? high : S;
+                uint32_t with_cum = s + cum[kk];
+                asm("" : "+v"(with_cum));  // (the multiply-add below takes it whole)
+                // (q << M) + (s - q f) + cum
+                const uint32_t next = (uint32_t)__umul24(quotient(s, over_reciprocal(f)), top - f) + with_cum;
+                S = coded ? next : S;
             }
         }
     };
@@ -374,7 +369,7 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
                 ChunkPos cp;
                 cp.p = left.p + (uint32_t)(kChunk * kH);
                 cp.len = (uint32_t)kChunk;
-                encode_chunk(ck, cp);
+                encode_chunk(ck, cp, std::true_type{});
             };
             half(std::integral_constant<int, 1>{});
             half(std::integral_constant<int, 0>{});
@@ -384,11 +379,14 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
             const ChunkPos cp = chunk_pos(g, sh, per_row, c);
             Chunk ck;
             load_chunk<kVec, true>(ck, cp.p, cp.len, g.total_px, img, mu, ls);
-            encode_chunk(ck, cp);
+            if (__all(cp.len == (uint32_t)kChunk))
+                encode_chunk(ck, cp, std::true_type{});
+            else
+                encode_chunk(ck, cp, std::false_type{});
         }
     }
     state_out = S;
-    return nwords;
+    return (next_word - first_word) >> 7;
 }
 
 // --------------------------------------------------------------------------------------------

@@ -456,9 +456,7 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
                 ++nwords;
                 S >>= 16;
             }
-            uint32_t rem;
-            const uint32_t q = div_small(S, f, __builtin_amdgcn_rcpf((float)f), m_bits < 12u, rem);
-            S = (q << m_bits) + rem + lo;
+            S = (uint32_t)__umul24(quotient(S, over_reciprocal(f)), top - f) + (S + lo);
         }
     }
     if (!ok) atomicMax(status_code, 7);

@@ -92,3 +92,38 @@ def test_wide_laws_decode_without_a_search(log_scale):
         times.append(min(took))
     print("log-scale %.1f: %.0f us, 2.0: %.0f us" % (log_scale, 1e3 * times[1], 1e3 * times[0]))
     assert times[1] < 1.8 * times[0]
+
+
+# The division of the encoder's step: every mass from 1 up to the largest, at the precisions where quotients are smallest and
+# largest.  With the narrowest law and the mean on the pixel a symbol has nearly all of the mass, off it a single count.
+@pytest.mark.parametrize("prec_bits", [10, 11, 12, 16])
+def test_division_from_the_smallest_to_the_largest_mass(prec_bits):
+    wl = synth.make_random_case(prec_bits, 4, 32, 40, prec_bits, 0, 320)
+    rng = np.random.default_rng(prec_bits)
+    wl.mu[...] = np.clip(wl.img * 256.0 + 256 * rng.choice([0, 0, 0, 1, -1, 2, 9], size=wl.img.shape), 0, 65535).astype(np.uint16)
+    wl.log_scale[...] = rng.integers(-16384, 24576, size=wl.img.shape).astype(np.int16)
+    wl.log_scale[0] = -16384
+    wl.log_scale[1] = 24575
+    wl.chan_coef[...] = 0
+    _check(wl, DeviceWorkload(wl))
+
+
+# A lane of 2^25 symbols and more, whose words the thread-per-lane encoder's 32-bit places do not reach: the block encoder
+# takes it whatever the policy says.
+def test_encode_a_lane_longer_than_the_places_reach():
+    n, h, w = 1, 2900, 3900
+    rng = np.random.default_rng(5)
+    wl = synth.make_random_case(5, 1, 8, 8, 12, 0, n * h * w)
+    wl.n, wl.h, wl.w = n, h, w
+    assert 3 * n * h * w >= 1 << 25
+    wl.img = rng.integers(0, 256, size=(n, h, w, 3), dtype=np.uint8)
+    wl.mu = wl.img.astype(np.uint16) << 8
+    wl.log_scale = np.zeros(wl.img.shape, dtype=np.int16)
+    wl.chan_coef = np.zeros((n, 3), dtype=np.int16)
+    wl.lane_a = n * h * w
+    rc, want = orc.encode(orc.make_geom(*wl.geom), wl.img, wl.mu, wl.log_scale, wl.chan_coef)
+    assert rc == orc.OK
+    device = DeviceWorkload(wl)
+    _, nbytes = device.encode()
+    got = device.coded_numpy()
+    assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
