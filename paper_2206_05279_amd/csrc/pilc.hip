@@ -1275,7 +1275,9 @@ int pilc_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t coded_by
     } else {
         const bool vec = chunks_aligned(g, img_out_dev, params);
         const bool pair = vec && chunks_pair_up(g, img_out_dev);
-        auto kern = pair ? k_decode_lanes<true, true> : (vec ? k_decode_lanes<true, false> : k_decode_lanes<false, false>);
+        const bool one_side = g.lanes > compute_units() * 256u;  // more than a wavefront a SIMD (figures at the kernel)
+        auto kern = one_side ? (pair ? k_decode_lanes<true, true, true> : vec ? k_decode_lanes<true, false, true> : k_decode_lanes<false, false, true>)
+                             : (pair ? k_decode_lanes<true, true, false> : vec ? k_decode_lanes<true, false, false> : k_decode_lanes<false, false, false>);
         const int bt = lane_block_threads(g);
         const uint32_t nb = (uint32_t)ceil_div64(g.lanes, bt);
         kern<<<nb, bt, (size_t)bt * kRingRow * sizeof(uint16_t), stream>>>(g, coded_dev, (unsigned long long)coded_bytes,

@@ -222,20 +222,18 @@ __device__ __forceinline__ EdgeLaw edge_law(int mu_eff, uint32_t inv_s)
 }
 __device__ __forceinline__ double edge_y(int k, const EdgeLaw &l) { return __builtin_fma((double)k, l.a, l.b); }
 
-// The positions of the two edges of a value: y(x) from d = 256 x - 128 - mu' and y(x + 1).  One conversion and two
-// multiply-adds; times 2^-6 is an addition to the exponent (inv_s is never 0), which issues in half a multiplication's time.
-struct EdgePair {
-    double lo, hi;
+// The position of one edge of a value, y(k) from d = 256 k - 128 - mu', and what the next is away: one conversion and one
+// multiply-add, and another for each neighbour.  (Times 2^-6 is an addition to the exponent, inv_s is never 0; it issues in
+// half a multiplication's time.)
+struct EdgeStep {
+    double y, unit;  // unit: inv_s * 2^-6
+    __device__ __forceinline__ EdgeStep(int d, uint32_t inv_s)
+    {
+        unit = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, (double)inv_s) - (6ull << 52));
+        y = __builtin_fma((double)d, unit, kEdgeBias);
+    }
+    __device__ __forceinline__ double above() const { return __builtin_fma(256.0, unit, y); }
 };
-__device__ __forceinline__ EdgePair edge_pair(int d, uint32_t inv_s)
-{
-    const double inv = (double)inv_s;
-    const double unit = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, inv) - (6ull << 52));
-    EdgePair p;
-    p.lo = __builtin_fma((double)d, unit, kEdgeBias);
-    p.hi = __builtin_fma(4.0, inv, p.lo);
-    return p;
-}
 
 __device__ __forceinline__ uint32_t edge_cdf(int d, uint32_t inv_s, const LdsTables &t)
 {
@@ -282,27 +280,32 @@ __device__ __forceinline__ uint32_t cum_at(int k, int mu_eff, uint32_t inv_s, ui
 // and goes on from there where they do not hold the symbol.
 // --------------------------------------------------------------------------------------------
 struct GuideScale {  // per launch
-    float half, mid, full, log_n;
+    float half, mid, full, log_n, log_s;
     __device__ __forceinline__ explicit GuideScale(uint32_t prec_bits)
     {
         const float n = (float)((1u << prec_bits) - 256u);
         full = n;
         half = 0.5f * n;
         mid = 0.5f * n - 0.5f + 1.0f / 64;  // (a little below slot + 1, so that rounding does not reach the next edge)
-        log_n = __logf(n) + 4.0f + kGuideShift;
+        log_n = __logf(n) + kGuideShift;
+        log_s = log_n + 4.0f;
     }
 };
 
-// The edge nearest to where the symbol begins, 1 .. 255, under the law with mean `mu_eff`, inverse scale `inv_s` (Q6.25)
-// and scale index `su`.
+// The edge nearest to where the symbol begins, 1 .. 255, under the law with mean `mu_eff` and inverse scale `inv_s` (Q6.25).
+// kShortChain: ln(1 / s) from the scale index `su`, before `slot` is needed, instead of with ln(1 - y) in one logarithm: two
+// instructions more, but one less between the slot and the edge.
+template <bool kShortChain>
 __device__ __forceinline__ uint32_t guide_edge(uint32_t slot, int mu_eff, uint32_t inv_s, int su, const GuideScale &gs,
                                                const float2 *guide)
 {
     const float mean = (float)mu_eff, inv = (float)inv_s * 0x1p-25f;
     const float s = __builtin_amdgcn_rcpf(inv);
     const float t = (float)slot - __builtin_fmaf(mean, 1.0f / 256, gs.mid);
-    const float not_y = __builtin_fminf(__builtin_fmaf(__builtin_fabsf(t), __builtin_amdgcn_rcpf(__builtin_fmaf(kGuideLine, s, gs.full)), 0.5f), 1.0f);
-    const float b = __builtin_fmaf(__builtin_amdgcn_logf(not_y), 0.693147181f, __builtin_fmaf((float)su, -1.0f / 4096, gs.log_n));
+    // (the middle one of three is a modifier of the multiply-add)
+    const float not_y = __builtin_amdgcn_fmed3f(__builtin_fmaf(__builtin_fabsf(t), __builtin_amdgcn_rcpf(__builtin_fmaf(kGuideLine, s, gs.full)), 0.5f), 0.0f, 1.0f);
+    const float b = kShortChain ? __builtin_fmaf(__builtin_amdgcn_logf(not_y), 0.693147181f, __builtin_fmaf((float)su, -1.0f / 4096, gs.log_s))
+                                : __builtin_fmaf(__builtin_amdgcn_logf(not_y * inv), 0.693147181f, gs.log_n);
     const float q = __builtin_fmaf(gs.half - __builtin_fabsf(t), inv, b);
     const float x = __builtin_fmaxf(q, 1.0f);  // below 2^21: half <= 32640, inv <= 54.6, b < 25
     const float2 line = guide[(__float_as_uint(x) >> (23 - kGuideBits)) - (127u << kGuideBits)];

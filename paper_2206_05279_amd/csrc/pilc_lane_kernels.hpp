@@ -292,7 +292,7 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
         // evaluations overlap freely.  Phase 2: the serial chain (App. A eq. (11)), last symbol first.  What bounds the
         // kernel is vector instructions (56 a symbol, 65 before), the waits for the tables and the stores of words.
         // The quotient is exact at the first go (quotient above), where a single-precision estimate took a
-        // remainder and a correction; an edge takes one conversion less (edge_pair).  Whole calls, us, before and
+        // remainder and a correction; an edge takes one conversion less (EdgeStep).  Whole calls, us, before and
         // now: 16,384 images of 64 x 64 with a lane a row 640 and 587, 1024 of 256 x 256 700 and 606, 30 frames of 1080 x 1920 in
         // tiles of 16 x 16 535 and 503, 8 images of 1365 x 2047 in the same 358 and 315.  A store in every step, of a word that
         // is written over if it does not count, leaves no branch in a part but costs more than the branches: 689,
@@ -318,12 +318,12 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
 #pragma unroll
                 for (int ch = 0; ch < 3; ++ch) {
                     const int x = ck.x[i][ch];
-                    const EdgePair y = edge_pair(e[ch] - 128, inv_scale(ck.l[i][ch], tab));
+                    const EdgeStep edge(e[ch] - 128, inv_scale(ck.l[i][ch], tab));
                     // both edges always, so that no branch keeps the evaluations of the half apart (the
                     // compiler would skip the one that is not needed): 0.48 -> 0.45 ms on 30 frames of
                     // 1080 x 1920 in tiles
-                    uint32_t lo = cum_inner(x, y.lo, scale, tab);
-                    uint32_t hi = cum_inner(x + 1, y.hi, scale, tab);
+                    uint32_t lo = cum_inner(x, edge.y, scale, tab);
+                    uint32_t hi = cum_inner(x + 1, edge.above(), scale, tab);
                     asm("" : "+v"(lo), "+v"(hi));
                     lo = x == 0 ? 0u : lo;
                     hi = x == 255 ? top : hi;
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
 
 // --------------------------------------------------------------------------------------------
 // Decode.  The symbol (App. A names a binary search for it) is guessed from the inverse of the law (guide_edge) and checked
-// at three edges of the exact C; from a guess that is not good enough the lanes concerned walk on edge by edge
+// at two or three edges of the exact C (kOneSide); from a guess that is not good enough the lanes concerned walk on edge by edge
 // (walk_to_symbol), which wide laws at a low precision take.  Bound by vector instructions where the lanes fill
 // the chip, by the length of a symbol's chain where they do not; the guess and three edges, whose
 // table reads are under way together, are 77 instructions and two waits for LDS instead of the 104 and
@@ -791,7 +791,7 @@ struct WordRing {
 // 376, 460, 692; 5.5 370, 455, 586; 2^M = 4096: 4.0 312, 460, 480; guesses that are all good 281.  (Slower than
 // the search alone only where nothing is known of a pixel: scales of 150 and more with means hundreds away from
 // every value, 545 against 463.)
-__device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below, uint32_t &mass, uint32_t slot, const EdgeLaw &law,
+__device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below, uint32_t &mass, uint32_t slot, double y, double a,
                                                    uint32_t scale, uint32_t m_bits, const LdsTables &tab)
 {
     const bool down = (int)below < 0;
@@ -799,7 +799,7 @@ __device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below
     uint32_t c_near = slot - below + (down ? 0u : mass);
     do {
         k = down ? k - 1u : k + 1u;  // within 0 .. 256: C(0) = 0 <= slot < 2^M = C(256)
-        uint32_t c = cum_inner((int)k, edge_y((int)k, law), scale, tab);
+        uint32_t c = cum_inner((int)k, __builtin_fma((double)(int)(k - mid), a, y), scale, tab);
         c = k == 0u ? 0u : c;
         c = k == 256u ? 1u << m_bits : c;
         below = slot - (down ? c : c_near);
@@ -813,7 +813,13 @@ __device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below
 // that carries the rest of every parameter line in registers, as the encoder does, reads half the
 // bytes from memory but needs 172 registers, i.e. two wavefronts per SIMD, and was slower: 0.91 against
 // 0.86 ms on 16,384 images of 64 x 64.)
-template <bool kVec, bool kPair>
+// kOneSide: after C at the guessed edge only the neighbour on the symbol's side is evaluated, behind a wait of its own: eight
+// instructions and a table read a symbol less, with the rest of it 82 instructions for 92.  For more than a wavefront a SIMD, where
+// instructions are what is waited for: 30 frames of 1080 x 1920 in tiles of 16 x 16 549 and 511 us, 8 images of 1365 x 2047 in
+// the same (88,064 lanes) 370 and 363, 16,384 images of 64 x 64 in tiles of 8 x 8 518 and 485, with a lane a row 616
+// and 597, 76,800 lanes of 64 109 and 106; up to there the wait is what counts: 65,472 lanes of 64 103 and 105, 38,400 95 and
+// 97, 65,536 tiles of 16 x 16 at 2^M = 1024 272 and 279.
+template <bool kVec, bool kPair, bool kOneSide>
 __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_lanes(Geo g, const uint8_t *__restrict__ coded,
                                unsigned long long coded_bytes, const uint16_t *__restrict__ mu,
                                const int16_t *__restrict__ ls, const int16_t *__restrict__ coef,
@@ -837,6 +843,8 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
     const uint32_t scale = mass_scale(m_bits), mask = (1u << m_bits) - 1u;
+    uint32_t top = 1u << m_bits;
+    asm("" : "+v"(top));  // (in a vector register, where the choice below takes it from)
     const uint32_t payload_bytes = (uint32_t)s_payload;
     const uint32_t per_row = (sh.tw + kChunk - 1) / kChunk;
     const uint32_t chunks = per_row * (sh.npx / sh.tw);
@@ -885,26 +893,49 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
                         me = ck.m[i][2] + rsh14_mul(a_br, (x[0] * 256 - ck.m[i][0])) +
                              rsh14_mul(a_bg, (x[1] * 256 - ck.m[i][1]));
                     const uint32_t inv_s = inv_scale(ck.l[i][ch], tab);
-                    const EdgeLaw law = edge_law(me, inv_s);
                     const uint32_t slot = S & mask;
-                    // C at the edge where the symbol should begin or end and at its two neighbours
-                    uint32_t mid = guide_edge(slot, me, inv_s, scale_index(ck.l[i][ch]), gs, guide);
-                    const double y = edge_y((int)mid, law);
-                    const uint32_t c_mid = cum_inner((int)mid, y, scale, tab);
-                    uint32_t c_below = cum_inner((int)mid - 1, y - law.a, scale, tab);
-                    uint32_t c_above = cum_inner((int)mid + 1, y + law.a, scale, tab);
-                    c_below = mid == 1u ? 0u : c_below;
-                    c_above = mid == 255u ? 1u << m_bits : c_above;
-                    bool up = c_mid <= slot;
-                    const uint32_t c_lo = up ? c_mid : c_below, c_hi = up ? c_above : c_mid;
+                    // C at the edge where the symbol should begin or end, and at the one that it should have on the other
+                    // side, or at both neighbours
+                    uint32_t mid, lo, c_lo, c_hi;
+                    double y, a;  // the position of `mid`, and what the next edge is away
+                    if (kOneSide) {
+                        mid = guide_edge<false>(slot, me, inv_s, 0, gs, guide);
+                        int from_mean = -128 - me;
+                        asm("" : "+v"(from_mean));  // (formed before the guess is there)
+                        const EdgeStep edge((int)(mid << 8) + from_mean, inv_s);
+                        const uint32_t c_mid = cum_inner((int)mid, edge.y, scale, tab);
+                        const bool down = slot < c_mid;
+                        const uint32_t other = mid + (down ? 0u - 1u : 1u);
+                        uint32_t c = cum_inner((int)other, __builtin_fma(down ? -256.0 : 256.0, edge.unit, edge.y), scale, tab);
+                        asm("" : "+v"(c));  // (no branch around its evaluation)
+                        c = other == 0u ? 0u : c;
+                        c = other == 256u ? top : c;
+                        lo = min(mid, other);
+                        c_lo = min(c_mid, c);
+                        c_hi = max(c_mid, c);
+                        y = edge.y;
+                        a = 256.0 * edge.unit;
+                    } else {
+                        const EdgeLaw law = edge_law(me, inv_s);
+                        mid = guide_edge<true>(slot, me, inv_s, scale_index(ck.l[i][ch]), gs, guide);
+                        y = edge_y((int)mid, law);
+                        a = law.a;
+                        const uint32_t c_mid = cum_inner((int)mid, y, scale, tab);
+                        uint32_t c_below = cum_inner((int)mid - 1, y - a, scale, tab);
+                        uint32_t c_above = cum_inner((int)mid + 1, y + a, scale, tab);
+                        c_below = mid == 1u ? 0u : c_below;
+                        c_above = mid == 255u ? top : c_above;
+                        const bool down = slot < c_mid;
+                        lo = mid - (down ? 1u : 0u);
+                        c_lo = down ? c_below : c_mid;
+                        c_hi = down ? c_mid : c_above;
+                    }
                     uint32_t below = slot - c_lo, mass = c_hi - c_lo;
                     if (__builtin_expect(__any(below >= mass), 0)) {
                         if (below >= mass) {
-                            mid = walk_to_symbol(mid, below, mass, slot, law, scale, m_bits, tab);
-                            up = true;
+                            lo = walk_to_symbol(mid, below, mass, slot, y, a, scale, m_bits, tab);
                         }
                     }
-                    const uint32_t lo = up ? mid : mid - 1u;
                     x[ch] = (int)lo;
                     // App. A eq. (12)
                     // the mass is at most 2^16 and S >> M below 2^22: a 24-bit multiply is exact

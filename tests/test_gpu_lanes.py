@@ -45,6 +45,24 @@ def test_guess_over_the_range_of_the_law(prec_bits, log_scale):
     _check(wl, DeviceWorkload(wl))
 
 
+# The same with more lanes than one wavefront a SIMD takes, where the decoder looks at one neighbour of the guessed edge: all
+# scales in one batch, chunks of single elements, of aligned eights and of pairs.
+@pytest.mark.parametrize("prec_bits", [10, 13, 16])
+@pytest.mark.parametrize("lane", [3, 8, 16])
+def test_guess_with_many_lanes(prec_bits, lane):
+    n, h, w = 9, 16 * lane, 512
+    wl = synth.make_random_case(prec_bits, n, h, w, prec_bits, 0, lane, wild=True)
+    assert n * h * w // lane > 65536
+    rng = np.random.default_rng(lane)
+    wl.img[...] = np.arange(wl.img.size, dtype=np.uint32).reshape(wl.img.shape) % 256
+    near = np.clip(wl.img * 256.0 + rng.normal(0, 700, wl.img.shape), 0, 65535)
+    far = rng.choice([0, 1, 128, 32768, 65407, 65535], size=wl.img.shape)
+    wl.mu[...] = np.where(rng.random(wl.img.shape) < 0.7, near, far).astype(np.uint16)
+    scales = np.array([-32768, -16384, -9000, 0, 8192, 12288, 20000, 24575, 32767], dtype=np.int16)
+    wl.log_scale[...] = scales[:, None, None, None]
+    _check(wl, DeviceWorkload(wl))
+
+
 # Rows of lanes shorter and longer than a chunk of eight pixels, arrays that start on any element: the last chunk of
 # the last row of the last image is the one that must not be read past.
 @pytest.mark.parametrize("w", [1, 7, 8, 9, 15, 17, 24])
