@@ -13,12 +13,14 @@
 //     forms the next state for its own candidates, and an OR over the row (four rotate-and-OR
 //     steps on the data-parallel-primitive path, no LDS round trip, no ballot) hands the one
 //     non-zero value to all 16 threads;
+//   - the mean of the next channel comes from the value first, up to asking for its table cells, and the state, the
+//     stream's position and what else there is to do for the symbol is done while the cells are on their way;
 //   - a pixel is decoded without a branch: whether every symbol was inside its window is
 //     looked at once per pixel, and a pixel with a symbol outside is decoded again from the state
 //     saved at its start by a bounded two-level search (32 values eight apart, then the nine of
 //     the band);
 //   - the candidates of a pixel's first channel do not depend on decoded values and are evaluated
-//     while the previous pixel is still being decoded;
+//     a batch ahead;
 //   - per-pixel parameters are prepared 16 pixels at a time, one pixel per thread, two batches
 //     ahead of their use, and handed over through LDS; the 96 stream words a batch can reach are
 //     fetched a batch ahead and wait in LDS, and the word a refill would take is read ahead of
@@ -47,50 +49,83 @@ constexpr int kRowBaseMax = 256 - kRowWindow; // window bases 0..224: candidates
 constexpr int kRowRedoLimit = 4;              // a batch with this many pixels outside their windows sends
 constexpr int kRowSearchBatches = 7;          // the wavefront's next 7 batches straight to the search
 
-// OR over the 16 threads of a row, result in every thread: rotate right by 1, 2, 4, 8 and OR.
-__device__ __forceinline__ uint32_t row_or(uint32_t v)
+// What the threads of a row make of their candidates {t < f}: the winner's x and next state f q + t (App. A eq. (12)), ORed over
+// the row, where all others have 0, into every thread.  Rotations by 1, 2, 4 and 8 by the DPP path, which may read a register
+// only two instructions after it was written: the two reductions and a third instruction, F1 .. F4 (something else
+// that has to be done there or a wait), take turns.  The choices read their masks two instructions after these were made.
+#define PILC_ROW_TURN(rotate, filler)                                                       \
+    "v_or_b32_dpp %[x], %[x], %[x] " rotate " row_mask:0xf bank_mask:0xf bound_ctrl:0\n"   \
+    "v_or_b32_dpp %[s], %[s], %[s] " rotate " row_mask:0xf bank_mask:0xf bound_ctrl:0\n" filler
+#define PILC_ROW_PICK(F1, F2, F3, F4)                                                       \
+    "v_cmp_lt_u32_e32 vcc, %[t0], %[f0]\n"                                                 \
+    "v_cmp_lt_u32_e64 %[m], %[t1], %[f1]\n"                                                \
+    "v_mad_u32_u24 %[s], %[f0], %[q], %[t0]\n"                                             \
+    "v_mad_u32_u24 %[u], %[f1], %[q], %[t1]\n"                                             \
+    "v_cndmask_b32_e32 %[x], 0, %[xw0], vcc\n"                                             \
+    "v_cndmask_b32_e32 %[s], 0, %[s], vcc\n"                                               \
+    "v_cndmask_b32_e64 %[x], %[x], %[xw1], %[m]\n"                                         \
+    "v_cndmask_b32_e64 %[s], %[s], %[u], %[m]\n" F1                                        \
+    PILC_ROW_TURN("row_ror:1", F2) PILC_ROW_TURN("row_ror:2", F3) PILC_ROW_TURN("row_ror:4", F4) PILC_ROW_TURN("row_ror:8", "")
+#define PILC_ROW_PICK_OUT [x] "=&v"(x), [s] "=&v"(s_new), [u] "=&v"(u), [m] "=&s"(m)
+#define PILC_ROW_PICK_IN                                                                    \
+    [t0] "v"(slot - cd.cv0), [f0] "v"(cd.f0), [t1] "v"(slot - cd.cv1), [f1] "v"(cd.f1), [q] "v"(q), [xw0] "v"(xw0), [xw1] "v"(xw1)
+
+// n - rsh14_mul(a, e), written out in one piece (the compiler waits after every piece that is written out by itself)
+__device__ __forceinline__ int minus_rsh14_mul(int n, int a, int e)
 {
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121 /* row_ror:1 */, 0xF, 0xF, false);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122 /* row_ror:2 */, 0xF, 0xF, false);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124 /* row_ror:4 */, 0xF, 0xF, false);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128 /* row_ror:8 */, 0xF, 0xF, false);
-    return v;
+    int r;
+    asm("v_mad_i32_i24 %[r], %[a], %[e], %[half]\n"
+        "v_ashrrev_i32_e32 %[r], 14, %[r]\n"
+        "v_sub_u32_e32 %[r], %[n], %[r]"
+        : [r] "=&v"(r) : [n] "v"(n), [a] "v"(a), [e] "v"(e), [half] "v"(8192));
+    return r;
 }
 
-// The same for two values at once, the steps of the two reductions taken in turn: a step reads
-// what the step before it wrote, so two independent reductions fill each other's waiting time.
-__device__ __forceinline__ void row_or2(uint32_t &a, uint32_t &b)
+// thread j of a row receives the value of thread j + 1 of the same row, the last one `last`
+__device__ __forceinline__ uint32_t row_next(uint32_t v, uint32_t last)
 {
-#define PILC_ROW_OR_STEP(ctrl)                                                                  \
-    a |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, ctrl, 0xF, 0xF, false);               \
-    b |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, ctrl, 0xF, 0xF, false);
-    PILC_ROW_OR_STEP(0x121)
-    PILC_ROW_OR_STEP(0x122)
-    PILC_ROW_OR_STEP(0x124)
-    PILC_ROW_OR_STEP(0x128)
-#undef PILC_ROW_OR_STEP
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x101 /* row_shl:1 */, 0xF, 0xF, false);
 }
 
-// thread j of a row receives the value of thread (j + 1) mod 16 of the same row
-__device__ __forceinline__ uint32_t row_next(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x12F /* row_ror:15 */, 0xF, 0xF, true);
-}
-
-// What one pixel's preparing thread leaves in LDS for the row (64 bytes).  The inverse scale of a
-// channel comes as what one step of k and one unit of the mean move the position of an edge by
+// What one pixel's preparing thread leaves in LDS for the row (64 bytes).  Values and window bases are kept times 256, like
+// the means, and a decoded one has its lowest bit set (`hit` below), so 256 x - m is the decoded number less 1 + m.  The
+// inverse scale of a channel comes as what one step of k and one unit of the mean move the position of an edge by
 // (see EdgeLaw: 1/s times 4 and times 2^-6, both exact).
 struct RowPixel {
-    uint4 r;            // -128 - m_r, -128 - m_g, -128 - m_b (Q8.8), window of R
+    uint4 r;            // -1 - m_r, -1 - m_g, -1 - m_b (Q8.8), window of R times 256
     uint4 s;            // a_gr, a_br, a_bg (Q2.14, sign-extended), 1/s of R
     double g[2], b[2];  // G and B: 1/s times 4, times 2^-6
 };
 
-// The candidates of one symbol as a thread holds them: C(k) at k = base + 2 j and base + 2 j + 1
-// and the masses up to their successors (0 for a candidate that cannot be the symbol).
+// The candidates of one symbol as a thread holds them: C(k) - base at k = base + 2 j and base + 2 j + 1
+// and the masses up to their successors (0 for a candidate that cannot be the symbol); base times 256.
 struct RowCand {
     uint32_t cv0, cv1, f0, f1;
     int base;
+};
+
+// Everything that the workgroup keeps in LDS, the tables first: an address below 2^16 fits into the instruction that reads them.
+template <bool kStaged>
+struct RowShared {
+    LdsTables tab;
+    RowPixel stage[2][kRowLanes][kRowBatch];
+    uint16_t words[2][kRowLanes][kRowWords];
+    // The candidates of every thread for the first channel of every pixel of a batch, {cv0 | f0 << 16, cv1 | f1 << 16}
+    // (a candidate is at most 255, so C and the masses are below 2^M <= 2^16)
+    uint2 first_cand[kStaged ? 2 : 1][kStaged ? kRowLanes : 1][kRowBatch][16];
+    // The workgroup has two wavefronts per four lanes: one decodes, the other (its stager) prepares
+    // the next batch's parameters and stream words in LDS meanwhile.  What passes between them:
+    uint32_t word_base[2][kRowLanes];  // stream position of words[buf][lane][0]
+    // Of batch b, in slot b & 1: the lane's stream position at its start and its 16 decoded pixels.
+    // (The decoder writes a slot again two batches later, and cannot start that batch before the
+    // stager, which reads the slot first, has staged it.)
+    uint32_t pos[2][kRowLanes];
+    uint32_t out[2][kStaged ? kRowLanes : 1][kRowBatch];
+    uint32_t posted[kRowWaves];        // batches the decoding wavefront has finished
+    uint32_t staged[kRowWaves];        // batches the stager has made ready
+    uint32_t abort;                    // a wait was given up: everybody leaves
+    int state;
+    unsigned long long payload;
 };
 
 // kStaged: with a stager per decoding wavefront (see above).  That form keeps twice the LDS per
@@ -106,34 +141,28 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     // wait_ticks: the bound of a wait between a decoding wavefront and its stager, in ticks of the
     // constant-rate clock; withhold: the stagers never say that a batch is ready (tests of the
     // give-up path)
-    __shared__ LdsTables tab;
-    __shared__ RowPixel stage[2][kRowLanes][kRowBatch];
-    __shared__ uint16_t words[2][kRowLanes][kRowWords];
-    // C(k) at the two candidates of every thread for the first channel of every pixel of a batch,
-    // 16 bits each (a candidate is at most 255, so C is below 2^M <= 2^16)
-    __shared__ uint32_t first_cand[kStaged ? 2 : 1][kStaged ? kRowLanes : 1][kRowBatch][16];
-    // The workgroup has two wavefronts per four lanes: one decodes, the other (its stager) prepares
-    // the next batch's parameters and stream words in LDS meanwhile.  What passes between them:
-    __shared__ uint32_t s_word_base[2][kRowLanes];  // stream position of words[buf][lane][0]
-    // Of batch b, in slot b & 1: the lane's stream position at its start and its 16 decoded pixels.
-    // (The decoder writes a slot again two batches later, and cannot start that batch before the
-    // stager, which reads the slot first, has staged it.)
-    __shared__ uint32_t s_pos[2][kRowLanes];
-    __shared__ uint32_t s_out[2][kStaged ? kRowLanes : 1][kRowBatch];
-    __shared__ uint32_t s_posted[kRowWaves];        // batches the decoding wavefront has finished
-    __shared__ uint32_t s_staged[kRowWaves];        // batches the stager has made ready
-    __shared__ uint32_t s_abort;                    // a wait was given up: everybody leaves
+    __shared__ RowShared<kStaged> sm;
+    const LdsTables &tab = sm.tab;
+    auto &stage = sm.stage;
+    auto &words = sm.words;
+    auto &first_cand = sm.first_cand;
+    auto &s_word_base = sm.word_base;
+    auto &s_pos = sm.pos;
+    auto &s_out = sm.out;
+    auto &s_posted = sm.posted;
+    auto &s_staged = sm.staged;
+    auto &s_abort = sm.abort;
+    auto &s_state = sm.state;
+    auto &s_payload = sm.payload;
     if (threadIdx.x < (uint32_t)kRowWaves) {
         s_posted[threadIdx.x] = 0u;
         s_staged[threadIdx.x] = 0u;
     }
-    __shared__ int s_state;
-    __shared__ unsigned long long s_payload;
     if (threadIdx.x == 0u) {
         s_abort = 0u;
         s_state = check_header(g, kMagicPilc, 0u, coded, coded_bytes, &s_payload);
     }
-    load_tables(tab);  // ends with a barrier
+    load_tables(sm.tab);  // ends with a barrier
     if (s_state != ST_OK) {
         if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, s_state);
         return;
@@ -207,14 +236,14 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         }
         return r;
     };
-    // (from n = -128 - mean)
+    // The window of a symbol whose effective mean is -1 - n: its base times 256, whole and within 0 .. kRowBaseMax.
     auto window_base = [](int n) {
-        return min(max((-128 - (256 * (kRowWindow / 2 - 1) - 128) - n) >> 8, 0), kRowBaseMax);
+        return min(max((-1 - (256 * (kRowWindow / 2 - 1) - 128) - n) & ~255, 0), 256 * kRowBaseMax);
     };
     auto put_stage = [&](const Raw &r, uint32_t buf) {
         RowPixel px;
-        const int n_r = -128 - (int)r.m[0];
-        px.r = make_uint4((uint32_t)n_r, (uint32_t)(-128 - (int)r.m[1]), (uint32_t)(-128 - (int)r.m[2]),
+        const int n_r = -1 - (int)r.m[0];
+        px.r = make_uint4((uint32_t)n_r, (uint32_t)(-1 - (int)r.m[1]), (uint32_t)(-1 - (int)r.m[2]),
                           (uint32_t)window_base(n_r));
         px.s = make_uint4((uint32_t)r.a[0], (uint32_t)r.a[1], (uint32_t)r.a[2], inv_scale(r.l[0], tab));
         const double i1 = (double)inv_scale(r.l[1], tab), i2 = (double)inv_scale(r.l[2], tab);
@@ -225,104 +254,117 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         stage[buf][lrow][j] = px;
     };
 
-    // Window of a symbol with effective mean -128 - n, and this thread's candidates k = base + 2 j and
+    // Window of a symbol with effective mean -1 - n, and this thread's candidates k = base + 2 j and
     // base + 2 j + 1 in it; `per_k` and `per_unit` as in RowPixel.  The evaluation comes in two
     // halves so that the wait for one symbol's table cells can be filled with another symbol's
     // arithmetic: `aim` goes as far as asking for the cells, `finish` takes it from there.
     struct RowAim {
         uint2 cell[2];
         uint32_t u[2];
-        int base, k0;
+        int base;
+        uint32_t c0_most;  // of C at the first candidate: 0 where that is C(0)
+        bool last;         // the last window
     };
-    const int j2 = 2 * (int)j;
+    const uint32_t j2 = 2u * j;
+    const int j_edge = 512 * (int)j - 127;  // from the window's base and n to 256 k - 128 - mean
+    const uint32_t j_not_first = j == 0u ? 0u : 0x7FFFFFFFu;
+    uint32_t top_left = top - (uint32_t)kRowBaseMax;  // C(256) less the last window's base
+    asm("" : "+v"(top_left));  // (in a vector register)
     auto aim = [&](int n, double per_k, double per_unit) {
         RowAim am;
         am.base = window_base(n);
-        am.k0 = am.base + j2;
-        const double y = __builtin_fma((double)((am.k0 << 8) + n), per_unit, kEdgeBias);
+        const double y = __builtin_fma((double)(am.base + j_edge + n), per_unit, kEdgeBias);
         am.u[0] = edge_pos(y);
         am.u[1] = edge_pos(y + per_k);
 #pragma unroll
         for (int c = 0; c < 2; ++c) am.cell[c] = sig[am.u[c] >> 21];
         return am;
     };
+    // what else `finish` needs of the window: for the wait for the cells
+    auto aimed = [&](RowAim &am) {
+        am.c0_most = ((uint32_t)am.base << 8) | j_not_first;
+        am.last = am.base == 256 * kRowBaseMax;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) am.u[c] |= 2047u;  // (see interpolate)
+    };
     auto aim_first = [&](const RowPixel &px) {  // the first channel, whose 1/s comes as it is
         const double inv = (double)px.s.w;
-        return aim((int)px.r.x, inv * 4.0, inv * 0x1p-6);
+        RowAim am = aim((int)px.r.x, inv * 4.0, inv * 0x1p-6);
+        aimed(am);
+        return am;
     };
-    // C(k) at the thread's two candidates, from the cells `aim` asked for
-    auto cum_pair = [&](const RowAim &am, uint32_t cv[2]) {
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-            cv[c] = (uint32_t)(am.k0 + c) + mass_of(interpolate(am.u[c], am.cell[c]), scale);
-        cv[0] = am.k0 == 0 ? 0u : cv[0];  // C(0) = 0
-    };
-    // The candidates of a symbol from its two values of C.  The second candidate is followed by the
+    // The candidates of a symbol, from the cells `aim` asked for.  The second candidate is followed by the
     // next thread's first; candidate 31 by C(base + 32), which is known only when it is C(256) = 2^M.
-    auto with_masses = [&](uint32_t cv0, uint32_t cv1, int base) {
+    auto finish = [&](const RowAim &am) {
         RowCand cd;
-        const uint32_t from_next = row_next(cv0);
-        const uint32_t after = j == 15u ? (base == kRowBaseMax ? top : cv1) : from_next;
-        cd.cv0 = cv0;
-        cd.cv1 = cv1;
-        cd.f0 = cv1 - cv0;
-        cd.f1 = after - cv1;
-        cd.base = base;
+        cd.base = am.base;
+        cd.cv0 = min(j2 + mass_of(interpolate(am.u[0], am.cell[0]), scale), am.c0_most);
+        cd.cv1 = j2 + 1u + mass_of(interpolate(am.u[1], am.cell[1]), scale);
+        cd.f0 = cd.cv1 - cd.cv0;
+        cd.f1 = row_next(cd.cv0, am.last ? top_left : cd.cv1) - cd.cv1;
         return cd;
     };
-    auto finish = [&](const RowAim &am) {
-        uint32_t cv[2];
-        cum_pair(am, cv);
-        return with_masses(cv[0], cv[1], am.base);
-    };
-    // the same for a pixel's first channel, whose two values of C the stager has left in LDS
-    auto first_channel = [&](uint32_t pair, uint32_t window) {
-        return with_masses(pair & 0xFFFFu, pair >> 16, (int)window);
+    // the same for a pixel's first channel, which the stager has left in LDS
+    auto first_channel = [&](uint2 pair, uint32_t window) {
+        return RowCand{pair.x & 0xFFFFu, pair.y & 0xFFFFu, pair.x >> 16, pair.y >> 16, (int)window};
     };
     // (stager) the first channel of the 16 pixels staged in `buf`, every thread its two candidates
     auto put_first_cand = [&](uint32_t buf) {
         wave_lds_sync();  // the parameters were written by this wavefront
 #pragma unroll 4
         for (int i = 0; i < kRowBatch; ++i) {
-            uint32_t cv[2];
-            cum_pair(aim_first(stage[buf][lrow][i]), cv);
-            first_cand[buf][lrow][i][j] = cv[0] | (cv[1] << 16);
+            const RowCand cd = finish(aim_first(stage[buf][lrow][i]));
+            first_cand[buf][lrow][i][j] = make_uint2(cd.cv0 | (cd.f0 << 16), cd.cv1 | (cd.f1 << 16));
         }
     };
 
-    const uint32_t xw0 = 2u * j | 256u, xw1 = xw0 | 1u;  // what a winning candidate contributes
-    const uint16_t *my_words = words[0][lrow];  // the current batch's words, from `wbase` on
-    uint32_t wbase = pos;
-    uint32_t wnext = 0;  // the word at `pos`
-    // One symbol of the four lanes of the wavefront, no branch.  Returns the value (meaningless
-    // where the window does not hold the symbol: bit 8 of `seen` is then cleared); updates S, pos,
-    // wnext of rows with `act`.
-    auto decode_symbol = [&](bool act, const RowCand &cd, uint32_t &seen) -> uint32_t {
-        const uint32_t slot = S & mask, q = S >> m_bits;
-        const uint32_t t0 = slot - cd.cv0, t1 = slot - cd.cv1;
-        const bool win0 = t0 < cd.f0, win1 = t1 < cd.f1;
-        // App. A eq. (12) as if this thread's candidate were the symbol: the mass is at most 2^16
-        // and S >> M below 2^22, so the 24-bit multiply is exact
-        const uint32_t s0 = (uint32_t)__umul24(cd.f0, q) + t0, s1 = (uint32_t)__umul24(cd.f1, q) + t1;
-        // at most one of the two is the symbol (no nested choice: it would become a branch)
-        uint32_t s_new = (win0 ? s0 : 0u) | (win1 ? s1 : 0u);
-        uint32_t xw = (win0 ? xw0 : 0u) | (win1 ? xw1 : 0u);
-        row_or2(xw, s_new);
-        // (kept as one value: left free, the compiler splits the last step of the reduction into a
-        // move, an OR and a three-operand AND for the two uses of xw below, four instructions for two)
-        asm("" : "+v"(xw));
-        seen &= xw;
+    const uint32_t xw0 = 512u * j | 1u, xw1 = xw0 | 256u;  // what a winning candidate contributes
+    const uint16_t *flat_words = &words[0][0][0];
+    uint32_t at = 0;     // place of the next word in `flat_words`, which holds the current batch's words
+    uint32_t wnext = 0;  // the word there
+    // One symbol of the four lanes of the wavefront, no branch, in two steps.  `pick`: 256 times the value less the window's base,
+    // and 1 (0 where the window does not hold the symbol), and in `s_new` the next state before it takes a word; `after_pick`:
+    // S, at and wnext of rows with `act`.  What needs the value comes between the two, so that its table reads are under way.
+    auto slot_in = [&](int base) { return (S & mask) - (((uint32_t)base >> 8) & 255u); };
+    auto pick = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new) {
+        uint32_t x, u;
+        unsigned long long m;
+        asm(PILC_ROW_PICK("s_nop 0\n", "s_nop 0\n", "s_nop 0\n", "s_nop 0\n") : PILC_ROW_PICK_OUT : PILC_ROW_PICK_IN : "vcc");
+        return x;
+    };
+    // the same, and n - rsh14_mul(a, e) into n
+    auto pick_beside_shift = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new, int &n, int a, int e) {
+        uint32_t x, u;
+        unsigned long long m;
+        int r;
+        asm(PILC_ROW_PICK("v_mad_i32_i24 %[r], %[a], %[e], %[half]\n", "v_ashrrev_i32_e32 %[r], 14, %[r]\n",
+                          "v_sub_u32_e32 %[r], %[n], %[r]\n", "s_nop 0\n")
+            : PILC_ROW_PICK_OUT, [r] "=&v"(r) : PILC_ROW_PICK_IN, [n] "v"(n), [a] "v"(a), [e] "v"(e), [half] "v"(8192) : "vcc");
+        n = r;
+        return x;
+    };
+    // the same, and the second bytes of lo and hi as the two lowest of `pair`
+    auto pick_beside_pair = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new, uint32_t lo, uint32_t hi,
+                                uint32_t &pair) {
+        uint32_t x, u, r;
+        unsigned long long m;
+        asm(PILC_ROW_PICK("v_perm_b32 %[r], %[hi], %[lo], %[sel]\n", "s_nop 0\n", "s_nop 0\n", "s_nop 0\n")
+            : PILC_ROW_PICK_OUT, [r] "=&v"(r) : PILC_ROW_PICK_IN, [lo] "v"(lo), [hi] "v"(hi), [sel] "s"(0x0C0C0501u) : "vcc");
+        pair = r;
+        return x;
+    };
+    auto after_pick = [&](bool act, uint32_t s_new) {
         const bool refill = s_new < (1u << 16);
         const uint32_t s_ref = (s_new << 16) | wnext;
         if (kRagged) {
             S = act ? (refill ? s_ref : s_new) : S;
-            pos += (act && refill) ? 1u : 0u;
+            at += (act && refill) ? 1u : 0u;
         } else {
             S = refill ? s_ref : s_new;
-            pos += refill ? 1u : 0u;
+            at += refill ? 1u : 0u;
         }
-        wnext = my_words[pos - wbase];
-        return (uint32_t)cd.base + (xw & 255u);
+        asm("" : "+v"(at));  // (one count, from which the address is made)
+        wnext = flat_words[at];
     };
     // The same by a bounded search with the general evaluation, on the state (Sr, pr): every 8th
     // value first (C(0) = 0 always counts), then the nine values of the band.
@@ -340,7 +382,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         const uint32_t c_hi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((gbase + n) << 2), (int)cf);
         uint32_t s_new = (uint32_t)__umul24(c_hi - c_lo, q) + (slot - c_lo);
         if (s_new < (1u << 16)) {
-            s_new = (s_new << 16) | my_words[pr - wbase];
+            s_new = (s_new << 16) | flat_words[pr];
             ++pr;
         }
         Sr = s_new;
@@ -432,14 +474,12 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         const uint32_t nb = t0 < npx ? min((uint32_t)kRowBatch, npx - t0) : 0u;
         if (kStaged) {
             if (!wait_for(&s_staged[wv], b + 1u)) break;
-            my_words = words[buf][lrow];
-            wbase = s_word_base[buf][lrow];
+            at = s_word_base[buf][lrow];
         } else {
             // this batch's words (fetched a batch ago, from where the stream stood then) into LDS, the
             // next batch's requested from where the stream stands now; the next batch's parameters
             // staged from the registers loaded a batch ago, and the batch after that requested
-            my_words = words[buf][lrow];
-            wbase = ahead_base;
+            at = ahead_base;
 #pragma unroll
             for (int r = 0; r < kRowWords / 16; ++r) words[buf][lrow][16 * r + j] = (uint16_t)ahead.w[r];
             ahead = fetch_words(pos);
@@ -448,14 +488,16 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
             raw_next = fetch_raw(t0 + 2 * kRowBatch);
             wave_lds_sync();
         }
-        wnext = my_words[pos - wbase];
+        at = (buf * kRowLanes + lrow) * kRowWords + pos - at;
+        const uint32_t at_start = at;
+        wnext = flat_words[at];
 
         const RowPixel *px = stage[buf][lrow];
         uint32_t v_out = 0;
         // The three symbols of a pixel by search, on the state (Sr, pr).
         auto search_pixel = [&](const RowPixel &cur, uint32_t &Sr, uint32_t &pr, uint32_t &y_r, uint32_t &y_g,
                                 uint32_t &y_b) {
-            const int m_r = -128 - (int)cur.r.x, m_g = -128 - (int)cur.r.y, m_b = -128 - (int)cur.r.z;
+            const int m_r = -1 - (int)cur.r.x, m_g = -1 - (int)cur.r.y, m_b = -1 - (int)cur.r.z;
             const int a_gr = (int)cur.s.x, a_br = (int)cur.s.y, a_bg = (int)cur.s.z;
             y_r = search_symbol(m_r, cur.s.w, Sr, pr);
             const int f_r = (int)(y_r << 8) - m_r;
@@ -467,11 +509,11 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
             // data the model does not fit (such as uniformly random pixels): the windows are not tried
             --search_batches;
             for (uint32_t i = 0; kRagged ? __any(i < nb) : i < (uint32_t)kRowBatch; ++i) {
-                uint32_t Sr = S, pr = pos, y_r, y_g, y_b;
+                uint32_t Sr = S, pr = at, y_r, y_g, y_b;
                 search_pixel(px[i], Sr, pr, y_r, y_g, y_b);
                 if (!kRagged || i < nb) {
                     S = Sr;
-                    pos = pr;
+                    at = pr;
                 }
                 v_out = j == i ? (y_r | (y_g << 8) | (y_b << 16)) : v_out;
             }
@@ -483,58 +525,63 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
             auto pixel = [&](uint32_t i, const RowPixel &cur, RowPixel &nxt, RowCand &cr) {
                 const bool act = i < nb;
                 nxt = px[(i + 1u) & (kRowBatch - 1)];
-                const uint32_t next_pair = kStaged ? first_cand[buf][lrow][(i + 1u) & (kRowBatch - 1)][j] : 0u;
+                const uint2 next_pair = kStaged ? first_cand[buf][lrow][(i + 1u) & (kRowBatch - 1)][j] : uint2{0u, 0u};
                 __builtin_amdgcn_sched_barrier(0);  // asked for here, used a pixel later
                 const int n_r = (int)cur.r.x, n_g = (int)cur.r.y, n_b = (int)cur.r.z;
                 const int a_gr = (int)cur.s.x, a_br = (int)cur.s.y, a_bg = (int)cur.s.z;
-                const uint32_t S0 = S, pos0 = pos;
-                uint32_t seen = 256u;
+                const uint32_t S0 = S, at0 = at;
+                uint32_t s_new, pair;
 
-                uint32_t x_r = decode_symbol(act, cr, seen);
-                const int e_r = (int)(x_r << 8) + n_r + 128;
-                const RowAim ag = aim(n_g - rsh14_mul(a_gr, e_r), cur.g[0], cur.g[1]);
+                const uint32_t p_r = pick(cr, slot_in(cr.base), S >> m_bits, s_new);
+                const uint32_t x_r = (uint32_t)cr.base + p_r;
+                const int e_r = (int)x_r + n_r;
+                RowAim ag = aim(minus_rsh14_mul(n_g, a_gr, e_r), cur.g[0], cur.g[1]);
                 __builtin_amdgcn_sched_barrier(0);
-                const int nb1 = n_b - rsh14_mul(a_br, e_r);
+                after_pick(act, s_new);
+                aimed(ag);
+                const uint32_t slot_g = slot_in(ag.base), q_g = S >> m_bits;
                 // The next pixel's first channel depends on no decoded value.  The stager has evaluated
-                // it, and what is left to do fills the wait for this channel's table cells; without a
-                // stager its evaluation fills the waits of the two channels that do depend.
-                RowCand cr_next = {};
+                // it; without a stager its evaluation fills the waits of the two channels that do depend.
                 RowAim an = {};
-                if (kStaged)
-                    cr_next = first_channel(next_pair, nxt.r.w);
-                else
-                    an = aim_first(nxt);
+                if (!kStaged) an = aim_first(nxt);
                 __builtin_amdgcn_sched_barrier(0);
                 const RowCand cg = finish(ag);
-                uint32_t x_g = decode_symbol(act, cg, seen);
-                const RowAim ab = aim(nb1 - rsh14_mul(a_bg, (int)(x_g << 8) + n_g + 128), cur.b[0], cur.b[1]);
+                int nb1 = n_b;
+                const uint32_t p_g = pick_beside_shift(cg, slot_g, q_g, s_new, nb1, a_br, e_r);
+                const uint32_t x_g = (uint32_t)cg.base + p_g;
+                RowAim ab = aim(minus_rsh14_mul(nb1, a_bg, (int)x_g + n_g), cur.b[0], cur.b[1]);
+                __builtin_amdgcn_sched_barrier(0);
+                after_pick(act, s_new);
+                aimed(ab);
+                const uint32_t slot_b = slot_in(ab.base), q_b = S >> m_bits;
                 __builtin_amdgcn_sched_barrier(0);
                 if (kStaged) {
-                    cr = cr_next;
+                    cr = first_channel(next_pair, nxt.r.w);
                 } else {
                     cr = finish(an);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 const RowCand cb = finish(ab);
-                uint32_t x_b = decode_symbol(act, cb, seen);
+                const uint32_t p_b = pick_beside_pair(cb, slot_b, q_b, s_new, x_r, x_g, pair);
+                const uint32_t x_b = (uint32_t)cb.base + p_b;
+                after_pick(act, s_new);
+                uint32_t rgb = __builtin_amdgcn_perm(x_b, pair, 0x0C050100u);  // and the second byte of the third
 
-                bool bad = (seen & 256u) == 0u;
+                bool bad = (p_r & p_g & p_b & 1u) == 0u;
                 if (kRagged) bad = bad && act;
                 if (__builtin_expect(__any(bad), 0)) {
                     // the pixel once more, from the state at its start, for the rows that need it
-                    uint32_t Sr = S0, pr = pos0, y_r, y_g, y_b;
+                    uint32_t Sr = S0, pr = at0, y_r, y_g, y_b;
                     search_pixel(cur, Sr, pr, y_r, y_g, y_b);
                     if (bad) {
                         S = Sr;
-                        pos = pr;
-                        x_r = y_r;
-                        x_g = y_g;
-                        x_b = y_b;
+                        at = pr;
+                        rgb = y_r | (y_g << 8) | (y_b << 16);
                     }
-                    wnext = my_words[pos - wbase];
+                    wnext = flat_words[at];
                     ++redone;
                 }
-                v_out = j == i ? (x_r | (x_g << 8) | (x_b << 16)) : v_out;
+                v_out = j == i ? rgb : v_out;
             };
             RowPixel pe = px[0], po;
             RowCand cr = kStaged ? first_channel(first_cand[buf][lrow][0][j], pe.r.w)
@@ -545,6 +592,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
             }
             if (redone >= (uint32_t)kRowRedoLimit) search_batches = kRowSearchBatches;
         }
+        pos += at - at_start;
         if (kStaged) {
             // the pixels and the position go to the stager, which may then go on to the batch after next
             s_out[buf][lrow][j] = v_out;
@@ -559,5 +607,10 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     }
     if (has_lane && npx != 0u && (S != (1u << 16) || pos != stop) && j == 0) raise_code(report, ST_CORRUPT);
 }
+
+#undef PILC_ROW_TURN
+#undef PILC_ROW_PICK
+#undef PILC_ROW_PICK_OUT
+#undef PILC_ROW_PICK_IN
 
 }  // namespace pilc
