@@ -2,8 +2,10 @@
 //
 // A lane is a serial chain (App. A eq. (12) of arXiv 2206.05279: every state depends on the one
 // before), so with a few thousand lanes a wavefront must be alone on its SIMD and the time is
-// (symbols per lane) x (instructions the wavefront issues per symbol) x 4 cycles.  This kernel
-// is built to keep that instruction count low:
+// (symbols per lane) x (instructions the wavefront issues per symbol) x some 5 cycles: a wavefront alone
+// issues a plain instruction every five cycles and a 64-bit one every nine, whether it depends on the one before or not, and
+// a wait state costs nearly as much.  This kernel is built to keep that count low (3125 lanes of 16,384 pixels 8110 us with 177
+// vector instructions and 13 waits a pixel, 6830 with 166 and 3, 1000 cycles a pixel):
 //   - a wavefront carries four lanes, one per 16-thread row, so 4096 lanes still leave every SIMD
 //     of the chip with at most one wavefront;
 //   - per symbol every thread evaluates C(k) at two neighbouring candidates of a 32-value window
@@ -70,16 +72,35 @@ constexpr int kRowSearchBatches = 7;          // the wavefront's next 7 batches 
 #define PILC_ROW_PICK_IN                                                                    \
     [t0] "v"(slot - cd.cv0), [f0] "v"(cd.f0), [t1] "v"(slot - cd.cv1), [f1] "v"(cd.f1), [q] "v"(q), [xw0] "v"(xw0), [xw1] "v"(xw1)
 
-// n - rsh14_mul(a, e), written out in one piece (the compiler waits after every piece that is written out by itself)
-__device__ __forceinline__ int minus_rsh14_mul(int n, int a, int e)
-{
-    int r;
-    asm("v_mad_i32_i24 %[r], %[a], %[e], %[half]\n"
-        "v_ashrrev_i32_e32 %[r], 14, %[r]\n"
-        "v_sub_u32_e32 %[r], %[n], %[r]"
-        : [r] "=&v"(r) : [n] "v"(n), [a] "v"(a), [e] "v"(e), [half] "v"(8192));
-    return r;
-}
+// What follows from a value up to the addresses of the next channel's two table cells, in one piece with the pick (the compiler
+// waits after every piece that is written out by itself): e = 256 x - m of the value, the next effective mean as
+// -1 - n = mean - rsh14_mul(a, e), the window (w and b2, its base), and from the positions u0 and u of the thread's
+// edges there (edge_pos) the cells' places in the table, w and d.
+#define PILC_ROW_AIM                                                                        \
+    "v_add3_u32 %[e], %[x], %[base], %[n]\n"                                               \
+    "v_mad_i32_i24 %[w], %[a], %[e], %[half]\n"                                            \
+    "v_ashrrev_i32_e32 %[w], 14, %[w]\n"                                                   \
+    "v_sub_u32_e32 %[d], %[mean], %[w]\n"                                                  \
+    "v_sub_u32_e32 %[w], %[centre], %[d]\n"                                                \
+    "v_and_b32_e32 %[w], 0xffffff00, %[w]\n"                                               \
+    "v_med3_i32 %[b2], %[w], 0, %[most]\n"                                                 \
+    "v_add3_u32 %[d], %[d], %[edge], %[b2]\n"                                              \
+    "v_cvt_f64_i32_e32 %[y], %[d]\n"                                                       \
+    "v_fma_f64 %[y], %[y], %[unit], %[bias]\n"                                             \
+    "v_cvt_u32_f64_e32 %[u0], %[y]\n"                                                      \
+    "v_add_f64 %[y], %[y], %[per_k]\n"                                                     \
+    "v_cvt_u32_f64_e32 %[u], %[y]\n"                                                       \
+    "v_lshrrev_b32_e32 %[w], 18, %[u0]\n"                                                  \
+    "v_lshrrev_b32_e32 %[d], 18, %[u]\n"                                                   \
+    "v_and_b32_e32 %[w], 0x3ff8, %[w]\n"                                                   \
+    "v_and_b32_e32 %[d], 0x3ff8, %[d]"
+#define PILC_ROW_AIM_OUT [e] "=&v"(e), [w] "=&v"(w), [d] "=&v"(d), [b2] "=&v"(am.base), [y] "=&v"(y), [u0] "=&v"(am.u[0])
+#define PILC_ROW_AIM_IN                                                                     \
+    [base] "v"(cd.base), [n] "v"(n), [a] "v"(a), [half] "v"(8192), [mean] "v"(mean), [centre] "s"(kRowCentre),        \
+    [most] "v"(256 * kRowBaseMax), [edge] "v"(j_edge), [unit] "v"(per_unit), [bias] "s"(kEdgeBias), [per_k] "v"(per_k)
+// The window's base less the effective mean: the mean lies between its middle two candidates.
+constexpr int kRowCentre = -1 - (256 * (kRowWindow / 2 - 1) - 128);
+static_assert(sizeof(uint2[kSigEntries]) - sizeof(uint2) == 0x3ff8, "a position's upper 11 bits are its cell");
 
 // thread j of a row receives the value of thread j + 1 of the same row, the last one `last`
 __device__ __forceinline__ uint32_t row_next(uint32_t v, uint32_t last)
@@ -238,7 +259,7 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     };
     // The window of a symbol whose effective mean is -1 - n: its base times 256, whole and within 0 .. kRowBaseMax.
     auto window_base = [](int n) {
-        return min(max((-1 - (256 * (kRowWindow / 2 - 1) - 128) - n) & ~255, 0), 256 * kRowBaseMax);
+        return min(max((kRowCentre - n) & ~255, 0), 256 * kRowBaseMax);
     };
     auto put_stage = [&](const Raw &r, uint32_t buf) {
         RowPixel px;
@@ -326,31 +347,68 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     // and 1 (0 where the window does not hold the symbol), and in `s_new` the next state before it takes a word; `after_pick`:
     // S, at and wnext of rows with `act`.  What needs the value comes between the two, so that its table reads are under way.
     auto slot_in = [&](int base) { return (S & mask) - (((uint32_t)base >> 8) & 255u); };
-    auto pick = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new) {
-        uint32_t x, u;
-        unsigned long long m;
-        asm(PILC_ROW_PICK("s_nop 0\n", "s_nop 0\n", "s_nop 0\n", "s_nop 0\n") : PILC_ROW_PICK_OUT : PILC_ROW_PICK_IN : "vcc");
+    auto ask_cells = [&](RowAim &am, uint32_t w, uint32_t d) {
+        am.cell[0] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(sig) + w);
+        am.cell[1] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(sig) + d);
+    };
+    // the first channel, and from e of its value the second channel's aim; beside it thread `before` takes the three second bytes
+    // of the pixel before, pair and last, into v_out
+    auto pick_first = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new, int n, int a, int mean, double per_k,
+                          double per_unit, int &e, RowAim &am, uint32_t before, uint32_t pair, uint32_t last, uint32_t &v_out) {
+        uint32_t x, u, w, d, rgb;
+        unsigned long long m, taker;
+        double y;
+        asm(PILC_ROW_PICK("v_cmp_eq_u32_e64 %[taker], %[j], %[before]\n", "v_perm_b32 %[rgb], %[last], %[pair], %[sel]\n",
+                          "v_cndmask_b32_e64 %[v_out], %[v_out], %[rgb], %[taker]\n", "s_nop 0\n") PILC_ROW_AIM
+            : PILC_ROW_PICK_OUT, PILC_ROW_AIM_OUT, [taker] "=&s"(taker), [rgb] "=&v"(rgb), [v_out] "+v"(v_out)
+            : PILC_ROW_PICK_IN, PILC_ROW_AIM_IN, [j] "v"(j), [before] "s"(before), [last] "v"(last), [pair] "v"(pair),
+              [sel] "s"(0x0C050100u)
+            : "vcc");
+        am.u[1] = u;
+        ask_cells(am, w, d);
         return x;
     };
-    // the same, and n - rsh14_mul(a, e) into n
-    auto pick_beside_shift = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new, int &n, int a, int e) {
-        uint32_t x, u;
+    // the second channel, and what the first says of the third's mean (a2, e2) on the way to the third's aim
+    auto pick_second = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new, int n, int a, int mean, int a2, int e2,
+                           double per_k, double per_unit, RowAim &am) {
+        uint32_t x, u, w, d;
         unsigned long long m;
-        int r;
-        asm(PILC_ROW_PICK("v_mad_i32_i24 %[r], %[a], %[e], %[half]\n", "v_ashrrev_i32_e32 %[r], 14, %[r]\n",
-                          "v_sub_u32_e32 %[r], %[n], %[r]\n", "s_nop 0\n")
-            : PILC_ROW_PICK_OUT, [r] "=&v"(r) : PILC_ROW_PICK_IN, [n] "v"(n), [a] "v"(a), [e] "v"(e), [half] "v"(8192) : "vcc");
-        n = r;
+        double y;
+        int e;
+        asm(PILC_ROW_PICK("v_mad_i32_i24 %[e2], %[a2], %[e2], %[half]\n", "v_ashrrev_i32_e32 %[e2], 14, %[e2]\n",
+                          "v_sub_u32_e32 %[mean], %[mean], %[e2]\n", "s_nop 0\n") PILC_ROW_AIM
+            : PILC_ROW_PICK_OUT, PILC_ROW_AIM_OUT, [mean] "+v"(mean), [e2] "+v"(e2)
+            : PILC_ROW_PICK_IN, [base] "v"(cd.base), [n] "v"(n), [a] "v"(a), [a2] "v"(a2), [half] "v"(8192), [centre] "s"(kRowCentre),
+              [most] "v"(256 * kRowBaseMax), [edge] "v"(j_edge), [unit] "v"(per_unit), [bias] "s"(kEdgeBias), [per_k] "v"(per_k)
+            : "vcc");
+        am.u[1] = u;
+        ask_cells(am, w, d);
         return x;
     };
-    // the same, and the second bytes of lo and hi as the two lowest of `pair`
-    auto pick_beside_pair = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new, uint32_t lo, uint32_t hi,
-                                uint32_t &pair) {
-        uint32_t x, u, r;
+    // the third channel; beside it the second bytes of lo and hi as the two lowest of `pair`, p & q of the first two channels and,
+    // of what the stager left for the next pixel's first, the masses
+    auto pick_third = [&](const RowCand &cd, uint32_t slot, uint32_t q, uint32_t &s_new, uint32_t lo, uint32_t hi, uint32_t &pair,
+                          uint2 next, uint2 &next_f, uint32_t p0, uint32_t p1, uint32_t &both) {
+        uint32_t x, u, r, b;
         unsigned long long m;
-        asm(PILC_ROW_PICK("v_perm_b32 %[r], %[hi], %[lo], %[sel]\n", "s_nop 0\n", "s_nop 0\n", "s_nop 0\n")
-            : PILC_ROW_PICK_OUT, [r] "=&v"(r) : PILC_ROW_PICK_IN, [lo] "v"(lo), [hi] "v"(hi), [sel] "s"(0x0C0C0501u) : "vcc");
+        if (kStaged) {
+            uint32_t g0, g1;
+            asm(PILC_ROW_PICK("v_perm_b32 %[r], %[hi], %[lo], %[sel]\n", "v_lshrrev_b32_e32 %[g0], 16, %[h0]\n",
+                              "v_lshrrev_b32_e32 %[g1], 16, %[h1]\n", "v_and_b32_e32 %[b], %[p0], %[p1]\n")
+                : PILC_ROW_PICK_OUT, [r] "=&v"(r), [g0] "=&v"(g0), [g1] "=&v"(g1), [b] "=&v"(b)
+                : PILC_ROW_PICK_IN, [lo] "v"(lo), [hi] "v"(hi), [sel] "s"(0x0C0C0501u), [h0] "v"(next.x), [h1] "v"(next.y),
+                  [p0] "v"(p0), [p1] "v"(p1)
+                : "vcc");
+            next_f = make_uint2(g0, g1);
+        } else {
+            asm(PILC_ROW_PICK("v_perm_b32 %[r], %[hi], %[lo], %[sel]\n", "v_and_b32_e32 %[b], %[p0], %[p1]\n", "s_nop 0\n", "s_nop 0\n")
+                : PILC_ROW_PICK_OUT, [r] "=&v"(r), [b] "=&v"(b)
+                : PILC_ROW_PICK_IN, [lo] "v"(lo), [hi] "v"(hi), [sel] "s"(0x0C0C0501u), [p0] "v"(p0), [p1] "v"(p1)
+                : "vcc");
+            next_f = make_uint2(0u, 0u);
+        }
         pair = r;
+        both = b;
         return x;
     };
     auto after_pick = [&](bool act, uint32_t s_new) {
@@ -522,6 +580,8 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
             // One pixel: `cur` holds its parameters (read from LDS a pixel ago), `nxt` receives the
             // next pixel's, and `cr` enters with this pixel's first-channel candidates and leaves
             // with the next pixel's.
+            // of the pixel before, until thread i - 1 takes them: the first two values, and the third times 256
+            uint32_t pair = 0, x_b = 0;
             auto pixel = [&](uint32_t i, const RowPixel &cur, RowPixel &nxt, RowCand &cr) {
                 const bool act = i < nb;
                 nxt = px[(i + 1u) & (kRowBatch - 1)];
@@ -530,13 +590,14 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
                 const int n_r = (int)cur.r.x, n_g = (int)cur.r.y, n_b = (int)cur.r.z;
                 const int a_gr = (int)cur.s.x, a_br = (int)cur.s.y, a_bg = (int)cur.s.z;
                 const uint32_t S0 = S, at0 = at;
-                uint32_t s_new, pair;
+                uint32_t s_new, both;
 
-                const uint32_t p_r = pick(cr, slot_in(cr.base), S >> m_bits, s_new);
-                const uint32_t x_r = (uint32_t)cr.base + p_r;
-                const int e_r = (int)x_r + n_r;
-                RowAim ag = aim(minus_rsh14_mul(n_g, a_gr, e_r), cur.g[0], cur.g[1]);
+                RowAim ag, ab;
+                int e_r;
+                const uint32_t p_r = pick_first(cr, slot_in(cr.base), S >> m_bits, s_new, n_r, a_gr, n_g, cur.g[0], cur.g[1],
+                                                e_r, ag, i - 1u, pair, x_b, v_out);
                 __builtin_amdgcn_sched_barrier(0);
+                const uint32_t x_r = (uint32_t)cr.base + p_r;
                 after_pick(act, s_new);
                 aimed(ag);
                 const uint32_t slot_g = slot_in(ag.base), q_g = S >> m_bits;
@@ -546,28 +607,26 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
                 if (!kStaged) an = aim_first(nxt);
                 __builtin_amdgcn_sched_barrier(0);
                 const RowCand cg = finish(ag);
-                int nb1 = n_b;
-                const uint32_t p_g = pick_beside_shift(cg, slot_g, q_g, s_new, nb1, a_br, e_r);
-                const uint32_t x_g = (uint32_t)cg.base + p_g;
-                RowAim ab = aim(minus_rsh14_mul(nb1, a_bg, (int)x_g + n_g), cur.b[0], cur.b[1]);
+                const uint32_t p_g = pick_second(cg, slot_g, q_g, s_new, n_g, a_bg, n_b, a_br, e_r, cur.b[0], cur.b[1], ab);
                 __builtin_amdgcn_sched_barrier(0);
+                const uint32_t x_g = (uint32_t)cg.base + p_g;
                 after_pick(act, s_new);
                 aimed(ab);
                 const uint32_t slot_b = slot_in(ab.base), q_b = S >> m_bits;
                 __builtin_amdgcn_sched_barrier(0);
-                if (kStaged) {
-                    cr = first_channel(next_pair, nxt.r.w);
-                } else {
+                if (!kStaged) {
                     cr = finish(an);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 const RowCand cb = finish(ab);
-                const uint32_t p_b = pick_beside_pair(cb, slot_b, q_b, s_new, x_r, x_g, pair);
-                const uint32_t x_b = (uint32_t)cb.base + p_b;
+                uint2 next_f;
+                const uint32_t p_b = pick_third(cb, slot_b, q_b, s_new, x_r, x_g, pair, next_pair, next_f, p_r, p_g, both);
+                if (kStaged)
+                    cr = RowCand{next_pair.x & 0xFFFFu, next_pair.y & 0xFFFFu, next_f.x, next_f.y, (int)nxt.r.w};
+                x_b = (uint32_t)cb.base + p_b;
                 after_pick(act, s_new);
-                uint32_t rgb = __builtin_amdgcn_perm(x_b, pair, 0x0C050100u);  // and the second byte of the third
 
-                bool bad = (p_r & p_g & p_b & 1u) == 0u;
+                bool bad = (both & p_b & 1u) == 0u;
                 if (kRagged) bad = bad && act;
                 if (__builtin_expect(__any(bad), 0)) {
                     // the pixel once more, from the state at its start, for the rows that need it
@@ -576,20 +635,22 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
                     if (bad) {
                         S = Sr;
                         at = pr;
-                        rgb = y_r | (y_g << 8) | (y_b << 16);
+                        pair = y_r | (y_g << 8);
+                        x_b = y_b << 8;
                     }
                     wnext = flat_words[at];
                     ++redone;
                 }
-                v_out = j == i ? rgb : v_out;
             };
             RowPixel pe = px[0], po;
             RowCand cr = kStaged ? first_channel(first_cand[buf][lrow][0][j], pe.r.w)
                                  : finish(aim_first(pe));
-            for (uint32_t i = 0; kRagged ? __any(i < nb) : i < (uint32_t)kRowBatch; i += 2) {
+            uint32_t i = 0;
+            for (; kRagged ? __any(i < nb) : i < (uint32_t)kRowBatch; i += 2) {
                 pixel(i, pe, po, cr);
                 pixel(i + 1u, po, pe, cr);
             }
+            v_out = j == i - 1u ? __builtin_amdgcn_perm(x_b, pair, 0x0C050100u) : v_out;
             if (redone >= (uint32_t)kRowRedoLimit) search_batches = kRowSearchBatches;
         }
         pos += at - at_start;
