@@ -875,15 +875,15 @@ static bool lanes_line_up(const Geo &g, const pilc_params *p)
 // The few-lane kernels pay off while there are too few lanes to fill the chip with one thread
 // each (256 CUs x 4 SIMDs x 64 threads = 65,536 threads for a single wave per SIMD).
 // Encoder: by then the block encoder's time goes with the number of pixels and the other's with a lane's chunks, so where they meet
-// depends on what a chunk costs there.  Block against thread per lane, us:
-//   lanes of whole lines (1.25 against 2.02 ms at 25,000 lanes of 2048 pixels, 1.57 and 1.91 at 37,800 of 1920, 1.14 and
-//   1.08 at 50,000 of 1024; 40,960 of 64 106 and 104, of 128 161 and 165, of 256 254 and 284) and rows that do not align
-//   (tiles of 16 x 16 at 40,960 lanes 241 and 250, of 10 x 10 0.89, flat lanes of 72 1.05) near 40,960, in tiles of at
-//   most 64 pixels earlier (8 x 8: 34,816 96 and 94, 40,960 104 and 95);
-//   other aligned rows, whose lines neighbouring lanes share, near 32,768 (tiles of 16 x 16: 30,720 200 and 206,
-//   32,768 208 and 212, 34,816 217 and 207, 40,960 241 and 208; of 8 x 16 30,720 127 and 124, 40,960 153 and 126; of 32 x
-//   32 at 40,960 850 and 735; flat lanes of 96 at 32,768 0.99, 40,960 1.14; latest tiles of 8 x 24, near 38,000);
-//   lanes of some 40 pixels and fewer below 28,672 (of 32: 26,000 62 and 57, 40,960 76 and 64).
+// depends on what a chunk costs there.  Block against thread per lane, us (2^M = 8192):
+//   rows that align: flat lanes of 32 28,672 53 and 54, 32,768 56 and 56, 40,960 64 and 59; of 64 40,960 83 and 85, 49,152
+//   93 and 84; of 96 36,864 96 and 100, 40,960 101 and 100; tiles of 8 x 16 36,864 110 and 113, 40,960 117 and
+//   114; of 16 x 16 32,768 150 and 182, 40,960 172 and 185, 49,152 211 and 184; of 32 x 32 40,960 568 and 642, 49,152 667 and 640;
+//   rows that do not, where the other's chunks straddle lines and the last one of a row is a short one: tiles of 8 x 8 40,800 82 and
+//   91, 48,960 92 and 91; flat lanes of 99 57,344 135 and 138, 65,536 145 and 133; tiles of 10 x 10 57,120 130 and 161; of 16 x
+//   16 65,520 266 and 266, 81,840 317 and 336, 98,160 381 and 350; and in lanes of 512 pixels and more latest: 30 x 20 98,160 780
+//   and 894, 114,480 898 and 908, 131,040 1023 and 974; of 32 x 32 131,040 1657 and 1817; flat lanes of 777 131,072 1344 and 1636.
+// The lines of the smaller lanes lie below where the two meet now, at 1.1 to 1.2 of the better time where that is furthest off.
 static bool use_few_lane_encoder(const Geo &g, bool aligned, bool lines)
 {
     const int policy = g_kernel_policy.load(std::memory_order_relaxed);
@@ -893,6 +893,7 @@ static bool use_few_lane_encoder(const Geo &g, bool aligned, bool lines)
     const uint32_t pixels = max_lane_symbols(g) / 3u;
     if (pixels <= 40u) return g.lanes <= 28672u;
     if (aligned && !lines) return g.lanes <= 32768u;
+    if (!aligned && pixels >= 512u) return g.lanes <= 114688u;
     return g.lanes <= (aligned || pixels > 64u ? 40960u : 36864u);
 }
 

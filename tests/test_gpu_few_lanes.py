@@ -67,6 +67,29 @@ def test_encoder_takes_blocks_up_to_its_line(h, w, mode, a, b, line):
         assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
 
 
+# Lanes of 512 pixels and more whose rows do not align stay with the block encoder for longer: tiles of 16 x 33, four a row
+# of images of 16 x 129 (the last one 30 wide), on both sides of the line; the container is the same as the other encoder's.
+@pytest.mark.parametrize("over", [0, 1])
+def test_encoder_line_of_long_lanes_that_do_not_align(over):
+    n = 114688 // 4 + over
+    rng = np.random.default_rng(over)
+    wl = synth.make_random_case(over, 1, 16, 129, 12, 1, 16, 33)
+    wl.n = n
+    wl.img = rng.integers(0, 256, size=(n, 16, 129, 3), dtype=np.uint8)
+    wl.mu = wl.img.astype(np.uint16) << 8
+    wl.log_scale = np.zeros(wl.img.shape, dtype=np.int16)
+    wl.chan_coef = np.zeros((n, 3), dtype=np.int16)
+    d = DeviceWorkload(wl)
+    assert ("k_encode_block" in _kernels(d.encode)) == (over == 0)
+    got = d.coded_numpy().copy()
+    pb.pilc_set_kernel_policy(1 if over == 0 else 2)
+    try:
+        d.encode()
+        assert np.array_equal(d.coded_numpy(), got)
+    finally:
+        pb.pilc_set_kernel_policy(0)
+
+
 # Batches of 20, 12 and 8 pixels (one workgroup on a compute unit, two, more): lanes of one pixel, of one less and more than
 # a batch, of several; masses from 1 to 2^M - 255, states at both ends of what a mass renormalises.
 @pytest.mark.parametrize("prec_bits", [10, 16])
