@@ -294,6 +294,10 @@ __global__ void k_scan_apply(uint32_t items, ItemBytes bytes, const uint32_t *__
 // --------------------------------------------------------------------------------------------
 constexpr int kPackMaxLanes = 256;
 constexpr uint32_t kPackBlocks = 1024, kPackLeast = 512;
+// So few lanes a workgroup: lanes of a thousand symbols and more, moved eight words a thread (a word a thread before; bound by the
+// number of loads and stores: 214 MB in 75 us on 3125 lanes of 16,384 pixels, in 38 now).  Whole calls, us: those 1055 and 1021, 3000 of 4096
+// 282 and 274, 4864 of 512 94 and 90, 4080 tiles of 32 x 32 105 and 102.
+constexpr uint32_t kPackLongLanes = 16;
 
 __global__ __launch_bounds__(kScanThreads) void k_pack(Geo g, uint32_t lanes_per_block,
                                                        const uint16_t *__restrict__ scratch,
@@ -324,6 +328,31 @@ __global__ __launch_bounds__(kScanThreads) void k_pack(Geo g, uint32_t lanes_per
     __syncthreads();
     const uint32_t w_begin = s_off[0] >> 1, w_end = s_off[n] >> 1;
     if (w_begin == w_end) return;
+    if (lanes_per_block <= kPackLongLanes) {
+        // long lanes: eight words a thread at whatever address they fall on, a wavefront a lane, or the whole workgroup where it
+        // has fewer than four; a lane's last eight are moved as such, whether or not some of them have been already
+        const uint32_t team = n < 4u ? blockDim.x : 64u, member = threadIdx.x & (team - 1u);
+        for (uint32_t l = n < 4u ? 0u : threadIdx.x >> 6; l < n; l += n < 4u ? 1u : blockDim.x >> 6) {
+            const uint32_t words = ((s_off[l + 1] - s_off[l]) >> 1) - 2u;  // (after the state)
+            const uint16_t *from = scratch + s_src[l];
+            uint16_t *to = payload + (s_off[l] >> 1);
+            if (member < 2u) to[member] = (uint16_t)(s_state[l] >> (16u * member));
+            to += 2;
+            if (words < 8u) {
+                if (member < words) to[member] = from[member];
+                continue;
+            }
+            for (uint32_t j = 8u * member; j < words; j += 16u * team) {
+                const uint32_t at[2] = {min(j, words - 8u), min(j + 8u * team, words - 8u)};
+                u32x4 v[2];
+                __builtin_memcpy(&v[0], from + at[0], 16);
+                __builtin_memcpy(&v[1], from + at[1], 16);
+                __builtin_memcpy(to + at[0], &v[0], 16);
+                __builtin_memcpy(to + at[1], &v[1], 16);
+            }
+        }
+        return;
+    }
     // four words per thread and turn, so that four loads are under way together (words past the
     // end read the last one again and are not written)
     for (uint32_t w0 = w_begin + threadIdx.x; w0 - threadIdx.x < w_end; w0 += 4u * blockDim.x) {

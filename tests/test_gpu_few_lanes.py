@@ -108,3 +108,25 @@ def test_block_encoder_at_the_edges_of_its_batches(groups, pixels, wild, prec_bi
         assert "k_encode_block" in _kernels(d.encode)
         got = d.coded_numpy()
         assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+
+
+# The packer of long lanes, eight words at a time: lanes of no words, of one to nine and of many side by side, one, two and
+# several of them a workgroup.
+@pytest.mark.parametrize("lanes,pixels", [(70, 400), (70, 6000), (2300, 400), (5000, 400)])
+def test_packer_of_long_lanes(lanes, pixels):
+    wl = synth.make_random_case(pixels, lanes, 1, pixels, 16, 0, pixels)
+    rng = np.random.default_rng(pixels)
+    wl.mu[...] = wl.img.astype(np.uint16) * 256
+    wl.log_scale[...] = -16384
+    for lane in range(lanes):  # a pixel off its mean takes about a word
+        far = rng.choice(pixels, size=min(pixels, lane % 70 if lane % 70 < 40 else 17 * (lane % 70)), replace=False)
+        wl.mu[lane, 0, far, 0] ^= 0x4000
+    wl.chan_coef[...] = 0
+    rc, want = orc.encode(orc.make_geom(*wl.geom), wl.img, wl.mu, wl.log_scale, wl.chan_coef)
+    assert rc == orc.OK
+    d = DeviceWorkload(wl)
+    assert "k_pack" in _kernels(d.encode)
+    got = d.coded_numpy()
+    assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+    words = np.diff(want[64:64 + 4 * (lanes + 1)].view("<u4").astype(np.int64)) // 2 - 2
+    assert words.min() < 8 <= words.max()
