@@ -29,69 +29,6 @@ struct Chunk {
 __device__ __forceinline__ int byte_of(const uint32_t *w, int i) { return (w[i >> 2] >> (8 * (i & 3))) & 0xFF; }
 __device__ __forceinline__ int half_of(const uint32_t *w, int i) { return (w[i >> 1] >> (16 * (i & 1))) & 0xFFFF; }
 
-// Fills `c` with the pixels p .. p+len-1 (len <= 8).  kVec: p is a multiple of 8 and the arrays
-// are 16-byte aligned, so a full chunk is 3 x 8 bytes of pixels and 3 x 16 bytes of each parameter.
-// Otherwise the same loads at whatever address they fall on, also for a row's last pixels, which are followed by other
-// pixels' values that nobody looks at; one by one only where eight pixels would reach past the
-// array's end (`total_px`).  (One by one everywhere, 72 loads of one or two bytes a chunk were what such batches
-// waited for: 8 images of 1365 x 2047 in tiles 733 -> 383 us to decode, 681 -> 376 to encode.)
-template <bool kVec, bool kPixels>
-__device__ __forceinline__ void load_chunk(Chunk &c, uint32_t p, uint32_t len, uint32_t total_px,
-                                           const uint8_t *__restrict__ img,
-                                           const uint16_t *__restrict__ mu,
-                                           const int16_t *__restrict__ ls)
-{
-    const size_t s = (size_t)p * 3;
-    if (kVec ? len == (uint32_t)kChunk : total_px - p >= (uint32_t)kChunk) {
-        uint32_t wm[12], wl[12];
-        if (kVec) {
-            const uint4 *pm = reinterpret_cast<const uint4 *>(mu + s);
-            const uint4 *pl = reinterpret_cast<const uint4 *>(ls + s);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const uint4 a = pm[q], b = pl[q];
-                wm[4 * q] = a.x; wm[4 * q + 1] = a.y; wm[4 * q + 2] = a.z; wm[4 * q + 3] = a.w;
-                wl[4 * q] = b.x; wl[4 * q + 1] = b.y; wl[4 * q + 2] = b.z; wl[4 * q + 3] = b.w;
-            }
-        } else {
-            __builtin_memcpy(wm, mu + s, 48);
-            __builtin_memcpy(wl, ls + s, 48);
-        }
-        uint32_t wx[6] = {0, 0, 0, 0, 0, 0};
-        if (kPixels) {
-            if (kVec) {
-                const uint2 *px = reinterpret_cast<const uint2 *>(img + s);
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    const uint2 a = px[q];
-                    wx[2 * q] = a.x; wx[2 * q + 1] = a.y;
-                }
-            } else {
-                __builtin_memcpy(wx, img + s, 24);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i)
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                if (kPixels) c.x[i][ch] = byte_of(wx, 3 * i + ch);
-                c.m[i][ch] = half_of(wm, 3 * i + ch);
-                c.l[i][ch] = (int)(short)half_of(wl, 3 * i + ch);
-            }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i)
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                const bool in = (uint32_t)i < len;
-                const size_t e = in ? s + 3 * i + ch : s;
-                if (kPixels) c.x[i][ch] = img[e];
-                c.m[i][ch] = mu[e];
-                c.l[i][ch] = ls[e];
-            }
-    }
-}
-
 // The 8 pixels held in the words wx (6 dwords of pixels), wm and wl (12 dwords each) into `c`.
 template <bool kPixels>
 __device__ __forceinline__ void unpack_chunk(Chunk &c, const uint32_t *wx, const uint32_t *wm,
@@ -105,6 +42,71 @@ __device__ __forceinline__ void unpack_chunk(Chunk &c, const uint32_t *wx, const
             c.m[i][ch] = half_of(wm, 3 * i + ch);
             c.l[i][ch] = (int)(short)half_of(wl, 3 * i + ch);
         }
+}
+
+// Fills `c` with the pixels p .. p+len-1 (len <= 8).  kVec: p is a multiple of 8 and the arrays
+// are 16-byte aligned, so a full chunk is 3 x 8 bytes of pixels and 3 x 16 bytes of each parameter.
+// Otherwise the same loads at whatever address they fall on, also for a row's last pixels, which are followed by other
+// pixels' values that nobody looks at; one by one only where eight pixels would reach past the
+// array's end (`total_px`).  (One by one everywhere, 72 loads of one or two bytes a chunk were what such batches
+// waited for: 8 images of 1365 x 2047 in tiles 733 -> 383 us to decode, 681 -> 376 to encode.)
+template <bool kVec, bool kPixels>
+__device__ __forceinline__ void load_chunk(Chunk &c, uint32_t p, uint32_t len, uint32_t total_px,
+                                           const uint8_t *__restrict__ img,
+                                           const uint16_t *__restrict__ mu,
+                                           const int16_t *__restrict__ ls)
+{
+    const size_t s = (size_t)p * 3;
+    uint32_t wx[6] = {0, 0, 0, 0, 0, 0}, wm[12] = {}, wl[12] = {};
+    if (kVec ? len == (uint32_t)kChunk : total_px - p >= (uint32_t)kChunk) {
+        if (kVec) {
+            const uint4 *pm = reinterpret_cast<const uint4 *>(mu + s);
+            const uint4 *pl = reinterpret_cast<const uint4 *>(ls + s);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const uint4 a = pm[q], b = pl[q];
+                wm[4 * q] = a.x; wm[4 * q + 1] = a.y; wm[4 * q + 2] = a.z; wm[4 * q + 3] = a.w;
+                wl[4 * q] = b.x; wl[4 * q + 1] = b.y; wl[4 * q + 2] = b.z; wl[4 * q + 3] = b.w;
+            }
+        } else {
+            __builtin_memcpy(wm, mu + s, 48);
+            __builtin_memcpy(wl, ls + s, 48);
+        }
+        if (kPixels) {
+            if (kVec) {
+                const uint2 *px = reinterpret_cast<const uint2 *>(img + s);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const uint2 a = px[q];
+                    wx[2 * q] = a.x; wx[2 * q + 1] = a.y;
+                }
+            } else {
+                __builtin_memcpy(wx, img + s, 24);
+            }
+        }
+    } else if (!kVec && kPixels) {
+        // into the same words, so that the two ways meet in 30 registers and not in 72
+#pragma unroll
+        for (int e = 0; e < 3 * kChunk; ++e) {
+            const size_t at = s + ((uint32_t)e < 3u * len ? e : 0);
+            wx[e >> 2] |= (uint32_t)img[at] << (8 * (e & 3));
+            wm[e >> 1] |= (uint32_t)mu[at] << (16 * (e & 1));
+            wl[e >> 1] |= (uint32_t)(uint16_t)ls[at] << (16 * (e & 1));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kChunk; ++i)
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const bool in = (uint32_t)i < len;
+                const size_t e = in ? s + 3 * i + ch : s;
+                if (kPixels) c.x[i][ch] = img[e];
+                c.m[i][ch] = mu[e];
+                c.l[i][ch] = ls[e];
+            }
+        return;
+    }
+    unpack_chunk<kPixels>(c, wx, wm, wl);
 }
 
 // Two neighbouring chunks (16 pixels from p, a multiple of 16) as raw words: 96 bytes of each
@@ -379,7 +381,12 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
             const ChunkPos cp = chunk_pos(g, sh, per_row, c);
             Chunk ck;
             load_chunk<kVec, true>(ck, cp.p, cp.len, g.total_px, img, mu, ls);
-            if (__all(cp.len == (uint32_t)kChunk))
+            // Rows that do not align have one copy of the code, for chunks of any length: with one for whole chunks beside it they
+            // take 150 registers for 124, three wavefronts a SIMD for four.  Policy 1, us, two copies and one: tiles of 10 x 10
+            // 66,000 lanes 190 and 182, 262,080 375 and 331; of 7 x 13 262,080 296 and 262, 499,950 506 and 460; flat lanes of 100
+            // 500,000 660 and 616, of 5 86 and 83.  (Aligned rows are not ahead with fewer: tiles of 8 x 24 at 114,984
+            // lanes 274 with 138 registers, 287 with 93.)
+            if (kVec && __all(cp.len == (uint32_t)kChunk))
                 encode_chunk(ck, cp, std::true_type{});
             else
                 encode_chunk(ck, cp, std::false_type{});

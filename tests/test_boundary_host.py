@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import re
 
+import msgpack
 import pytest
 
 from paper_2206_05279_amd import binding as pb
@@ -31,6 +32,25 @@ def test_library_was_built_from_the_current_sources():
     from paper_2206_05279_amd import build
     pb.lib()
     assert build.built_digest() == build.source_digest(), "run python -m paper_2206_05279_amd.build"
+
+
+def _registers():
+    """What the library's code object says of its kernels: {name: (vector registers, bytes of private memory)}."""
+    blob = open(pb.LIB_PATH, "rb").read()
+    at = blob.index(b"AMDGPU\0\0\x83\xaeamdhsa.kernels")  # a note's name, padded, and its contents in MessagePack
+    size = int.from_bytes(blob[at - 8:at - 4], "little")
+    kernels = msgpack.unpackb(blob[at + 8:at + 8 + size])["amdhsa.kernels"]
+    return {k[".name"]: (k[".vgpr_count"], k[".private_segment_fixed_size"]) for k in kernels}
+
+
+# Template arguments of a kernel and the wavefronts a SIMD that its registers leave room for (of 512 in all, eight at a time).
+@pytest.mark.parametrize("kernel,waves", [
+    ("k_encode_lanesILb0ELb0ELb0ELb0E", 4), ("k_encode_lanesILb0ELb1ELb1ELb0E", 4), ("k_encode_lanesILb0ELb1ELb1ELb1E", 3),
+    ("k_decode_lanesILb0ELb0E", 4), ("k_decode_lanesILb1ELb0E", 4), ("k_decode_lanesILb1ELb1E", 4)])
+def test_wavefronts_of_the_lane_kernels(kernel, waves):
+    pb.lib()
+    found = [v for name, (v, _) in _registers().items() if kernel in name]
+    assert found and all(512 // (-(-v // 8) * 8) >= waves for v in found), found
 
 
 def test_version_and_messages():
