@@ -53,6 +53,13 @@ def test_wavefronts_of_the_lane_kernels(kernel, waves):
     assert found and all(512 // (-(-v // 8) * 8) >= waves for v in found), found
 
 
+def test_lane_kernels_keep_nothing_in_private_memory():
+    pb.lib()
+    kernels = {n: private for n, (_, private) in _registers().items()
+               if any(k in n for k in ("k_encode_lanesILb0", "k_decode_lanes", "k_encode_block", "k_decode_rows"))}
+    assert len(kernels) >= 17 and not any(kernels.values()), kernels
+
+
 def test_version_and_messages():
     assert pb.pilc_version() == 1
     for code in range(-7, 1):
