@@ -910,8 +910,11 @@ static bool lanes_line_up(const Geo &g, const pilc_params *p)
 //   114; of 16 x 16 32,768 150 and 182, 40,960 172 and 185, 49,152 211 and 184; of 32 x 32 40,960 568 and 642, 49,152 667 and 640;
 //   rows that do not, where the other's chunks straddle lines and the last one of a row is a short one: tiles of 8 x 8 40,800 82 and
 //   91, 48,960 92 and 91; flat lanes of 99 57,344 135 and 138, 65,536 145 and 133; tiles of 10 x 10 57,120 130 and 161; of 16 x
-//   16 65,520 266 and 266, 81,840 317 and 336, 98,160 381 and 350; and in lanes of 512 pixels and more latest: 30 x 20 98,160 780
-//   and 894, 114,480 898 and 908, 131,040 1023 and 974; of 32 x 32 131,040 1657 and 1817; flat lanes of 777 131,072 1344 and 1636.
+//   16 65,520 266 and 266, 81,840 317 and 336, 98,160 381 and 350; and in lanes of 512 pixels and more latest: 30 x 20 98,000 725
+//   and 856, 114,000 825 and 901; 32 x 32 114,000 1361 and 1651; flat lanes of 515 114,000 767 and 936, of 777 1090 and 1477; 35 x 15
+//   114,000 742 and 742; 74 x 7 98,000 644 and 729, 114,000 732 and 756; but in tiles of one or two whole chunks a row,
+//   which waste nothing thread per lane, sooner: 64 x 8 80,000 531 and 574, 89,000 578 and 585, 97,000 618 and 597, 113,000 706 and 620;
+//   96 x 8 90,000 829 and 903, 114,000 1019 and 969; 32 x 16 89,000 579 and 622, 105,000 666 and 651, 113,000 711 and 664.
 // The lines of the smaller lanes lie below where the two meet now, at 1.1 to 1.2 of the better time where that is furthest off.
 static bool use_few_lane_encoder(const Geo &g, bool aligned, bool lines)
 {
@@ -922,7 +925,8 @@ static bool use_few_lane_encoder(const Geo &g, bool aligned, bool lines)
     const uint32_t pixels = max_lane_symbols(g) / 3u;
     if (pixels <= 40u) return g.lanes <= 28672u;
     if (aligned && !lines) return g.lanes <= 32768u;
-    if (!aligned && pixels >= 512u) return g.lanes <= 114688u;
+    if (!aligned && pixels >= 512u)
+        return g.lanes <= (g.lane_mode == 1u && (g.lane_b == 8u || g.lane_b == 16u) ? 92160u : 114688u);
     return g.lanes <= (aligned || pixels > 64u ? 40960u : 36864u);
 }
 

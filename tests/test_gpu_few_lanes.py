@@ -90,6 +90,29 @@ def test_encoder_line_of_long_lanes_that_do_not_align(over):
         pb.pilc_set_kernel_policy(0)
 
 
+# Tiles of one or two whole chunks a row leave it sooner: tiles of 64 x 8, two an image of 64 x 9, and of 32 x 16, two of 32 x 17.
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("h,w,a,b", [(64, 9, 64, 8), (32, 17, 32, 16)])
+def test_encoder_line_of_long_lanes_in_whole_chunks(h, w, a, b, over):
+    n = 92160 // 2 + over
+    rng = np.random.default_rng(over)
+    wl = synth.make_random_case(over, 1, h, w, 12, 1, a, b)
+    wl.n = n
+    wl.img = rng.integers(0, 256, size=(n, h, w, 3), dtype=np.uint8)
+    wl.mu = wl.img.astype(np.uint16) << 8
+    wl.log_scale = np.zeros(wl.img.shape, dtype=np.int16)
+    wl.chan_coef = np.zeros((n, 3), dtype=np.int16)
+    d = DeviceWorkload(wl)
+    assert ("k_encode_block" in _kernels(d.encode)) == (over == 0)
+    got = d.coded_numpy().copy()
+    pb.pilc_set_kernel_policy(1 if over == 0 else 2)
+    try:
+        d.encode()
+        assert np.array_equal(d.coded_numpy(), got)
+    finally:
+        pb.pilc_set_kernel_policy(0)
+
+
 # Batches of 20, 12 and 8 pixels (one workgroup on a compute unit, two, more): lanes of one pixel, of one less and more than
 # a batch, of several; masses from 1 to 2^M - 255, states at both ends of what a mass renormalises.
 @pytest.mark.parametrize("prec_bits", [10, 16])
