@@ -153,3 +153,40 @@ def test_packer_of_long_lanes(lanes, pixels):
     assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
     words = np.diff(want[64:64 + 4 * (lanes + 1)].view("<u4").astype(np.int64)) // 2 - 2
     assert words.min() < 8 <= words.max()
+
+
+# What the second wavefront of the row decoder prepares goes as far as the longest lane of its wavefront: lanes of one pixel up to a
+# batch of 16 and two more, alone, beside lanes of one pixel (edge tiles), with a shorter last lane; with and without that wavefront.
+@pytest.mark.parametrize("lanes", [70, 5000])
+@pytest.mark.parametrize("px", [1, 3, 4, 5, 8, 12, 13, 15, 16, 17, 20, 31, 33])
+def test_row_decoder_on_short_lanes(px, lanes):
+    cases = [(lanes, 1, px, 0, px, 0), (lanes // 2, 1, px + 1, 1, 1, px), (lanes * px - px // 2, 1, 1, 0, px, 0)]
+    for i, (n, h, w, mode, a, b) in enumerate(cases):
+        wl = synth.make_random_case(px + i, n, h, w, 12, mode, a, b)
+        d = DeviceWorkload(wl)
+        d.encode()
+        assert "k_decode_rows" in _kernels(d.decode)
+        assert np.array_equal(d.decoded_numpy(), wl.img)
+
+
+# ... and a call with such lanes does not wait for pixels that they do not have (9.8 and 19.7 us; 15.1 when it did).
+def test_row_decoder_of_one_pixel_a_lane_is_sooner_than_of_a_batch():
+    times = []
+    for px in (1, 16):
+        wl = synth.make_random_case(px, 4096, 1, px, 12, 0, px)
+        wl.mu[...] = wl.img.astype(np.uint16) << 8  # (every symbol in its window: no search)
+        wl.log_scale[...] = 0
+        wl.chan_coef[...] = 0
+        d = DeviceWorkload(wl)
+        d.encode()
+        pb.pilc_set_timing(True)
+        try:
+            took = []
+            for _ in range(40):
+                d.decode()
+                took += [ms for name, ms in pb.pilc_last_timing() if name == "k_decode_rows"]
+        finally:
+            pb.pilc_set_timing(False)
+        times.append(1e3 * min(took))
+    print("a pixel a lane: %.1f us, 16: %.1f us" % tuple(times))
+    assert times[0] < 0.66 * times[1]
