@@ -1309,7 +1309,8 @@ int pilc_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t coded_by
     } else {
         const bool vec = chunks_aligned(g, img_out_dev, params);
         const bool pair = vec && chunks_pair_up(g, img_out_dev);
-        const bool one_side = g.lanes > compute_units() * 256u;  // more than a wavefront a SIMD (figures at the kernel)
+        // more than a wavefront a SIMD, or than two in long rows that do not align (figures at the kernel)
+        const bool one_side = g.lanes > compute_units() * (vec || (g.lane_mode == 1u ? g.lane_b : g.lane_a) <= 32u ? 256u : 512u);
         auto kern = one_side ? (pair ? k_decode_lanes<true, true, true> : vec ? k_decode_lanes<true, false, true> : k_decode_lanes<false, false, true>)
                              : (pair ? k_decode_lanes<true, true, false> : vec ? k_decode_lanes<true, false, false> : k_decode_lanes<false, false, false>);
         const int bt = lane_block_threads(g);

@@ -824,7 +824,10 @@ __device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below
 // instructions are what is waited for: 30 frames of 1080 x 1920 in tiles of 16 x 16 549 and 511 us, 8 images of 1365 x 2047 in
 // the same (88,064 lanes) 370 and 363, 16,384 images of 64 x 64 in tiles of 8 x 8 518 and 485, with a lane a row 616
 // and 597, 76,800 lanes of 64 109 and 106; up to there the wait is what counts: 65,472 lanes of 64 103 and 105, 38,400 95 and
-// 97, 65,536 tiles of 16 x 16 at 2^M = 1024 272 and 279.
+// 97, 65,536 tiles of 16 x 16 at 2^M = 1024 272 and 279.  Long rows that do not align wait for memory as much, also with
+// two wavefronts a SIMD: flat lanes of 100 67,000 165 and 163, 131,000 193 and 197, 139,000 214 and 207, 262,000 348 and 349;
+// of 250 80,000 442 and 447, 131,000 503 and 508, 139,000 585 and 585; of 500 67,000 822 and 830; tiles of 8 x 61 115,000 960
+// and 970; short ones do not: tiles of 24 x 24 67,000 851 and 847, of 7 x 13 154 and 152, of 10 x 10 197 and 192.
 template <bool kVec, bool kPair, bool kOneSide>
 __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_lanes(Geo g, const uint8_t *__restrict__ coded,
                                unsigned long long coded_bytes, const uint16_t *__restrict__ mu,

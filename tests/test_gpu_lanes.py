@@ -45,14 +45,14 @@ def test_guess_over_the_range_of_the_law(prec_bits, log_scale):
     _check(wl, DeviceWorkload(wl))
 
 
-# The same with more lanes than one wavefront a SIMD takes, where the decoder looks at one neighbour of the guessed edge: all
-# scales in one batch, chunks of single elements, of aligned eights and of pairs.
+# The same with more lanes than one wavefront a SIMD takes, where the decoder looks at one neighbour of the guessed edge (in
+# rows of more than 32 pixels that do not align: with more than two take): all scales in one batch, chunks of single elements, of aligned eights and of pairs.
 @pytest.mark.parametrize("prec_bits", [10, 13, 16])
-@pytest.mark.parametrize("lane", [3, 8, 16])
-def test_guess_with_many_lanes(prec_bits, lane):
-    n, h, w = 9, 16 * lane, 512
-    wl = synth.make_random_case(prec_bits, n, h, w, prec_bits, 0, lane, wild=True)
-    assert n * h * w // lane > 65536
+@pytest.mark.parametrize("lane,rows,mode", [(3, 16, 0), (8, 16, 0), (16, 16, 0), (3, 16, 1), (35, 16, 0), (35, 32, 0)])
+def test_guess_with_many_lanes(prec_bits, lane, rows, mode):
+    n, h, w = 9, rows * lane, 512
+    wl = synth.make_random_case(prec_bits, n, h, w, prec_bits, mode, 1 if mode else lane, lane, wild=True)
+    assert n * h * w // lane > 4096 * rows
     rng = np.random.default_rng(lane)
     wl.img[...] = np.arange(wl.img.size, dtype=np.uint32).reshape(wl.img.shape) % 256
     near = np.clip(wl.img * 256.0 + rng.normal(0, 700, wl.img.shape), 0, 65535)
