@@ -126,22 +126,28 @@ def test_division_from_the_smallest_to_the_largest_mass(prec_bits):
     _check(wl, DeviceWorkload(wl))
 
 
-# A lane of 2^25 symbols and more, whose words the thread-per-lane encoder's 32-bit places do not reach: the block encoder
-# takes it whatever the policy says.
-def test_encode_a_lane_longer_than_the_places_reach():
-    n, h, w = 1, 2900, 3900
-    rng = np.random.default_rng(5)
-    wl = synth.make_random_case(5, 1, 8, 8, 12, 0, n * h * w)
-    wl.n, wl.h, wl.w = n, h, w
-    assert 3 * n * h * w >= 1 << 25
-    wl.img = rng.integers(0, 256, size=(n, h, w, 3), dtype=np.uint8)
-    wl.mu = wl.img.astype(np.uint16) << 8
-    wl.log_scale = np.zeros(wl.img.shape, dtype=np.int16)
-    wl.chan_coef = np.zeros((n, 3), dtype=np.int16)
-    wl.lane_a = n * h * w
+# The longest lane that the thread-per-lane encoder takes, and one that is a pixel longer, which the block encoder takes whatever
+# the policy says.  Every symbol has a mass of 1 and costs a word of 16 bits, so that the words' 32-bit places are used up to their end.
+@pytest.mark.parametrize("pixels,policies,kernel", [
+    ((2**25 - 1) // 3, (1,), "k_encode_lanes"), ((2**25 - 1) // 3 + 1, (1, 3), "k_encode_block")])
+def test_longest_lane_thread_per_lane(pixels, policies, kernel):
+    wl = synth.make_random_case(5, 1, 8, 8, 16, 0, 64)
+    wl.h, wl.w, wl.lane_a = 1, pixels, pixels
+    wl.img = np.random.default_rng(5).integers(100, 250, size=(1, 1, pixels, 3), dtype=np.uint8)
+    wl.mu = np.zeros(wl.img.shape, dtype=np.uint16)
+    wl.log_scale = np.full(wl.img.shape, -16384, dtype=np.int16)
+    wl.chan_coef[...] = 0
     rc, want = orc.encode(orc.make_geom(*wl.geom), wl.img, wl.mu, wl.log_scale, wl.chan_coef)
-    assert rc == orc.OK
+    assert rc == orc.OK and want.size > 6 * pixels
     device = DeviceWorkload(wl)
-    _, nbytes = device.encode()
-    got = device.coded_numpy()
-    assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+    pb.pilc_set_timing(True)
+    try:
+        for policy in policies:
+            pb.pilc_set_kernel_policy(policy)
+            device.coded.zero_()
+            device.encode()
+            assert kernel in [name for name, _ in pb.pilc_last_timing()]
+            got = device.coded_numpy()
+            assert got.size == want.size and np.array_equal(got, want), first_difference(got, want)
+    finally:
+        pb.pilc_set_timing(False)
