@@ -112,8 +112,8 @@ def test_wide_laws_decode_without_a_search(log_scale):
     assert times[1] < 1.8 * times[0]
 
 
-# The division of the encoder's step: every mass from 1 up to the largest, at the precisions where quotients are smallest and
-# largest.  With the narrowest law and the mean on the pixel a symbol has nearly all of the mass, off it a single count.
+# The division of the encoder's step under masses of 1 up to the largest, at the precisions where quotients are smallest and
+# largest (test_division_arithmetic.py has every mass).  With the narrowest law and the mean on the pixel a symbol has nearly all of the mass, off it a single count.
 @pytest.mark.parametrize("prec_bits", [10, 11, 12, 16])
 def test_division_from_the_smallest_to_the_largest_mass(prec_bits):
     wl = synth.make_random_case(prec_bits, 4, 32, 40, prec_bits, 0, 320)
