@@ -294,10 +294,13 @@ __global__ void k_scan_apply(uint32_t items, ItemBytes bytes, const uint32_t *__
 // --------------------------------------------------------------------------------------------
 constexpr int kPackMaxLanes = 256;
 constexpr uint32_t kPackBlocks = 1024, kPackLeast = 512;
-// So few lanes a workgroup: lanes of a thousand symbols and more, moved eight words a thread (a word a thread before; bound by the
-// number of loads and stores: 214 MB in 75 us on 3125 lanes of 16,384 pixels, in 38 now).  Whole calls, us: those 1055 and 1021, 3000 of 4096
-// 282 and 274, 4864 of 512 94 and 90, 4080 tiles of 32 x 32 105 and 102.
-constexpr uint32_t kPackLongLanes = 16;
+// Up to so many lanes a workgroup they are moved a wavefront a lane, eight words a thread (a word a thread otherwise; bound by the
+// number of loads and stores: 214 MB in 75 us on 3125 lanes of 16,384 pixels, in 38 this way).  Those are lanes of a thousand symbols
+// and more, and in batches below some 17,400 lanes, which are cut into 1024 runs, nearly all others, where few of a wavefront's threads
+// have words to move, but it is no slower.  A word a thread and eight, this kernel, us: 500 lanes of 40 pixels 7.2 and 6.4; 2048 of 16
+// 8.5 and 8.3, of 32 8.3 and 7.8, of 64 8.3 and 8.2; 8192 of 16 9.2 and 8.9, of 64 9.7 and 8.8; 16,384 of 16 9.8 and 9.9, of 32 9.7
+// and 9.9, of 64 11.9 and 10.1, of 128 15.5 and 10.8; 4096 of 512 13.2 and 8.9.
+constexpr uint32_t kPackByWave = 16;
 
 __global__ __launch_bounds__(kScanThreads) void k_pack(Geo g, uint32_t lanes_per_block,
                                                        const uint16_t *__restrict__ scratch,
@@ -328,8 +331,8 @@ __global__ __launch_bounds__(kScanThreads) void k_pack(Geo g, uint32_t lanes_per
     __syncthreads();
     const uint32_t w_begin = s_off[0] >> 1, w_end = s_off[n] >> 1;
     if (w_begin == w_end) return;
-    if (lanes_per_block <= kPackLongLanes) {
-        // long lanes: eight words a thread at whatever address they fall on, a wavefront a lane, or the whole workgroup where it
+    if (lanes_per_block <= kPackByWave) {
+        // eight words a thread at whatever address they fall on, a wavefront a lane, or the whole workgroup where it
         // has fewer than four; a lane's last eight are moved as such, whether or not some of them have been already
         const uint32_t team = n < 4u ? blockDim.x : 64u, member = threadIdx.x & (team - 1u);
         for (uint32_t l = n < 4u ? 0u : threadIdx.x >> 6; l < n; l += n < 4u ? 1u : blockDim.x >> 6) {

@@ -1,5 +1,5 @@
-"""The few-lane kernels: a lane whose words do not fit 32 bits of bytes from the first one (2^27 symbols and more), and
-the numbers of lanes up to which they are taken."""
+"""The few-lane kernels: the longest lanes, the numbers of lanes up to which they are taken, the block encoder's batches, the
+packer behind it, short lanes in the row decoder."""
 import numpy as np
 import pytest
 import torch
@@ -133,9 +133,10 @@ def test_block_encoder_at_the_edges_of_its_batches(groups, pixels, wild, prec_bi
         assert d.nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
 
 
-# The packer of long lanes, eight words at a time: lanes of no words, of one to nine and of many side by side, one, two and
-# several of them a workgroup.
-@pytest.mark.parametrize("lanes,pixels", [(70, 400), (70, 6000), (2300, 400), (5000, 400)])
+# The packer that moves eight words at a time: lanes of no words, of one to nine and of many side by side, one, two and
+# several of them a workgroup; short lanes, of which a workgroup has up to 16, and on both sides of that.
+@pytest.mark.parametrize("lanes,pixels", [(70, 400), (70, 6000), (2300, 400), (5000, 400), (2048, 16), (2048, 32), (16384, 16),
+                                          (16384, 32), (17407, 24), (17408, 24)])
 def test_packer_of_long_lanes(lanes, pixels):
     wl = synth.make_random_case(pixels, lanes, 1, pixels, 16, 0, pixels)
     rng = np.random.default_rng(pixels)
