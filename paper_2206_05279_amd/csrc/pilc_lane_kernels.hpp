@@ -791,21 +791,22 @@ struct WordRing {
 
 // On from one of the two symbols that meet at edge `mid` to the one that holds `slot`, which is neither: an edge a step.
 // `below`, `mass`: of the symbol begun with and then of the one returned, the slots of its own below this one (negative
-// where the symbol is further down) and its mass.  Nearly always one step; two or three are
+// where the symbol is further down) and its mass; position(k): of edge k.  Nearly always one step; two or three are
 // rare while the mean is within the values of a pixel.  8 frames of 1080 x 1920 in tiles, by log-scale, us, against a search by
 // bisection for every symbol and one behind each guess that missed: 2^M = 1024: 3.4 326, 462, 579; 4.0 384, 461, 712; 4.6
 // 376, 460, 692; 5.5 370, 455, 586; 2^M = 4096: 4.0 312, 460, 480; guesses that are all good 281.  (Slower than
 // the search alone only where nothing is known of a pixel: scales of 150 and more with means hundreds away from
 // every value, 545 against 463.)
-__device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below, uint32_t &mass, uint32_t slot, double y, double a,
-                                                   uint32_t scale, uint32_t m_bits, const LdsTables &tab)
+template <class Position>
+__device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below, uint32_t &mass, uint32_t slot, uint32_t scale,
+                                                   uint32_t m_bits, const LdsTables &tab, Position position)
 {
     const bool down = (int)below < 0;
     uint32_t k = down ? mid - 1u : mid + 1u;  // the edge that was looked at last
     uint32_t c_near = slot - below + (down ? 0u : mass);
     do {
         k = down ? k - 1u : k + 1u;  // within 0 .. 256: C(0) = 0 <= slot < 2^M = C(256)
-        uint32_t c = cum_inner((int)k, __builtin_fma((double)(int)(k - mid), a, y), scale, tab);
+        uint32_t c = cum_inner((int)k, position(k), scale, tab);
         c = k == 0u ? 0u : c;
         c = k == 256u ? 1u << m_bits : c;
         below = slot - (down ? c : c_near);
@@ -905,10 +906,9 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
                     const uint32_t slot = S & mask;
                     // C at the edge where the symbol should begin or end, and at the one that it should have on the other
                     // side, or at both neighbours
-                    uint32_t mid, lo, c_lo, c_hi;
-                    double y, a;  // the position of `mid`, and what the next edge is away
+                    uint32_t lo, below, mass;
                     if (kOneSide) {
-                        mid = guide_edge<false>(slot, me, inv_s, 0, gs, guide);
+                        const uint32_t mid = guide_edge<false>(slot, me, inv_s, 0, gs, guide);
                         int from_mean = -128 - me;
                         asm("" : "+v"(from_mean));  // (formed before the guess is there)
                         const EdgeStep edge((int)(mid << 8) + from_mean, inv_s);
@@ -920,30 +920,35 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
                         c = other == 0u ? 0u : c;
                         c = other == 256u ? top : c;
                         lo = min(mid, other);
-                        c_lo = min(c_mid, c);
-                        c_hi = max(c_mid, c);
-                        y = edge.y;
-                        a = 256.0 * edge.unit;
+                        const uint32_t c_lo = min(c_mid, c);
+                        below = slot - c_lo;
+                        mass = max(c_mid, c) - c_lo;
+                        if (__builtin_expect(__any(below >= mass), 0)) {
+                            if (below >= mass)
+                                lo = walk_to_symbol(mid, below, mass, slot, scale, m_bits, tab, [&](uint32_t k) {
+                                    return __builtin_fma((double)(int)(k - mid), 256.0 * edge.unit, edge.y);
+                                });
+                        }
                     } else {
                         const EdgeLaw law = edge_law(me, inv_s);
-                        mid = guide_edge<true>(slot, me, inv_s, scale_index(ck.l[i][ch]), gs, guide);
-                        y = edge_y((int)mid, law);
-                        a = law.a;
+                        uint32_t mid = guide_edge<true>(slot, me, inv_s, scale_index(ck.l[i][ch]), gs, guide);
+                        const double y = edge_y((int)mid, law);
                         const uint32_t c_mid = cum_inner((int)mid, y, scale, tab);
-                        uint32_t c_below = cum_inner((int)mid - 1, y - a, scale, tab);
-                        uint32_t c_above = cum_inner((int)mid + 1, y + a, scale, tab);
+                        uint32_t c_below = cum_inner((int)mid - 1, y - law.a, scale, tab);
+                        uint32_t c_above = cum_inner((int)mid + 1, y + law.a, scale, tab);
                         c_below = mid == 1u ? 0u : c_below;
                         c_above = mid == 255u ? top : c_above;
-                        const bool down = slot < c_mid;
-                        lo = mid - (down ? 1u : 0u);
-                        c_lo = down ? c_below : c_mid;
-                        c_hi = down ? c_mid : c_above;
-                    }
-                    uint32_t below = slot - c_lo, mass = c_hi - c_lo;
-                    if (__builtin_expect(__any(below >= mass), 0)) {
-                        if (below >= mass) {
-                            lo = walk_to_symbol(mid, below, mass, slot, y, a, scale, m_bits, tab);
+                        bool up = c_mid <= slot;
+                        const uint32_t c_lo = up ? c_mid : c_below;
+                        below = slot - c_lo;
+                        mass = (up ? c_above : c_mid) - c_lo;
+                        if (__builtin_expect(__any(below >= mass), 0)) {
+                            if (below >= mass) {
+                                mid = walk_to_symbol(mid, below, mass, slot, scale, m_bits, tab, [&](uint32_t k) { return edge_y((int)k, law); });
+                                up = true;
+                            }
                         }
+                        lo = up ? mid : mid - 1u;
                     }
                     x[ch] = (int)lo;
                     // App. A eq. (12)

@@ -678,5 +678,8 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
 #undef PILC_ROW_PICK
 #undef PILC_ROW_PICK_OUT
 #undef PILC_ROW_PICK_IN
+#undef PILC_ROW_AIM
+#undef PILC_ROW_AIM_OUT
+#undef PILC_ROW_AIM_IN
 
 }  // namespace pilc
