@@ -908,17 +908,19 @@ static bool lanes_line_up(const Geo &g, const pilc_params *p)
 // each (256 CUs x 4 SIMDs x 64 threads = 65,536 threads for a single wave per SIMD).
 // Encoder: by then the block encoder's time goes with the number of pixels and the other's with a lane's chunks, so where they meet
 // depends on what a chunk costs there.  Block against thread per lane, us (2^M = 8192):
-//   rows that align: flat lanes of 32 28,672 53 and 54, 32,768 56 and 56, 40,960 64 and 59; of 64 40,960 83 and 85, 49,152
-//   93 and 84; of 96 36,864 96 and 100, 40,960 101 and 100; tiles of 8 x 16 36,864 110 and 113, 40,960 117 and
-//   114; of 16 x 16 32,768 150 and 182, 40,960 172 and 185, 49,152 211 and 184; of 32 x 32 40,960 568 and 642, 49,152 667 and 640;
-//   rows that do not, where the other's chunks straddle lines and the last one of a row is a short one: tiles of 8 x 8 40,800 82 and
-//   91, 48,960 92 and 91; flat lanes of 99 57,344 135 and 138, 65,536 145 and 133; tiles of 10 x 10 57,120 130 and 161; of 16 x
-//   16 65,520 266 and 266, 81,840 317 and 336, 98,160 381 and 350; and in lanes of 512 pixels and more latest: 30 x 20 98,000 725
-//   and 856, 114,000 825 and 901; 32 x 32 114,000 1361 and 1651; flat lanes of 515 114,000 767 and 936, of 777 1090 and 1477; 35 x 15
-//   114,000 742 and 742; 74 x 7 98,000 644 and 729, 114,000 732 and 756; but in tiles of one or two whole chunks a row,
+//   rows that align: flat lanes of 32 28,672 52 and 54, 32,768 57 and 56, 40,960 63 and 58; of 64 40,960 84 and 84, 49,152
+//   95 and 85; of 96 36,864 98 and 103, 40,960 101 and 101; tiles of 8 x 16 36,864 112 and 115, 40,960 119 and
+//   114; of 16 x 16 32,768 154 and 184, 40,960 178 and 187, 49,152 214 and 184; of 32 x 32 40,960 527 and 647, 57,344 702 and 703;
+//   rows that do not, where the other's chunks straddle lines and the last one of a row is a short one: tiles of 8 x 8 40,800 83 and
+//   91, 48,960 92 and 90; flat lanes of 99 57,344 136 and 136, 65,536 148 and 132, of 333 98,304 453 and 545; tiles of 10 x 10 65,520
+//   141 and 163, 98,160 185 and 187; of 16 x 16 57,120 244 and 253, 65,520 274 and 262; and in lanes of 512 pixels and more latest:
+//   30 x 20 98,300 710 and 851, 114,600 815 and 893; 32 x 32 114,600 1333 and 1631; flat lanes of 515 114,000 767 and 936, of 777 1067
+//   and 1456; 35 x 15 114,000 742 and 742; 74 x 7 98,000 644 and 729, 114,000 732 and 756; but in tiles of one or two whole chunks a row,
 //   which waste nothing thread per lane, sooner: 64 x 8 80,000 531 and 574, 89,000 578 and 585, 97,000 618 and 597, 113,000 706 and 620;
 //   96 x 8 90,000 829 and 903, 114,000 1019 and 969; 32 x 16 89,000 579 and 622, 105,000 666 and 651, 113,000 711 and 664.
-// The lines of the smaller lanes lie below where the two meet now, at 1.1 to 1.2 of the better time where that is furthest off.
+// The lines of lanes below 512 pixels lie where the two met before the block encoder became faster: between a line and where they meet
+// now a call takes up to 1.45 times the better time (aligned tiles of 32 x 32 at 36,864 lanes 644 and not 479, of 16 x 16 186 and
+// not 164; unaligned ones of 10 x 10 at 44,880 156 and not 112; flat lanes of 333 at 45,056 315 and not 237).  All for 256 compute units.
 static bool use_few_lane_encoder(const Geo &g, bool aligned, bool lines)
 {
     const int policy = g_kernel_policy.load(std::memory_order_relaxed);

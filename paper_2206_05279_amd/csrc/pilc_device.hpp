@@ -276,8 +276,8 @@ __device__ __forceinline__ uint32_t cum_at(int k, int mu_eff, uint32_t inv_s, ui
 // that is met.  The two values around the nearest edge to the result hold the symbol while 2^M is large against s.  Over
 // all slots, with means within the values of a pixel, they miss for 2^M = 1024 none up to s = 20, 1.5 % of the symbols at 33, 8 %
 // at 55 and 90, 3 % at 150 and 5 % at 400, by one and now and then by two; for 4096 at most 1 %, by one; from 2^14 on
-// none.  (With the tangent 2.6, 11, 14, 10 and 5 %, by up to three.)  The caller evaluates the exact C at three edges
-// and goes on from there where they do not hold the symbol.
+// none.  (With the tangent 2.6, 11, 14, 10 and 5 %, by up to three.)  The caller evaluates the exact C at two or three
+// edges and goes on from there where they do not hold the symbol.
 // --------------------------------------------------------------------------------------------
 struct GuideScale {  // per launch
     float half, mid, full, log_n, log_s;

@@ -295,8 +295,8 @@ __device__ __forceinline__ uint32_t encode_lane(const Geo &g, uint32_t lane, con
         // kernel is vector instructions (56 a symbol, 65 before), the waits for the tables and the stores of words.
         // The quotient is exact at the first go (quotient above), where a single-precision estimate took a
         // remainder and a correction; an edge takes one conversion less (EdgeStep).  Whole calls, us, before and
-        // now: 16,384 images of 64 x 64 with a lane a row 640 and 587, 1024 of 256 x 256 700 and 606, 30 frames of 1080 x 1920 in
-        // tiles of 16 x 16 535 and 503, 8 images of 1365 x 2047 in the same 358 and 315.  A store in every step, of a word that
+        // now: 16,384 images of 64 x 64 with a lane a row 641 and 578, 1024 of 256 x 256 721 and 616, 30 frames of 1080 x 1920 in
+        // tiles of 16 x 16 523 and 491, 8 images of 1365 x 2047 in the same 359 and 308.  A store in every step, of a word that
         // is written over if it does not count, leaves no branch in a part but costs more than the branches: 689,
         // 749, 580 and 328.
         constexpr int kHalf = kLine ? kChunk / 4 : kChunk / 2;
@@ -657,9 +657,9 @@ __global__ __launch_bounds__(kLaneMaxThreads) __attribute__((amdgpu_waves_per_eu
 // at two or three edges of the exact C (kOneSide); from a guess that is not good enough the lanes concerned walk on edge by edge
 // (walk_to_symbol), which wide laws at a low precision take.  Bound by vector instructions where the lanes fill
 // the chip, by the length of a symbol's chain where they do not; the guess and three edges, whose
-// table reads are under way together, are 77 instructions and two waits for LDS instead of the 104 and
-// eight of eight steps of bisection: 30 frames of 1080 x 1920 in tiles of 16 x 16 809 -> 560 us, 16,384
-// images of 64 x 64 with a lane a row 805 -> 622, 256 lanes of 16,384 pixels 25.1 -> 14.3 ms.
+// table reads are under way together, have two waits for LDS, with two edges three, in place of the eight
+// of eight steps of bisection (104 instructions without the rest of a symbol; with it 94 and 85 now): 30 frames of 1080 x 1920 in tiles
+// of 16 x 16 809 -> 515 us, 16,384 images of 64 x 64 with a lane a row 805 -> 603, 256 lanes of 16,384 pixels 25.1 -> 14.1 ms.
 // --------------------------------------------------------------------------------------------
 
 // A lane's 16-bit words, fetched as aligned 32-byte pairs of 16-byte pieces, a piece ahead of
@@ -823,8 +823,8 @@ __device__ __forceinline__ uint32_t walk_to_symbol(uint32_t mid, uint32_t &below
 // that carries the rest of every parameter line in registers, as the encoder does, reads half the
 // bytes from memory but needs 172 registers, i.e. two wavefronts per SIMD, and was slower: 0.91 against
 // 0.86 ms on 16,384 images of 64 x 64.)
-// kOneSide: after C at the guessed edge only the neighbour on the symbol's side is evaluated, behind a wait of its own: eight
-// instructions and a table read a symbol less, with the rest of it 82 instructions for 92.  For more than a wavefront a SIMD, where
+// kOneSide: after C at the guessed edge only the neighbour on the symbol's side is evaluated, behind a wait of its own: ten
+// instructions and a table read a symbol less, with the rest of it 85 instructions for 94.  For more than a wavefront a SIMD, where
 // instructions are what is waited for: 30 frames of 1080 x 1920 in tiles of 16 x 16 549 and 511 us, 8 images of 1365 x 2047 in
 // the same (88,064 lanes) 370 and 363, 16,384 images of 64 x 64 in tiles of 8 x 8 518 and 485, with a lane a row 616
 // and 597, 76,800 lanes of 64 109 and 106; up to there the wait is what counts: 65,472 lanes of 64 103 and 105, 38,400 95 and
