@@ -4,7 +4,6 @@ import ctypes as C
 import os
 import re
 
-import msgpack
 import pytest
 
 from paper_2206_05279_amd import binding as pb
@@ -35,12 +34,19 @@ def test_library_was_built_from_the_current_sources():
 
 
 def _registers():
-    """What the library's code object says of its kernels: {name: (vector registers, bytes of private memory)}."""
+    """What the library's code object says of its kernels: {name: (vector registers, bytes of private memory)}.  Its note is a
+    list of maps in MessagePack, whose keys are sorted; an integer is a byte below 128, or 0xcc .. 0xce and 1, 2 or 4 bytes."""
+    def integer(at):
+        size = {0xCC: 1, 0xCD: 2, 0xCE: 4}.get(note[at], 0)
+        return int.from_bytes(note[at + 1:at + 1 + size], "big") if size else note[at]
+
     blob = open(pb.LIB_PATH, "rb").read()
-    at = blob.index(b"AMDGPU\0\0\x83\xaeamdhsa.kernels")  # a note's name, padded, and its contents in MessagePack
-    size = int.from_bytes(blob[at - 8:at - 4], "little")
-    kernels = msgpack.unpackb(blob[at + 8:at + 8 + size])["amdhsa.kernels"]
-    return {k[".name"]: (k[".vgpr_count"], k[".private_segment_fixed_size"]) for k in kernels}
+    at = blob.index(b"AMDGPU\0\0\x83\xaeamdhsa.kernels")  # the note's name, padded, and how its contents begin
+    note = blob[at + 8:at + 8 + int.from_bytes(blob[at - 8:at - 4], "little")]
+    found = {}
+    for m in re.finditer(rb"\.name(?:\xd9.|\xda..|[\xa0-\xbf])(_ZN4pilc\w+)\xbb(\.private_segment_fixed_size)", note, re.S):
+        found[m.group(1).decode()] = (integer(note.index(b".vgpr_count", m.end()) + len(".vgpr_count")), integer(m.end()))
+    return found
 
 
 # Template arguments of a kernel and the wavefronts a SIMD that its registers leave room for (of 512 in all, eight at a time).
