@@ -292,12 +292,17 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
 // What bounds this is the chain of the red channel: an image takes at least w + h dependent steps,
 // however many threads work on it.  Only red needs the row above; green and blue of a row need that
 // row alone.  So the channels of 64 rows (a thread per row) are decoded by three wavefronts, green
-// a block of 16 columns behind red and blue a block behind green, and moving the data is the
+// a block of 16 columns or two behind red and blue as far behind green, and moving the data is the
 // business of two more, one that fetches residuals four blocks ahead and one that stores pixels.
-// A red step is then eight vector instructions, and a block of 16 takes 1210 cycles, barrier included.
-// (One wavefront that did all three channels took 280 cycles a step: 30 frames of 1080 x 1920 487 us,
-// now 265; and rows that were not whole 16-byte pieces went 64 at a time through one wavefront, 16
-// images of 1365 x 2047 in 37.8 ms, now 227 us.)
+// (One wavefront that did all three channels took 280 cycles a step: 30 frames of 1080 x 1920 487 us;
+// and rows that were not whole 16-byte pieces went 64 at a time through one wavefront, 16
+// images of 1365 x 2047 in 37.8 ms, now 206 us.)
+//
+// Two kernels.  k_twar_inverse_strips goes a band of 64 rows at a time and is made small, four workgroups to a compute
+// unit, for batches of many strips.  k_twar_inverse_bands runs an image's bands at the same time and is made for
+// a short interval between barriers, as every interval and the trip from band to band are waited for by all
+// below.  (With the former's steps, bands anywhere on the chip, and words cleared by a launch before, 30 frames of
+// 1080 x 1920 took 286 us, now 211; 16 images of 1365 x 2047 257 and 206; 112 of 1024 x 400 400 and 179.)
 //
 // Thread r of a wavefront runs r columns behind thread 0, so its block of 16 columns number b is
 // the window [16 b - r, 16 b - r + 16) of its row.  Data is moved in these windows, as 48 bytes at
@@ -306,23 +311,25 @@ __global__ __launch_bounds__(64 * kTwarWaves) void k_twar_inverse(TwarK p, uint3
 // reaches past the ends of its row at the row's first and last blocks; what is read there is not
 // used, what is decoded there is not stored.
 //
-// A workgroup takes 64 rows, a band, and steps in time with one barrier per block.  An image's bands run
-// at the same time in workgroups of their own, each some eleven blocks behind the one above: the last row of
-// a band is passed on through global memory as 64-bit words of four red values and a mark, each
-// stored and loaded whole at device scope, so that a word that has its mark has its values and
-// neither side waits for anything but the word itself.  A sixth wavefront asks for the next eight
+// A workgroup takes 64 rows, a band, and steps in time with one barrier per block.  Bands that run together
+// follow each other some thirteen blocks apart: the last row of a band is passed on through global memory, a 32-bit word a
+// value with the launch's mark above it, stored and loaded at device scope, so that a word that has the mark has its
+// value and neither side waits for anything but the word itself.  A sixth wavefront asks for the next eight
 // blocks of such words over and over and puts what has arrived into LDS.  Bands number themselves
-// with a ticket (image by image, top to bottom), so the band above is always a workgroup that is
+// with a ticket (the first bands of all strips, then the second ones: those that share a compute unit, or come one after the
+// other on it, are then many bands apart), so the band above is always a workgroup that is
 // already running and never waits for the band below.  The wait is bounded by the constant-rate clock;
 // a band that gives up sets an abort word and goes on with what it has, bands below it that find the
 // word set do the same, every loop has a fixed count, and the host returns PILC_E_TIMEOUT.
 // (Two or three times 64 rows in a workgroup, which pass their last rows on through LDS, save
-// that trip through memory, 3.3 us a band, but the wavefronts that then share a SIMD cost more: one
-// frame of 2160 x 3840 takes 0.30 ms with 64 rows, 0.35 with 128, 0.45 with 192.)
+// that trip through memory, but the wavefronts that then share a SIMD cost more: with the steps of the other kernel one
+// frame of 2160 x 3840 took 0.30 ms with 64 rows, 0.35 with 128, 0.45 with 192.)
 constexpr int kDiagAhead = 4;   // blocks between asking for a window and putting it into LDS
-constexpr int kDiagSlots = 6;   // intervals a window stays in LDS: put, taken apart, red, green, blue, stored
+constexpr int kStripSlots = 6;  // intervals a window stays in LDS: put, taken apart, red, green, blue, stored
+constexpr int kDiagSlots = 8;   // with bands together: put, taken up, red, taken up, green, taken up, blue, stored
 constexpr int kDiagCarry = 32;  // blocks of the row above a band kept in LDS
 constexpr int kDiagPolls = 4;   // requests for words of the row above under way at once
+constexpr int kDeviceScope = 16;  // of a buffer store: seen by every compute unit (sc1)
 
 struct Diag {
     uint32_t h, w;
@@ -330,10 +337,13 @@ struct Diag {
     unsigned long long rows;    // n h
     uint32_t blocks;            // of 16 columns, ceil((w + 63) / 16): the last thread has to get through its row
     unsigned long long strip0;  // this launch: strips from strip0 on, bands band0 .. band0 + bands - 1
-    uint32_t band0, bands;
-    unsigned long long *words;  // [strip, band][block][4]: {four red values of a band's last row, mark}; null: one band
+    uint32_t strips, band0, bands;
+    uint32_t *words;            // [strip, band][block][16]: red values of a band's last row, the mark above each; null: one band
+    uint32_t mark;              // of this launch, 1 .. 255
     uint32_t *ticket;           // null: one band
+    uint32_t first_ticket;      // what it stands at before this launch
     uint32_t *abort_word;
+    Report *report;
     unsigned long long wait_ticks;
     uint32_t withhold;          // tests of the give-up path: nothing is passed on
 };
@@ -346,6 +356,7 @@ extern "C" __device__ int mul_i24(int a, int b) __asm("llvm.amdgcn.mul.i24.i32")
 // half of the clamped sum; beyond 2^26 a bias saturates the prediction whatever the three products are.
 __device__ __forceinline__ int diag_weight(int w) { return 4 * w; }
 __device__ __forceinline__ int diag_bias(int bias) { return 4 * (min(max(bias, -(1 << 26)), 1 << 26) + 8192); }
+
 // (the prediction with sum `acc` plus the residual) mod 256
 __device__ __forceinline__ int diag_value(int acc, int residual)
 {
@@ -470,22 +481,17 @@ __device__ __forceinline__ void interval_barrier()
     __syncthreads();
 }
 
-__global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, const uint8_t *__restrict__ res,
+// A band of each strip, a workgroup each; the row above, if any, is in the image.  26 KB of LDS and 80 registers: four workgroups
+// share a compute unit, which is what batches of many strips live on.
+__global__ __launch_bounds__(64 * 6) void k_twar_inverse_strips(TwarK p, Diag a, const uint8_t *__restrict__ res,
                                                               uint8_t *__restrict__ img)
 {
-    __shared__ u32x4 raw[kDiagSlots][3][64];  // [slot][third of the window][row]: residuals, then pixels
+    __shared__ u32x4 raw[kStripSlots][3][64];  // [slot][third of the window][row]: residuals, then pixels
     __shared__ u32x4 red[4][64];              // [block mod 4][row]
     __shared__ u32x4 green[2][64];            // [block mod 2][row]
     __shared__ uint32_t carry[kDiagCarry][4]; // [block mod kDiagCarry][word]: red of the row above
-    __shared__ uint32_t s_id;
-    uint32_t id = blockIdx.x;
-    if (a.ticket != nullptr) {
-        if (threadIdx.x == 0u) s_id = atomicAdd(a.ticket, 1u);
-        __syncthreads();
-        id = s_id;
-    }
-    const uint32_t in_strip = id / a.bands, band = a.band0 + (id - in_strip * a.bands);
-    const unsigned long long strip = a.strip0 + in_strip;
+    const uint32_t band = a.band0;
+    const unsigned long long strip = a.strip0 + blockIdx.x;
     const uint32_t role = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t band_row0 = band * 64u;       // row of the strip
@@ -501,8 +507,6 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
         const int w_upleft = top ? 0 : diag_weight(p.w[0][0]), w_up = top ? 0 : diag_weight(p.w[0][1]);
         const int w_left = diag_weight(p.w[0][2]);
         const int bias = diag_bias(p.bias[0]);
-        const bool passes_on = a.words != nullptr && a.withhold == 0u && band + 1u < a.band0 + a.bands;
-        unsigned long long *out = a.words + (size_t)id * (4u * a.blocks);
         uint32_t left = 0, up = 0;  // the last four values, and the four above them as red_steps keeps them
         uint32_t slot = 0, e[4] = {};
         for (int time = 0; time < times; ++time) {
@@ -543,17 +547,12 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
                 o.z = x[2];
                 o.w = x[3];
                 red[b & 3][lane] = o;
-                if (passes_on && lane == 63u) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        __hip_atomic_store(out + 4 * b + k, (1ull << 32) | x[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
             }
             // the next block's residuals, which no barrier has to be waited for
             u32x4 d[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) d[i] = raw[slot][i][lane];
-            slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
+            slot = slot + 1u == (uint32_t)kStripSlots ? 0u : slot + 1u;
             window_channel<0>(d, e);
         }
     } else if (role == 1u || role == 2u) {  // ---- green and blue
@@ -614,7 +613,433 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
 #pragma unroll
                     for (int i = 0; i < 3; ++i) raw[slot][i][lane] = d[i];
                 }
+                slot = slot + 1u == (uint32_t)kStripSlots ? 0u : slot + 1u;
+            }
+        };
+        if (role == 1u)
+            channel(std::false_type{});
+        else
+            channel(std::true_type{});
+    } else if (role == 3u) {  // ---- residuals from memory to LDS
+        // the windows of 64 rows move as 192 pieces of 16 bytes, three neighbouring threads taking the
+        // 48 bytes of a row.  An address outside the array is moved inside; that brings the wrong
+        // bytes only where none is used, or at the end of the array's last row, where they are put right.
+        const long long last = (long long)(a.rows * a.w * 3ull) - 16;
+        long long at[3];
+        uint32_t put[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;  // r = k / 3 for k < 192
+            const unsigned long long row = strip * a.strip_rows + band_row0 + r;
+            at[i] = (long long)(row * a.w * 3ull) + 16ll * part - 3ll * r;  // block 0
+            put[i] = part * 64u + r;
+        }
+        u32x4 ahead[kDiagAhead][3];
+#pragma unroll
+        for (int j = 0; j < kDiagAhead; ++j)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) ahead[j][i] = u32x4{};
+        // Without a condition on anything, so that the number of loads under way is known when one is
+        // waited for: what is put before the first block or after the last is not looked at (a
+        // slot is written again no sooner than the interval after its pixels have been stored).
+        uint32_t slot = kStripSlots - kDiagAhead;  // of block -kDiagAhead
+        static_assert(kStripSlots >= kDiagAhead, "");
+        for (int time0 = 0; time0 < times; time0 += kDiagAhead) {
+#pragma unroll
+            for (int j = 0; j < kDiagAhead; ++j) {
+                interval_barrier();
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    (&raw[slot][0][0])[put[i]] = ahead[j][i];
+                    const long long over = at[i] - 48 * kDiagAhead - last;
+                    if (over > 0 && over < 16) {  // the array's end is inside the piece: a few pieces near it
+                        uint8_t *q = reinterpret_cast<uint8_t *>(&raw[slot][0][0] + put[i]);
+#pragma unroll 1
+                        for (int k = 0; k < 16 - (int)over; ++k) q[k] = q[k + (int)over];
+                    }
+                }
+                slot = slot + 1u == (uint32_t)kStripSlots ? 0u : slot + 1u;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const long long from = min(max(at[i], 0ll), last);
+                    ahead[j][i] = *reinterpret_cast<const u32x4_any *>(res + from);
+                    at[i] += 48;
+                }
+            }
+        }
+    } else if (role == 4u) {  // ---- pixels from LDS to memory
+        const int row_bytes = (int)(3u * a.w);
+        uint8_t *to[3];
+        int in_row[3];  // where the piece lies in its row
+        uint32_t get[3];
+        bool have[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;
+            const uint32_t u = band_row0 + r;
+            const unsigned long long row = strip * a.strip_rows + u;
+            have[i] = u < a.strip_rows && row < a.rows;
+            in_row[i] = 16 * (int)part - 3 * (int)r;
+            to[i] = img + (long long)((have[i] ? row : 0ull) * a.w * 3ull) + in_row[i];
+            get[i] = part * 64u + r;
+        }
+        uint32_t slot = 0;
+        for (int time = 0; time < times; ++time) {
+            interval_barrier();
+            const int b = time - lead - 3;
+            if (b < 0 || b >= blocks) continue;
+            u32x4 v[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) v[i] = (&raw[slot][0][0])[get[i]];
+            slot = slot + 1u == (uint32_t)kStripSlots ? 0u : slot + 1u;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int first = in_row[i] + 48 * b;
+                uint8_t *q = to[i] + 48ll * b;
+                if (!have[i]) continue;
+                if (first >= 0 && first + 16 <= row_bytes) {
+                    *reinterpret_cast<u32x4_any *>(q) = v[i];
+                } else if (first > -16 && first < row_bytes) {  // an end of the row
+                    const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+                    for (int k = 0; k < 16; ++k)
+                        if (first + k >= 0 && first + k < row_bytes) q[k] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
+                }
+            }
+        }
+    } else {  // ---- red of the row above the band, which is in the image
+        // Block q, word k of the band above holds columns 16 q + 4 k - 63 .. + 3 of its last row.  Red's block
+        // b needs blocks b + 3 and b + 4.  Threads 0 .. 31 fetch eight blocks every four intervals, an interval or more ahead.
+        if (band == 0u) {
+            for (int time = 0; time < times; ++time) interval_barrier();
+            return;
+        }
+        const uint8_t *above_row = img + (size_t)((strip * a.strip_rows + band_row0 - 1u) * a.w) * 3u;
+        const int k = (int)(lane & 3u);
+        uint32_t v = 0;
+        int base = 0, got = 0;  // blocks asked for from `base` on; blocks in LDS so far
+        for (int time = 0; time < times; ++time) {
+            interval_barrier();
+            if ((time & 3) != 0) continue;
+            const int now = time - lead;
+            if (time != 0) {
+                const int upto = min(min(base + 8, blocks), now + kDiagCarry), q = base + (int)(lane >> 2);
+                if (lane < 32u && q < upto) carry[q % kDiagCarry][k] = v;
+                got = max(got, upto);
+            }
+            base = got;
+            const int q = min(base + (int)((lane & 31u) >> 2), blocks - 1);
+            v = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int col = 16 * q + 4 * k + i - 63;
+                v |= (uint32_t)above_row[3 * min(max(col, 0), (int)a.w - 1)] << (8 * i);  // (outside the row: not used)
+            }
+        }
+    }
+}
+
+// ---- bands together
+// Sixteen steps of a channel, four a piece of assembly, a register a value.  The steps are written out for
+// three reasons.  The prediction, the residual's byte and the mod 256 are one instruction (sub-dword operands pick the
+// upper half of the sum and a byte of the window as it was loaded, and only the low byte of the value's register
+// is written).  An instruction that reads a register whose byte the instruction before it wrote, or a
+// neighbour's register less than three instructions after it was written, would get old values: the order keeps
+// both apart.  And nothing of the neighbour's value has to be moved before it is used:
+//
+// Red, six instructions a step: the value above is moved over from the thread above as it is wanted, and is
+// the one above to the left of the next step.  Thread 0 has no thread above, the move leaves its lane alone, and
+// this holds the value of the row above the band beforehand.
+// (With four values packed to a register, which took a byte picked for every product, a step took eight.)
+//
+// `MASK`: in the first four blocks a thread gets through the column before its row's first, where its
+// value has to read as zero; a bit that moves up by one thread a step says whose turn it is.
+#define PILC_RED_STEP(X, L, U, UL, E, B, MASK)                                                       \
+    "v_mad_i32_i24 %[t], " UL ", %[w_upleft], %[bias]\n"                                            \
+    "v_mad_i32_i24 %[t], " L ", %[w_left], %[t]\n"                                                  \
+    "v_mov_b32_dpp " U ", " L " wave_shr:1 row_mask:0xf bank_mask:0xf\n"                            \
+    "v_mad_i32_i24 %[t], " U ", %[w_up], %[t]\n"                                                    \
+    "v_med3_i32 %[t], %[t], 0, %[most]\n"                                                           \
+    "v_add_u32_sdwa " X ", %[t], %[" E "] dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:WORD_1 src1_sel:BYTE_" #B "\n" MASK(X)
+// Green and blue, five instructions a step, from the channel decoded before.
+#define PILC_ROW_STEP(X, L, V, VL, E, B, MASK)                                                       \
+    "v_mad_i32_i24 %[t], %[" V "], %[w_before], %[bias]\n"                                          \
+    "v_mad_i32_i24 %[t], %[" VL "], %[w_left_before], %[t]\n"                                       \
+    "v_mad_i32_i24 %[t], " L ", %[w_left], %[t]\n"                                               \
+    "v_med3_i32 %[t], %[t], 0, %[most]\n"                                                           \
+    "v_add_u32_sdwa " X ", %[t], %[" E "] dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:WORD_1 src1_sel:BYTE_" #B "\n" MASK(X)
+#define PILC_NO_MASK(X) ""
+#define PILC_MASK(X)                                                                                 \
+    "s_lshl_b64 %[mask], %[mask], 1\n"                                                              \
+    "v_cndmask_b32_e64 " X ", " X ", %[zero], %[mask]\n"
+
+// The sixteen values, and those above them, have fixed registers: four of them are one operand of a load or store
+// of sixteen bytes, whose parts the assembly could not name otherwise, and as operands of their own they
+// cost a move each.
+struct RedWeights {
+    int upleft, up, left, bias;
+};
+#define PILC_RED_FOUR(MASK, X0, X1, X2, X3, L, U0, U1, U2, U3)                                       \
+    PILC_RED_STEP(X0, L, U0, "%[ul]", "e0", 0, MASK)                                                \
+    PILC_RED_STEP(X1, X0, U1, U0, "e0", 3, MASK)                                                    \
+    PILC_RED_STEP(X2, X1, U2, U1, "e1", 2, MASK)                                                    \
+    PILC_RED_STEP(X3, X2, U3, U2, "e2", 1, MASK)
+#define PILC_RED_INPUTS                                                                              \
+    [ul] "v"(last_up), [e0] "v"(e0), [e1] "v"(e1), [e2] "v"(e2), [w_upleft] "v"(w.upleft), [w_up] "v"(w.up),      \
+        [w_left] "v"(w.left), [bias] "v"(w.bias), [most] "v"(0xFFFFFF)
+#define PILC_RED_GROUP(G, XQ, PQ, UQ, ...)                                                           \
+    if (kG == G) {                                                                                  \
+        if (kFirst)                                                                                 \
+            asm(PILC_RED_FOUR(PILC_MASK, __VA_ARGS__)                                               \
+                : "+{" XQ "}"(x[G]), "+{" UQ "}"(above), [t] "=&v"(t), [mask] "+s"(mask)            \
+                : "{" PQ "}"(x[(G + 3) & 3]), PILC_RED_INPUTS, [zero] "v"(zero) : "scc");           \
+        else                                                                                        \
+            asm(PILC_RED_FOUR(PILC_NO_MASK, __VA_ARGS__)                                            \
+                : "+{" XQ "}"(x[G]), "+{" UQ "}"(above), [t] "=&v"(t)                               \
+                : "{" PQ "}"(x[(G + 3) & 3]), PILC_RED_INPUTS);                                     \
+    }
+// `x`: all sixteen values; group kG of four is decoded here, from the group before it, or, for the first, from the
+// last of the block before.  `above`: the values above thread 0; `last_up`: the value above the one before these.
+// `e`: the window's three dwords of these pixels.
+template <int kG, bool kFirst>
+__device__ __forceinline__ void red_four(const RedWeights &w, u32x4 (&x)[4], u32x4 above, uint32_t &last_up,
+                                         const uint32_t e0, const uint32_t e1, const uint32_t e2, uint32_t zero,
+                                         unsigned long long &mask)
+{
+    int t;
+    PILC_RED_GROUP(0, "v[64:67]", "v[76:79]", "v[48:51]", "v64", "v65", "v66", "v67", "v79", "v48", "v49", "v50", "v51")
+    PILC_RED_GROUP(1, "v[68:71]", "v[64:67]", "v[52:55]", "v68", "v69", "v70", "v71", "v67", "v52", "v53", "v54", "v55")
+    PILC_RED_GROUP(2, "v[72:75]", "v[68:71]", "v[56:59]", "v72", "v73", "v74", "v75", "v71", "v56", "v57", "v58", "v59")
+    PILC_RED_GROUP(3, "v[76:79]", "v[72:75]", "v[60:63]", "v76", "v77", "v78", "v79", "v75", "v60", "v61", "v62", "v63")
+    last_up = above.w;
+}
+#undef PILC_RED_GROUP
+#undef PILC_RED_INPUTS
+#undef PILC_RED_FOUR
+
+struct RowWeights {
+    int left, left_before, before, bias;
+};
+#define PILC_GREEN_FOUR(MASK, X0, X1, X2, X3, L)                                                     \
+    PILC_ROW_STEP(X0, L, "v0", "vl", "e0", 1, MASK)                                                 \
+    PILC_ROW_STEP(X1, X0, "v1", "v0", "e1", 0, MASK)                                                \
+    PILC_ROW_STEP(X2, X1, "v2", "v1", "e1", 3, MASK)                                                \
+    PILC_ROW_STEP(X3, X2, "v3", "v2", "e2", 2, MASK)
+#define PILC_BLUE_FOUR(MASK, X0, X1, X2, X3, L)                                                      \
+    PILC_ROW_STEP(X0, L, "v0", "vl", "e0", 2, MASK)                                                 \
+    PILC_ROW_STEP(X1, X0, "v1", "v0", "e1", 1, MASK)                                                \
+    PILC_ROW_STEP(X2, X1, "v2", "v1", "e2", 0, MASK)                                                \
+    PILC_ROW_STEP(X3, X2, "v3", "v2", "e2", 3, MASK)
+#define PILC_ROW_INPUTS                                                                              \
+    [v0] "v"(v.x), [v1] "v"(v.y), [v2] "v"(v.z), [v3] "v"(v.w), [vl] "v"(vl), [e0] "v"(e0), [e1] "v"(e1), [e2] "v"(e2), \
+        [w_left] "v"(w.left), [w_left_before] "v"(w.left_before), [w_before] "v"(w.before), [bias] "v"(w.bias),         \
+        [most] "v"(0xFFFFFF)
+#define PILC_ROW_GROUP(G, FOUR, XQ, PQ, ...)                                                         \
+    if (kG == G) {                                                                                  \
+        if (kFirst)                                                                                 \
+            asm(FOUR(PILC_MASK, __VA_ARGS__)                                                        \
+                : "+{" XQ "}"(x[G]), [t] "=&v"(t), [mask] "+s"(mask)                                \
+                : "{" PQ "}"(x[(G + 3) & 3]), PILC_ROW_INPUTS, [zero] "v"(0) : "scc");              \
+        else                                                                                        \
+            asm(FOUR(PILC_NO_MASK, __VA_ARGS__)                                                     \
+                : "+{" XQ "}"(x[G]), [t] "=&v"(t)                                                   \
+                : "{" PQ "}"(x[(G + 3) & 3]), PILC_ROW_INPUTS);                                     \
+    }
+// Likewise for channel kCh; `v`: the values of the channel decoded before, `vl`: the one before these.
+template <int kCh, int kG, bool kFirst>
+__device__ __forceinline__ void row_four(const RowWeights &w, u32x4 (&x)[4], const u32x4 v, const uint32_t vl,
+                                         const uint32_t e0, const uint32_t e1, const uint32_t e2, unsigned long long &mask)
+{
+    int t;
+    if (kCh == 1) {
+        PILC_ROW_GROUP(0, PILC_GREEN_FOUR, "v[64:67]", "v[76:79]", "v64", "v65", "v66", "v67", "v79")
+        PILC_ROW_GROUP(1, PILC_GREEN_FOUR, "v[68:71]", "v[64:67]", "v68", "v69", "v70", "v71", "v67")
+        PILC_ROW_GROUP(2, PILC_GREEN_FOUR, "v[72:75]", "v[68:71]", "v72", "v73", "v74", "v75", "v71")
+        PILC_ROW_GROUP(3, PILC_GREEN_FOUR, "v[76:79]", "v[72:75]", "v76", "v77", "v78", "v79", "v75")
+    } else {
+        PILC_ROW_GROUP(0, PILC_BLUE_FOUR, "v[64:67]", "v[76:79]", "v64", "v65", "v66", "v67", "v79")
+        PILC_ROW_GROUP(1, PILC_BLUE_FOUR, "v[68:71]", "v[64:67]", "v68", "v69", "v70", "v71", "v67")
+        PILC_ROW_GROUP(2, PILC_BLUE_FOUR, "v[72:75]", "v[68:71]", "v72", "v73", "v74", "v75", "v71")
+        PILC_ROW_GROUP(3, PILC_BLUE_FOUR, "v[76:79]", "v[72:75]", "v76", "v77", "v78", "v79", "v75")
+    }
+}
+#undef PILC_ROW_GROUP
+#undef PILC_GREEN_FOUR
+#undef PILC_BLUE_FOUR
+#undef PILC_ROW_INPUTS
+#undef PILC_RED_STEP
+#undef PILC_ROW_STEP
+#undef PILC_MASK
+#undef PILC_NO_MASK
+
+// The twelve bytes of four pixels from their channels (the low bytes of the registers).
+__device__ __forceinline__ void four_pixels(const u32x4 r, const u32x4 g, const u32x4 b, uint32_t (&w)[3])
+{
+    auto perm = [](uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); };
+    w[0] = perm(perm(r.y, b.x, 0x04000000u), perm(g.x, r.x, 0x0C0C0400u), 0x07060100u);
+    w[1] = perm(perm(g.z, r.z, 0x04000000u), perm(b.y, g.y, 0x0C0C0400u), 0x07060100u);
+    w[2] = perm(perm(b.w, g.w, 0x04000000u), perm(r.w, b.z, 0x0C0C0400u), 0x07060100u);
+}
+
+__device__ __forceinline__ uint32_t dword_of(const u32x4 (&d)[3], int i)
+{
+    const u32x4 v = d[i >> 2];
+    return (i & 3) == 0 ? v.x : (i & 3) == 1 ? v.y : (i & 3) == 2 ? v.z : v.w;
+}
+
+constexpr uint32_t kDiagRawBytes = kDiagSlots * 3 * 64 * 16;  // the dynamic part of its LDS; the rest is 30 KB
+constexpr uint32_t kDiagAloneBytes = 56 * 1024;                // as much as leaves no room for a second workgroup
+
+__global__ __launch_bounds__(64 * 6) void k_twar_inverse_bands(TwarK p, Diag a, const uint8_t *__restrict__ res,
+                                                              uint8_t *__restrict__ img)
+{
+    // (The windows in dynamic memory: told of all 55 KB, of which a compute unit holds two, the compiler gives the kernel as
+    // many registers as leave a SIMD three wavefronts, and two workgroups of six then do not always fit.)
+    extern __shared__ u32x4 diag_lds[];
+    u32x4(*const raw)[3][64] = reinterpret_cast<u32x4(*)[3][64]>(diag_lds);  // [slot][third of the window][row]: residuals, then pixels
+    __shared__ u32x4 red[5][4][64];         // [block mod 5][four of its values][row]: blue is four blocks behind
+    __shared__ u32x4 green[2][4][64];       // [block mod 2][four of its values][row]
+    __shared__ u32x4 carry[kDiagCarry][4];  // [block + 4, mod kDiagCarry][four of them]: red of the row above the band
+    __shared__ uint32_t s_id;
+    uint32_t id = blockIdx.x;
+    if (a.ticket != nullptr) {
+        if (threadIdx.x == 0u) s_id = atomicAdd(a.ticket, 1u) - a.first_ticket;
+        __syncthreads();
+        id = s_id;
+    }
+    const uint32_t in_launch = id / a.strips, in_strip = id - in_launch * a.strips, band = a.band0 + in_launch;
+    const unsigned long long strip = a.strip0 + in_strip;
+    const uint32_t place = in_strip * a.bands + in_launch;  // of this band's words
+    const uint32_t role = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t band_row0 = band * 64u;       // row of the strip
+    const int blocks = (int)a.blocks;
+    // intervals between barriers, a multiple of 4: a window is fetched kDiagAhead intervals before it is put
+    // into LDS, red takes it up in the next and decodes it in the one after; green takes it up in the next and
+    // decodes it in the one after, blue likewise, and then it is stored
+    const int lead = kDiagAhead + 2;
+    const int times = (lead + blocks + 5 + 3) & ~3;
+
+    if (role == 0u) {  // ---- red
+        const uint32_t u = band_row0 + lane;
+        const bool top = u % a.h == 0u;  // the row above is padding: its two weights are zero here
+        RedWeights w = {top ? 0 : diag_weight(p.w[0][0]), top ? 0 : diag_weight(p.w[0][1]), diag_weight(p.w[0][2]),
+                        diag_bias(p.bias[0])};
+        // (in vector registers: from scalar ones they would be copied at every use)
+        asm volatile("" : "+v"(w.left), "+v"(w.bias));
+        const bool passes_on = a.words != nullptr && a.withhold == 0u && band + 1u < a.band0 + a.bands;
+        uint32_t *out = a.words + (size_t)place * (16u * a.blocks);
+        const __amdgpu_buffer_rsrc_t out_buffer =
+            __builtin_amdgcn_make_buffer_rsrc(out, 0, 64 * blocks, 0x00020000);
+        // the values, with the mark of this launch above them
+        const uint32_t mark = a.mark << 24;
+        u32x4 x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = u32x4{mark, mark, mark, mark};
+        uint32_t last_up = 0;
+        unsigned long long mask = 1ull;
+        uint32_t slot = 0;
+        u32x4 d[2][3] = {};
+        for (int time0 = 0; time0 < times; time0 += 2) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                interval_barrier();
+                const int b = time0 + j - lead;
+                if (b < -1 || b >= blocks) continue;
+                // the next block's residuals, which are wanted after the next barrier
+#pragma unroll
+                for (int i = 0; i < 3; ++i) d[1 - j][i] = raw[slot][i][lane];
                 slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
+                if (b < 0) continue;
+                // thread 0 is at columns 16 b .. + 15; column v of the row above is value v + 63 of its blocks
+                const uint32_t c = (uint32_t)(b + 4) % kDiagCarry;
+                auto steps = [&](auto first) {
+                    constexpr bool kFirst = decltype(first)::value;
+#define PILC_RED_GROUP(G)                                                                            \
+    red_four<G, kFirst>(w, x, carry[c][G], last_up, dword_of(d[j], 3 * G), dword_of(d[j], 3 * G + 1),   \
+                        dword_of(d[j], 3 * G + 2), mark, mask);                                     \
+    red[(uint32_t)b % 5u][G][lane] = x[G];
+                    PILC_RED_GROUP(0)
+                    PILC_RED_GROUP(1)
+                    PILC_RED_GROUP(2)
+                    PILC_RED_GROUP(3)
+#undef PILC_RED_GROUP
+                };
+                if (b >= 4)
+                    steps(std::false_type{});
+                else
+                    steps(std::true_type{});
+                if (passes_on && lane == 63u) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)  // at device scope
+                        __builtin_amdgcn_raw_buffer_store_b128(x[k], out_buffer, 64 * b + 16 * k, 0, kDeviceScope);
+                }
+            }
+        }
+    } else if (role == 1u || role == 2u) {  // ---- green and blue
+        auto channel = [&](auto blue) {
+            constexpr int kCh = decltype(blue)::value ? 2 : 1;
+            // green from the left green, the left red and the red here; blue likewise from blue and green
+            RowWeights w = {diag_weight(p.w[kCh][0]), diag_weight(p.w[kCh][1]), diag_weight(p.w[kCh][2]),
+                            diag_bias(p.bias[kCh])};
+            // (in vector registers: from scalar ones they would be copied at every use)
+            asm volatile("" : "+v"(w.left), "+v"(w.left_before), "+v"(w.before), "+v"(w.bias));
+            u32x4 x[4] = {};
+            uint32_t before_left = 0;  // the last value of the channel decoded before this one
+            unsigned long long mask = 1ull;
+            uint32_t slot = 0, next_slot = 0;
+            u32x4 d[2][3] = {}, v[2][4] = {};  // a block's residuals and the channel before, asked for an interval ahead
+            auto interval = [&](int time, auto odd, auto first) {
+                constexpr bool kFirst = decltype(first)::value;
+                constexpr int j = decltype(odd)::value ? 1 : 0;
+                interval_barrier();
+                const int b = time - lead - 2 * kCh;
+                if (b < -1 || b >= blocks) return;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    v[1 - j][k] = kCh == 1 ? red[(uint32_t)(b + 1) % 5u][k][lane] : green[(b + 1) & 1][k][lane];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) d[1 - j][i] = raw[next_slot][i][lane];
+                next_slot = next_slot + 1u == (uint32_t)kDiagSlots ? 0u : next_slot + 1u;
+                if (b < 0) return;
+                u32x4 r[4];
+                if (kCh == 2)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) r[k] = red[(uint32_t)b % 5u][k][lane];
+                uint32_t pixels[12];
+#define PILC_ROW_FOUR(G, VL)                                                                         \
+    row_four<kCh, G, kFirst>(w, x, v[j][G], VL, dword_of(d[j], 3 * G), dword_of(d[j], 3 * G + 1),       \
+                             dword_of(d[j], 3 * G + 2), mask);                                      \
+    if (kCh == 1) {                                                                                 \
+        green[b & 1][G][lane] = x[G];                                                               \
+    } else {                                                                                        \
+        uint32_t q[3];                                                                              \
+        four_pixels(r[G], v[j][G], x[G], q);                                                        \
+        pixels[3 * G] = q[0];                                                                       \
+        pixels[3 * G + 1] = q[1];                                                                   \
+        pixels[3 * G + 2] = q[2];                                                                   \
+    }
+                PILC_ROW_FOUR(0, before_left)
+                PILC_ROW_FOUR(1, v[j][0].w)
+                PILC_ROW_FOUR(2, v[j][1].w)
+                PILC_ROW_FOUR(3, v[j][2].w)
+#undef PILC_ROW_FOUR
+                if (kCh == 2) {  // all three channels are here: the window's pixels take the place of its residuals
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        raw[slot][i][lane] = u32x4{pixels[4 * i], pixels[4 * i + 1], pixels[4 * i + 2], pixels[4 * i + 3]};
+                    slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
+                }
+                before_left = v[j][3].w;
+            };
+            int time = 0;
+            for (; time < min(times, lead + 2 * kCh + 4); time += 2) {
+                interval(time, std::false_type{}, std::true_type{});
+                interval(time + 1, std::true_type{}, std::true_type{});
+            }
+            for (; time < times; time += 2) {
+                interval(time, std::false_type{}, std::false_type{});
+                interval(time + 1, std::true_type{}, std::false_type{});
             }
         };
         if (role == 1u)
@@ -687,7 +1112,7 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
         uint32_t slot = 0;
         for (int time = 0; time < times; ++time) {
             interval_barrier();
-            const int b = time - lead - 3;
+            const int b = time - lead - 5;
             if (b < 0 || b >= blocks) continue;
             u32x4 v[3];
 #pragma unroll
@@ -708,37 +1133,47 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
                 }
             }
         }
-    } else {  // ---- the red values of the row above the band
-        // Block q, word k of the band above holds columns 16 q + 4 k - 63 .. + 3 of its last row.  Red's block
-        // b needs blocks b + 3 and b + 4.  Threads 0 .. 31 ask for eight blocks at a time.
+    } else {  // ---- the row above the band
+        // Block q, value k of the band above is column 16 q + k - 63 of its last row.  Red's block
+        // b needs the last two values of block b + 3 and b + 4 but for its last.  A thread asks for two values, the
+        // wavefront for eight blocks at a time, and leaves what has arrived in `carry`.
         const bool some = band != 0u, first_of_launch = band == a.band0;
         // (the first band of a launch: the band above is done, its last row is in the image)
         const uint8_t *above_row =
             img + (size_t)((strip * a.strip_rows + (some ? band_row0 - 1u : 0u)) * a.w) * 3u;
-        const unsigned long long *words = a.words + (size_t)(id - (some && !first_of_launch ? 1u : 0u)) * (4u * a.blocks);
+        const unsigned long long *words = reinterpret_cast<const unsigned long long *>(
+            a.words + (size_t)(place - (some && !first_of_launch ? 1u : 0u)) * (16u * a.blocks));
         int got = 0;  // blocks in LDS so far
         bool gave_up = false;
         auto follow = [&](auto in_image) {
             auto ask = [&](int base) -> unsigned long long {
-                const int q = min(base + (int)((lane & 31u) >> 2), blocks - 1), k = (int)(lane & 3u);
+                const int q = min(base + (int)(lane >> 3), blocks - 1), k = (int)(lane & 7u);
                 if (!decltype(in_image)::value)
-                    return __hip_atomic_load(words + 4 * q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                uint32_t v = 0;
+                    return __hip_atomic_load(words + 8 * q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                unsigned long long v = 0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int col = 16 * q + 4 * k + i - 63;
+                for (int i = 0; i < 2; ++i) {
+                    const int col = 16 * q + 2 * k + i - 63;
                     const uint32_t x = above_row[3 * min(max(col, 0), (int)a.w - 1)];
-                    v |= x << (8 * i);  // (what is outside the row is not used)
+                    // (left of the row is padding; what is right of it is not used)
+                    v |= (unsigned long long)((a.mark << 24) | (col < 0 ? 0u : x)) << (32 * i);
                 }
-                return (1ull << 32) | v;
+                return v;
             };
             // `now`: the block red is at; a block goes into LDS once the one it replaces has been used
             auto take = [&](unsigned long long v, int base, int now) {
-                const uint32_t missing = ~(uint32_t)__ballot((uint32_t)(v >> 32) != 0u);
-                const int whole = missing == 0u ? 8 : (__ffs((int)missing) - 1) >> 2;
+                const uint32_t v0 = (uint32_t)v, v1 = (uint32_t)(v >> 32);
+                const unsigned long long missing = ~__ballot((v0 >> 24) == a.mark && (v1 >> 24) == a.mark);
+                const int whole = missing == 0u ? 8 : (__ffsll(missing) - 1) >> 3;
                 const int upto = min(min(base + whole, blocks), now + kDiagCarry);
-                const int q = base + (int)(lane >> 2);
-                if (lane < 32u && q >= got && q < upto) carry[q % kDiagCarry][lane & 3u] = (uint32_t)v;
+                const int q = base + (int)(lane >> 3);
+                if (q >= got && q < upto) {
+                    // value number v is above thread 0 at step v - 63
+                    uint32_t *up = reinterpret_cast<uint32_t *>(&carry[0][0]);
+                    const uint32_t at = 16u * (uint32_t)q + 2u * (lane & 7u), size = 16u * kDiagCarry;
+                    up[(at + 1u) % size] = v0;
+                    up[(at + 2u) % size] = v1;
+                }
                 got = max(got, upto);
             };
             unsigned long long asked[kDiagPolls] = {};
@@ -765,6 +1200,7 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
                             if (wall_clock64() - since > a.wait_ticks) {
                                 gave_up = true;
                                 __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                raise_code(a.report, ST_TIMEOUT);
                                 break;
                             }
                             __builtin_amdgcn_s_sleep(8);
@@ -789,52 +1225,91 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_diag(TwarK p, Diag a, c
 // entry points take no workspace), handed out under a lock so that concurrent calls do not share
 // one; a call that finds none free goes a band at a time, a launch each, every band reading the row
 // above it from the image.
+//
+// A set is not cleared between calls: the words of a launch carry its mark, of which there are 255, and its
+// workgroups count on from where the ticket stands.  It is cleared before a mark comes back, and after a call that
+// gave up or failed.  (Cleared by a kernel before each launch, and with the abort word copied back instead of raised in
+// pinned memory, 30 frames of 1080 x 1920 took 12 us more.)
 constexpr uint32_t kTileManyImages = 1024;  // a wavefront for every SIMD
 constexpr int kBandSlots = 4;
-constexpr uint32_t kBandWords = 1u << 19;  // 4 MB a set: 127 bands of 16384 columns, 1057 of 1920
+constexpr uint32_t kBandWords = 1u << 21;  // 8 MB a set: 127 bands of 16384 columns, 1057 of 1920
+constexpr uint32_t kBandMarks = 255;
 struct BandSet {
-    unsigned long long words[kBandWords];
+    uint32_t words[kBandWords];
     uint32_t ticket, abort_word;
+    Report report;  // of a call that finds no place in pinned memory
+};
+struct BandState {  // what the host knows of a set; its holder's alone while it is taken
+    bool taken = false, stale = false;
+    uint32_t mark = 0, tickets = 0;  // of the last launch; workgroups that have taken a ticket so far
 };
 static __device__ BandSet g_band_sets[kBandSlots];
+struct BandDevice {
+    BandSet *sets = nullptr;
+    BandState state[kBandSlots];
+};
 static std::mutex g_band_mutex;
-static bool g_band_in_use[kBandSlots];
-static std::map<int, BandSet *> g_band_base;  // per device: address of g_band_sets there
+static std::map<int, BandDevice> g_band_devices;
 
-__global__ __launch_bounds__(256) void k_band_clear(BandSet *set, uint32_t words, bool first)
+__global__ __launch_bounds__(256) void k_band_clear(BandSet *set)
 {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x) set->words[i] = 0ull;
-    if (blockIdx.x == 0u && threadIdx.x == 0u) {
-        set->ticket = 0u;
-        if (first) set->abort_word = 0u;
-    }
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < kBandWords; i += gridDim.x * blockDim.x) set->words[i] = 0u;
+    if (blockIdx.x == 0u && threadIdx.x == 0u) set->ticket = set->abort_word = 0u;
 }
 
-// A free set on the current device (null if none), and its release.
-static BandSet *band_set_acquire(int *slot_out)
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-    std::lock_guard<std::mutex> lock(g_band_mutex);
-    auto it = g_band_base.find(dev);
-    if (it == g_band_base.end()) {
-        void *ptr = nullptr;
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_band_sets)) != hipSuccess) return nullptr;
-        it = g_band_base.emplace(dev, static_cast<BandSet *>(ptr)).first;
+// A free set on the current device (null if none), given back at the end.
+class BandLease {
+public:
+    BandLease() = default;
+    ~BandLease()
+    {
+        if (!state_) return;
+        std::lock_guard<std::mutex> lock(g_band_mutex);
+        state_->taken = false;
     }
-    for (int i = 0; i < kBandSlots; ++i)
-        if (!g_band_in_use[i]) {
-            g_band_in_use[i] = true;
-            *slot_out = i;
-            return it->second + i;
+    BandLease(const BandLease &) = delete;
+    BandLease &operator=(const BandLease &) = delete;
+    void acquire()
+    {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return;
+        std::lock_guard<std::mutex> lock(g_band_mutex);
+        BandDevice &d = g_band_devices[dev];
+        if (!d.sets) {
+            void *ptr = nullptr;
+            if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_band_sets)) != hipSuccess) return;
+            d.sets = static_cast<BandSet *>(ptr);
         }
-    return nullptr;
-}
-static void band_set_release(int slot)
-{
-    std::lock_guard<std::mutex> lock(g_band_mutex);
-    g_band_in_use[slot] = false;
-}
+        for (int i = 0; i < kBandSlots; ++i)
+            if (!d.state[i].taken) {
+                set_ = d.sets + i;
+                state_ = &d.state[i];  // (a map's elements stay where they are)
+                state_->taken = true;
+                clear_ = state_->stale;
+                state_->stale = true;  // until the call says that all went well
+                return;
+            }
+    }
+    BandSet *set() const { return set_; }
+    // The mark of the next launch, of `workgroups`, and where the ticket stands before it.
+    void next_launch(uint32_t workgroups, hipStream_t stream, uint32_t *mark, uint32_t *first_ticket)
+    {
+        if (clear_ || state_->mark == kBandMarks) {
+            k_band_clear<<<1024, 256, 0, stream>>>(set_);
+            state_->mark = state_->tickets = 0u;
+            clear_ = false;
+        }
+        *mark = ++state_->mark;
+        *first_ticket = state_->tickets;
+        state_->tickets += workgroups;
+    }
+    void all_went_well() { state_->stale = false; }
+
+private:
+    BandSet *set_ = nullptr;
+    BandState *state_ = nullptr;
+    bool clear_ = false;
+};
 
 static int make_twar(const pilc_twar_params *in, uint32_t n, uint32_t h, uint32_t w, TwarK *k)
 {
@@ -886,30 +1361,43 @@ int pilc_twar_forward(uint32_t n, uint32_t h, uint32_t w, const uint8_t *img_dev
     return PILC_OK;
 }
 
-// Whether the bands of a batch are decoded one at a time, a launch each, and not together.  Together, a band waits
-// a good part of its time for the one above and takes a place that another strip could have; one at a
-// time, a launch has no more workgroups than there are strips.  So it depends on how well the strips
-// fill the chip by themselves, and how far beyond its places (four workgroups a compute unit, 1024) all bands
-// together would go; wider rows wait less.  Together against one at a time, us:
-//   strips x bands   64 columns    400 columns       strips x bands   64 columns    400 columns
-//     64 x 12         106  166      137  291           160 x 8        163  124      203  203
-//    112 x 10         152  150      189  247           160 x 12       264  178      327  300
-//    112 x 16         274  232      337  389           176 x 5         94   83      123  133
-//    128 x 8          129  123      165  202           200 x 3         60   53       86   87
-//    128 x 12         218  178      263  296           250 x 5        136   79      185  135
-// and two bands of up to 192 columns are too short to gain anything from running together (48 x 2, 128 columns:
-// 49 and 46; 160 x 2: 55 and 47).
-static bool bands_one_at_a_time(uint64_t strips, uint32_t bands, uint32_t w)
+// Whether the bands of a batch are decoded one at a time, a launch each, and not together: where the strips by themselves
+// fill the chip with workgroups of the kernel that goes a band at a time, four on a compute unit (two of the other),
+// and there are few bands, or short ones, which together spend much of their time on getting under way.  Together
+// (two a unit) against one at a time, us:
+//   strips x bands x columns                strips x bands x columns
+//     256 x 2 x 256     47    52              500 x 3 x 400    116   105
+//     300 x 2 x 256     57    61              250 x 5 x 400    102   135
+//     400 x 2 x 256     65    62             1000 x 8 x 256    480   518
+//     500 x 2 x 512    108    87              500 x 4 x 64      92    80
+//     300 x 3 x 400     89   104             2000 x 8 x 96     633   499
+//     400 x 3 x 400     95   104             1000 x 4 x 256    238   250
+static bool bands_one_at_a_time(uint64_t strips, uint32_t bands, uint32_t blocks)
 {
-    if (strips >= 192u || (bands == 2u && w < 192u)) return true;
-    return strips * strips * bands >= (w < 192u ? 131000u : 200000u);
+    return strips >= 384u && (bands <= 3u || blocks <= 14u);
 }
 
-// pilc_twar_inverse by k_twar_inverse_diag.
+// Whether bands that run together have a compute unit each.  A band that has one to itself is half as fast again, and one that
+// is slow holds up all below it; but two on a unit get more done where there are so many strips that those behind
+// are not waited for.  One a unit against two, us:
+//   strips x bands x columns                strips x bands x columns
+//      30 x 17 x 1920   211   263             112 x 10 x 400   130   112
+//      60 x 17 x 1920   344   404             128 x 12 x 400   152   135
+//      64 x 12 x 64      77    89             128 x 8 x 128     85   103
+//      64 x 12 x 400    102   118             160 x 12 x 64    123    98
+//      50 x 10 x 800    103   110             150 x 5 x 800    116   112
+//     191 x 4 x 1500    192   216             300 x 4 x 600    150   122
+static bool bands_alone_on_a_unit(uint64_t strips, uint32_t blocks)
+{
+    return blocks >= 64u || (strips < 144u && strips * (blocks + 9u) <= 3300u);
+}
+
+// pilc_twar_inverse along the diagonals.
 static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev, const TwarK &k,
                              uint8_t *img_dev, hipStream_t stream, Timer &timer)
 {
     Diag a = {};
+    a.mark = 1u;  // (0 is what a word that is not there has)
     a.h = h;
     a.w = w;
     a.rows = (unsigned long long)n * h;
@@ -917,13 +1405,15 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
     a.blocks = (w + 63u + 15u) / 16u;
     const uint64_t strips = (a.rows + a.strip_rows - 1u) / a.strip_rows;
     const uint32_t bands = (a.strip_rows + 63u) / 64u;
-    int slot = -1;
-    BandSet *set = bands > 1u && !bands_one_at_a_time(strips, bands, w) ? band_set_acquire(&slot) : nullptr;
+    BandLease lease;
+    if (bands > 1u && !bands_one_at_a_time(strips, bands, a.blocks)) lease.acquire();
+    BandSet *const set = lease.set();
+    std::optional<CallReport> report;
     // bands of a strip and strips in a launch: what the words passed on have room for
-    const uint32_t band_words = 4u * a.blocks;
+    const uint32_t band_words = 16u * a.blocks;
     const uint32_t together = set ? (uint32_t)std::min<uint64_t>(bands, kBandWords / band_words) : 1u;
-    const uint64_t most_strips = together > 1u ? std::max<uint64_t>(1u, kBandWords / ((uint64_t)together * band_words)) : 1u << 20;
-    const uint32_t threads = bands > 1u ? 64u * 6u : 64u * 5u;
+    uint64_t most_strips = together > 1u ? std::max<uint64_t>(1u, kBandWords / ((uint64_t)together * band_words)) : 1u << 20;
+    most_strips = ceil_div64(strips, ceil_div64(strips, most_strips));  // launches of one size
     int dev = 0, khz = 0;
     const unsigned long long wait = g_one_pass_wait.load(std::memory_order_relaxed);
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -932,39 +1422,39 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
     a.wait_ticks = wait ? wait : 2000ull * (unsigned long long)khz;
     a.withhold = (uint32_t)g_one_pass_withhold.load(std::memory_order_relaxed);
     if (set) {
+        report.emplace(&set->report, stream, true);
         a.ticket = &set->ticket;
         a.abort_word = &set->abort_word;
+        a.report = report->dev();
     }
-    int rc = PILC_OK;
-    bool first = true;
-    for (uint64_t s = 0; rc == PILC_OK && s < strips; s += most_strips) {
+    for (uint64_t s = 0; s < strips; s += most_strips) {
         const uint32_t here = (uint32_t)std::min<uint64_t>(most_strips, strips - s);
         for (uint32_t b = 0; b < bands; b += together) {
             a.strip0 = s;
+            a.strips = here;
             a.band0 = b;
             a.bands = std::min(together, bands - b);
             a.words = a.bands > 1u ? set->words : nullptr;
-            if (set) {
-                const uint32_t words = a.bands > 1u ? here * a.bands * band_words : 0u;
-                k_band_clear<<<std::max(1u, std::min(1024u, words / 256u)), 256, 0, stream>>>(set, words, first);
-                first = false;
+            if (a.bands > 1u) {
+                lease.next_launch(here * a.bands, stream, &a.mark, &a.first_ticket);
+                const uint32_t lds = bands_alone_on_a_unit(here, a.blocks) ? kDiagAloneBytes : kDiagRawBytes;
+                k_twar_inverse_bands<<<here * a.bands, 64 * 6, lds, stream>>>(k, a, res_dev, img_dev);
+            } else {
+                k_twar_inverse_strips<<<here, bands > 1u ? 64 * 6 : 64 * 5, 0, stream>>>(k, a, res_dev, img_dev);
             }
-            k_twar_inverse_diag<<<here * a.bands, threads, 0, stream>>>(k, a, res_dev, img_dev);
         }
     }
     timer.mark("k_twar_inverse");
-    uint32_t aborted = 0u;
-    if (rc == PILC_OK) {
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess && set)
-            e = hipMemcpyAsync(&aborted, &set->abort_word, sizeof(aborted), hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-        if (e != hipSuccess) rc = hip_fail(e, "k_twar_inverse_diag");
-    }
-    if (set) band_set_release(slot);
-    if (rc != PILC_OK) return rc;
+    HIP_TRY(hipGetLastError());
+    Report seen = {};
+    if (set)
+        HIP_TRY(report->wait(&seen));
+    else
+        HIP_TRY(hipStreamSynchronize(stream));
     timer.finish();
-    return aborted ? PILC_E_TIMEOUT : PILC_OK;
+    if (raised_code(seen) != ST_OK) return status_to_error(raised_code(seen));
+    if (set) lease.all_went_well();
+    return PILC_OK;
 }
 
 // Whether images of more than 64 rows whose rows fit a tile go 64 rows after 64 through the tile kernel.  That takes

@@ -198,6 +198,36 @@ def test_more_calls_at_once_than_sets_of_words():
     assert not wrong
 
 
+# Bands together or one at a time (384 strips, by bands and by blocks of columns), and together with a compute unit
+# each or two to one (64 blocks; 144 strips; strips times blocks): either side of every line, odd sizes among them.
+@pytest.mark.parametrize("shape", [(383, 130, 64), (384, 130, 64), (384, 200, 161), (384, 200, 162), (143, 131, 161),
+                                   (144, 131, 161), (132, 129, 176), (132, 129, 194), (20, 140, 945), (20, 140, 946),
+                                   (1, 65, 1), (1, 127, 17), (1, 193, 33)], ids=lambda s: "x".join(map(str, s)))
+def test_lines_of_bands(shape):
+    print("shape", shape, flush=True)
+    rng = np.random.default_rng(sum(shape))
+    noise = rng.integers(0, 256, shape + (3,), dtype=np.uint8)
+    _, wq, bq = list(models(rng))[1]
+    d_back = torch.full(noise.shape, 0xA5, dtype=torch.uint8, device="cuda:0")
+    pb.pilc_twar_inverse(pb.make_twar_params(wq, bq), torch.from_numpy(noise).cuda(), d_back)
+    assert np.array_equal(d_back.cpu().numpy(), to.inverse(to.make_params(wq, bq), noise))
+
+
+def test_more_launches_than_marks():
+    """The words that bands pass on carry the mark of their launch, of which there are 255: 600 calls in a row on two
+    images by turns, of different heights, so that words of all earlier launches stand where a band looks."""
+    rng = np.random.default_rng(12)
+    wq, bq = [[ONE // 2, ONE // 4, ONE // 4]] * 3, [3 * ONE, 0, 0]
+    p, q = pb.make_twar_params(wq, bq), to.make_params(wq, bq)
+    images = [rng.integers(0, 256, s, dtype=np.uint8) for s in ((1, 140, 100, 3), (2, 200, 61, 3))]
+    residuals = [torch.from_numpy(to.forward(q, i)).cuda() for i in images]
+    images = [torch.from_numpy(i).cuda() for i in images]
+    for turn in range(600):
+        back = torch.full_like(images[turn % 2], 0xA5)
+        pb.pilc_twar_inverse(p, residuals[turn % 2], back)
+        assert torch.equal(back, images[turn % 2]), turn
+
+
 def test_bad_arguments():
     img = torch.zeros((2, 4, 4, 3), dtype=torch.uint8, device="cuda:0")
     out = torch.zeros_like(img)
