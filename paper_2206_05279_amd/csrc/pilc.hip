@@ -1352,8 +1352,8 @@ static int mix_built_for(const pilc_mix_params *p)
     return aligned ? (int)p->num_comp : 0;
 }
 
-#define PILC_MIX_KERNEL_FOR(NAME)                                                                \
-    static decltype(&NAME<0>) NAME##_for(int built)                                              \
+#define PILC_MIX_KERNEL_FOR(NAME, NONE)                                                          \
+    static decltype(&NAME<1>) NAME##_for(int built)                                              \
     {                                                                                            \
         switch (built) {                                                                         \
         case 1: return NAME<1>;                                                                  \
@@ -1372,11 +1372,11 @@ static int mix_built_for(const pilc_mix_params *p)
         case 14: return NAME<14>;                                                                \
         case 15: return NAME<15>;                                                                \
         case 16: return NAME<16>;                                                                \
-        default: return NAME<0>;                                                                 \
+        default: return NONE;                                                                    \
         }                                                                                        \
     }
-PILC_MIX_KERNEL_FOR(k_mix_encode)
-PILC_MIX_KERNEL_FOR(k_mix_decode)
+PILC_MIX_KERNEL_FOR(k_mix_encode_chunks, nullptr)
+PILC_MIX_KERNEL_FOR(k_mix_decode, k_mix_decode<0>)
 #undef PILC_MIX_KERNEL_FOR
 
 int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mix_params *params,
@@ -1407,15 +1407,24 @@ int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mi
     const MixArgs args = {params->mu, params->log_scale, params->weight, params->chan_coef,
                           params->num_comp};
     const int built = mix_built_for(params);
-    const size_t lds = mix_lds_bytes(params->num_comp, built == 0);
-    auto kern = k_mix_encode_for(built);
-    if ((rc = allow_large_lds(reinterpret_cast<const void *>(kern))) != PILC_OK) return rc;
+    const uint32_t lane_cap = max_lane_symbols(g);
+    auto chunks = k_mix_encode_chunks_for(built);
+    const size_t lds = chunks ? mix_encode_lds_bytes(built) : mix_lds_bytes(params->num_comp, true);
+    if ((rc = allow_large_lds(chunks ? reinterpret_cast<const void *>(chunks) : reinterpret_cast<const void *>(&k_mix_encode))) != PILC_OK)
+        return rc;
 
     Timer timer(stream);
     k_init_status<<<1, 1, 0, stream>>>(status);
-    const uint32_t lane_cap = max_lane_symbols(g);
-    kern<<<(uint32_t)ceil_div64(g.lanes, kMixThreads), kMixThreads, lds, stream>>>(
-        g, img_dev, args, scratch, lane_cap, lane_words, lane_state, &status->code);
+    if (chunks) {
+        const MixChunk c = mix_chunk(g.lanes, lane_cap / 3u);
+        const uint64_t waves = ceil_div64(g.lanes, 1u << c.log_lanes);
+        const uint32_t threads = (uint32_t)mix_encode_threads(built);
+        chunks<<<(uint32_t)ceil_div64(waves, threads / 64u), threads, lds, stream>>>(
+            g, c, img_dev, args, scratch, lane_cap, lane_words, lane_state, &status->code);
+    } else {
+        k_mix_encode<<<(uint32_t)ceil_div64(g.lanes, kMixThreads), kMixThreads, lds, stream>>>(
+            g, img_dev, args, scratch, lane_cap, lane_words, lane_state, &status->code);
+    }
     timer.mark("k_mix_encode");
     const HeaderWords head = {{kMagicMix, PILC_VERSION, g.n, g.h, g.w, 3u, g.prec_bits, g.lane_mode,
                                g.lane_a, g.lane_b, g.lanes, params->num_comp}};

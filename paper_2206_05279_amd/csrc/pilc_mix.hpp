@@ -1,4 +1,5 @@
-// rANS lanes under a mixture of K logistic laws per subpixel, one thread per lane (gfx950).
+// rANS lanes under a mixture of K logistic laws per subpixel (gfx950): one thread per lane, but for the encoder of
+// aligned arrays, whose evaluations are shared out by pixels (k_mix_encode_chunks).
 //
 // Sec. 2 of arXiv 2206.05279 names this workload (a dynamic rANS coder fed a mixture of ten
 // logistic laws per symbol) as what holds earlier learned codecs near 1 MB/s; the coder itself is
@@ -37,20 +38,18 @@ struct MixArgs {
 // 8-byte elements, then per thread the pixel's raw means (3 K halfwords), log-scales (3 K) and
 // weights (K), each rounded up to dwords, as [dword][thread].  The kernels built for one K have
 // neither the pairs nor the weights there.
-constexpr uint32_t kMixImageBlock = 32;   // bytes of the image a thread of the encoder keeps in LDS
-constexpr uint32_t kMixWeightBlock = 64;  // bytes of the weights a thread keeps there (kernels built for one K)
+constexpr uint32_t kMixImageBlock = 32;  // bytes of the image a thread of the general encoder keeps in LDS
 
 struct MixSlots {
     uint2 *pairs;    // this thread's column of the pairs
     uint32_t *base;  // this thread's column of the raw parameters
-    uint32_t k, stride, raw_ls, raw_w, image_block, weight_block;
+    uint32_t k, stride, raw_ls, raw_w, image_block;
     static constexpr uint32_t raw_mu = 0u;
     __device__ __forceinline__ MixSlots(uint32_t *lds, uint32_t k_, bool with_pairs = true)
         : pairs(reinterpret_cast<uint2 *>(lds) + threadIdx.x),
           base(lds + (with_pairs ? 2u * k_ * blockDim.x : 0u) + threadIdx.x), k(k_), stride(blockDim.x),
           raw_ls((3u * k_ + 1u) / 2u), raw_w(2u * ((3u * k_ + 1u) / 2u)),
-          image_block(2u * ((3u * k_ + 1u) / 2u) + (with_pairs ? (k_ + 1u) / 2u : 0u)),
-          weight_block(image_block + kMixImageBlock / 4u)
+          image_block(2u * ((3u * k_ + 1u) / 2u) + (k_ + 1u) / 2u)
     {
     }
     __device__ __forceinline__ uint32_t &dword(uint32_t i) const { return base[i * stride]; }
@@ -69,14 +68,12 @@ struct MixSlots {
     }
 };
 
-// with_pairs false: the kernels built for one K, which keep the pairs and the weights in registers.
-// The blocks of image bytes and of weights are the encoder's (the decoder's columns have them too,
-// unused: one layout for both).
+// with_pairs false: the decoders built for one K, which keep the pairs and the weights in registers.  (The block of
+// image bytes is the general encoder's; the general decoder has it too, unused: one layout for both.)
 static inline size_t mix_lds_bytes(uint32_t k, bool with_pairs)
 {
     return (size_t)kMixThreads * 4u *
-           ((with_pairs ? 2u * k + (k + 1u) / 2u : kMixWeightBlock / 4u) + 2u * ((3u * k + 1u) / 2u) +
-            kMixImageBlock / 4u);
+           ((with_pairs ? 2u * k + (k + 1u) / 2u + kMixImageBlock / 4u : 0u) + 2u * ((3u * k + 1u) / 2u));
 }
 
 // An aligned block of kBytes of global memory in a thread's LDS column ([dword][thread]), loaded
@@ -178,8 +175,7 @@ __device__ __forceinline__ bool mix_can_run_ahead(const MixArgs &a)
                                  reinterpret_cast<uintptr_t>(a.weight)) & 3u) == 0u;
 }
 
-// kWeights false: the weights come some other way (the encoder built for one K has an LdsBlock).
-template <int kK, bool kWeights = true>
+template <int kK>
 __device__ __forceinline__ void mix_fetch_ahead(const MixArgs &a, uint32_t p, MixAhead<kK> &r)
 {
     const uint32_t k = kK > 0 ? (uint32_t)kK : a.k;
@@ -194,46 +190,16 @@ __device__ __forceinline__ void mix_fetch_ahead(const MixArgs &a, uint32_t p, Mi
 #pragma unroll
     for (int i = 0; i < MixAhead<kK>::kMu; ++i)
         if ((uint32_t)i < n3) r.l[i] = gl[i];
-    if constexpr (kWeights) {
 #pragma unroll
-        for (int i = 0; i < MixAhead<kK>::kW; ++i)
-            if ((uint32_t)i < n1) r.w[i] = gw[i];
-    }
-}
-
-// The weights of pixel p into `regs`, through the thread's block (dword-aligned array), highest
-// address first: the encoder walks its lane backwards.  False if they do not sum to 2^15.
-template <int kK>
-__device__ __forceinline__ bool mix_load_weights(const MixArgs &a, uint32_t p, LdsBlock<kMixWeightBlock> &block,
-                                                 MixRegs<kK> &regs)
-{
-    const uintptr_t at = reinterpret_cast<uintptr_t>(a.weight + (size_t)p * kK);
-    uint32_t sum = 0;
-    if constexpr (kK % 2 == 0) {
-#pragma unroll
-        for (int i = kK / 2 - 1; i >= 0; --i) {
-            const uint32_t w2 = block.dword(at + 4u * i);
-            regs.w[2 * i] = w2 & 0xFFFFu;
-            regs.w[2 * i + 1] = w2 >> 16;
-        }
-    } else {  // a halfword at a time: the pixel's weights start on either half of a dword
-#pragma unroll
-        for (int j = kK - 1; j >= 0; --j) {
-            const uintptr_t b = at + 2u * j;
-            const uint32_t w2 = block.dword(b);
-            regs.w[j] = (b & 2u) ? w2 >> 16 : w2 & 0xFFFFu;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < kK; ++j) sum += regs.w[j];
-    return sum == (1u << 15);
+    for (int i = 0; i < MixAhead<kK>::kW; ++i)
+        if ((uint32_t)i < n1) r.w[i] = gw[i];
 }
 
 // The fetched pixel into the slots, its weights into `regs` in the kernels built for one K; false
-// if the weights do not sum to 2^15.  kWeights as above (then true).  `upper`: the pixel's blocks
+// if the weights do not sum to 2^15.  `upper`: the pixel's blocks
 // start on the upper half of the first dword fetched (odd K, every other pixel) and are moved down
 // by a halfword on the way.
-template <int kK, bool kWeights = true>
+template <int kK>
 __device__ __forceinline__ bool mix_store_ahead(const MixAhead<kK> &r, const MixSlots &s, MixRegs<kK> &regs,
                                                 bool upper)
 {
@@ -251,7 +217,6 @@ __device__ __forceinline__ bool mix_store_ahead(const MixAhead<kK> &r, const Mix
 #pragma unroll
     for (int i = 0; i < MixAhead<kK>::kMu; ++i)
         if ((uint32_t)i < n3) s.dword(s.raw_ls + i) = lowered(r.l, i, MixAhead<kK>::kMu);
-    if constexpr (!kWeights) return true;
 #pragma unroll
     for (int i = 0; i < MixAhead<kK>::kW; ++i)
         if ((uint32_t)i < n1) {
@@ -386,10 +351,8 @@ __device__ __forceinline__ uint32_t mix_cum_inner(int k, const MixRegs<kK> &regs
 // us, now 501; of 4096 at K = 9 2178, now 1856.
 constexpr int mix_waves(int k) { return k >= 4 ? 2 : 8; }
 
-// kK > 0: built for that many components (even, dword-aligned arrays: the host checks), which then
-// live in registers; kK == 0: any K, components in LDS.
-template <int kK>
-__global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, mix_waves(kK)))) void k_mix_encode(
+// The encoder for arrays off the 4-byte grid: any K, components in LDS, a thread per lane.
+__global__ __launch_bounds__(kMixThreads) void k_mix_encode(
     Geo g, const uint8_t *__restrict__ img, MixArgs a, uint16_t *__restrict__ scratch,
     uint32_t lane_cap, uint32_t *__restrict__ lane_words, uint32_t *__restrict__ lane_state,
     int *__restrict__ status_code)
@@ -399,7 +362,7 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
     load_tables(tab);
     const uint32_t lane = blockIdx.x * blockDim.x + threadIdx.x;
     if (lane >= g.lanes) return;
-    const MixSlots slots(mix_lds, kK > 0 ? (uint32_t)kK : a.k, kK == 0);
+    const MixSlots slots(mix_lds, a.k, true);
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
     const uint32_t scale = mass_scale(m_bits), top = 1u << m_bits;
@@ -408,18 +371,9 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
     uint32_t nwords = 0, S = 1u << 16;
     bool ok = true;
     // pixels last-first, and B, G, R inside a pixel (App. A eq. (11) runs against the decoder)
-    const bool ahead = kK > 0 || mix_can_run_ahead(a);
-    MixAhead<kK> pre;
-    MixRegs<kK> regs;
     PixelBytes bytes(slots);
-    LdsBlock<kMixWeightBlock> weights(slots.base + slots.weight_block * slots.stride, slots.stride);
     uint32_t im_now = 0xFFFFFFFFu;
     int a_gr = 0, a_br = 0, a_bg = 0;
-    // built for one K: the weights reach the registers through a block in LDS, which costs a wait
-    // when the block runs out and saves most of their traffic (the decoder, bound by its
-    // arithmetic, keeps fetching them ahead with the other parameters)
-    constexpr bool kAheadW = kK == 0;
-    if (ahead && sh.npx != 0u) mix_fetch_ahead<kK, kAheadW>(a, lane_pixel(g, sh, sh.npx - 1u), pre);
     for (uint32_t t = sh.npx; t-- > 0u;) {
         const uint32_t p = lane_pixel(g, sh, t);
         const uint32_t im = g.by_hw.div(p);
@@ -427,28 +381,15 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
             im_now = im;
             a_gr = a.coef[3 * im]; a_br = a.coef[3 * im + 1]; a_bg = a.coef[3 * im + 2];
         }
-        if (ahead) {
-            ok = mix_store_ahead<kK, kAheadW>(pre, slots, regs, (kK & 1) != 0 && (p & 1u) != 0u) && ok;
-            if constexpr (!kAheadW) ok = mix_load_weights<kK>(a, p, weights, regs) && ok;
-            if (t != 0u) mix_fetch_ahead<kK, kAheadW>(a, lane_pixel(g, sh, t - 1u), pre);
-        } else {
-            ok = mix_load_pixel(a, p, slots) && ok;
-        }
+        ok = mix_load_pixel(a, p, slots) && ok;
         const uint32_t xb = bytes.pixel(img, p);
         const int x[3] = {(int)(xb & 0xFFu), (int)((xb >> 8) & 0xFFu), (int)(xb >> 16)};
 #pragma unroll 1
         for (int ch = 2; ch >= 0; --ch) {
             const int v = ch == 0 ? x[0] : (ch == 1 ? x[1] : x[2]);
-            uint32_t lo, hi;
-            if constexpr (kK > 0) {
-                mix_load_channel(slots, regs, ch, x[0], x[1], a_gr, a_br, a_bg, tab);
-                lo = v == 0 ? 0u : mix_cum_inner(v, regs, scale, tab);
-                hi = v == 255 ? top : mix_cum_inner(v + 1, regs, scale, tab);
-            } else {
-                mix_load_channel(slots, ch, x[0], x[1], a_gr, a_br, a_bg, tab);
-                lo = v == 0 ? 0u : mix_cum_inner(v, slots, scale, tab);
-                hi = v == 255 ? top : mix_cum_inner(v + 1, slots, scale, tab);
-            }
+            mix_load_channel(slots, ch, x[0], x[1], a_gr, a_br, a_bg, tab);
+            const uint32_t lo = v == 0 ? 0u : mix_cum_inner(v, slots, scale, tab);
+            const uint32_t hi = v == 255 ? top : mix_cum_inner(v + 1, slots, scale, tab);
             const uint32_t f = hi - lo;
             if (S >= (f << (32u - m_bits))) {
                 *wout = (uint16_t)(S & 0xFFFFu);
@@ -462,6 +403,159 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
     if (!ok) atomicMax(status_code, 7);
     lane_words[lane] = nwords;
     lane_state[lane] = S;
+}
+
+// --------------------------------------------------------------------------------------------
+// The encoder for arrays on 4-byte boundaries, built for each component count.
+//
+// All an encoder has to evaluate is known beforehand, so the evaluations are shared out by where the parameters lie: a
+// wavefront takes 2^log_lanes lanes, and of every lane a chunk of 2^log_chunk pixels at a time, last chunk first.  Its threads
+// evaluate the chunk, neighbouring threads neighbouring pixels, and leave {C, mass} of every symbol in LDS; then a thread
+// per lane runs the serial chain over them.  A pixel's parameters go straight from memory to the registers of the thread
+// that uses them, and those of a chunk are one run of memory, so a line is fetched once or twice instead of once a
+// pixel.  (A thread per lane, which comes back for the rest of a line when it has long left the L2, read 2.7 times the
+// parameters, at 6.1 TB/s: 2048 images of 64 x 64, ten components, a lane a row, whole call 558 us, now 376; and a small batch
+// went a pixel after another: 64 such images 366 us, now 91; two photographs of 1365 x 2047 with a lane a row 13.3 ms, now 1.2.)
+// The wavefronts share nothing but the tables, so there is no barrier.
+// --------------------------------------------------------------------------------------------
+// Four wavefronts on a SIMD, in workgroups of eight that share the tables; from twelve components on the registers are those of
+// three, in workgroups of four (at four, K = 16 spills 164 bytes a thread: 1024 images of 64 x 64 595 us, now 325).
+constexpr int mix_encode_waves(int k) { return k >= 12 ? 3 : 4; }
+constexpr int mix_encode_threads(int k) { return k >= 12 ? 256 : 512; }
+constexpr uint32_t kMixEncRecords = 512;  // pixels of a wavefront's chunks: most lanes times pixels
+
+struct MixChunk {  // how a launch shares out its lanes: lanes of a wavefront and pixels of a lane at a time
+    uint32_t log_lanes, log_chunk;
+};
+
+// Pixels a chunk: sixteen where lanes have four chunks and more (a run of 960 bytes with ten components, 1.13 lines fetched for
+// one; with eight 425 us for 417), fewer where they would leave threads without a pixel.  Lanes a wavefront: the chain is run by
+// a thread a lane and costs 4 / lanes of the evaluations, so 32, unless that leaves less than one and a half wavefronts a
+// SIMD; at least so many that every thread has a pixel.  Lines at 1024, 1536, 3072, 4096 wavefronts, us: 32,768 lanes of 64
+// pixels 216, 150, 156, 156; 16,384 137, 113, 121, 123; 15,876 tiles 301, 299, 327, 325.
+static MixChunk mix_chunk(uint32_t lanes, uint32_t lane_pixels)
+{
+    MixChunk c;
+    c.log_chunk = lane_pixels >= 64u ? 4u : lane_pixels >= 16u ? 3u : lane_pixels >= 4u ? 2u : lane_pixels >= 2u ? 1u : 0u;
+    c.log_lanes = 6u - c.log_chunk;
+    while (c.log_lanes < 5u && (lanes >> (c.log_lanes + 1u)) >= 1536u) ++c.log_lanes;
+    return c;
+}
+
+static inline size_t mix_encode_lds_bytes(int k) { return (size_t)(mix_encode_threads(k) / 64) * (kMixEncRecords * 12u + 64u * 16u); }
+
+template <int kK>
+__global__ __launch_bounds__(mix_encode_threads(kK)) __attribute__((amdgpu_waves_per_eu(mix_encode_waves(kK)))) void k_mix_encode_chunks(
+    Geo g, MixChunk c, const uint8_t *__restrict__ img, MixArgs a, uint16_t *__restrict__ scratch, uint32_t lane_cap,
+    uint32_t *__restrict__ lane_words, uint32_t *__restrict__ lane_state, int *__restrict__ status_code)
+{
+    __shared__ LdsTables tab;
+    extern __shared__ uint32_t mix_lds[];
+    load_tables(tab);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), t = threadIdx.x & 63u;
+    const uint32_t lanes_here = 1u << c.log_lanes, chunk = 1u << c.log_chunk;
+    const uint32_t lane0 = (blockIdx.x * (mix_encode_threads(kK) / 64) + wave) << c.log_lanes;
+    if (lane0 >= g.lanes) return;
+    uint32_t *rec = mix_lds + wave * (kMixEncRecords * 3u + 64u * 4u);  // [symbol of the chunk][lane]: C | mass << 16
+    uint4 *shapes = reinterpret_cast<uint4 *>(rec + kMixEncRecords * 3u);
+    const uint32_t m_bits = g.prec_bits, scale = mass_scale(m_bits), top = 1u << m_bits;
+
+    // this thread's lane in the chain; the shapes of all lanes for whoever has one of their pixels
+    const uint32_t lane = lane0 + t;
+    const bool mine = t < lanes_here && lane < g.lanes;
+    uint32_t npx = 0u;
+    if (mine) {
+        const LaneShape sh = lane_shape(g, lane);
+        npx = sh.npx;
+        shapes[t] = make_uint4(sh.first, sh.npx, sh.tw, 0u);
+    } else if (t < lanes_here) {
+        shapes[t] = make_uint4(0u, 0u, 1u, 0u);
+    }
+    wave_lds_sync();
+    uint32_t longest = npx;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) longest = max(longest, (uint32_t)__shfl_xor((int)longest, d));
+    const uint32_t turns = 1u << (c.log_lanes + c.log_chunk - 6u);
+
+    uint16_t *wout = scratch + lane_scratch_base(lane, lane_cap);
+    uint32_t nwords = 0, S = 1u << 16;
+    bool ok = true;
+    for (uint32_t q = (longest + chunk - 1u) >> c.log_chunk; q-- > 0u;) {
+        const uint32_t px0 = q << c.log_chunk;
+#pragma unroll 1
+        for (uint32_t turn = 0; turn < turns; ++turn) {
+            const uint32_t task = (turn << 6) + t, l = task >> c.log_chunk, i = task & (chunk - 1u);
+            const uint4 sh = shapes[l];
+            if (px0 + i >= sh.y) continue;
+            uint32_t p = sh.x + px0 + i;
+            if (g.lane_mode != 0u) {
+                const uint32_t row = (px0 + i) / sh.z;
+                p += row * (g.w - sh.z);
+            }
+            constexpr int kHalves = 3 * kK;
+            uint32_t m[(kHalves + 1) / 2] = {}, s[(kHalves + 1) / 2] = {}, wt[(kK + 1) / 2] = {};
+            __builtin_memcpy(m, a.mu + (size_t)p * kHalves, 2 * kHalves);
+            __builtin_memcpy(s, a.ls + (size_t)p * kHalves, 2 * kHalves);
+            __builtin_memcpy(wt, a.weight + (size_t)p * kK, 2 * kK);
+            uint32_t xb = 0;
+            __builtin_memcpy(&xb, img + 3 * (size_t)p, 3);
+            const int16_t *coef = a.coef + 3 * g.by_hw.div(p);
+            const int a_gr = coef[0], a_br = coef[1], a_bg = coef[2];
+            auto half = [](const uint32_t *d, int e) { return (e & 1) != 0 ? d[e >> 1] >> 16 : d[e >> 1] & 0xFFFFu; };
+            uint32_t sum = 0;
+#pragma unroll
+            for (int j = 0; j < kK; ++j) sum += half(wt, j);
+            ok = ok && sum == 1u << 15;
+            const int x[3] = {(int)(xb & 0xFFu), (int)((xb >> 8) & 0xFFu), (int)((xb >> 16) & 0xFFu)};
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const int v = x[ch];
+                unsigned long long acc_lo = 0ull, acc_hi = 0ull;
+#pragma unroll
+                for (int j = 0; j < kK; ++j) {
+                    int me = (int)half(m, ch * kK + j);
+                    if (ch >= 1) {
+                        const int e_r = x[0] * 256 - (int)half(m, j);
+                        if (ch == 1)
+                            me += rsh14_mul(a_gr, e_r);
+                        else
+                            me += rsh14_mul(a_br, e_r) + rsh14_mul(a_bg, x[1] * 256 - (int)half(m, kK + j));
+                    }
+                    const EdgeStep e(256 * v - 128 - me, inv_scale((int)(short)half(s, ch * kK + j), tab));
+                    const uint32_t w = half(wt, j);
+                    acc_lo += (unsigned long long)w * edge_at(e.y, tab);
+                    acc_hi += (unsigned long long)w * edge_at(e.above(), tab);
+                }
+                const uint32_t lo = v == 0 ? 0u : (uint32_t)v + mass_of((uint32_t)(acc_lo >> 15), scale);
+                const uint32_t hi = v == 255 ? top : (uint32_t)v + 1u + mass_of((uint32_t)(acc_hi >> 15), scale);
+                rec[((3u * i + ch) << c.log_lanes) + l] = lo | ((hi - lo) << 16);
+            }
+        }
+        wave_lds_sync();
+        // pixels last-first, and B, G, R inside a pixel (App. A eq. (11) runs against the decoder)
+        for (uint32_t i = npx > px0 ? min(npx - px0, chunk) : 0u; i-- > 0u;) {
+            uint32_t r[3];
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) r[ch] = rec[((3u * i + ch) << c.log_lanes) + t];
+#pragma unroll
+            for (int ch = 2; ch >= 0; --ch) {
+                const uint32_t lo = r[ch] & 0xFFFFu, f = r[ch] >> 16;
+                if (S >= (f << (32u - m_bits))) {
+                    *wout = (uint16_t)(S & 0xFFFFu);
+                    wout += 64;
+                    ++nwords;
+                    S >>= 16;
+                }
+                S = (uint32_t)__umul24(quotient(S, over_reciprocal(f)), top - f) + (S + lo);
+            }
+        }
+        wave_lds_sync();
+    }
+    if (!ok) atomicMax(status_code, 7);
+    if (mine) {
+        lane_words[lane] = nwords;
+        lane_state[lane] = S;
+    }
 }
 
 // Decoded bytes of consecutive addresses, gathered into aligned 8-byte stores; single bytes only

@@ -59,6 +59,29 @@ def test_container_and_image_identical_to_oracle(name, make):
     assert np.array_equal(d.decoded_numpy(), wl.img)
 
 
+# The encoder evaluates chunks of 1, 2, 4, 8 or 16 pixels of a lane at a time, by the lanes' length, and takes 4 to 64 lanes
+# a wavefront, by how many there are: lengths around whole chunks, counts on both sides of the lines, partly
+# filled last wavefronts, tiles clipped to a pixel, register budgets of few and of many components.
+CHUNKS = ([(n, 1, px, 12, 0, px, 0, k) for k, n in ((1, 67), (5, 33), (10, 19), (12, 6), (16, 5))
+           for px in (1, 2, 3, 4, 7, 8, 15, 16, 17, 63, 64, 65, 100)]
+          + [(n, 1, 64, 14, 0, 64, 0, 2) for n in (12287, 12288, 24577)]
+          + [(n, 1, 5, 10, 0, 5, 0, 3) for n in (49151, 49152)]
+          + [(7, 3, 6, 13, 0, 90, 0, 7), (5, 33, 41, 15, 1, 8, 8, 10), (3, 17, 33, 16, 1, 16, 16, 4)])
+
+
+@pytest.mark.parametrize("case", CHUNKS, ids=lambda c: "x".join(map(str, c)))
+def test_chunks_of_every_length(case):
+    print("case", case, flush=True)
+    n, h, w, bits, mode, a, b, k = case
+    wl = synth_mix.from_base(synth.make_random_case(n + w, n, h, w, bits, mode, a, b, wild=n < 100), k, n + w)
+    rc, want = mx.encode(orc.make_geom(*wl.geom), wl.num_comp, wl.img, wl.mu, wl.log_scale, wl.weight, wl.chan_coef)
+    assert rc == mx.OK
+    d = DeviceMix(wl)
+    rc, nbytes = d.encode()
+    got = d.coded_numpy()
+    assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
+
+
 def test_ten_components_in_arrays_off_the_dword_grid_take_the_general_kernels():
     wl = synth_mix.make_mix_workload(2, 4, 10)
     g = orc.make_geom(*wl.geom)
