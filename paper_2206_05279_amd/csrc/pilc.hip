@@ -206,7 +206,7 @@ __global__ void k_scan_spine(HeaderWords head, uint32_t items, uint32_t nblocks,
     spine_scan(head, items, nblocks, block_sums, coded, coded_capacity, status, report);
 }
 
-// For a batch of few tiles the two in one: the workgroup that is done last goes on with the sums of all.  `status->ticket`
+// For a batch of few tiles (but more lanes than kScanAloneLanes) the two in one: the workgroup that is done last goes on with the sums of all.  `status->ticket`
 // is zero before the launch.  The packers of such a batch form the offset table themselves (lane_offsets), so that
 // one launch stands where there were three.  Up to kScanFewTiles: 100,000 lanes of 63 pixels 153 -> 139 us, 8 images of 64 x
 // 64 in 512 lanes 53 -> 42; with 1600 tiles, where every workgroup's fence and every packer's sums of its tile
@@ -235,29 +235,103 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(HeaderWords head, ui
     spine_scan(head, items, nblocks, block_sums, coded, coded_capacity, status, report);
 }
 
+// A batch of few lanes has no scan at all: every workgroup of the packer sums the counts of all lanes, and of those before its own,
+// and the first one writes the header and the outcome.  What that costs is a read of all counts from the L2 by every
+// workgroup; what it saves is a launch.  With the launch and without, whole encode calls, us: 2048 lanes of 32 pixels 35.8 and 31.1,
+// 4000 of 512 69.5 and 67.2, 8000 of 32 38.4 and 37.8, 16,000 of 32 42.0 and 45.6.
+constexpr uint32_t kScanAloneLanes = 8192;
+struct PackAlone {
+    uint32_t alone;  // else the rest is not looked at
+    HeaderWords head;
+    uint8_t *coded;
+    unsigned long long capacity;
+    Report *report;
+};
+
+// The sums of `v` and `w` over the workgroup.
+__device__ __forceinline__ void block_sum_two(unsigned long long &v, unsigned long long &w)
+{
+    __shared__ unsigned long long wave_sum[2][kScanThreads / 64];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        v += __shfl_xor(v, d, 64);
+        w += __shfl_xor(w, d, 64);
+    }
+    if ((threadIdx.x & 63u) == 0u) {
+        wave_sum[0][threadIdx.x >> 6] = v;
+        wave_sum[1][threadIdx.x >> 6] = w;
+    }
+    __syncthreads();
+    v = w = 0ull;
+#pragma unroll
+    for (int i = 0; i < kScanThreads / 64; ++i) {
+        v += wave_sum[0][i];
+        w += wave_sum[1][i];
+    }
+}
+
+// What lies before lane l0 in the payload of a batch without a scan; false if the payload does not fit (then nothing is packed).
+__device__ __forceinline__ bool sum_alone(const PackAlone &pk, uint32_t l0, uint32_t lanes, const ItemBytes &bytes,
+                                          const uint32_t *__restrict__ counts, unsigned long long *before_out)
+{
+    unsigned long long before = 0ull, all = 0ull;
+    for (uint32_t i0 = threadIdx.x; i0 < lanes; i0 += 8u * kScanThreads) {
+        uint32_t c[8];
+#pragma unroll
+        for (uint32_t k = 0; k < 8u; ++k) c[k] = counts[min(i0 + k * kScanThreads, lanes - 1u)];
+#pragma unroll
+        for (uint32_t k = 0; k < 8u; ++k) {
+            const uint32_t i = i0 + k * kScanThreads;
+            const unsigned long long b = i < lanes ? bytes(c[k]) : 0ull;
+            all += b;
+            before += i < l0 ? b : 0ull;
+        }
+    }
+    block_sum_two(before, all);
+    *before_out = before;
+    const int code = all >= (1ull << 32) ? ST_TOO_LARGE
+                     : kHeaderBytes + 4ull * ((unsigned long long)lanes + 1ull) + all > pk.capacity ? ST_CAPACITY : ST_OK;
+    if (blockIdx.x == 0u && threadIdx.x < 16u) {
+        uint32_t *h = reinterpret_cast<uint32_t *>(pk.coded);
+        const uint32_t w = threadIdx.x;
+        h[w] = w < 12u ? pk.head.w[w] : w == 12u ? (uint32_t)all : w == 13u ? (uint32_t)(all >> 32) : 0u;
+        if (w == 0u) {
+            if (code != ST_OK) raise_code(pk.report, code);
+            __hip_atomic_store(&pk.report->payload_bytes, all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+    return code == ST_OK;
+}
+
 // Where the bytes of lanes l0 .. l0 + n - 1 (n <= kScanThreads) begin in the payload, thread i that of lane l0 + i, from
 // the sums before the tiles and the counts of l0's tile; the same into the offset table.
-// `formed`: the table is there already.
-__device__ __forceinline__ unsigned long long lane_offsets(bool formed, uint32_t l0, uint32_t n, uint32_t lanes, const ItemBytes &bytes,
-                                                           const uint32_t *__restrict__ counts,
+// `formed`: the table is there already.  `fits`: false if the batch turns out here not to fit (PackAlone).
+__device__ __forceinline__ unsigned long long lane_offsets(const PackAlone &pk, bool formed, uint32_t l0, uint32_t n, uint32_t lanes,
+                                                           const ItemBytes &bytes, const uint32_t *__restrict__ counts,
                                                            const unsigned long long *__restrict__ block_sums,
-                                                           uint32_t *__restrict__ offsets, unsigned long long *end)
+                                                           uint32_t *__restrict__ offsets, unsigned long long *end, bool *fits)
 {
+    *fits = true;
     if (formed) {  // (the same for every thread)
         __syncthreads();
         *end = threadIdx.x < n ? offsets[l0 + threadIdx.x + 1u] : 0u;
         return threadIdx.x < n ? offsets[l0 + threadIdx.x] : 0u;
     }
-    const uint32_t tile = l0 / kScanTile;
     unsigned long long before = 0, total;
-#pragma unroll
-    for (uint32_t k = 0; k < (uint32_t)kScanItems; ++k) {
-        const uint32_t i = tile * kScanTile + k * kScanThreads + threadIdx.x;
-        if (i < l0) before += bytes(counts[i]);
-    }
     const unsigned long long mine = threadIdx.x < n ? bytes(counts[l0 + threadIdx.x]) : 0ull;
-    (void)block_exclusive_scan(before, &total);
-    before = total + block_sums[tile];
+    if (pk.alone != 0u) {
+        *fits = sum_alone(pk, l0, lanes, bytes, counts, &before);
+        if (!*fits) return 0ull;
+    } else {
+        const uint32_t tile = l0 / kScanTile;
+#pragma unroll
+        for (uint32_t k = 0; k < (uint32_t)kScanItems; ++k) {
+            const uint32_t i = tile * kScanTile + k * kScanThreads + threadIdx.x;
+            if (i < l0) before += bytes(counts[i]);
+        }
+        (void)block_exclusive_scan(before, &total);
+        before = total + block_sums[tile];
+    }
     const unsigned long long at = block_exclusive_scan(mine, &total) + before;
     if (threadIdx.x < n) {
         offsets[l0 + threadIdx.x] = (uint32_t)at;
@@ -309,7 +383,7 @@ __global__ __launch_bounds__(kScanThreads) void k_pack(Geo g, uint32_t lanes_per
                                                        const unsigned long long *__restrict__ block_sums,
                                                        bool formed, uint32_t *__restrict__ offsets,
                                                        uint16_t *__restrict__ payload,
-                                                       const Status *__restrict__ status)
+                                                       const Status *__restrict__ status, PackAlone pk)
 {
     if (status->code != ST_OK) return;
     __shared__ uint32_t s_off[kPackMaxLanes + 1];
@@ -319,7 +393,9 @@ __global__ __launch_bounds__(kScanThreads) void k_pack(Geo g, uint32_t lanes_per
     const uint32_t n = min(lanes_per_block, g.lanes - l0);
     static_assert(kPackMaxLanes <= kScanThreads, "a thread per lane");
     unsigned long long lane_end;
-    const uint32_t begin = (uint32_t)lane_offsets(formed, l0, n, g.lanes, kLaneBytes, lane_words, block_sums, offsets, &lane_end);
+    bool fits;
+    const uint32_t begin = (uint32_t)lane_offsets(pk, formed, l0, n, g.lanes, kLaneBytes, lane_words, block_sums, offsets, &lane_end, &fits);
+    if (!fits) return;  // (the same for every thread)
     const uint32_t i = threadIdx.x;
     if (i < n) {
         const LaneShape sh = lane_shape(g, l0 + i);
@@ -400,7 +476,7 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_by_thread(uint32_t lanes,
                                                                  const unsigned long long *__restrict__ block_sums,
                                                                  bool formed, uint32_t *__restrict__ offsets,
                                                                  uint16_t *__restrict__ payload,
-                                                                 const Status *__restrict__ status)
+                                                                 const Status *__restrict__ status, PackAlone pk)
 {
     if (status->code != ST_OK) return;
     __shared__ uint32_t s_first[64];  // payload word index of the lane's state
@@ -411,7 +487,10 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_by_thread(uint32_t lanes,
     const uint32_t l0 = blockIdx.x * 64u;
     if (t == 0) s_max = 0u;
     unsigned long long lane_end;  // (ends with a barrier)
-    const uint32_t begin = (uint32_t)lane_offsets(formed, l0, min(64u, lanes - l0), lanes, kLaneBytes, lane_words, block_sums, offsets, &lane_end);
+    bool fits;
+    const uint32_t begin = (uint32_t)lane_offsets(pk, formed, l0, min(64u, lanes - l0), lanes, kLaneBytes, lane_words, block_sums,
+                                                  offsets, &lane_end, &fits);
+    if (!fits) return;  // (the same for every thread)
     if (t < 64u) {
         uint32_t nw = 0u, first = 0u;
         if (l0 + t < lanes) {
@@ -484,6 +563,9 @@ __device__ __forceinline__ int check_header(const Geo &g, uint32_t magic, uint32
     const uint32_t *h = reinterpret_cast<const uint32_t *>(coded);
     int st = ST_OK;
     const unsigned long long payload = (unsigned long long)h[12] | ((unsigned long long)h[13] << 32);
+    // (the callers have seen that a header and the offsets fit in coded_bytes: asked for beside the header)
+    const uint32_t *offsets = h + kHeaderBytes / 4;
+    const uint32_t first = offsets[0], last = offsets[g.lanes];
     if (h[0] != magic || h[1] != PILC_VERSION) st = ST_FORMAT;
     if (word11 != 0u && h[11] != word11) st = ST_FORMAT;
     if (h[2] != g.n || h[3] != g.h || h[4] != g.w || h[5] != 3u || h[6] != g.prec_bits ||
@@ -491,11 +573,7 @@ __device__ __forceinline__ int check_header(const Geo &g, uint32_t magic, uint32
         st = ST_FORMAT;
     if (coded_bytes != kHeaderBytes + 4ull * ((unsigned long long)g.lanes + 1ull) + payload)
         st = ST_FORMAT;
-    if (st == ST_OK) {
-        const uint32_t *offsets = h + kHeaderBytes / 4;
-        if (payload >= (1ull << 32) || offsets[0] != 0u || offsets[g.lanes] != (uint32_t)payload)
-            st = ST_CORRUPT;
-    }
+    if (st == ST_OK && (payload >= (1ull << 32) || first != 0u || last != (uint32_t)payload)) st = ST_CORRUPT;
     *payload_bytes = payload;
     return st;
 }
@@ -1162,9 +1240,10 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
     }
     timer.mark(few_lanes ? "k_encode_block" : "k_encode_lanes");
     if (!one_pass) {
-        const bool formed = launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev, coded_capacity,
-                                        status, report->dev(), offsets, false, stream);
-        timer.mark("scan");
+        const PackAlone pk = {g.lanes <= kScanAloneLanes ? 1u : 0u, head, coded_dev, coded_capacity, report->dev()};
+        const bool formed = pk.alone == 0u && launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev,
+                                                          coded_capacity, status, report->dev(), offsets, false, stream);
+        if (pk.alone == 0u) timer.mark("scan");
         // a run of lanes per workgroup: about 16K symbols' worth, at most 256 lanes; of a small batch less, so that
         // there are kPackBlocks workgroups, but not less than kPackLeast symbols (64 images of 32 x 32 in
         // 2048 lanes 28.5 -> 8.0 us, 400 of 64 x 64 in 25,600 lanes 28.7 -> 13.4; with 512 workgroups of
@@ -1175,10 +1254,10 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
         pack_lanes = std::min(std::max(pack_lanes, 1u), (uint32_t)kPackMaxLanes);
         if (lane_cap != 0u)
             (lane_cap <= 256u ? k_pack_by_thread<128> : k_pack_by_thread<256>)<<<(uint32_t)ceil_div64(g.lanes, 64), kScanThreads, 0, stream>>>(
-                g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status);
+                g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, pk);
         else
             k_pack<<<(uint32_t)ceil_div64(g.lanes, pack_lanes), kScanThreads, 0, stream>>>(
-                g, pack_lanes, scratch, lane_words, lane_state, sums, formed, offsets, payload, status);
+                g, pack_lanes, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, pk);
         timer.mark(lane_cap != 0u ? "k_pack_by_thread" : "k_pack");
     }
     HIP_TRY(hipGetLastError());
@@ -1432,7 +1511,7 @@ int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mi
                                     status, nullptr, offsets, false, stream);
     timer.mark("scan");
     (lane_cap <= 256u ? k_pack_by_thread<128> : k_pack_by_thread<256>)<<<(uint32_t)ceil_div64(g.lanes, 64), kScanThreads, 0, stream>>>(
-        g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status);
+        g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, PackAlone{});
     timer.mark("k_pack_by_thread");
     HIP_TRY(hipGetLastError());
     Status host_status;

@@ -183,12 +183,6 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         s_abort = 0u;
         s_state = check_header(g, kMagicPilc, 0u, coded, coded_bytes, &s_payload);
     }
-    load_tables(sm.tab);  // ends with a barrier
-    if (s_state != ST_OK) {
-        if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, s_state);
-        return;
-    }
-
     const bool stager = kStaged && threadIdx.x >= 64u * kRowWaves;
     const uint32_t tix = threadIdx.x - (stager ? 64u * kRowWaves : 0u);  // index among the threads of its kind
     const uint32_t tid = tix & 63u, wv = tix >> 6;
@@ -202,26 +196,30 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
     const uint32_t m_bits = g.prec_bits;
     const uint32_t mask = (1u << m_bits) - 1u, top = 1u << m_bits;
     const uint32_t scale = mass_scale(m_bits);
-    const uint32_t payload_bytes = (uint32_t)s_payload;
+    // (The offsets are asked for before the header and the tables are waited for: the host has seen that they fit in coded_bytes.)
     const uint32_t *offsets = reinterpret_cast<const uint32_t *>(coded + 64);
+    const uint32_t begin = offsets[lane], end = offsets[lane + 1];
     const uint16_t *payload =
         reinterpret_cast<const uint16_t *>(coded + 64 + 4ull * ((size_t)g.lanes + 1));
     const uint2 *sig = tab.sig;
+    load_tables(sm.tab);  // ends with a barrier
+    if (s_state != ST_OK) {
+        if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, s_state);
+        return;
+    }
+    const uint32_t payload_bytes = (uint32_t)s_payload;
 
     // row-uniform state: S, the stream position `pos` (word index into the payload) and the end
     // of the lane's words `stop`
     uint32_t npx = 0, stop = 0, S = 1u << 16, pos = 0;
-    {
-        const uint32_t begin = offsets[lane], end = offsets[lane + 1];
-        if (end < begin || end > payload_bytes || end - begin < 4u || ((begin | end) & 1u)) {
-            if (j == 0 && has_lane) raise_code(report, ST_CORRUPT);
-        } else {
-            npx = sh.npx;
-            stop = end >> 1;
-            pos = begin >> 1;
-            S = (uint32_t)payload[pos] | ((uint32_t)payload[pos + 1] << 16);
-            pos += 2;
-        }
+    if (end < begin || end > payload_bytes || end - begin < 4u || ((begin | end) & 1u)) {
+        if (j == 0 && has_lane) raise_code(report, ST_CORRUPT);
+    } else {
+        npx = sh.npx;
+        stop = end >> 1;
+        pos = begin >> 1;
+        S = (uint32_t)payload[pos] | ((uint32_t)payload[pos + 1] << 16);
+        pos += 2;
     }
     // The stream words from `from` on, thread j those at j, j + 16, ...: words past `stop` read
     // as 0, and an overrun shows at the end of the lane as pos != stop.
@@ -497,10 +495,11 @@ __global__ __launch_bounds__((kStaged ? 2 : 1) * 64 * kRowWaves) void k_decode_r
         // a batch ago) and its stream words: the 112 words from where the stream stood when batch b
         // began, of which batch b takes at most 48 and batch b + 1 at most 48 more; and the pixels of
         // batch b - 1 go to the image.
+        const Ahead first_words = fetch_words(pos);
         put_stage(fetch_raw(0), 0);
         Raw raw_next = fetch_raw(kRowBatch);
         put_first_cand(0u, 0u);
-        put_words(fetch_words(pos), 0u, pos);
+        put_words(first_words, 0u, pos);
         if (!withhold) raise(&s_staged[wv], 1u);
         uint32_t from = pos, t0 = 0, b = 0;
         for (; __any(t0 < npx); t0 += kRowBatch, ++b) {

@@ -192,3 +192,28 @@ def test_static_encode_says_what_does_not_fit(policy):
                 assert nbytes == c.want.size and np.array_equal(d.coded[:nbytes].cpu().numpy(), c.want)
     finally:
         pb.pilc_set_kernel_policy(0)
+
+
+@pytest.mark.parametrize("policy", [1, 2])
+@pytest.mark.parametrize("lanes", [1, 2, 255, 257, 2047, 2049, 8191, 8192, 8193])
+def test_packers_without_a_scan(lanes, policy):
+    """Up to 8192 lanes the packers sum the lanes' bytes themselves, write the header and say what does not fit."""
+    wl = synth.make_random_case(lanes, lanes, 1, 9, 12, 0, 9)
+    rc, want = orc.encode(orc.make_geom(*wl.geom), wl.img, wl.mu, wl.log_scale, wl.chan_coef)
+    assert rc == orc.OK
+    d = DeviceWorkload(wl)
+
+    def encode(capacity):
+        return pb.pilc_encode(d.geom, d.img, d.mu, d.log_scale, d.chan_coef, d.workspace, d.coded[:capacity], check=False)
+    pb.pilc_set_kernel_policy(policy)
+    try:
+        for capacity in (d.coded.numel(), want.size):
+            d.coded.fill_(0x5A)
+            rc, nbytes = encode(capacity)
+            assert rc == pb.PILC_OK and nbytes == want.size
+            assert np.array_equal(d.coded[:nbytes].cpu().numpy(), want) and bool((d.coded[nbytes:] == 0x5A).all())
+        d.coded.fill_(0x5A)
+        assert encode(want.size - 1)[0] == pb.PILC_E_CAPACITY
+        assert bool((d.coded[64 + 4 * (lanes + 1):] == 0x5A).all())
+    finally:
+        pb.pilc_set_kernel_policy(0)
