@@ -248,6 +248,14 @@ struct PackAlone {
     Report *report;
 };
 
+// Whether the kernels before have raised an error, which without a scan nobody else reports.
+__device__ __forceinline__ bool nothing_to_pack(const Status *status, const PackAlone &pk)
+{
+    if (status->code == ST_OK) return false;
+    if (pk.alone != 0u && blockIdx.x == 0u && threadIdx.x == 0u) raise_code(pk.report, status->code);
+    return true;
+}
+
 // The sums of `v` and `w` over the workgroup.
 __device__ __forceinline__ void block_sum_two(unsigned long long &v, unsigned long long &w)
 {
@@ -385,7 +393,7 @@ __global__ __launch_bounds__(kScanThreads) void k_pack(Geo g, uint32_t lanes_per
                                                        uint16_t *__restrict__ payload,
                                                        const Status *__restrict__ status, PackAlone pk)
 {
-    if (status->code != ST_OK) return;
+    if (nothing_to_pack(status, pk)) return;
     __shared__ uint32_t s_off[kPackMaxLanes + 1];
     __shared__ uint32_t s_src[kPackMaxLanes];    // scratch index of the lane's first word
     __shared__ uint32_t s_state[kPackMaxLanes];
@@ -478,7 +486,7 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_by_thread(uint32_t lanes,
                                                                  uint16_t *__restrict__ payload,
                                                                  const Status *__restrict__ status, PackAlone pk)
 {
-    if (status->code != ST_OK) return;
+    if (nothing_to_pack(status, pk)) return;
     __shared__ uint32_t s_first[64];  // payload word index of the lane's state
     __shared__ uint32_t s_nw[64];     // words after the state
     __shared__ uint32_t s_max;
@@ -576,15 +584,6 @@ __device__ __forceinline__ int check_header(const Geo &g, uint32_t magic, uint32
     if (st == ST_OK && (payload >= (1ull << 32) || first != 0u || last != (uint32_t)payload)) st = ST_CORRUPT;
     *payload_bytes = payload;
     return st;
-}
-
-__global__ void k_check_header(Geo g, uint32_t magic, uint32_t word11,
-                               const uint8_t *__restrict__ coded, unsigned long long coded_bytes,
-                               Status *__restrict__ status)
-{
-    unsigned long long payload;
-    status->code = check_header(g, magic, word11, coded, coded_bytes, &payload);
-    status->payload_bytes = payload;
 }
 
 }  // namespace pilc
@@ -1492,6 +1491,7 @@ int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mi
     if ((rc = allow_large_lds(chunks ? reinterpret_cast<const void *>(chunks) : reinterpret_cast<const void *>(&k_mix_encode))) != PILC_OK)
         return rc;
 
+    CallReport report(reinterpret_cast<Report *>(base + ws.report_off), stream, true);
     Timer timer(stream);
     k_init_status<<<1, 1, 0, stream>>>(status);
     if (chunks) {
@@ -1507,19 +1507,19 @@ int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mi
     timer.mark("k_mix_encode");
     const HeaderWords head = {{kMagicMix, PILC_VERSION, g.n, g.h, g.w, 3u, g.prec_bits, g.lane_mode,
                                g.lane_a, g.lane_b, g.lanes, params->num_comp}};
-    const bool formed = launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev, coded_capacity,
-                                    status, nullptr, offsets, false, stream);
-    timer.mark("scan");
+    const PackAlone pk = {g.lanes <= kScanAloneLanes ? 1u : 0u, head, coded_dev, coded_capacity, report.dev()};
+    const bool formed = pk.alone == 0u && launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev,
+                                                      coded_capacity, status, report.dev(), offsets, false, stream);
+    if (pk.alone == 0u) timer.mark("scan");
     (lane_cap <= 256u ? k_pack_by_thread<128> : k_pack_by_thread<256>)<<<(uint32_t)ceil_div64(g.lanes, 64), kScanThreads, 0, stream>>>(
-        g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, PackAlone{});
+        g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, pk);
     timer.mark("k_pack_by_thread");
     HIP_TRY(hipGetLastError());
-    Status host_status;
-    HIP_TRY(hipMemcpyAsync(&host_status, status, sizeof(Status), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
+    Report seen;
+    HIP_TRY(report.wait(&seen));
     timer.finish();
-    if (host_status.code != ST_OK) return status_to_error(host_status.code);
-    *coded_bytes_host = table_end + host_status.payload_bytes;
+    if (raised_code(seen) != ST_OK) return status_to_error(raised_code(seen));
+    *coded_bytes_host = table_end + seen.payload_bytes;
     return PILC_OK;
 }
 
@@ -1539,7 +1539,6 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
     if ((rc = ensure_tables()) != PILC_OK) return rc;
 
     hipStream_t stream = (hipStream_t)hip_stream;
-    Status *status = reinterpret_cast<Status *>(static_cast<uint8_t *>(workspace_dev) + ws.status_off);
     const MixArgs args = {params->mu, params->log_scale, params->weight, params->chan_coef,
                           params->num_comp};
     const int built = mix_built_for(params);
@@ -1547,19 +1546,16 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
     auto kern = k_mix_decode_for(built);
     if ((rc = allow_large_lds(reinterpret_cast<const void *>(kern))) != PILC_OK) return rc;
 
+    CallReport report(reinterpret_cast<Report *>(static_cast<uint8_t *>(workspace_dev) + ws.report_off), stream, true);
     Timer timer(stream);
-    k_check_header<<<1, 1, 0, stream>>>(g, kMagicMix, params->num_comp, coded_dev,
-                                        (unsigned long long)coded_bytes, status);
-    timer.mark("k_check_header");
     kern<<<(uint32_t)ceil_div64(g.lanes, kMixThreads), kMixThreads, lds, stream>>>(
-        g, coded_dev, args, img_out_dev, &status->code, &status->payload_bytes);
+        g, coded_dev, (unsigned long long)coded_bytes, args, img_out_dev, report.dev());
     timer.mark("k_mix_decode");
     HIP_TRY(hipGetLastError());
-    Status host_status;
-    HIP_TRY(hipMemcpyAsync(&host_status, status, sizeof(Status), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
+    Report seen;
+    HIP_TRY(report.wait(&seen));
     timer.finish();
-    return status_to_error(host_status.code);
+    return status_to_error(raised_code(seen));
 }
 
 }  // extern "C"

@@ -609,27 +609,28 @@ __global__ __launch_bounds__(64 * kAnsaiPackWaves) void k_ansai_pack(
 // ---------------------------------------------------------------------------------------------
 // Decode (Alg. 4)
 // ---------------------------------------------------------------------------------------------
+// Whether the tables are those of this shape; the status block for the kernels that follow.
+__device__ __forceinline__ int ansai_tables_state(const AShape &sh, const ATabHeader *__restrict__ tab)
+{
+    return tab->magic == kAnsaiTabMagic && tab->ok == 1u && tab->M == sh.M && tab->D == sh.D && tab->X == sh.X ? ST_OK : ST_ARG;
+}
 __global__ void k_ansai_begin(AShape sh, const ATabHeader *__restrict__ tab, Status *status)
 {
-    status->code = (tab->magic == kAnsaiTabMagic && tab->ok == 1u && tab->M == sh.M && tab->D == sh.D &&
-                    tab->X == sh.X)
-                       ? ST_OK
-                       : ST_ARG;
-    status->ticket = 0;
-    status->payload_bytes = 0;
+    init_status(status);
+    status->code = ansai_tables_state(sh, tab);
 }
 
-__global__ void k_ansai_check_header(AShape sh, const uint8_t *__restrict__ coded,
+// The same for a decoder, and whether the container's header is that of this shape.
+__global__ void k_ansai_check_header(AShape sh, const ATabHeader *__restrict__ tab, const uint8_t *__restrict__ coded,
                                      unsigned long long coded_bytes, Status *__restrict__ status)
 {
-    if (status->code != ST_OK) return;
+    init_status(status);
     const uint32_t *h = reinterpret_cast<const uint32_t *>(coded);
-    int st = ST_OK;
     const unsigned long long payload = (unsigned long long)h[12] | ((unsigned long long)h[13] << 32);
-    if (h[0] != kAnsaiMagic || h[1] != 1u || h[2] != sh.pieces || h[3] != sh.count || h[4] != sh.M ||
-        h[5] != sh.D || h[6] != sh.X)
-        st = ST_FORMAT;
-    if (coded_bytes != kHeaderBytes + 4ull * ((unsigned long long)sh.pieces + 1ull) + payload)
+    int st = ansai_tables_state(sh, tab);
+    if (st == ST_OK && (h[0] != kAnsaiMagic || h[1] != 1u || h[2] != sh.pieces || h[3] != sh.count || h[4] != sh.M ||
+                        h[5] != sh.D || h[6] != sh.X ||
+                        coded_bytes != kHeaderBytes + 4ull * ((unsigned long long)sh.pieces + 1ull) + payload))
         st = ST_FORMAT;
     if (st == ST_OK && payload >= (1ull << 32)) st = ST_CORRUPT;
     status->code = st;
@@ -931,10 +932,14 @@ constexpr int kAnsaiDecLeastWaves = 3;
 template <bool kWide, bool kTabLds, bool kLines>
 __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
     AShape sh, const uint8_t *__restrict__ coded, const uint8_t *__restrict__ dist, const uint8_t *__restrict__ theta_g,
-    const void *__restrict__ nb_g, uint8_t *__restrict__ out, uint32_t maxw, Status *status)
+    const void *__restrict__ nb_g, uint8_t *__restrict__ out, uint32_t maxw, const Status *__restrict__ status,
+    Report *__restrict__ report)
 {
     extern __shared__ uint32_t lds[];
-    if (status->code != ST_OK) return;
+    if (status->code != ST_OK) {
+        if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, status->code);
+        return;
+    }
     const uint8_t *theta = theta_g;
     const void *nb = nb_g;
     uint32_t *stage_base = lds;
@@ -1043,11 +1048,11 @@ __global__ __launch_bounds__(64 * kAnsaiDecMaxWaves) void k_ansai_decode(
         }
     }
     if (mine && (L.s != 0u || L.pos != 32u * L.first)) corrupt = 1u;
-    // many threads may report: the larger code (a damaged container) wins, whatever the order
+    // many threads may report: the highest code (a damaged container) is the call's
     if (corrupt)
-        atomicMax(&status->code, ST_CORRUPT);
+        raise_code(report, ST_CORRUPT);
     else if (bad)
-        atomicMax(&status->code, ST_ARG);
+        raise_code(report, ST_ARG);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1111,7 +1116,7 @@ static int make_ashape(const pilc_ansai_shape *in, AShape *sh)
 }
 
 struct AWorkspace {
-    size_t status_off, bits_off, state_off, sums_off, scratch_off, total;
+    size_t status_off, report_off, bits_off, state_off, sums_off, scratch_off, total;
     uint32_t scan_blocks, maxw, waves;
 };
 
@@ -1122,8 +1127,10 @@ static AWorkspace ansai_layout(const AShape &sh)
     w.maxw = (uint32_t)(((uint64_t)sh.count * sh.M + 31) / 32);
     w.waves = (uint32_t)ceil_div64(sh.pieces, 64);
     size_t off = 0;
+    static_assert(sizeof(Status) <= 64 && sizeof(Report) <= 128, "both in the first 256 bytes");
     w.status_off = off;
-    off = align256(off + sizeof(Status));
+    w.report_off = off + 128;
+    off = align256(off + 256);
     w.bits_off = off;
     off = align256(off + 4 * (size_t)sh.pieces);
     w.state_off = off;
@@ -1250,6 +1257,7 @@ int pilc_ansai_encode(const pilc_ansai_shape *shape, const uint8_t *sym_dev, con
     const uint8_t *tb = static_cast<const uint8_t *>(tables_dev);
     const uint2 *enc_tab = reinterpret_cast<const uint2 *>(tb + t.enc_off);
 
+    CallReport report(reinterpret_cast<Report *>(base + ws.report_off), stream, true);
     Timer timer(stream);
     k_ansai_begin<<<1, 1, 0, stream>>>(sh, reinterpret_cast<const ATabHeader *>(tb), status);
     const size_t tab_lds = 8 * ((size_t)sh.D * 256 + 2);
@@ -1267,19 +1275,18 @@ int pilc_ansai_encode(const pilc_ansai_shape *shape, const uint8_t *sym_dev, con
     timer.mark("k_ansai_encode");
     const ItemBytes piece_bytes = {8u, 4u, 31u, 5u};  // state, bit count, 32-bit words
     const HeaderWords head = {{kAnsaiMagic, 1u, sh.pieces, sh.count, sh.M, sh.D, sh.X, 0u, 0u, 0u, 0u, 0u}};
-    (void)launch_scan(head, sh.pieces, ws.scan_blocks, piece_bytes, piece_bits, sums, coded_dev, coded_capacity, status, nullptr,
+    (void)launch_scan(head, sh.pieces, ws.scan_blocks, piece_bytes, piece_bits, sums, coded_dev, coded_capacity, status, report.dev(),
                       offsets, true, stream);
     timer.mark("scan");
     k_ansai_pack<<<(uint32_t)ceil_div64(ws.waves, kAnsaiPackWaves), 64 * kAnsaiPackWaves, 0, stream>>>(
         sh, scratch, ws.maxw, piece_bits, piece_state, offsets, payload, status);
     timer.mark("k_ansai_pack");
     HIP_TRY(hipGetLastError());
-    Status host_status;
-    HIP_TRY(hipMemcpyAsync(&host_status, status, sizeof(Status), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
+    Report seen;
+    HIP_TRY(report.wait(&seen));
     timer.finish();
-    if (host_status.code != ST_OK) return ansai_status_to_error(host_status.code);
-    *coded_bytes_host = table_end + host_status.payload_bytes;
+    if (raised_code(seen) != ST_OK) return ansai_status_to_error(raised_code(seen));
+    *coded_bytes_host = table_end + seen.payload_bytes;
     return PILC_OK;
 }
 
@@ -1350,8 +1357,9 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
         waves = asked < fit ? asked : (uint32_t)fit;
     }
     Timer timer(stream);
-    k_ansai_begin<<<1, 1, 0, stream>>>(sh, reinterpret_cast<const ATabHeader *>(tb), status);
-    k_ansai_check_header<<<1, 1, 0, stream>>>(sh, coded_dev, (unsigned long long)coded_bytes, status);
+    CallReport report(reinterpret_cast<Report *>(static_cast<uint8_t *>(workspace_dev) + ws.report_off), stream, true);
+    k_ansai_check_header<<<1, 1, 0, stream>>>(sh, reinterpret_cast<const ATabHeader *>(tb), coded_dev,
+                                              (unsigned long long)coded_bytes, status);
     timer.mark("k_ansai_check_header");
     // A build of this kernel that needed private memory (register spills) once decoded wrongly in
     // the wavefronts beyond the fourth of a workgroup, and the cause was never found.  The kernel as
@@ -1371,7 +1379,8 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
         const uint32_t blocks = (uint32_t)ceil_div64(ws.waves, waves);                                \
         if ((rc = allow_large_lds(reinterpret_cast<const void *>(kern))) != PILC_OK) return rc;       \
         kern<<<blocks, 64 * waves, lds_bytes, stream>>>(sh, coded_dev, dist_dev, tb + t.theta_off,    \
-                                                        tb + t.nb_off, sym_out_dev, ws.maxw, status); \
+                                                        tb + t.nb_off, sym_out_dev, ws.maxw, status,  \
+                                                        report.dev());                                \
     } while (0)
     // Rows cut at the array's lines or at their own start.  A row cut at its own start has no step without a symbol, but
     // its lines are asked for twice, 128 symbols apart, and written in pieces; that costs nothing while the
@@ -1402,11 +1411,10 @@ int pilc_ansai_decode(const pilc_ansai_shape *shape, const uint8_t *coded_dev, s
 #undef PILC_ANSAI_DECODE
     timer.mark("k_ansai_decode");
     HIP_TRY(hipGetLastError());
-    Status host_status;
-    HIP_TRY(hipMemcpyAsync(&host_status, status, sizeof(Status), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
+    Report seen;
+    HIP_TRY(report.wait(&seen));
     timer.finish();
-    return ansai_status_to_error(host_status.code);
+    return ansai_status_to_error(raised_code(seen));
 }
 
 }  // extern "C"

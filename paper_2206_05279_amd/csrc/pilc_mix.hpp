@@ -593,27 +593,33 @@ struct ByteRun {
 
 template <int kK>  // as k_mix_encode
 __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, mix_waves(kK)))) void k_mix_decode(
-    Geo g, const uint8_t *__restrict__ coded, MixArgs a, uint8_t *__restrict__ out,
-    int *__restrict__ status_code, const unsigned long long *__restrict__ status_payload)
+    Geo g, const uint8_t *__restrict__ coded, unsigned long long coded_bytes, MixArgs a, uint8_t *__restrict__ out,
+    Report *__restrict__ report)
 {
     __shared__ LdsTables tab;
+    __shared__ int s_state;
+    __shared__ unsigned long long s_payload;
     extern __shared__ uint32_t mix_lds[];
-    load_tables(tab);
-    if (*status_code != 0) return;  // uniform: written by an earlier kernel
+    if (threadIdx.x == 0u) s_state = check_header(g, kMagicMix, a.k, coded, coded_bytes, &s_payload);
+    load_tables(tab);  // ends with a barrier
+    if (s_state != ST_OK) {
+        if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, s_state);
+        return;
+    }
     const uint32_t lane = blockIdx.x * blockDim.x + threadIdx.x;
     if (lane >= g.lanes) return;
     const MixSlots slots(mix_lds, kK > 0 ? (uint32_t)kK : a.k, kK == 0);
     const LaneShape sh = lane_shape(g, lane);
     const uint32_t m_bits = g.prec_bits;
     const uint32_t scale = mass_scale(m_bits), mask = (1u << m_bits) - 1u;
-    const uint32_t payload_bytes = (uint32_t)*status_payload;
+    const uint32_t payload_bytes = (uint32_t)s_payload;
 
     const uint32_t *offsets = reinterpret_cast<const uint32_t *>(coded + 64);
     const uint16_t *payload =
         reinterpret_cast<const uint16_t *>(coded + 64 + 4ull * ((size_t)g.lanes + 1));
     const uint32_t begin = offsets[lane], end = offsets[lane + 1];
     if (end < begin || end > payload_bytes || end - begin < 4u || ((begin | end) & 1u)) {
-        atomicMax(status_code, 6);
+        raise_code(report, ST_CORRUPT);
         return;
     }
     const uint32_t adj = (uint32_t)(reinterpret_cast<uintptr_t>(payload) & 31u);
@@ -687,8 +693,8 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
         run.put3(out, (uint32_t)x_r | ((uint32_t)x_g << 8) | ((uint32_t)x_b << 16));
     }
     run.end(out);
-    if (!ok) atomicMax(status_code, 7);
-    if (S != (1u << 16) || words.taken(first) != (end - begin) >> 1) atomicMax(status_code, 6);
+    if (!ok) raise_code(report, ST_PARAMS);
+    if (S != (1u << 16) || words.taken(first) != (end - begin) >> 1) raise_code(report, ST_CORRUPT);
 }
 
 }  // namespace pilc
