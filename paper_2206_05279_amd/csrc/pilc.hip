@@ -1455,6 +1455,7 @@ static int mix_built_for(const pilc_mix_params *p)
     }
 PILC_MIX_KERNEL_FOR(k_mix_encode_chunks, nullptr)
 PILC_MIX_KERNEL_FOR(k_mix_decode, k_mix_decode<0>)
+PILC_MIX_KERNEL_FOR(k_mix_decode_rows, nullptr)
 #undef PILC_MIX_KERNEL_FOR
 
 int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mix_params *params,
@@ -1541,14 +1542,17 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
     hipStream_t stream = (hipStream_t)hip_stream;
     const MixArgs args = {params->mu, params->log_scale, params->weight, params->chan_coef,
                           params->num_comp};
+    const bool rows = g.lanes <= kMixRowLanes;
     const int built = mix_built_for(params);
-    const size_t lds = mix_lds_bytes(params->num_comp, built == 0);
-    auto kern = k_mix_decode_for(built);
+    const size_t lds = rows ? 0 : mix_lds_bytes(params->num_comp, built == 0);
+    auto kern = rows ? k_mix_decode_rows_for((int)params->num_comp) : k_mix_decode_for(built);
+    const uint32_t group = rows ? kMixRowThreads / 16u : (uint32_t)kMixThreads;  // lanes of a workgroup
+    static_assert(kMixRowThreads == kMixThreads, "one launch for both");
     if ((rc = allow_large_lds(reinterpret_cast<const void *>(kern))) != PILC_OK) return rc;
 
     CallReport report(reinterpret_cast<Report *>(static_cast<uint8_t *>(workspace_dev) + ws.report_off), stream, true);
     Timer timer(stream);
-    kern<<<(uint32_t)ceil_div64(g.lanes, kMixThreads), kMixThreads, lds, stream>>>(
+    kern<<<(uint32_t)ceil_div64(g.lanes, group), kMixThreads, lds, stream>>>(
         g, coded_dev, (unsigned long long)coded_bytes, args, img_out_dev, report.dev());
     timer.mark("k_mix_decode");
     HIP_TRY(hipGetLastError());

@@ -697,4 +697,144 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
     if (S != (1u << 16) || words.taken(first) != (end - begin) >> 1) raise_code(report, ST_CORRUPT);
 }
 
+// --------------------------------------------------------------------------------------------
+// The decoder for few lanes: a row of 16 threads a lane, four lanes a wavefront, for arrays at any address.
+//
+// A lane is a serial chain, and a thread by itself evaluates C(k) eight times a symbol, ten laws each.  Here the row evaluates it
+// at sixteen places at once, so twice a symbol: every sixteenth value, then the sixteen between two of them.  Thread j has the
+// parameters of component j, asked for a pixel ahead, forms its law (the scales, which need no decoded value, a
+// pixel ahead as well) and leaves it in LDS for the row.
+// Bound by the length of that chain while a SIMD has one wavefront, then by the instructions of the sixteen evaluations.
+// --------------------------------------------------------------------------------------------
+constexpr int kMixRowThreads = 256;
+// Up to so many lanes.  Rows against thread per lane, lanes of 64 pixels, us: ten components 2048 178 and 635, 8192 237 and 650, 16,384 393
+// and 670, 24,576 532 and 670, 32,768 700 and 690; two 16,384 201 and 284, 24,576 269 and 292, 32,768 339 and 301; sixteen 16,384
+// 653 and 972, 24,576 961 and 979, 32,768 1264 and 987; a photograph of 1365 x 2047 in tiles of 16 x 16 1118 and 2636.
+constexpr uint32_t kMixRowLanes = 24576;
+
+template <int kK>
+__global__ __launch_bounds__(kMixRowThreads) void k_mix_decode_rows(
+    Geo g, const uint8_t *__restrict__ coded, unsigned long long coded_bytes, MixArgs a, uint8_t *__restrict__ out,
+    Report *__restrict__ report)
+{
+    __shared__ LdsTables tab;
+    __shared__ int s_state;
+    __shared__ unsigned long long s_payload;
+    __shared__ EdgeLaw s_law[kMixRowThreads / 16][kK];
+    __shared__ uint32_t s_weight[kMixRowThreads / 16][kK];
+    if (threadIdx.x == 0u) s_state = check_header(g, kMagicMix, a.k, coded, coded_bytes, &s_payload);
+    load_tables(tab);  // ends with a barrier
+    if (s_state != ST_OK) {
+        if (blockIdx.x == 0u && threadIdx.x == 0u) raise_code(report, s_state);
+        return;
+    }
+    const uint32_t j = threadIdx.x & 15u, row = threadIdx.x >> 4, first_of_row = threadIdx.x & 48u;
+    const uint32_t lane = blockIdx.x * (kMixRowThreads / 16) + row;
+    if (lane >= g.lanes) return;
+    const LaneShape sh = lane_shape(g, lane);
+    const uint32_t m_bits = g.prec_bits;
+    const uint32_t scale = mass_scale(m_bits), mask = (1u << m_bits) - 1u, top = 1u << m_bits;
+    const uint32_t payload_bytes = (uint32_t)s_payload;
+    const uint32_t *offsets = reinterpret_cast<const uint32_t *>(coded + 64);
+    const uint16_t *payload = reinterpret_cast<const uint16_t *>(coded + 64 + 4ull * ((size_t)g.lanes + 1));
+    const uint32_t begin = offsets[lane], end = offsets[lane + 1];
+    if (end < begin || end > payload_bytes || end - begin < 4u || ((begin | end) & 1u)) {
+        if (j == 0u) raise_code(report, ST_CORRUPT);
+        return;
+    }
+    const uint32_t adj = (uint32_t)(reinterpret_cast<uintptr_t>(payload) & 31u);
+    const uint16_t *base = reinterpret_cast<const uint16_t *>(reinterpret_cast<const uint8_t *>(payload) - adj);
+    const uint32_t first = (adj + begin) >> 1;
+    const uint32_t lim = (uint32_t)(((unsigned long long)adj + payload_bytes + 1ull) >> 1);
+    WordStream words;  // (every thread of the row the same)
+    words.open(base, first, lim);
+    uint32_t S = words.take(base, lim);
+    S |= words.take(base, lim) << 16;
+
+    struct Own {  // of component j (threads past the last one have its)
+        uint32_t m[3], w;
+        int l[3], c[3];
+    };
+    const uint32_t own = min(j, (uint32_t)kK - 1u);
+    auto fetch = [&](uint32_t t) {
+        const uint32_t p = lane_pixel(g, sh, min(t, sh.npx - 1u));
+        const size_t at = (size_t)p * (3u * kK) + own;
+        const int16_t *coef = a.coef + 3 * g.by_hw.div(p);
+        Own o;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            o.m[ch] = a.mu[at + ch * kK];
+            o.l[ch] = a.ls[at + ch * kK];
+            o.c[ch] = coef[ch];
+        }
+        o.w = a.weight[(size_t)p * kK + own];
+        return o;
+    };
+    bool ok = true;
+    uint32_t w[kK];
+    EdgeLaw law[kK];
+    auto cum = [&](uint32_t k) {  // C(k), 0 <= k <= 255
+        unsigned long long acc = 0ull;
+#pragma unroll
+        for (int c = 0; c < kK; ++c) acc += (unsigned long long)w[c] * edge_at(edge_y((int)k, law[c]), tab);
+        return k == 0u ? 0u : k + mass_of((uint32_t)(acc >> 15), scale);
+    };
+    auto row_count = [&](bool pred) { return (uint32_t)__popc((uint32_t)(__ballot(pred) >> first_of_row) & 0xFFFFu); };
+    auto from_thread = [&](uint32_t n, uint32_t v) {  // v of thread n of the row
+        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)((first_of_row + n) << 2), (int)v);
+    };
+    Own now = fetch(0u);
+    uint32_t inv_s[3];
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) inv_s[ch] = inv_scale(now.l[ch], tab);
+    for (uint32_t t = 0; t < sh.npx; ++t) {
+        const Own next = fetch(t + 1u);
+        if (j < (uint32_t)kK) s_weight[row][j] = now.w;
+        int x[3] = {0, 0, 0};
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            int me = (int)now.m[ch];
+            if (ch >= 1) {
+                const int e_r = x[0] * 256 - (int)now.m[0];
+                me += ch == 1 ? rsh14_mul(now.c[0], e_r) : rsh14_mul(now.c[1], e_r) + rsh14_mul(now.c[2], x[1] * 256 - (int)now.m[1]);
+            }
+            wave_lds_sync();  // (the channel before has been read)
+            if (j < (uint32_t)kK) s_law[row][j] = edge_law(me, inv_s[ch]);
+            wave_lds_sync();
+            if (ch == 0) {
+                uint32_t sum = 0;
+#pragma unroll
+                for (int c = 0; c < kK; ++c) {
+                    w[c] = s_weight[row][c];
+                    sum += w[c];
+                }
+                ok = ok && sum == 1u << 15;
+            }
+#pragma unroll
+            for (int c = 0; c < kK; ++c) law[c] = s_law[row][c];
+            const uint32_t slot = S & mask;
+            // the band of sixteen values: n - 1, of which C(16 (n - 1)) <= slot < C(16 n)
+            const uint32_t c16 = cum(16u * j);
+            const uint32_t n = row_count(c16 <= slot);
+            const uint32_t beyond = n < 16u ? from_thread(n, c16) : top;
+            // (with weights that do not sum to 2^15 there may be none: a value all the same)
+            const uint32_t band = 16u * (max(n, 1u) - 1u);
+            const uint32_t c1 = cum(band + j);
+            const uint32_t k = max(row_count(c1 <= slot), 1u) - 1u;
+            const uint32_t c_lo = from_thread(k, c1), c_next = from_thread(min(k + 1u, 15u), c1);
+            const uint32_t c_hi = k < 15u ? c_next : beyond;
+            x[ch] = (int)(band + k);
+            // App. A eq. (12); the mass is at most 2^16 and S >> M below 2^22: a 24-bit multiply is exact
+            S = (uint32_t)__umul24(c_hi - c_lo, S >> m_bits) + slot - c_lo;
+            if (S < (1u << 16)) S = (S << 16) | words.take(base, lim);
+        }
+        if (j < 3u) out[3 * (size_t)lane_pixel(g, sh, t) + j] = (uint8_t)(j == 0u ? x[0] : j == 1u ? x[1] : x[2]);
+        now = next;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) inv_s[ch] = inv_scale(now.l[ch], tab);
+    }
+    if (!ok) raise_code(report, ST_PARAMS);
+    if (j == 0u && (S != (1u << 16) || words.taken(first) != (end - begin) >> 1)) raise_code(report, ST_CORRUPT);
+}
+
 }  // namespace pilc

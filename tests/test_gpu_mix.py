@@ -59,6 +59,27 @@ def test_container_and_image_identical_to_oracle(name, make):
     assert np.array_equal(d.decoded_numpy(), wl.img)
 
 
+# Decoding goes by rows of 16 threads up to 24,576 lanes and by a thread a lane above: both sides of the line, and the kernels
+# above it, of which every count of components has its own, and one for arrays off the 4-byte grid.
+@pytest.mark.parametrize("off_grid", [False, True], ids=["aligned", "off-grid"])
+@pytest.mark.parametrize("case", [(24576, 2), (24577, 2)] + [(24580 + k, k) for k in range(1, 17)], ids=lambda c: "%dxk%d" % c)
+def test_decode_with_many_lanes(case, off_grid):
+    lanes, k = case
+    print("case", case, off_grid, flush=True)
+    wl = synth_mix.from_base(synth.make_random_case(lanes, lanes, 1, 3, 10 + k % 7, 0, 3, wild=k % 2 == 0), k, k)
+    rc, want = mx.encode(orc.make_geom(*wl.geom), wl.num_comp, wl.img, wl.mu, wl.log_scale, wl.weight, wl.chan_coef)
+    assert rc == mx.OK
+    d = DeviceMix(wl)
+    if off_grid:
+        def shifted(t):
+            buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+            buf[1:] = t.reshape(-1)
+            return buf[1:].reshape(t.shape)
+        d.mu, d.log_scale, d.weight = shifted(d.mu), shifted(d.log_scale), shifted(d.weight)
+    assert d.decode(coded=torch.from_numpy(want).cuda(), nbytes=want.size) == pb.PILC_OK
+    assert np.array_equal(d.decoded_numpy(), wl.img)
+
+
 # The encoder evaluates chunks of 1, 2, 4, 8 or 16 pixels of a lane at a time, by the lanes' length, and takes 4 to 64 lanes
 # a wavefront, by how many there are: lengths around whole chunks, counts on both sides of the lines, partly
 # filled last wavefronts, tiles clipped to a pixel, register budgets of few and of many components.
