@@ -21,9 +21,10 @@
  *     The library's only process-wide state: the constant tables (filled once per device under a
  *     lock), the knobs pilc_set_timing, pilc_set_kernel_policy, pilc_set_one_pass_wait and
  *     pilc_set_ansai_decode_waves (atomic integers, read once at the start of a call), the scratch array of pilc_encode_static, four
- *     sets of words (4 MB each, on every GPU) that calls of pilc_twar_inverse on tall images pass rows on
- *     through, one a call, and a few KB of pinned host memory in which pilc_encode and pilc_decode report
- *     their outcome (64 places, one a call; allocated by the first such call and kept).
+ *     sets of words (8 MB each, on every GPU) that calls of pilc_twar_inverse on tall images pass rows on
+ *     through, one a call, and a few KB of pinned host memory in which calls that encode or decode, and
+ *     pilc_twar_inverse on tall images, report their outcome (64 places, one a call; allocated by the first such
+ *     call and kept).
  *   - Tensors are dense, row-major, channel-interleaved: index ((i*h + y)*w + x)*3 + c.
  */
 #ifndef PILC_H
@@ -174,7 +175,8 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
  * kernel with HIP events on the stream the kernel is launched on.  pilc_last_timing returns
  * the durations in milliseconds of the most recent call on the calling thread: index 0 is
  * the whole GPU part of the call, 1.. are its kernels in launch order (pilc_timing_name
- * gives the kernel's function name; "scan" covers the kernels of the scan).  Returns the number of entries written (<= capacity), 0 if timing
+ * gives the kernel's function name; "scan" covers the kernels of the scan, which a
+ * batch of up to 8192 lanes has not).  Returns the number of entries written (<= capacity), 0 if timing
  * was off. */
 void pilc_set_timing(int enabled);
 int pilc_last_timing(float *ms_out_host, int capacity);
@@ -301,8 +303,8 @@ int pilc_twar_forward(uint32_t n, uint32_t h, uint32_t w, const uint8_t *img_dev
 
 /* The image back from the residual (Sec. 3.1: the anti-diagonal / column schedule of the paper's
  * decoding figure, here one walk along the anti-diagonals of 64 rows at a time).  Images of more than
- * 64 rows that are too few to fill the GPU by themselves (fewer than 192, at most) are decoded in bands
- * of 64 rows that follow each other through words in the library's device globals (16 MB on every GPU,
+ * 64 rows, unless they are many and short, are decoded in bands
+ * of 64 rows that follow each other through words in the library's device globals (32 MB on every GPU,
  * there from the time the library is loaded); their wait for the band above is bounded
  * like the one-pass encoder's (pilc_set_one_pass_wait) and ends in PILC_E_TIMEOUT.
  * Errors: PILC_E_ARG, PILC_E_TOO_LARGE, PILC_E_HIP, PILC_E_TIMEOUT (img_dev contents undefined). */

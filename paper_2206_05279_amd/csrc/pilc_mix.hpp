@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kMixThreads) void k_mix_encode(
 // per lane runs the serial chain over them.  A pixel's parameters go straight from memory to the registers of the thread
 // that uses them, and those of a chunk are one run of memory, so a line is fetched once or twice instead of once a
 // pixel.  (A thread per lane, which comes back for the rest of a line when it has long left the L2, read 2.7 times the
-// parameters, at 6.1 TB/s: 2048 images of 64 x 64, ten components, a lane a row, whole call 558 us, now 376; and a small batch
+// parameters, at 6.1 TB/s: 2048 images of 64 x 64, ten components, a lane a row, whole call 558 us, now 368, 1.1 times the parameters read and 79 % of the issue slots used; and a small batch
 // went a pixel after another: 64 such images 366 us, now 91; two photographs of 1365 x 2047 with a lane a row 13.3 ms, now 1.2.)
 // The wavefronts share nothing but the tables, so there is no barrier.
 // --------------------------------------------------------------------------------------------
