@@ -303,7 +303,7 @@ int pilc_twar_forward(uint32_t n, uint32_t h, uint32_t w, const uint8_t *img_dev
 
 /* The image back from the residual (Sec. 3.1: the anti-diagonal / column schedule of the paper's
  * decoding figure, here one walk along the anti-diagonals of 64 rows at a time).  Images of more than
- * 64 rows, unless they are many and short, are decoded in bands
+ * 64 rows, unless there are so many that they fill the GPU with one such band each, are decoded in bands
  * of 64 rows that follow each other through words in the library's device globals (32 MB on every GPU,
  * there from the time the library is loaded); their wait for the band above is bounded
  * like the one-pass encoder's (pilc_set_one_pass_wait) and ends in PILC_E_TIMEOUT.

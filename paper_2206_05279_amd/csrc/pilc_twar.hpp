@@ -14,6 +14,8 @@
 // Included at the end of pilc.hip.
 #pragma once
 
+#include "pilc_twar_rules.hpp"
+
 namespace pilc {
 
 struct TwarK {
@@ -481,7 +483,7 @@ __device__ __forceinline__ void interval_barrier()
     __syncthreads();
 }
 
-// A band of each strip, a workgroup each; the row above, if any, is in the image.  26 KB of LDS and 80 registers: four workgroups
+// A band of each strip, a workgroup each; the row above, if any, is in the image.  25,088 bytes of LDS and 80 registers: four workgroups
 // share a compute unit, which is what batches of many strips live on.
 __global__ __launch_bounds__(64 * 6) void k_twar_inverse_strips(TwarK p, Diag a, const uint8_t *__restrict__ res,
                                                               uint8_t *__restrict__ img)
@@ -1234,7 +1236,6 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_bands(TwarK p, Diag a, 
 // pinned memory, 30 frames of 1080 x 1920 took 12 us more.)
 constexpr uint32_t kTileManyImages = 1024;  // a wavefront for every SIMD
 constexpr int kBandSlots = 4;
-constexpr uint32_t kBandWords = 1u << 21;  // 8 MB a set: 127 bands of 16384 columns, 1057 of 1920
 constexpr uint32_t kBandMarks = 255;
 struct BandSet {
     uint32_t words[kBandWords];
@@ -1363,37 +1364,6 @@ int pilc_twar_forward(uint32_t n, uint32_t h, uint32_t w, const uint8_t *img_dev
     return PILC_OK;
 }
 
-// Whether the bands of a batch are decoded one at a time, a launch each, and not together: where the strips by themselves
-// fill the chip with workgroups of the kernel that goes a band at a time, four on a compute unit (two of the other),
-// and there are few bands, or short ones, which together spend much of their time on getting under way.  Together
-// (two a unit) against one at a time, us:
-//   strips x bands x columns                strips x bands x columns
-//     256 x 2 x 256     47    52              500 x 3 x 400    116   105
-//     300 x 2 x 256     57    61              250 x 5 x 400    102   135
-//     400 x 2 x 256     65    62             1000 x 8 x 256    480   518
-//     500 x 2 x 512    108    87              500 x 4 x 64      92    80
-//     300 x 3 x 400     89   104             2000 x 8 x 96     633   499
-//     400 x 3 x 400     95   104             1000 x 4 x 256    238   250
-static bool bands_one_at_a_time(uint64_t strips, uint32_t bands, uint32_t blocks)
-{
-    return strips >= 384u && (bands <= 3u || blocks <= 14u);
-}
-
-// Whether bands that run together have a compute unit each.  A band that has one to itself is half as fast again, and one that
-// is slow holds up all below it; but two on a unit get more done where there are so many strips that those behind
-// are not waited for.  One a unit against two, us:
-//   strips x bands x columns                strips x bands x columns
-//      30 x 17 x 1920   211   263             112 x 10 x 400   130   112
-//      60 x 17 x 1920   344   404             128 x 12 x 400   152   135
-//      64 x 12 x 64      77    89             128 x 8 x 128     85   103
-//      64 x 12 x 400    102   118             160 x 12 x 64    123    98
-//      50 x 10 x 800    103   110             150 x 5 x 800    116   112
-//     191 x 4 x 1500    192   216             300 x 4 x 600    150   122
-static bool bands_alone_on_a_unit(uint64_t strips, uint32_t blocks)
-{
-    return blocks >= 64u || (strips < 144u && strips * (blocks + 9u) <= 3300u);
-}
-
 // pilc_twar_inverse along the diagonals.
 static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *res_dev, const TwarK &k,
                              uint8_t *img_dev, hipStream_t stream, Timer &timer)
@@ -1411,11 +1381,9 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
     if (bands > 1u && !bands_one_at_a_time(strips, bands, a.blocks)) lease.acquire();
     BandSet *const set = lease.set();
     std::optional<CallReport> report;
-    // bands of a strip and strips in a launch: what the words passed on have room for
-    const uint32_t band_words = 16u * a.blocks;
-    const uint32_t together = set ? (uint32_t)std::min<uint64_t>(bands, kBandWords / band_words) : 1u;
-    uint64_t most_strips = together > 1u ? std::max<uint64_t>(1u, kBandWords / ((uint64_t)together * band_words)) : 1u << 20;
-    most_strips = ceil_div64(strips, ceil_div64(strips, most_strips));  // launches of one size
+    const BandLaunch launch = band_launches(strips, bands, a.blocks);
+    const uint32_t together = set ? launch.bands : 1u;
+    const uint64_t most_strips = set ? launch.strips : 1u << 20;
     int dev = 0, khz = 0;
     const unsigned long long wait = g_one_pass_wait.load(std::memory_order_relaxed);
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -1439,7 +1407,7 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
             a.words = a.bands > 1u ? set->words : nullptr;
             if (a.bands > 1u) {
                 lease.next_launch(here * a.bands, stream, &a.mark, &a.first_ticket);
-                const uint32_t lds = bands_alone_on_a_unit(here, a.blocks) ? kDiagAloneBytes : kDiagRawBytes;
+                const uint32_t lds = bands_alone_on_a_unit(here, a.bands, a.blocks) ? kDiagAloneBytes : kDiagRawBytes;
                 k_twar_inverse_bands<<<here * a.bands, 64 * 6, lds, stream>>>(k, a, res_dev, img_dev);
             } else {
                 k_twar_inverse_strips<<<here, bands > 1u ? 64 * 6 : 64 * 5, 0, stream>>>(k, a, res_dev, img_dev);

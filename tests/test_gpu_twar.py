@@ -130,8 +130,8 @@ def test_any_width_at_any_address(shape, offset):
         assert bool((whole[:16 + offset] == fill).all()) and bool((whole[16 + offset + size:] == fill).all()), fill
 
 
-# Images of more than 64 rows on either side of each line at which the route changes: tiles or diagonals (by how
-# many there are and how wide), bands together or one at a time (by how many strips, bands and columns).
+# Images of more than 64 rows on either side of each line between tiles and diagonals (by how many there are and how
+# wide); from 191 images of 150 rows on, bands of the diagonals in several shapes (their lines: test_lines_of_bands).
 @pytest.mark.parametrize("offset", [0, 1], ids=lambda o: "at%d" % o)
 @pytest.mark.parametrize("shape", [(256, 65, 24), (257, 97, 24), (257, 97, 28), (300, 65, 36), (300, 65, 40), (512, 97, 36),
                                    (513, 97, 36), (513, 97, 40), (768, 97, 84), (769, 97, 84), (769, 129, 27),
@@ -154,13 +154,15 @@ def test_both_sides_of_every_line(shape, offset):
     assert (back[:16 + offset] == 0xA5).all() and (back[16 + offset + size:] == 0xA5).all()
 
 
-@pytest.mark.parametrize("shape", [(70, 1080, 1920), (23, 150, 50000), (1, 4100, 65535), (6000, 129, 100)],
+@pytest.mark.parametrize("shape", [(70, 1080, 1920), (23, 150, 50000), (1, 4100, 65535), (6000, 129, 100), (250, 200, 2047),
+                                   (190, 300, 3200)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_more_bands_than_one_launch_takes(shape):
     """More bands than there is room for the rows they pass on: several launches with all bands of an image, over
     the images (62 and 8 frames, 13 and 10 wide images), whose rows pass through the same words; for an image
     with more bands than that by itself, over its bands; and so many images that bands go one at a time, a
-    launch each."""
+    launch each, or as many wide ones as make up a round of workgroups and more bands than a launch takes (and somewhat fewer, which
+    go together)."""
     print("shape", shape, flush=True)
     g = torch.Generator(device="cuda:0").manual_seed(3)
     img = torch.randint(0, 256, shape + (3,), dtype=torch.uint8, device="cuda:0", generator=g)
@@ -198,9 +200,16 @@ def test_more_calls_at_once_than_sets_of_words():
     assert not wrong
 
 
-# Bands together or one at a time (384 strips, by bands and by blocks of columns), and together with a compute unit
-# each or two to one (64 blocks; 144 strips; strips times blocks): either side of every line, odd sizes among them.
-@pytest.mark.parametrize("shape", [(383, 130, 64), (384, 130, 64), (384, 200, 161), (384, 200, 162), (143, 131, 161),
+# Bands one at a time or together (two bands of short rows; strips, whole rounds of them, bands times blocks; long rows), and
+# together with a compute unit each or two to one (strips by blocks, bands together, long rows): either side of the lines of
+# csrc/pilc_twar_rules.hpp, odd sizes among them.
+@pytest.mark.parametrize("shape", [(255, 70, 64), (256, 70, 64), (384, 70, 240), (385, 70, 240), (399, 130, 200), (400, 130, 200),
+                                   (400, 130, 401), (400, 130, 418), (429, 130, 418), (430, 130, 418), (520, 520, 98),
+                                   (520, 520, 114), (449, 1500, 34), (450, 1500, 34), (200, 70, 1074), (211, 70, 1073),
+                                   (211, 70, 1074), (230, 200, 881), (230, 200, 882), (112, 450, 50), (113, 450, 50),
+                                   (150, 450, 66), (151, 450, 66), (103, 450, 304), (104, 450, 304), (100, 448, 304),
+                                   (140, 200, 1010), (141, 200, 1010), (141, 200, 1009), (140, 130, 1682), (141, 130, 1682),
+                                   (383, 130, 64), (384, 130, 64), (384, 200, 161), (384, 200, 162), (143, 131, 161),
                                    (144, 131, 161), (132, 129, 176), (132, 129, 194), (20, 140, 945), (20, 140, 946),
                                    (1, 65, 1), (1, 127, 17), (1, 193, 33)], ids=lambda s: "x".join(map(str, s)))
 def test_lines_of_bands(shape):
