@@ -176,7 +176,7 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
  * the durations in milliseconds of the most recent call on the calling thread: index 0 is
  * the whole GPU part of the call, 1.. are its kernels in launch order (pilc_timing_name
  * gives the kernel's function name; "scan" covers the kernels of the scan, which a
- * batch of up to 8192 lanes has not).  Returns the number of entries written (<= capacity), 0 if timing
+ * batch of few lanes has not: up to 8192, fewer where they are long).  Returns the number of entries written (<= capacity), 0 if timing
  * was off. */
 void pilc_set_timing(int enabled);
 int pilc_last_timing(float *ms_out_host, int capacity);

@@ -206,10 +206,10 @@ __global__ void k_scan_spine(HeaderWords head, uint32_t items, uint32_t nblocks,
     spine_scan(head, items, nblocks, block_sums, coded, coded_capacity, status, report);
 }
 
-// For a batch of few tiles (but more lanes than kScanAloneLanes) the two in one: the workgroup that is done last goes on with the sums of all.  `status->ticket`
-// is zero before the launch.  The packers of such a batch form the offset table themselves (lane_offsets), so that
-// one launch stands where there were three.  Up to kScanFewTiles: 100,000 lanes of 63 pixels 153 -> 139 us, 8 images of 64 x
-// 64 in 512 lanes 53 -> 42; with 1600 tiles, where every workgroup's fence and every packer's sums of its tile
+// For a batch of few tiles (but too large for scans_alone) the two in one: the workgroup that is done last goes on with the
+// sums of all.  `status->ticket` is zero before the launch.  The packers of such a batch form the offset table themselves
+// (lane_offsets), so that one launch stands where there were three.  Up to kScanFewTiles: 100,000 lanes of 63 pixels
+// 153 -> 139 us; with 1600 tiles, where every workgroup's fence and every packer's sums of its tile
 // cost more than two launches, 50,000 images of 32 x 32 in lanes of 32 pixels 508 -> 573.
 constexpr uint32_t kScanFewTiles = 128;
 __global__ __launch_bounds__(kScanThreads) void k_scan_sums(HeaderWords head, uint32_t items, ItemBytes bytes,
@@ -238,8 +238,15 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(HeaderWords head, ui
 // A batch of few lanes has no scan at all: every workgroup of the packer sums the counts of all lanes, and of those before its own,
 // and the first one writes the header and the outcome.  What that costs is a read of all counts from the L2 by every
 // workgroup; what it saves is a launch.  With the launch and without, whole encode calls, us: 2048 lanes of 32 pixels 35.8 and 31.1,
-// 4000 of 512 69.5 and 67.2, 8000 of 32 38.4 and 37.8, 16,000 of 32 42.0 and 45.6.
+// 4000 of 512 69.5 and 67.2, 8000 of 32 38.4 and 37.8, 16,000 of 32 42.0 and 45.6.  Long lanes have a workgroup for every few
+// of them, so the line is also at so many workgroups times lanes.  What the calls take longer without the launch, us, mean of
+// some hundred batches: at 10 million -0.7, 12 -1 (of 200 to 300), 20 -1.2, 25 0.3 to 2.4 (of 320 to 490), 60 7.5 (of 520).
 constexpr uint32_t kScanAloneLanes = 8192;
+constexpr uint64_t kScanAloneReads = 1u << 24;
+static bool scans_alone(uint32_t lanes, uint32_t pack_blocks)
+{
+    return lanes <= kScanAloneLanes && (uint64_t)lanes * pack_blocks <= kScanAloneReads;
+}
 struct PackAlone {
     uint32_t alone;  // else the rest is not looked at
     HeaderWords head;
@@ -1239,10 +1246,6 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
     }
     timer.mark(few_lanes ? "k_encode_block" : "k_encode_lanes");
     if (!one_pass) {
-        const PackAlone pk = {g.lanes <= kScanAloneLanes ? 1u : 0u, head, coded_dev, coded_capacity, report->dev()};
-        const bool formed = pk.alone == 0u && launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev,
-                                                          coded_capacity, status, report->dev(), offsets, false, stream);
-        if (pk.alone == 0u) timer.mark("scan");
         // a run of lanes per workgroup: about 16K symbols' worth, at most 256 lanes; of a small batch less, so that
         // there are kPackBlocks workgroups, but not less than kPackLeast symbols (64 images of 32 x 32 in
         // 2048 lanes 28.5 -> 8.0 us, 400 of 64 x 64 in 25,600 lanes 28.7 -> 13.4; with 512 workgroups of
@@ -1250,12 +1253,17 @@ static int encode_checked(const Geo &g, const uint8_t *img_dev, const pilc_param
         const uint32_t lane_sym = std::max(1u, max_lane_symbols(g));
         uint32_t pack_lanes = 16384u / lane_sym;
         pack_lanes = std::min(pack_lanes, std::max(g.lanes / kPackBlocks, kPackLeast / lane_sym));
-        pack_lanes = std::min(std::max(pack_lanes, 1u), (uint32_t)kPackMaxLanes);
+        pack_lanes = lane_cap != 0u ? 64u : std::min(std::max(pack_lanes, 1u), (uint32_t)kPackMaxLanes);
+        const uint32_t pack_blocks = (uint32_t)ceil_div64(g.lanes, pack_lanes);
+        const PackAlone pk = {scans_alone(g.lanes, pack_blocks) ? 1u : 0u, head, coded_dev, coded_capacity, report->dev()};
+        const bool formed = pk.alone == 0u && launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev,
+                                                          coded_capacity, status, report->dev(), offsets, false, stream);
+        if (pk.alone == 0u) timer.mark("scan");
         if (lane_cap != 0u)
-            (lane_cap <= 256u ? k_pack_by_thread<128> : k_pack_by_thread<256>)<<<(uint32_t)ceil_div64(g.lanes, 64), kScanThreads, 0, stream>>>(
+            (lane_cap <= 256u ? k_pack_by_thread<128> : k_pack_by_thread<256>)<<<pack_blocks, kScanThreads, 0, stream>>>(
                 g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, pk);
         else
-            k_pack<<<(uint32_t)ceil_div64(g.lanes, pack_lanes), kScanThreads, 0, stream>>>(
+            k_pack<<<pack_blocks, kScanThreads, 0, stream>>>(
                 g, pack_lanes, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, pk);
         timer.mark(lane_cap != 0u ? "k_pack_by_thread" : "k_pack");
     }
@@ -1508,11 +1516,12 @@ int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mi
     timer.mark("k_mix_encode");
     const HeaderWords head = {{kMagicMix, PILC_VERSION, g.n, g.h, g.w, 3u, g.prec_bits, g.lane_mode,
                                g.lane_a, g.lane_b, g.lanes, params->num_comp}};
-    const PackAlone pk = {g.lanes <= kScanAloneLanes ? 1u : 0u, head, coded_dev, coded_capacity, report.dev()};
+    const uint32_t pack_blocks = (uint32_t)ceil_div64(g.lanes, 64);
+    const PackAlone pk = {scans_alone(g.lanes, pack_blocks) ? 1u : 0u, head, coded_dev, coded_capacity, report.dev()};
     const bool formed = pk.alone == 0u && launch_scan(head, g.lanes, ws.scan_blocks, kLaneBytes, lane_words, sums, coded_dev,
                                                       coded_capacity, status, report.dev(), offsets, false, stream);
     if (pk.alone == 0u) timer.mark("scan");
-    (lane_cap <= 256u ? k_pack_by_thread<128> : k_pack_by_thread<256>)<<<(uint32_t)ceil_div64(g.lanes, 64), kScanThreads, 0, stream>>>(
+    (lane_cap <= 256u ? k_pack_by_thread<128> : k_pack_by_thread<256>)<<<pack_blocks, kScanThreads, 0, stream>>>(
         g.lanes, lane_cap, scratch, lane_words, lane_state, sums, formed, offsets, payload, status, pk);
     timer.mark("k_pack_by_thread");
     HIP_TRY(hipGetLastError());

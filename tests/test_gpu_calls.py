@@ -217,3 +217,20 @@ def test_packers_without_a_scan(lanes, policy):
         assert bool((d.coded[64 + 4 * (lanes + 1):] == 0x5A).all())
     finally:
         pb.pilc_set_kernel_policy(0)
+
+
+@pytest.mark.parametrize("lanes", [4096, 4097])
+def test_packers_of_long_lanes_have_a_scan(lanes):
+    """With a workgroup of the packer for every lane, 4096 lanes are the most whose counts every workgroup sums."""
+    wl = synth.make_random_case(lanes, lanes, 1, 2731, 12, 0, 2731)
+    rc, want = orc.encode(orc.make_geom(*wl.geom), wl.img, wl.mu, wl.log_scale, wl.chan_coef)
+    assert rc == orc.OK
+    d = DeviceWorkload(wl)
+    pb.pilc_set_timing(True)
+    try:
+        rc, nbytes = d.encode()
+        names = [name for name, _ in pb.pilc_last_timing()]
+    finally:
+        pb.pilc_set_timing(False)
+    assert ("scan" in names) == (lanes > 4096), names
+    assert nbytes == want.size and np.array_equal(d.coded[:nbytes].cpu().numpy(), want)
