@@ -419,7 +419,8 @@ __global__ __launch_bounds__(kMixThreads) void k_mix_encode(
 // The wavefronts share nothing but the tables, so there is no barrier.
 // --------------------------------------------------------------------------------------------
 // Four wavefronts on a SIMD, in workgroups of eight that share the tables; from twelve components on the registers are those of
-// three, in workgroups of four (at four, K = 16 spills 164 bytes a thread: 1024 images of 64 x 64 595 us, now 325).
+// three, in workgroups of four (at four, K = 16 spills 164 bytes a thread: 1024 images of 64 x 64 595 us, now 300; with those of
+// two, two photographs of 1365 x 2047 in tiles of 16 x 16 580, now 470).
 constexpr int mix_encode_waves(int k) { return k >= 12 ? 3 : 4; }
 constexpr int mix_encode_threads(int k) { return k >= 12 ? 256 : 512; }
 constexpr uint32_t kMixEncRecords = 512;  // pixels of a wavefront's chunks: most lanes times pixels
@@ -479,6 +480,8 @@ __global__ __launch_bounds__(mix_encode_threads(kK)) __attribute__((amdgpu_waves
 
     uint16_t *wout = scratch + lane_scratch_base(lane, lane_cap);
     uint32_t nwords = 0, S = 1u << 16;
+    // With sixteen components there are no registers left for what only the chain needs: it lies beside the lane's shape.
+    constexpr bool kChainInLds = kK >= 16;
     bool ok = true;
     for (uint32_t q = (longest + chunk - 1u) >> c.log_chunk; q-- > 0u;) {
         const uint32_t px0 = q << c.log_chunk;
@@ -509,7 +512,7 @@ __global__ __launch_bounds__(mix_encode_threads(kK)) __attribute__((amdgpu_waves
             const int x[3] = {(int)(xb & 0xFFu), (int)((xb >> 8) & 0xFFu), (int)((xb >> 16) & 0xFFu)};
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                const int v = x[ch];
+                const int v = (int)((xb >> (8 * ch)) & 0xFFu);
                 unsigned long long acc_lo = 0ull, acc_hi = 0ull;
 #pragma unroll
                 for (int j = 0; j < kK; ++j) {
@@ -533,7 +536,12 @@ __global__ __launch_bounds__(mix_encode_threads(kK)) __attribute__((amdgpu_waves
         }
         wave_lds_sync();
         // pixels last-first, and B, G, R inside a pixel (App. A eq. (11) runs against the decoder)
-        for (uint32_t i = npx > px0 ? min(npx - px0, chunk) : 0u; i-- > 0u;) {
+        uint32_t own = npx;
+        if (kChainInLds) {
+            own = t < lanes_here ? shapes[t].y : 0u;
+            nwords = shapes[t].w;
+        }
+        for (uint32_t i = own > px0 ? min(own - px0, chunk) : 0u; i-- > 0u;) {
             uint32_t r[3];
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) r[ch] = rec[((3u * i + ch) << c.log_lanes) + t];
@@ -549,6 +557,7 @@ __global__ __launch_bounds__(mix_encode_threads(kK)) __attribute__((amdgpu_waves
                 S = (uint32_t)__umul24(quotient(S, over_reciprocal(f)), top - f) + (S + lo);
             }
         }
+        if (kChainInLds && mine) shapes[t].w = nwords;
         wave_lds_sync();
     }
     if (!ok) atomicMax(status_code, 7);
