@@ -176,8 +176,8 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
  * the durations in milliseconds of the most recent call on the calling thread: index 0 is
  * the whole GPU part of the call, 1.. are its kernels in launch order (pilc_timing_name
  * gives the kernel's function name; "scan" covers the kernels of the scan, which a
- * batch of few lanes has not: up to 8192, fewer where they are long).  Returns the number of entries written (<= capacity), 0 if timing
- * was off. */
+ * batch of few lanes has not: up to 8192, fewer where they are long; "k_twar_inverse" the launches
+ * of the residual's inverse).  Returns the number of entries written (<= capacity), 0 if timing was off. */
 void pilc_set_timing(int enabled);
 int pilc_last_timing(float *ms_out_host, int capacity);
 const char *pilc_timing_name(int index_in_last_call);

@@ -1513,7 +1513,7 @@ int pilc_mix_encode(const pilc_geom *geom, const uint8_t *img_dev, const pilc_mi
         k_mix_encode<<<(uint32_t)ceil_div64(g.lanes, kMixThreads), kMixThreads, lds, stream>>>(
             g, img_dev, args, scratch, lane_cap, lane_words, lane_state, &status->code);
     }
-    timer.mark("k_mix_encode");
+    timer.mark(chunks ? "k_mix_encode_chunks" : "k_mix_encode");
     const HeaderWords head = {{kMagicMix, PILC_VERSION, g.n, g.h, g.w, 3u, g.prec_bits, g.lane_mode,
                                g.lane_a, g.lane_b, g.lanes, params->num_comp}};
     const uint32_t pack_blocks = (uint32_t)ceil_div64(g.lanes, 64);
@@ -1563,7 +1563,7 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
     Timer timer(stream);
     kern<<<(uint32_t)ceil_div64(g.lanes, group), kMixThreads, lds, stream>>>(
         g, coded_dev, (unsigned long long)coded_bytes, args, img_out_dev, report.dev());
-    timer.mark("k_mix_decode");
+    timer.mark(rows ? "k_mix_decode_rows" : "k_mix_decode");
     HIP_TRY(hipGetLastError());
     Report seen;
     HIP_TRY(report.wait(&seen));

@@ -42,6 +42,17 @@ CASES = [
 ]
 
 
+def off_the_dword_grid(d):
+    """The parameters of `d` at addresses that are 2 but not 4 bytes aligned."""
+    def shifted(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        buf[1:] = t.reshape(-1)
+        assert buf[1:].data_ptr() % 4 == 2
+        return buf[1:].reshape(t.shape)
+
+    d.mu, d.log_scale, d.weight = shifted(d.mu), shifted(d.log_scale), shifted(d.weight)
+
+
 @pytest.mark.parametrize("name,make", CASES, ids=[c[0] for c in CASES])
 def test_container_and_image_identical_to_oracle(name, make):
     wl = make()
@@ -71,11 +82,7 @@ def test_decode_with_many_lanes(case, off_grid):
     assert rc == mx.OK
     d = DeviceMix(wl)
     if off_grid:
-        def shifted(t):
-            buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
-            buf[1:] = t.reshape(-1)
-            return buf[1:].reshape(t.shape)
-        d.mu, d.log_scale, d.weight = shifted(d.mu), shifted(d.log_scale), shifted(d.weight)
+        off_the_dword_grid(d)
     assert d.decode(coded=torch.from_numpy(want).cuda(), nbytes=want.size) == pb.PILC_OK
     assert np.array_equal(d.decoded_numpy(), wl.img)
 
@@ -109,19 +116,30 @@ def test_ten_components_in_arrays_off_the_dword_grid_take_the_general_kernels():
     rc, want = mx.encode(g, wl.num_comp, wl.img, wl.mu, wl.log_scale, wl.weight, wl.chan_coef)
     assert rc == mx.OK
     d = DeviceMix(wl)
-
-    def shifted(t):  # the same values at an address that is 2 but not 4 bytes aligned
-        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
-        buf[1:] = t.reshape(-1)
-        assert buf[1:].data_ptr() % 4 == 2
-        return buf[1:].reshape(t.shape)
-
-    d.mu, d.log_scale, d.weight = shifted(d.mu), shifted(d.log_scale), shifted(d.weight)
+    off_the_dword_grid(d)
     rc, nbytes = d.encode()
     got = d.coded_numpy()
     assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
     assert d.decode() == pb.PILC_OK
     assert np.array_equal(d.decoded_numpy(), wl.img)
+
+
+@pytest.mark.parametrize("lanes,off_grid,encoder,decoder", [
+    (200, False, "k_mix_encode_chunks", "k_mix_decode_rows"), (200, True, "k_mix_encode", "k_mix_decode_rows"),
+    (24577, False, "k_mix_encode_chunks", "k_mix_decode")], ids=["rows", "rows-off-grid", "threads"])
+def test_timing_names_the_kernel_that_ran(lanes, off_grid, encoder, decoder):
+    d = DeviceMix(synth_mix.from_base(synth.make_random_case(lanes, lanes, 1, 3, 12, 0, 3), 4, 1))
+    if off_grid:
+        off_the_dword_grid(d)
+    pb.pilc_set_timing(True)
+    try:
+        d.encode()
+        names = [name for name, _ in pb.pilc_last_timing()]
+        assert names[1:] == [encoder] + ["scan"] * (lanes > 8192) + ["k_pack_by_thread"]
+        d.decode()
+        assert [name for name, _ in pb.pilc_last_timing()][1:] == [decoder]
+    finally:
+        pb.pilc_set_timing(False)
 
 
 def test_one_component_matches_the_single_law_path():
