@@ -186,7 +186,8 @@ const char *pilc_timing_name(int index_in_last_call);
  * thread per lane, 2 = the kernels for few long lanes (workgroup-cooperative encode, a row of 16
  * threads per lane in decode), 3 = one thread per lane with the one-pass encoder (the lane kernel
  * also computes the offsets and places its lanes in the container, instead of leaving that to the
- * scan and pack kernels; measured no faster, kept for comparison).  Lanes of 2^25 symbols and more
+ * scan and pack kernels; measured no faster, kept for comparison).  pilc_mix_decode goes a thread per
+ * lane under 1 and 3 and a row per lane under 2; pilc_mix_encode does not look at it.  Lanes of 2^25 symbols and more
  * are encoded by the kernels for few long lanes whatever is set (their words are out of the other
  * encoder's reach), so that under 3 the bounded wait below has nothing to bound in the encoder.
  * All choices produce the same

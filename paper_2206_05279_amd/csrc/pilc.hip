@@ -1551,7 +1551,8 @@ int pilc_mix_decode(const pilc_geom *geom, const uint8_t *coded_dev, size_t code
     hipStream_t stream = (hipStream_t)hip_stream;
     const MixArgs args = {params->mu, params->log_scale, params->weight, params->chan_coef,
                           params->num_comp};
-    const bool rows = g.lanes <= kMixRowLanes;
+    const int policy = g_kernel_policy.load(std::memory_order_relaxed);
+    const bool rows = policy == 0 ? g.lanes <= kMixRowLanes : policy == 2;
     const int built = mix_built_for(params);
     const size_t lds = rows ? 0 : mix_lds_bytes(params->num_comp, built == 0);
     auto kern = rows ? k_mix_decode_rows_for((int)params->num_comp) : k_mix_decode_for(built);

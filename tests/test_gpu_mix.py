@@ -42,6 +42,14 @@ CASES = [
 ]
 
 
+@pytest.fixture(params=[1, 2], ids=["thread-per-lane", "row-per-lane"])
+def decoder(request):
+    """Every decoder on the same input: a thread per lane and a row per lane, whatever the number of lanes."""
+    pb.pilc_set_kernel_policy(request.param)
+    yield request.param
+    pb.pilc_set_kernel_policy(0)
+
+
 def off_the_dword_grid(d):
     """The parameters of `d` at addresses that are 2 but not 4 bytes aligned."""
     def shifted(t):
@@ -54,7 +62,7 @@ def off_the_dword_grid(d):
 
 
 @pytest.mark.parametrize("name,make", CASES, ids=[c[0] for c in CASES])
-def test_container_and_image_identical_to_oracle(name, make):
+def test_container_and_image_identical_to_oracle(name, make, decoder):
     wl = make()
     g = orc.make_geom(*wl.geom)
     rc, want = mx.encode(g, wl.num_comp, wl.img, wl.mu, wl.log_scale, wl.weight, wl.chan_coef)
@@ -66,6 +74,9 @@ def test_container_and_image_identical_to_oracle(name, make):
     assert np.array_equal(got, want), first_difference(got, want)
     # decode the oracle's container on the GPU
     coded = torch.from_numpy(want).cuda()
+    assert d.decode(coded=coded, nbytes=want.size) == pb.PILC_OK
+    assert np.array_equal(d.decoded_numpy(), wl.img)
+    off_the_dword_grid(d)  # (the thread per lane has another kernel for these)
     assert d.decode(coded=coded, nbytes=want.size) == pb.PILC_OK
     assert np.array_equal(d.decoded_numpy(), wl.img)
 
@@ -110,7 +121,7 @@ def test_chunks_of_every_length(case):
     assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
 
 
-def test_ten_components_in_arrays_off_the_dword_grid_take_the_general_kernels():
+def test_ten_components_in_arrays_off_the_dword_grid_take_the_general_kernels(decoder):
     wl = synth_mix.make_mix_workload(2, 4, 10)
     g = orc.make_geom(*wl.geom)
     rc, want = mx.encode(g, wl.num_comp, wl.img, wl.mu, wl.log_scale, wl.weight, wl.chan_coef)
@@ -124,10 +135,21 @@ def test_ten_components_in_arrays_off_the_dword_grid_take_the_general_kernels():
     assert np.array_equal(d.decoded_numpy(), wl.img)
 
 
-@pytest.mark.parametrize("lanes,off_grid,encoder,decoder", [
+def test_policy_chooses_the_decoder(decoder):
+    d = DeviceMix(synth_mix.make_mix_workload(0, 4, 2))
+    d.encode()
+    pb.pilc_set_timing(True)
+    try:
+        d.decode()
+        assert pb.pilc_last_timing()[-1][0] == ("k_mix_decode_rows" if decoder == 2 else "k_mix_decode")
+    finally:
+        pb.pilc_set_timing(False)
+
+
+@pytest.mark.parametrize("lanes,off_grid,encoder,by_lanes", [
     (200, False, "k_mix_encode_chunks", "k_mix_decode_rows"), (200, True, "k_mix_encode", "k_mix_decode_rows"),
     (24577, False, "k_mix_encode_chunks", "k_mix_decode")], ids=["rows", "rows-off-grid", "threads"])
-def test_timing_names_the_kernel_that_ran(lanes, off_grid, encoder, decoder):
+def test_timing_names_the_kernel_that_ran(lanes, off_grid, encoder, by_lanes):
     d = DeviceMix(synth_mix.from_base(synth.make_random_case(lanes, lanes, 1, 3, 12, 0, 3), 4, 1))
     if off_grid:
         off_the_dword_grid(d)
@@ -137,7 +159,7 @@ def test_timing_names_the_kernel_that_ran(lanes, off_grid, encoder, decoder):
         names = [name for name, _ in pb.pilc_last_timing()]
         assert names[1:] == [encoder] + ["scan"] * (lanes > 8192) + ["k_pack_by_thread"]
         d.decode()
-        assert [name for name, _ in pb.pilc_last_timing()][1:] == [decoder]
+        assert [name for name, _ in pb.pilc_last_timing()][1:] == [by_lanes]
     finally:
         pb.pilc_set_timing(False)
 
@@ -154,10 +176,13 @@ def test_one_component_matches_the_single_law_path():
     assert np.array_equal(mix[64:], single[64:]) and np.array_equal(mix[8:44], single[8:44])
 
 
+@pytest.mark.parametrize("off_grid", [False, True], ids=["aligned", "off-grid"])
 @pytest.mark.parametrize("k", [3, 10])
-def test_bad_weights_and_component_counts_are_rejected(k):
+def test_bad_weights_and_component_counts_are_rejected(k, off_grid, decoder):
     wl = synth_mix.make_mix_workload(0, 4, k)
     d = DeviceMix(wl)
+    if off_grid:
+        off_the_dword_grid(d)
     rc, _ = d.encode()
     good = d.nbytes
     bad = wl.weight.copy()
@@ -172,10 +197,13 @@ def test_bad_weights_and_component_counts_are_rejected(k):
     assert d.decode(check=False, k=17) == pb.PILC_E_ARG
 
 
-def test_damaged_containers_fail_like_the_oracle():
+@pytest.mark.parametrize("off_grid", [False, True], ids=["aligned", "off-grid"])
+def test_damaged_containers_fail_like_the_oracle(off_grid, decoder):
     wl = synth_mix.make_mix_workload(0, 4, 2)
     g = orc.make_geom(*wl.geom)
     d = DeviceMix(wl)
+    if off_grid:
+        off_the_dword_grid(d)
     d.encode()
     coded = d.coded_numpy()
     args = (wl.mu, wl.log_scale, wl.weight, wl.chan_coef)

@@ -56,7 +56,8 @@ def test_random_geometry_matches_oracle(seed, policy):
 
 
 @pytest.mark.parametrize("seed", range(12))
-def test_random_geometry_mixture_matches_oracle(seed):
+@pytest.mark.parametrize("policy", [0, 1, 2], ids=["auto", "thread-per-lane", "row-per-lane"])
+def test_random_geometry_mixture_matches_oracle(seed, policy):
     n, h, w, m, mode, la, lb = _random_geometry(100 + seed)
     k = int(np.random.default_rng(seed).integers(1, 17))
     wl = synth_mix.from_base(synth.make_random_case(seed, n, h, w, m, mode, la, lb, wild=(seed % 4 == 0)), k, seed)
@@ -67,5 +68,9 @@ def test_random_geometry_mixture_matches_oracle(seed):
     _, nbytes = d.encode()
     got = d.coded_numpy()
     assert nbytes == want.size and np.array_equal(got, want), first_difference(got, want)
-    assert d.decode() == pb.PILC_OK
-    assert np.array_equal(d.decoded_numpy(), wl.img)
+    pb.pilc_set_kernel_policy(policy)
+    try:
+        assert d.decode() == pb.PILC_OK
+        assert np.array_equal(d.decoded_numpy(), wl.img)
+    finally:
+        pb.pilc_set_kernel_policy(0)
