@@ -1,5 +1,7 @@
-// rANS lanes under a mixture of K logistic laws per subpixel (gfx950): one thread per lane, but for the encoder of
-// aligned arrays, whose evaluations are shared out by pixels (k_mix_encode_chunks).
+// rANS lanes under a mixture of K logistic laws per subpixel (gfx950): an encoder whose evaluations are shared out by
+// pixels (k_mix_encode_chunks), a decoder of many lanes with a thread per lane (k_mix_decode) and one of few with a row of
+// 16 threads per lane (k_mix_decode_rows).  The first two want arrays on 4-byte boundaries and are built for every
+// component count K; arrays that are not there go a thread per lane through general kernels (k_mix_encode, k_mix_decode<0>).
 //
 // Sec. 2 of arXiv 2206.05279 names this workload (a dynamic rANS coder fed a mixture of ten
 // logistic laws per symbol) as what holds earlier learned codecs near 1 MB/s; the coder itself is
@@ -8,15 +10,14 @@
 // single-law edge CDF, and C(k) = k + floor(F(k) (2^M - 256) / 2^24); the channel conditioning
 // of Sec. 3.1 eqs. (3)-(4) shifts every component's mean with that component's own innovations.
 //
-// In the general kernels K is a run-time value, so nothing per component lives in registers (the
-// kernels built for one K keep the channel's components and the pixel's weights there; they are
-// the same kernels with the component count as a template argument).  A thread first copies
+// In the general kernels K is a run-time value, so nothing per component lives in registers.  A thread first copies
 // the 7 K 16-bit parameters of a pixel into its own LDS slots in one burst of loads (every
 // 128-byte line of the arrays is then asked for by one or two bursts rather than by dozens of
 // separate loads spread over the pixel's work), then, before a subpixel is coded, turns the
 // channel's components into {shifted mean, 1/scale} pairs in further slots; every evaluation of
-// C(k) walks those.  All slots are [index][thread] arrays of dwords, so a wavefront's accesses
-// are conflict free.  The 16-bit words go through the thread-per-lane scratch layout and packer.
+// C(k) walks those.  The thread-per-lane decoder built for one K has the raw parameters in such slots, the channel's
+// components and the pixel's weights in registers.  All slots are [index][thread] arrays of dwords, so a wavefront's
+// accesses are conflict free.  The 16-bit words go through the thread-per-lane scratch layout and packer.
 #pragma once
 
 #include "pilc_lane_kernels.hpp"
@@ -125,25 +126,13 @@ struct PixelBytes {
     }
 };
 
-// The pixel's parameters into the slots; false if its weights do not sum to 2^15.
+// The pixel's parameters into the slots of a general kernel; false if its weights do not sum to 2^15.
 __device__ __forceinline__ bool mix_load_pixel(const MixArgs &a, uint32_t p, const MixSlots &s)
 {
     const size_t px = (size_t)p * 3u * a.k;
-    if ((a.k & 1u) == 0u && ((reinterpret_cast<uintptr_t>(a.mu) | reinterpret_cast<uintptr_t>(a.ls) |
-                              reinterpret_cast<uintptr_t>(a.weight)) & 3u) == 0u) {
-        // even K: a pixel's block of every array is a whole number of aligned dwords
-        const uint32_t *gm = reinterpret_cast<const uint32_t *>(a.mu + px);
-        const uint32_t *gl = reinterpret_cast<const uint32_t *>(a.ls + px);
-        const uint32_t *gw = reinterpret_cast<const uint32_t *>(a.weight + (size_t)p * a.k);
-        const uint32_t n3 = 3u * a.k / 2u, n1 = a.k / 2u;
-        for (uint32_t i = 0; i < n3; ++i) s.dword(s.raw_mu + i) = gm[i];
-        for (uint32_t i = 0; i < n3; ++i) s.dword(s.raw_ls + i) = gl[i];
-        for (uint32_t i = 0; i < n1; ++i) s.dword(s.raw_w + i) = gw[i];
-    } else {
-        for (uint32_t e = 0; e < 3u * a.k; ++e) s.set_half(s.raw_mu, e, a.mu[px + e]);
-        for (uint32_t e = 0; e < 3u * a.k; ++e) s.set_half(s.raw_ls, e, (uint16_t)a.ls[px + e]);
-        for (uint32_t e = 0; e < a.k; ++e) s.set_half(s.raw_w, e, a.weight[(size_t)p * a.k + e]);
-    }
+    for (uint32_t e = 0; e < 3u * a.k; ++e) s.set_half(s.raw_mu, e, a.mu[px + e]);
+    for (uint32_t e = 0; e < 3u * a.k; ++e) s.set_half(s.raw_ls, e, (uint16_t)a.ls[px + e]);
+    for (uint32_t e = 0; e < a.k; ++e) s.set_half(s.raw_w, e, a.weight[(size_t)p * a.k + e]);
     uint32_t sum = 0;
     for (uint32_t j = 0; j < a.k; ++j) sum += s.half(s.raw_w, j);
     return sum == (1u << 15);
@@ -152,59 +141,42 @@ __device__ __forceinline__ bool mix_load_pixel(const MixArgs &a, uint32_t p, con
 // Dword-aligned arrays: a pixel's raw parameters lie in ceil(3 K / 2) + ceil(3 K / 2) + ceil(K / 2)
 // aligned dwords (for odd K the blocks of every other pixel start on the upper half of a dword and
 // end on a lower half: the same number of dwords, one halfword of a neighbour at either end), and
-// the kernels keep the NEXT pixel's dwords in registers while they work on the current one, so that
+// the decoder keeps the NEXT pixel's dwords in registers while it works on the current one, so that
 // the loads have a pixel's worth of arithmetic to arrive in.
-// kK is the component count a kernel was built for, 0 for the kernels that take it at run time
-// (those run ahead for even K only).
 template <int kK> struct MixAhead {
-    static constexpr int kComp = kK > 0 ? kK : kMixMaxComp;
-    static constexpr int kMu = (3 * kComp + 1) / 2, kW = (kComp + 1) / 2;
+    static constexpr int kMu = (3 * kK + 1) / 2, kW = (kK + 1) / 2;
     uint32_t m[kMu], l[kMu], w[kW];
 };
 
-// The components of the channel being coded, in registers: only in the kernels built for one K,
-// where every index into these arrays is a compile-time constant.
+// The components of the channel being coded, in registers: every index into these arrays is a compile-time constant.
 template <int kK> struct MixRegs {
-    EdgeLaw law[kK > 0 ? kK : 1];     // position of an edge under the component
-    uint32_t w[kK > 0 ? kK : 1];      // the pixel's weights
+    EdgeLaw law[kK];     // position of an edge under the component
+    uint32_t w[kK];      // the pixel's weights
 };
-
-__device__ __forceinline__ bool mix_can_run_ahead(const MixArgs &a)
-{
-    return (a.k & 1u) == 0u && ((reinterpret_cast<uintptr_t>(a.mu) | reinterpret_cast<uintptr_t>(a.ls) |
-                                 reinterpret_cast<uintptr_t>(a.weight)) & 3u) == 0u;
-}
 
 template <int kK>
 __device__ __forceinline__ void mix_fetch_ahead(const MixArgs &a, uint32_t p, MixAhead<kK> &r)
 {
-    const uint32_t k = kK > 0 ? (uint32_t)kK : a.k;
-    const size_t px = (size_t)p * 3u * k;  // in halfwords: the aligned dwords from px / 2 on
+    const size_t px = (size_t)p * (3u * kK);  // in halfwords: the aligned dwords from px / 2 on
     const uint32_t *gm = reinterpret_cast<const uint32_t *>(a.mu) + (px >> 1);
     const uint32_t *gl = reinterpret_cast<const uint32_t *>(a.ls) + (px >> 1);
-    const uint32_t *gw = reinterpret_cast<const uint32_t *>(a.weight) + (((size_t)p * k) >> 1);
-    const uint32_t n3 = (3u * k + 1u) / 2u, n1 = (k + 1u) / 2u;
+    const uint32_t *gw = reinterpret_cast<const uint32_t *>(a.weight) + (((size_t)p * kK) >> 1);
 #pragma unroll
-    for (int i = 0; i < MixAhead<kK>::kMu; ++i)
-        if ((uint32_t)i < n3) r.m[i] = gm[i];
+    for (int i = 0; i < MixAhead<kK>::kMu; ++i) r.m[i] = gm[i];
 #pragma unroll
-    for (int i = 0; i < MixAhead<kK>::kMu; ++i)
-        if ((uint32_t)i < n3) r.l[i] = gl[i];
+    for (int i = 0; i < MixAhead<kK>::kMu; ++i) r.l[i] = gl[i];
 #pragma unroll
-    for (int i = 0; i < MixAhead<kK>::kW; ++i)
-        if ((uint32_t)i < n1) r.w[i] = gw[i];
+    for (int i = 0; i < MixAhead<kK>::kW; ++i) r.w[i] = gw[i];
 }
 
-// The fetched pixel into the slots, its weights into `regs` in the kernels built for one K; false
-// if the weights do not sum to 2^15.  `upper`: the pixel's blocks
-// start on the upper half of the first dword fetched (odd K, every other pixel) and are moved down
+// The fetched pixel into the slots, its weights into `regs`; false if the weights do not sum to 2^15.  `upper`: the
+// pixel's blocks start on the upper half of the first dword fetched (odd K, every other pixel) and are moved down
 // by a halfword on the way.
 template <int kK>
 __device__ __forceinline__ bool mix_store_ahead(const MixAhead<kK> &r, const MixSlots &s, MixRegs<kK> &regs,
                                                 bool upper)
 {
     constexpr bool kOdd = kK % 2 != 0;
-    const uint32_t n3 = (3u * s.k + 1u) / 2u, n1 = (s.k + 1u) / 2u;
     auto lowered = [&](const uint32_t *d, int i, int n) {  // dword i of the block, from the n fetched
         if constexpr (!kOdd) return d[i];
         const uint32_t next = i + 1 < n ? d[i + 1] : 0u;
@@ -212,27 +184,19 @@ __device__ __forceinline__ bool mix_store_ahead(const MixAhead<kK> &r, const Mix
     };
     uint32_t sum = 0;
 #pragma unroll
-    for (int i = 0; i < MixAhead<kK>::kMu; ++i)
-        if ((uint32_t)i < n3) s.dword(s.raw_mu + i) = lowered(r.m, i, MixAhead<kK>::kMu);
+    for (int i = 0; i < MixAhead<kK>::kMu; ++i) s.dword(s.raw_mu + i) = lowered(r.m, i, MixAhead<kK>::kMu);
 #pragma unroll
-    for (int i = 0; i < MixAhead<kK>::kMu; ++i)
-        if ((uint32_t)i < n3) s.dword(s.raw_ls + i) = lowered(r.l, i, MixAhead<kK>::kMu);
+    for (int i = 0; i < MixAhead<kK>::kMu; ++i) s.dword(s.raw_ls + i) = lowered(r.l, i, MixAhead<kK>::kMu);
 #pragma unroll
-    for (int i = 0; i < MixAhead<kK>::kW; ++i)
-        if ((uint32_t)i < n1) {
-            const uint32_t w2 = lowered(r.w, i, MixAhead<kK>::kW);
-            if constexpr (kK > 0) {
-                regs.w[2 * i] = w2 & 0xFFFFu;
-                sum += w2 & 0xFFFFu;
-                if (2 * i + 1 < kK) {
-                    regs.w[2 * i + 1] = w2 >> 16;
-                    sum += w2 >> 16;
-                }
-            } else {
-                s.dword(s.raw_w + i) = w2;
-                sum += (w2 & 0xFFFFu) + (w2 >> 16);
-            }
+    for (int i = 0; i < MixAhead<kK>::kW; ++i) {
+        const uint32_t w2 = lowered(r.w, i, MixAhead<kK>::kW);
+        regs.w[2 * i] = w2 & 0xFFFFu;
+        sum += w2 & 0xFFFFu;
+        if (2 * i + 1 < kK) {
+            regs.w[2 * i + 1] = w2 >> 16;
+            sum += w2 >> 16;
         }
+    }
     return sum == (1u << 15);
 }
 
@@ -262,7 +226,6 @@ template <int kK>
 __device__ __forceinline__ void mix_load_channel(const MixSlots &s, MixRegs<kK> &regs, int ch, int x_r,
                                                  int x_g, int a_gr, int a_br, int a_bg, const LdsTables &tab)
 {
-    static_assert(kK > 0, "built for one component count");
     if constexpr (kK % 2 != 0) {  // a channel's block starts on either half of a dword: halfword reads
         // (the scales before the means: the branches on the channel below would part their table reads, and every
         // component would wait for its own; encode of 3000 images of 64 x 64 at K = 13 1912 -> 1748 us)
@@ -600,11 +563,14 @@ struct ByteRun {
     }
 };
 
-template <int kK>  // as k_mix_encode
+// A thread per lane.  kK > 0: built for that many components (arrays on 4-byte boundaries: the host checks), which live
+// in registers; 0: any number, in LDS, and arrays at any address.
+template <int kK>
 __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, mix_waves(kK)))) void k_mix_decode(
     Geo g, const uint8_t *__restrict__ coded, unsigned long long coded_bytes, MixArgs a, uint8_t *__restrict__ out,
     Report *__restrict__ report)
 {
+    constexpr int kBuilt = kK > 0 ? kK : 1;
     __shared__ LdsTables tab;
     __shared__ int s_state;
     __shared__ unsigned long long s_payload;
@@ -644,12 +610,12 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
     ByteRun run;
     run.begin(0);
     uint32_t p_next = 0xFFFFFFFFu;  // the pixel that would continue the current run of bytes
-    const bool ahead = kK > 0 || mix_can_run_ahead(a);
-    MixAhead<kK> pre;
-    MixRegs<kK> regs;
+    MixAhead<kBuilt> pre;  // (of the kernels built for one K, as are the registers)
+    MixRegs<kBuilt> regs;
     uint32_t im_now = 0xFFFFFFFFu;
     int a_gr = 0, a_br = 0, a_bg = 0;
-    if (ahead && sh.npx != 0u) mix_fetch_ahead(a, lane_pixel(g, sh, 0u), pre);
+    if constexpr (kK > 0)
+        if (sh.npx != 0u) mix_fetch_ahead(a, lane_pixel(g, sh, 0u), pre);
     for (uint32_t t = 0; t < sh.npx; ++t) {
         const uint32_t p = lane_pixel(g, sh, t);
         if (p != p_next) {  // a new row of the lane
@@ -662,7 +628,7 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
             im_now = im;
             a_gr = a.coef[3 * im]; a_br = a.coef[3 * im + 1]; a_bg = a.coef[3 * im + 2];
         }
-        if (ahead) {
+        if constexpr (kK > 0) {
             ok = mix_store_ahead(pre, slots, regs, (kK & 1) != 0 && (p & 1u) != 0u) && ok;
             if (t + 1u < sh.npx) mix_fetch_ahead(a, lane_pixel(g, sh, t + 1u), pre);
         } else {
