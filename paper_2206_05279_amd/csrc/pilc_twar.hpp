@@ -340,9 +340,10 @@ struct Diag {
     uint32_t blocks;            // of 16 columns, ceil((w + 63) / 16): the last thread has to get through its row
     unsigned long long strip0;  // this launch: strips from strip0 on, bands band0 .. band0 + bands - 1
     uint32_t strips, band0, bands;
-    uint32_t *words;            // [strip, band][block][16]: red values of a band's last row, the mark above each; null: one band
+    // of bands that run together (k_twar_inverse_bands):
+    uint32_t *words;            // [strip, band][block][16]: red values of a band's last row, the mark above each
     uint32_t mark;              // of this launch, 1 .. 255
-    uint32_t *ticket;           // null: one band
+    uint32_t *ticket;
     uint32_t first_ticket;      // what it stands at before this launch
     uint32_t *abort_word;
     Report *report;
@@ -905,12 +906,9 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_bands(TwarK p, Diag a, 
     __shared__ u32x4 green[2][4][64];       // [block mod 2][four of its values][row]
     __shared__ u32x4 carry[kDiagCarry][4];  // [block + 4, mod kDiagCarry][four of them]: red of the row above the band
     __shared__ uint32_t s_id;
-    uint32_t id = blockIdx.x;
-    if (a.ticket != nullptr) {
-        if (threadIdx.x == 0u) s_id = atomicAdd(a.ticket, 1u) - a.first_ticket;
-        __syncthreads();
-        id = s_id;
-    }
+    if (threadIdx.x == 0u) s_id = atomicAdd(a.ticket, 1u) - a.first_ticket;
+    __syncthreads();
+    const uint32_t id = s_id;
     const uint32_t in_launch = id / a.strips, in_strip = id - in_launch * a.strips, band = a.band0 + in_launch;
     const unsigned long long strip = a.strip0 + in_strip;
     const uint32_t place = in_strip * a.bands + in_launch;  // of this band's words
@@ -931,7 +929,7 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_bands(TwarK p, Diag a, 
                         diag_bias(p.bias[0])};
         // (in vector registers: from scalar ones they would be copied at every use)
         asm volatile("" : "+v"(w.left), "+v"(w.bias));
-        const bool passes_on = a.words != nullptr && a.withhold == 0u && band + 1u < a.band0 + a.bands;
+        const bool passes_on = a.withhold == 0u && band + 1u < a.band0 + a.bands;
         uint32_t *out = a.words + (size_t)place * (16u * a.blocks);
         const __amdgpu_buffer_rsrc_t out_buffer =
             __builtin_amdgcn_make_buffer_rsrc(out, 0, 64 * blocks, 0x00020000);
@@ -1369,7 +1367,6 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
                              uint8_t *img_dev, hipStream_t stream, Timer &timer)
 {
     Diag a = {};
-    a.mark = 1u;  // (0 is what a word that is not there has)
     a.h = h;
     a.w = w;
     a.rows = (unsigned long long)n * h;
@@ -1393,6 +1390,7 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
     a.withhold = (uint32_t)g_one_pass_withhold.load(std::memory_order_relaxed);
     if (set) {
         report.emplace(&set->report, stream, true);
+        a.words = set->words;
         a.ticket = &set->ticket;
         a.abort_word = &set->abort_word;
         a.report = report->dev();
@@ -1404,7 +1402,6 @@ static int twar_inverse_diag(uint32_t n, uint32_t h, uint32_t w, const uint8_t *
             a.strips = here;
             a.band0 = b;
             a.bands = std::min(together, bands - b);
-            a.words = a.bands > 1u ? set->words : nullptr;
             if (a.bands > 1u) {
                 lease.next_launch(here * a.bands, stream, &a.mark, &a.first_ticket);
                 const uint32_t lds = bands_alone_on_a_unit(here, a.bands, a.blocks) ? kDiagAloneBytes : kDiagRawBytes;
