@@ -484,6 +484,107 @@ __device__ __forceinline__ void interval_barrier()
     __syncthreads();
 }
 
+// The wavefront that brings the windows of residuals from memory to LDS, and the one that takes the pixels back from there.
+// `raw`: [slot][third of the window][row], kSlots of them; `lag`: intervals from a block's turn in red to its store.
+template <int kSlots>
+__device__ __forceinline__ void fetch_windows(const Diag &a, const uint8_t *__restrict__ res, u32x4 (*raw)[3][64],
+                                              unsigned long long strip, uint32_t band_row0, uint32_t lane, int times)
+{
+    // the windows of 64 rows move as 192 pieces of 16 bytes, three neighbouring threads taking the
+    // 48 bytes of a row.  An address outside the array is moved inside; that brings the wrong
+    // bytes only where none is used, or at the end of the array's last row, where they are put right.
+    const long long last = (long long)(a.rows * a.w * 3ull) - 16;
+    long long at[3];
+    uint32_t put[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;  // r = k / 3 for k < 192
+        const unsigned long long row = strip * a.strip_rows + band_row0 + r;
+        at[i] = (long long)(row * a.w * 3ull) + 16ll * part - 3ll * r;  // block 0
+        put[i] = part * 64u + r;
+    }
+    u32x4 ahead[kDiagAhead][3];
+#pragma unroll
+    for (int j = 0; j < kDiagAhead; ++j)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) ahead[j][i] = u32x4{};
+    // Without a condition on anything, so that the number of loads under way is known when one is
+    // waited for: what is put before the first block or after the last is not looked at (a
+    // slot is written again no sooner than the interval after its pixels have been stored).
+    uint32_t slot = kSlots - kDiagAhead;  // of block -kDiagAhead
+    static_assert(kSlots >= kDiagAhead, "");
+    for (int time0 = 0; time0 < times; time0 += kDiagAhead) {
+#pragma unroll
+        for (int j = 0; j < kDiagAhead; ++j) {
+            interval_barrier();
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                (&raw[slot][0][0])[put[i]] = ahead[j][i];
+                const long long over = at[i] - 48 * kDiagAhead - last;
+                if (over > 0 && over < 16) {  // the array's end is inside the piece: a few pieces near it
+                    uint8_t *q = reinterpret_cast<uint8_t *>(&raw[slot][0][0] + put[i]);
+#pragma unroll 1
+                    for (int k = 0; k < 16 - (int)over; ++k) q[k] = q[k + (int)over];
+                }
+            }
+            slot = slot + 1u == (uint32_t)kSlots ? 0u : slot + 1u;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const long long from = min(max(at[i], 0ll), last);
+                ahead[j][i] = *reinterpret_cast<const u32x4_any *>(res + from);
+                at[i] += 48;
+            }
+        }
+    }
+}
+
+template <int kSlots>
+__device__ __forceinline__ void store_windows(const Diag &a, uint8_t *__restrict__ img, const u32x4 (*raw)[3][64],
+                                              unsigned long long strip, uint32_t band_row0, uint32_t lane, int times,
+                                              int lead, int lag)
+{
+    const int blocks = (int)a.blocks;
+    const int row_bytes = (int)(3u * a.w);
+    uint8_t *to[3];
+    int in_row[3];  // where the piece lies in its row
+    uint32_t get[3];
+    bool have[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;
+        const uint32_t u = band_row0 + r;
+        const unsigned long long row = strip * a.strip_rows + u;
+        have[i] = u < a.strip_rows && row < a.rows;
+        in_row[i] = 16 * (int)part - 3 * (int)r;
+        to[i] = img + (long long)((have[i] ? row : 0ull) * a.w * 3ull) + in_row[i];
+        get[i] = part * 64u + r;
+    }
+    uint32_t slot = 0;
+    for (int time = 0; time < times; ++time) {
+        interval_barrier();
+        const int b = time - lead - lag;
+        if (b < 0 || b >= blocks) continue;
+        u32x4 v[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = (&raw[slot][0][0])[get[i]];
+        slot = slot + 1u == (uint32_t)kSlots ? 0u : slot + 1u;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int first = in_row[i] + 48 * b;
+            uint8_t *q = to[i] + 48ll * b;
+            if (!have[i]) continue;
+            if (first >= 0 && first + 16 <= row_bytes) {
+                *reinterpret_cast<u32x4_any *>(q) = v[i];
+            } else if (first > -16 && first < row_bytes) {  // an end of the row
+                const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    if (first + k >= 0 && first + k < row_bytes) q[k] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
+            }
+        }
+    }
+}
+
 // A band of each strip, a workgroup each; the row above, if any, is in the image.  25,088 bytes of LDS and 80 registers: four workgroups
 // share a compute unit, which is what batches of many strips live on.
 __global__ __launch_bounds__(64 * 6) void k_twar_inverse_strips(TwarK p, Diag a, const uint8_t *__restrict__ res,
@@ -623,93 +724,10 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_strips(TwarK p, Diag a,
             channel(std::false_type{});
         else
             channel(std::true_type{});
-    } else if (role == 3u) {  // ---- residuals from memory to LDS
-        // the windows of 64 rows move as 192 pieces of 16 bytes, three neighbouring threads taking the
-        // 48 bytes of a row.  An address outside the array is moved inside; that brings the wrong
-        // bytes only where none is used, or at the end of the array's last row, where they are put right.
-        const long long last = (long long)(a.rows * a.w * 3ull) - 16;
-        long long at[3];
-        uint32_t put[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;  // r = k / 3 for k < 192
-            const unsigned long long row = strip * a.strip_rows + band_row0 + r;
-            at[i] = (long long)(row * a.w * 3ull) + 16ll * part - 3ll * r;  // block 0
-            put[i] = part * 64u + r;
-        }
-        u32x4 ahead[kDiagAhead][3];
-#pragma unroll
-        for (int j = 0; j < kDiagAhead; ++j)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) ahead[j][i] = u32x4{};
-        // Without a condition on anything, so that the number of loads under way is known when one is
-        // waited for: what is put before the first block or after the last is not looked at (a
-        // slot is written again no sooner than the interval after its pixels have been stored).
-        uint32_t slot = kStripSlots - kDiagAhead;  // of block -kDiagAhead
-        static_assert(kStripSlots >= kDiagAhead, "");
-        for (int time0 = 0; time0 < times; time0 += kDiagAhead) {
-#pragma unroll
-            for (int j = 0; j < kDiagAhead; ++j) {
-                interval_barrier();
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    (&raw[slot][0][0])[put[i]] = ahead[j][i];
-                    const long long over = at[i] - 48 * kDiagAhead - last;
-                    if (over > 0 && over < 16) {  // the array's end is inside the piece: a few pieces near it
-                        uint8_t *q = reinterpret_cast<uint8_t *>(&raw[slot][0][0] + put[i]);
-#pragma unroll 1
-                        for (int k = 0; k < 16 - (int)over; ++k) q[k] = q[k + (int)over];
-                    }
-                }
-                slot = slot + 1u == (uint32_t)kStripSlots ? 0u : slot + 1u;
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const long long from = min(max(at[i], 0ll), last);
-                    ahead[j][i] = *reinterpret_cast<const u32x4_any *>(res + from);
-                    at[i] += 48;
-                }
-            }
-        }
-    } else if (role == 4u) {  // ---- pixels from LDS to memory
-        const int row_bytes = (int)(3u * a.w);
-        uint8_t *to[3];
-        int in_row[3];  // where the piece lies in its row
-        uint32_t get[3];
-        bool have[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;
-            const uint32_t u = band_row0 + r;
-            const unsigned long long row = strip * a.strip_rows + u;
-            have[i] = u < a.strip_rows && row < a.rows;
-            in_row[i] = 16 * (int)part - 3 * (int)r;
-            to[i] = img + (long long)((have[i] ? row : 0ull) * a.w * 3ull) + in_row[i];
-            get[i] = part * 64u + r;
-        }
-        uint32_t slot = 0;
-        for (int time = 0; time < times; ++time) {
-            interval_barrier();
-            const int b = time - lead - 3;
-            if (b < 0 || b >= blocks) continue;
-            u32x4 v[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) v[i] = (&raw[slot][0][0])[get[i]];
-            slot = slot + 1u == (uint32_t)kStripSlots ? 0u : slot + 1u;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int first = in_row[i] + 48 * b;
-                uint8_t *q = to[i] + 48ll * b;
-                if (!have[i]) continue;
-                if (first >= 0 && first + 16 <= row_bytes) {
-                    *reinterpret_cast<u32x4_any *>(q) = v[i];
-                } else if (first > -16 && first < row_bytes) {  // an end of the row
-                    const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-                    for (int k = 0; k < 16; ++k)
-                        if (first + k >= 0 && first + k < row_bytes) q[k] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
-                }
-            }
-        }
+    } else if (role == 3u) {
+        fetch_windows<kStripSlots>(a, res, raw, strip, band_row0, lane, times);
+    } else if (role == 4u) {
+        store_windows<kStripSlots>(a, img, raw, strip, band_row0, lane, times, lead, 3);
     } else {  // ---- red of the row above the band, which is in the image
         // Block q, word k of the band above holds columns 16 q + 4 k - 63 .. + 3 of its last row.  Red's block
         // b needs blocks b + 3 and b + 4.  Threads 0 .. 31 fetch eight blocks every four intervals, an interval or more ahead.
@@ -759,7 +777,7 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_strips(TwarK p, Diag a,
 //
 // `MASK`: in the first four blocks a thread gets through the column before its row's first, where its
 // value has to read as zero; a bit that moves up by one thread a step says whose turn it is.
-#define PILC_RED_STEP(X, L, U, UL, E, B, MASK)                                                       \
+#define PILC_BAND_RED_STEP(X, L, U, UL, E, B, MASK)                                                       \
     "v_mad_i32_i24 %[t], " UL ", %[w_upleft], %[bias]\n"                                            \
     "v_mad_i32_i24 %[t], " L ", %[w_left], %[t]\n"                                                  \
     "v_mov_b32_dpp " U ", " L " wave_shr:1 row_mask:0xf bank_mask:0xf\n"                            \
@@ -767,7 +785,7 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_strips(TwarK p, Diag a,
     "v_med3_i32 %[t], %[t], 0, %[most]\n"                                                           \
     "v_add_u32_sdwa " X ", %[t], %[" E "] dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:WORD_1 src1_sel:BYTE_" #B "\n" MASK(X)
 // Green and blue, five instructions a step, from the channel decoded before.
-#define PILC_ROW_STEP(X, L, V, VL, E, B, MASK)                                                       \
+#define PILC_BAND_ROW_STEP(X, L, V, VL, E, B, MASK)                                                       \
     "v_mad_i32_i24 %[t], %[" V "], %[w_before], %[bias]\n"                                          \
     "v_mad_i32_i24 %[t], %[" VL "], %[w_left_before], %[t]\n"                                       \
     "v_mad_i32_i24 %[t], " L ", %[w_left], %[t]\n"                                               \
@@ -784,22 +802,22 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_strips(TwarK p, Diag a,
 struct RedWeights {
     int upleft, up, left, bias;
 };
-#define PILC_RED_FOUR(MASK, X0, X1, X2, X3, L, U0, U1, U2, U3)                                       \
-    PILC_RED_STEP(X0, L, U0, "%[ul]", "e0", 0, MASK)                                                \
-    PILC_RED_STEP(X1, X0, U1, U0, "e0", 3, MASK)                                                    \
-    PILC_RED_STEP(X2, X1, U2, U1, "e1", 2, MASK)                                                    \
-    PILC_RED_STEP(X3, X2, U3, U2, "e2", 1, MASK)
+#define PILC_BAND_RED_FOUR(MASK, X0, X1, X2, X3, L, U0, U1, U2, U3)                                       \
+    PILC_BAND_RED_STEP(X0, L, U0, "%[ul]", "e0", 0, MASK)                                                \
+    PILC_BAND_RED_STEP(X1, X0, U1, U0, "e0", 3, MASK)                                                    \
+    PILC_BAND_RED_STEP(X2, X1, U2, U1, "e1", 2, MASK)                                                    \
+    PILC_BAND_RED_STEP(X3, X2, U3, U2, "e2", 1, MASK)
 #define PILC_RED_INPUTS                                                                              \
     [ul] "v"(last_up), [e0] "v"(e0), [e1] "v"(e1), [e2] "v"(e2), [w_upleft] "v"(w.upleft), [w_up] "v"(w.up),      \
         [w_left] "v"(w.left), [bias] "v"(w.bias), [most] "v"(0xFFFFFF)
 #define PILC_RED_GROUP(G, XQ, PQ, UQ, ...)                                                           \
     if (kG == G) {                                                                                  \
         if (kFirst)                                                                                 \
-            asm(PILC_RED_FOUR(PILC_MASK, __VA_ARGS__)                                               \
+            asm(PILC_BAND_RED_FOUR(PILC_MASK, __VA_ARGS__)                                               \
                 : "+{" XQ "}"(x[G]), "+{" UQ "}"(above), [t] "=&v"(t), [mask] "+s"(mask)            \
                 : "{" PQ "}"(x[(G + 3) & 3]), PILC_RED_INPUTS, [zero] "v"(zero) : "scc");           \
         else                                                                                        \
-            asm(PILC_RED_FOUR(PILC_NO_MASK, __VA_ARGS__)                                            \
+            asm(PILC_BAND_RED_FOUR(PILC_NO_MASK, __VA_ARGS__)                                            \
                 : "+{" XQ "}"(x[G]), "+{" UQ "}"(above), [t] "=&v"(t)                               \
                 : "{" PQ "}"(x[(G + 3) & 3]), PILC_RED_INPUTS);                                     \
     }
@@ -820,21 +838,21 @@ __device__ __forceinline__ void red_four(const RedWeights &w, u32x4 (&x)[4], u32
 }
 #undef PILC_RED_GROUP
 #undef PILC_RED_INPUTS
-#undef PILC_RED_FOUR
+#undef PILC_BAND_RED_FOUR
 
 struct RowWeights {
     int left, left_before, before, bias;
 };
 #define PILC_GREEN_FOUR(MASK, X0, X1, X2, X3, L)                                                     \
-    PILC_ROW_STEP(X0, L, "v0", "vl", "e0", 1, MASK)                                                 \
-    PILC_ROW_STEP(X1, X0, "v1", "v0", "e1", 0, MASK)                                                \
-    PILC_ROW_STEP(X2, X1, "v2", "v1", "e1", 3, MASK)                                                \
-    PILC_ROW_STEP(X3, X2, "v3", "v2", "e2", 2, MASK)
+    PILC_BAND_ROW_STEP(X0, L, "v0", "vl", "e0", 1, MASK)                                                 \
+    PILC_BAND_ROW_STEP(X1, X0, "v1", "v0", "e1", 0, MASK)                                                \
+    PILC_BAND_ROW_STEP(X2, X1, "v2", "v1", "e1", 3, MASK)                                                \
+    PILC_BAND_ROW_STEP(X3, X2, "v3", "v2", "e2", 2, MASK)
 #define PILC_BLUE_FOUR(MASK, X0, X1, X2, X3, L)                                                      \
-    PILC_ROW_STEP(X0, L, "v0", "vl", "e0", 2, MASK)                                                 \
-    PILC_ROW_STEP(X1, X0, "v1", "v0", "e1", 1, MASK)                                                \
-    PILC_ROW_STEP(X2, X1, "v2", "v1", "e2", 0, MASK)                                                \
-    PILC_ROW_STEP(X3, X2, "v3", "v2", "e2", 3, MASK)
+    PILC_BAND_ROW_STEP(X0, L, "v0", "vl", "e0", 2, MASK)                                                 \
+    PILC_BAND_ROW_STEP(X1, X0, "v1", "v0", "e1", 1, MASK)                                                \
+    PILC_BAND_ROW_STEP(X2, X1, "v2", "v1", "e2", 0, MASK)                                                \
+    PILC_BAND_ROW_STEP(X3, X2, "v3", "v2", "e2", 3, MASK)
 #define PILC_ROW_INPUTS                                                                              \
     [v0] "v"(v.x), [v1] "v"(v.y), [v2] "v"(v.z), [v3] "v"(v.w), [vl] "v"(vl), [e0] "v"(e0), [e1] "v"(e1), [e2] "v"(e2), \
         [w_left] "v"(w.left), [w_left_before] "v"(w.left_before), [w_before] "v"(w.before), [bias] "v"(w.bias),         \
@@ -872,8 +890,8 @@ __device__ __forceinline__ void row_four(const RowWeights &w, u32x4 (&x)[4], con
 #undef PILC_GREEN_FOUR
 #undef PILC_BLUE_FOUR
 #undef PILC_ROW_INPUTS
-#undef PILC_RED_STEP
-#undef PILC_ROW_STEP
+#undef PILC_BAND_RED_STEP
+#undef PILC_BAND_ROW_STEP
 #undef PILC_MASK
 #undef PILC_NO_MASK
 
@@ -1048,93 +1066,10 @@ __global__ __launch_bounds__(64 * 6) void k_twar_inverse_bands(TwarK p, Diag a, 
             channel(std::false_type{});
         else
             channel(std::true_type{});
-    } else if (role == 3u) {  // ---- residuals from memory to LDS
-        // the windows of 64 rows move as 192 pieces of 16 bytes, three neighbouring threads taking the
-        // 48 bytes of a row.  An address outside the array is moved inside; that brings the wrong
-        // bytes only where none is used, or at the end of the array's last row, where they are put right.
-        const long long last = (long long)(a.rows * a.w * 3ull) - 16;
-        long long at[3];
-        uint32_t put[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;  // r = k / 3 for k < 192
-            const unsigned long long row = strip * a.strip_rows + band_row0 + r;
-            at[i] = (long long)(row * a.w * 3ull) + 16ll * part - 3ll * r;  // block 0
-            put[i] = part * 64u + r;
-        }
-        u32x4 ahead[kDiagAhead][3];
-#pragma unroll
-        for (int j = 0; j < kDiagAhead; ++j)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) ahead[j][i] = u32x4{};
-        // Without a condition on anything, so that the number of loads under way is known when one is
-        // waited for: what is put before the first block or after the last is not looked at (a
-        // slot is written again no sooner than the interval after its pixels have been stored).
-        uint32_t slot = kDiagSlots - kDiagAhead;  // of block -kDiagAhead
-        static_assert(kDiagSlots >= kDiagAhead, "");
-        for (int time0 = 0; time0 < times; time0 += kDiagAhead) {
-#pragma unroll
-            for (int j = 0; j < kDiagAhead; ++j) {
-                interval_barrier();
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    (&raw[slot][0][0])[put[i]] = ahead[j][i];
-                    const long long over = at[i] - 48 * kDiagAhead - last;
-                    if (over > 0 && over < 16) {  // the array's end is inside the piece: a few pieces near it
-                        uint8_t *q = reinterpret_cast<uint8_t *>(&raw[slot][0][0] + put[i]);
-#pragma unroll 1
-                        for (int k = 0; k < 16 - (int)over; ++k) q[k] = q[k + (int)over];
-                    }
-                }
-                slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const long long from = min(max(at[i], 0ll), last);
-                    ahead[j][i] = *reinterpret_cast<const u32x4_any *>(res + from);
-                    at[i] += 48;
-                }
-            }
-        }
-    } else if (role == 4u) {  // ---- pixels from LDS to memory
-        const int row_bytes = (int)(3u * a.w);
-        uint8_t *to[3];
-        int in_row[3];  // where the piece lies in its row
-        uint32_t get[3];
-        bool have[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const uint32_t k = 64u * i + lane, r = (k * 171u) >> 9, part = k - 3u * r;
-            const uint32_t u = band_row0 + r;
-            const unsigned long long row = strip * a.strip_rows + u;
-            have[i] = u < a.strip_rows && row < a.rows;
-            in_row[i] = 16 * (int)part - 3 * (int)r;
-            to[i] = img + (long long)((have[i] ? row : 0ull) * a.w * 3ull) + in_row[i];
-            get[i] = part * 64u + r;
-        }
-        uint32_t slot = 0;
-        for (int time = 0; time < times; ++time) {
-            interval_barrier();
-            const int b = time - lead - 5;
-            if (b < 0 || b >= blocks) continue;
-            u32x4 v[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) v[i] = (&raw[slot][0][0])[get[i]];
-            slot = slot + 1u == (uint32_t)kDiagSlots ? 0u : slot + 1u;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int first = in_row[i] + 48 * b;
-                uint8_t *q = to[i] + 48ll * b;
-                if (!have[i]) continue;
-                if (first >= 0 && first + 16 <= row_bytes) {
-                    *reinterpret_cast<u32x4_any *>(q) = v[i];
-                } else if (first > -16 && first < row_bytes) {  // an end of the row
-                    const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-                    for (int k = 0; k < 16; ++k)
-                        if (first + k >= 0 && first + k < row_bytes) q[k] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
-                }
-            }
-        }
+    } else if (role == 3u) {
+        fetch_windows<kDiagSlots>(a, res, raw, strip, band_row0, lane, times);
+    } else if (role == 4u) {
+        store_windows<kDiagSlots>(a, img, raw, strip, band_row0, lane, times, lead, 5);
     } else {  // ---- the row above the band
         // Block q, value k of the band above is column 16 q + k - 63 of its last row.  Red's block
         // b needs the last two values of block b + 3 and b + 4 but for its last.  A thread asks for two values, the
