@@ -55,3 +55,16 @@ def test_launches_hold_their_words(rules):
     for (strips, bands, columns), (_, each, together, launches) in zip(shapes, rules(shapes)):
         assert 2 <= together <= bands and each * launches >= strips > each * (launches - 1)
         assert each * together * 16 * ((columns + 78) // 16) <= 1 << words
+
+
+def test_lines_on_the_gpu_are_the_lines_of_the_rules(rules):
+    """test_gpu_twar.py's shapes for either side of a line are on either side of one: each has a neighbour in the list, at one
+    dimension, that goes another way."""
+    text = open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "test_gpu_twar.py")).read()
+    shapes = [tuple(map(int, t)) for t in re.findall(r"\((\d+), (\d+), (\d+)\)", text[text.index("LINES = ["):text.index("LINES + [")])]
+    assert len(shapes) >= 50
+    ways = dict(zip(shapes, (r[0] for r in rules([(n, -(-h // 64), w) for n, h, w in shapes]))))
+    for a in shapes:
+        near = [b for b in shapes if b != a and sum(x != y for x, y in zip(a, b)) == 1
+                and max(abs(x - y) for x, y in zip(a, b)) <= 2]
+        assert any(ways[b] != ways[a] for b in near), (a, ways[a])

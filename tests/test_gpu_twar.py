@@ -200,18 +200,24 @@ def test_more_calls_at_once_than_sets_of_words():
     assert not wrong
 
 
-# Bands one at a time or together (two bands of short rows; strips, whole rounds of them, bands times blocks; long rows), and
-# together with a compute unit each or two to one (strips by blocks, bands together, long rows): either side of the lines of
-# csrc/pilc_twar_rules.hpp, odd sizes among them.
-@pytest.mark.parametrize("shape", [(255, 70, 64), (256, 70, 64), (384, 70, 240), (385, 70, 240), (399, 130, 200), (400, 130, 200),
-                                   (400, 130, 401), (400, 130, 418), (429, 130, 418), (430, 130, 418), (520, 520, 98),
-                                   (520, 520, 114), (449, 1500, 34), (450, 1500, 34), (200, 70, 1074), (211, 70, 1073),
-                                   (211, 70, 1074), (230, 200, 881), (230, 200, 882), (112, 450, 50), (113, 450, 50),
-                                   (150, 450, 66), (151, 450, 66), (103, 450, 304), (104, 450, 304), (100, 448, 304),
-                                   (140, 200, 1010), (141, 200, 1010), (141, 200, 1009), (140, 130, 1682), (141, 130, 1682),
-                                   (383, 130, 64), (384, 130, 64), (384, 200, 161), (384, 200, 162), (143, 131, 161),
-                                   (144, 131, 161), (132, 129, 176), (132, 129, 194), (20, 140, 945), (20, 140, 946),
-                                   (1, 65, 1), (1, 127, 17), (1, 193, 33)], ids=lambda s: "x".join(map(str, s)))
+# Either side of the lines of csrc/pilc_twar_rules.hpp that batches of up to some 130 MB reach: one at a time or together (two
+# bands by strips and blocks, by how rounds are filled, long rows), then together with a compute unit each or two to one
+# (eight bands by strips, by strips times blocks, seven bands, long rows of many and of two bands).  The last ones are odd sizes on
+# no line.
+LINES = [(255, 70, 64), (256, 70, 64), (384, 70, 240), (385, 70, 240), (513, 70, 641), (513, 70, 642), (512, 70, 642),
+         (410, 130, 64), (411, 130, 64), (450, 193, 258), (451, 193, 258), (470, 129, 658), (471, 129, 658),
+         (512, 193, 258), (513, 193, 258), (614, 193, 258), (615, 193, 258), (768, 193, 258), (769, 193, 258),
+         (819, 449, 98), (820, 449, 98), (230, 200, 881), (230, 200, 882), (211, 70, 1681), (211, 70, 1682),
+         (210, 70, 1682), (100, 450, 34), (101, 450, 34), (124, 450, 50), (125, 450, 50), (150, 450, 66),
+         (151, 450, 66), (103, 450, 304), (104, 450, 304), (103, 448, 304), (119, 400, 66), (120, 400, 66),
+         (20, 400, 65), (20, 400, 66), (20, 400, 209), (20, 400, 210), (96, 449, 689), (96, 449, 690), (95, 449, 690),
+         (60, 321, 1009), (60, 321, 1010), (140, 200, 1010), (141, 200, 1010), (141, 200, 1009), (140, 130, 1682),
+         (141, 130, 1682), (281, 70, 1521), (281, 70, 1522), (280, 70, 1522)]
+
+
+@pytest.mark.parametrize("shape", LINES + [(383, 130, 64), (384, 130, 64), (384, 200, 161), (384, 200, 162), (143, 131, 161),
+                                           (144, 131, 161), (132, 129, 176), (132, 129, 194), (20, 140, 945), (20, 140, 946),
+                                           (1, 65, 1), (1, 127, 17), (1, 193, 33)], ids=lambda s: "x".join(map(str, s)))
 def test_lines_of_bands(shape):
     print("shape", shape, flush=True)
     rng = np.random.default_rng(sum(shape))
