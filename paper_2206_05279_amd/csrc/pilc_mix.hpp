@@ -307,12 +307,15 @@ __device__ __forceinline__ uint32_t mix_cum_inner(int k, const MixRegs<kK> &regs
     return (uint32_t)k + mass_of((uint32_t)(acc >> 15), scale);
 }
 
-// Wavefronts per SIMD to allocate registers for.  From four components on, LDS lets two workgroups of 256 share a
-// compute unit (one from 13 on), so 256 registers a thread cost nothing.  Left to
-// itself the compiler saved registers for a third or fourth wavefront that cannot come, at K = 6 and 9
-// by taking the table reads of an evaluation one at a time: decode of 512 images of 64 x 64 at K = 6 642
-// us, now 501; of 4096 at K = 9 2178, now 1856.
-constexpr int mix_waves(int k) { return k >= 4 ? 2 : 8; }
+// Most wavefronts on a SIMD of the decoder with a thread a lane.  LDS (the tables and 12 K bytes a thread) has room for five
+// workgroups of 256 on a compute unit at K = 4, four at 5 and 6, three from 7 to 11, two from 12 on.  From five to eight components the
+// decoder has them all that its registers allow: with two against these, lanes of 64 pixels, us: 160,000 lanes K = 5 1069
+// and 807, 6 1068 and 830, 8 1214 and 956; 262,144 lanes 1259 and 1150, 1300 and 1273, 1517 and 1408; 131,072 the same.
+// From nine on two: left to itself the compiler saves registers for a third by taking the table reads of an evaluation
+// one at a time (131,072 lanes of 42 pixels, K = 9, 650 and 738), and from ten on it takes too many for it anyway.  With four
+// components more are in each other's way: 160,000 lanes 860 and, with four, 713, but 262,144 1048 and 1081 (their lines are
+// gone from the L2 before the lanes come back).
+constexpr int mix_waves(int k) { return k <= 3 ? 8 : k == 5 ? 4 : k >= 6 && k <= 8 ? 3 : 2; }
 
 // The encoder for arrays off the 4-byte grid: any K, components in LDS, a thread per lane.
 __global__ __launch_bounds__(kMixThreads) void k_mix_encode(

@@ -59,6 +59,15 @@ def test_wavefronts_of_the_lane_kernels(kernel, waves):
     assert found and all(512 // (-(-v // 8) * 8) >= waves for v in found), found
 
 
+def test_wavefronts_of_the_mixture_decoder():
+    """With up to eight components the decoder lives on more than two wavefronts a SIMD: its registers leave room for them."""
+    pb.lib()
+    registers = {int(m.group(1)): v for name, (v, _) in _registers().items() for m in [re.search(r"k_mix_decodeILi(\d+)E", name)] if m}
+    assert len(registers) == 17
+    for k in range(1, 17):
+        assert 512 // (-(-registers[k] // 8) * 8) >= (4 if k <= 5 else 3 if k <= 8 else 2), (k, registers[k])
+
+
 def test_lane_kernels_keep_nothing_in_private_memory():
     pb.lib()
     kernels = {n: private for n, (_, private) in _registers().items()
