@@ -380,8 +380,9 @@ __global__ __launch_bounds__(kMixThreads) void k_mix_encode(
 // per lane runs the serial chain over them.  A pixel's parameters go straight from memory to the registers of the thread
 // that uses them, and those of a chunk are one run of memory, so a line is fetched once or twice instead of once a
 // pixel.  (A thread per lane, which comes back for the rest of a line when it has long left the L2, read 2.7 times the
-// parameters, at 6.1 TB/s: 2048 images of 64 x 64, ten components, a lane a row, whole call 558 us, now 368, 1.1 times the parameters read and 79 % of the issue slots used; and a small batch
-// went a pixel after another: 64 such images 366 us, now 91; two photographs of 1365 x 2047 with a lane a row 13.3 ms, now 1.2.)
+// parameters, at 6.1 TB/s: 2048 images of 64 x 64, ten components, a lane a row, whole call 558 us, now 368, 1.1 times the
+// parameters read and 79 % of the issue slots used; and a small batch went a pixel after another: 64 such images 366 us,
+// now 91; two photographs of 1365 x 2047 with a lane a row 13.3 ms, now 1.2.)
 // The wavefronts share nothing but the tables, so there is no barrier.
 // --------------------------------------------------------------------------------------------
 // Four wavefronts on a SIMD, in workgroups of eight that share the tables; from twelve components on the registers are those of
@@ -592,6 +593,8 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(1, 
     const uint32_t scale = mass_scale(m_bits), mask = (1u << m_bits) - 1u;
     const uint32_t payload_bytes = (uint32_t)s_payload;
 
+    // (k_mix_decode_rows opens its lanes likewise.  With one function for both, the registers of this loop come out otherwise: 2048
+    // images of 64 x 64, K = 16, 1312 us, 1533 with the function.)
     const uint32_t *offsets = reinterpret_cast<const uint32_t *>(coded + 64);
     const uint16_t *payload =
         reinterpret_cast<const uint16_t *>(coded + 64 + 4ull * ((size_t)g.lanes + 1));
